@@ -464,13 +464,13 @@ static KeydiffArgs keydiff_args(kvp_cache* c, int layer, int count, int n_tokens
 }
 
 // The scoring pass (proxy queries: row statistics, then column sums; or the keys alone) for `count`
-// consecutive layers whose blocks went through prefill_impl with `defer`: one launch of each
+// consecutive layers whose blocks prefill_layers left unscored: one launch of each
 // kernel for up to kMaxGroupLayers layers in the same state, else layer by layer.
 static int score_deferred_layers(kvp_cache* c, int first, int count, hipStream_t s) {
   const kvp_config& cfg = c->cfg;
   for (int done = 0; done < count;) {
     Layer& A = c->layers[first + done];
-    if (A.unscored == 0) {          // scored inside prefill_impl already (nothing to evict, or a long list)
+    if (A.unscored == 0) {          // scored inside prefill_layers already (nothing to evict, or a long list)
       ++done;
       continue;
     }
@@ -510,40 +510,50 @@ static int score_deferred_layers(kvp_cache* c, int first, int count, hipStream_t
   return KVP_OK;
 }
 
-// kvp_prefill_chunk and its variants: attention for the block; the scores come from the block's
-// own queries, from proxy queries, or from the keys alone
-// `defer`: leave the scoring pass of proxy queries or of the keys alone to score_deferred_layers,
-// which launches it for a group of layers at once (kvp_prefill_block); the layer is PENDING and
-// `unscored` until then.
-static int prefill_impl(kvp_cache* c, int32_t layer, int32_t token_begin, int32_t n_tokens, const void* q,
-                 const void* k, const void* v, void* out, const void* q_obs, int32_t n_obs, int mode,
-                 void* stream, bool defer = false) {
-  const bool proxy = mode == kScoreProxy;
+// What kvp_prefill_chunk and its variants check before anything is enqueued for `layer`.
+static int check_block(const kvp_cache* c, int32_t layer, int32_t token_begin, int32_t n_tokens, const void* q,
+                       const void* k, const void* v, const void* out, const void* q_obs, int32_t n_obs, int mode) {
   if (!c || layer < 0 || layer >= c->cfg.n_layers) return KVP_EINVAL;
   if (n_tokens < 1 || n_tokens > c->cfg.chunk_max) return KVP_EINVAL;
   if (!c->dry && (!q || !k || !v || !out)) return KVP_EINVAL;
-  if (proxy && (n_obs < 1 || n_obs > c->cfg.chunk_max || (!c->dry && !q_obs))) return KVP_EINVAL;
-  Layer& L = c->layers[layer];
+  if (mode == kScoreProxy && (n_obs < 1 || n_obs > c->cfg.chunk_max || (!c->dry && !q_obs))) return KVP_EINVAL;
+  const Layer& L = c->layers[layer];
   if (L.state != READY) return KVP_ESTATE;
   if (token_begin != L.next_token) return KVP_ESTATE;
   if ((long long)token_begin + n_tokens > c->n_tokens) return KVP_EINVAL;
-  const int set_i = layer % c->lay.n_sets;
-  if (c->set_owner[set_i] != -1) return KVP_ESTATE;   // another layer's block is still pending there
+  if (c->set_owner[layer % c->lay.n_sets] != -1) return KVP_ESTATE;   // another layer's block is still pending there
+  return KVP_OK;
+}
 
+// Attention for the block of `count` consecutive layers that passed check_block, that hold the same
+// number of cached entries and use different scratch sets (count <= kMaxGroupLayers): ONE launch.
+// The scores come from the block's own queries (in the same launch), from proxy queries or from
+// the keys alone.  `defer`: leave the scoring pass of the latter two to score_deferred_layers; the
+// layers are PENDING and `unscored` until then.  q, k, v, out, q_obs: one pointer per layer.
+static int prefill_layers(kvp_cache* c, int first, int count, int32_t token_begin, int32_t n_tokens,
+                          const void* const* q, const void* const* k, const void* const* v, void* const* out,
+                          const void* const* q_obs, int32_t n_obs, int mode, hipStream_t s, bool defer) {
   const kvp_config& cfg = c->cfg;
   const Layout& lay = c->lay;
-  unsigned char* set = c->set(layer);
-  hipStream_t s = static_cast<hipStream_t>(stream);
+  unsigned char* set = c->set(first);
+  const int cached = c->layers[first].count;
+  for (int i = 0; i < count; ++i) {
+    Layer& L = c->layers[first + i];
+    L.t0 = token_begin; L.n = n_tokens;
+    L.k = static_cast<const u16*>(k[i]);
+    L.v = static_cast<const u16*>(v[i]);
+    L.unscored = 0;
+  }
 
   AttnArgs aa{};
-  aa.q = static_cast<const u16*>(q);
-  aa.k_new = static_cast<const u16*>(k);
-  aa.v_new = static_cast<const u16*>(v);
-  aa.out = static_cast<u16*>(out);
-  aa.k_cache = c->k_cache(layer);
-  aa.v_cache = c->v_cache(layer);
+  const LayerGroup group = make_group(c, first, count);
+  aa.g = group;
+  for (int i = 0; i < count; ++i)
+    aa.layer[i] = AttnLayer{static_cast<const u16*>(q[i]), group.k_new[i], group.v_new[i], static_cast<u16*>(out[i])};
+  aa.k_cache = c->k_cache(first);
+  aa.v_cache = c->v_cache(first);
   aa.lse2 = reinterpret_cast<float*>(set + lay.lse_off);
-  aa.n = n_tokens; aa.c = L.count;
+  aa.n = n_tokens; aa.c = cached;
   aa.n_keys = n_tokens; aa.shift = 0;
   aa.n_q_heads = cfg.n_q_heads; aa.n_kv_heads = cfg.n_kv_heads;
   aa.budget = cfg.budget; aa.lse_stride = cfg.chunk_max;
@@ -552,7 +562,7 @@ static int prefill_impl(kvp_cache* c, int32_t layer, int32_t token_begin, int32_
   // The scores decide an eviction; a block that fits into the cache as it is needs none.  Scored
   // by its own queries, the block's attention launch leaves the column sums itself (a second
   // sweep inside the kernel), one partial array per workgroup of a KV head.
-  const bool evicts = L.count + n_tokens > cfg.budget;
+  const bool evicts = cached + n_tokens > cfg.budget;
   const int own_partials = (cfg.n_q_heads / cfg.n_kv_heads) * aa.n_row_tiles;
   const bool fused = evicts && mode == kScoreOwn && own_partials <= lay.max_partials && c->fused_scores;
   if (fused) {
@@ -560,70 +570,66 @@ static int prefill_impl(kvp_cache* c, int32_t layer, int32_t token_begin, int32_
     aa.n_partials = own_partials;
     aa.cand_stride = lay.cand_stride;
   }
-  int rc = launch(c, KVP_K_ATTENTION, 1, s, [&] { return launch_attention(aa, cfg.head_dim, s); });
+  int rc = launch(c, KVP_K_ATTENTION, count, s, [&] { return launch_attention(aa, cfg.head_dim, s); });
   if (rc) return rc;
-  aa.partial = nullptr;
-  L.unscored = 0;
-  if (fused) {
-    L.n_partials = own_partials;
-  } else if (evicts) {
-    // the block as the scoring kernels see it: this layer alone
-    LayerGroup one{};
-    one.n_layers = 1;
-    one.first_set = set_i; one.n_sets = lay.n_sets;
-    one.k_new[0] = aa.k_new; one.v_new[0] = aa.v_new;
-    bool deferred = false;
-    if (proxy) {
-      // row statistics of the proxy queries over all candidates (nothing hidden, no output);
-      // they replace the block's own in the scratch set
-      aa.q = static_cast<const u16*>(q_obs);
-      aa.out = nullptr;
-      aa.n = n_obs;
-      aa.shift = n_tokens;
-      if (proxy_by_rowstat(c, L.count + n_tokens, n_obs)) {
-        if (defer) {
-          deferred = true;
-        } else {
-          RowstatArgs ra = rowstat_args(c, layer, L.count, n_tokens, n_obs);
-          ra.g = one;
-          ra.q_layer[0] = aa.q;
-          rc = launch(c, KVP_K_ROWSTAT, 1, s, [&] { return launch_rowstat(ra, cfg.head_dim, s); });
+  int n_partials = fused ? own_partials : 0, unscored = 0;
+  if (evicts && !fused) {
+    if (mode != kScoreOwn) {
+      // a short list of proxy queries, or the keys alone: score_deferred_layers, now or later
+      unscored = mode == kScoreKeydiff || proxy_by_rowstat(c, cached + n_tokens, n_obs) ? mode : 0;
+      if (unscored == 0) {
+        // a long list: row statistics of the proxy queries over all candidates (nothing hidden, no
+        // output) from the attention kernel; they replace the block's own in the scratch set
+        aa.partial = nullptr;
+        for (int i = 0; i < count; ++i) {
+          aa.layer[i].q = static_cast<const u16*>(q_obs[i]);
+          aa.layer[i].out = nullptr;
         }
-      } else {
+        aa.n = n_obs;
+        aa.shift = n_tokens;
         plan_attention(aa, cfg.head_dim, c->attn_shape);
-        rc = launch(c, KVP_K_ATTENTION, 1, s, [&] { return launch_attention(aa, cfg.head_dim, s); });
+        rc = launch(c, KVP_K_ATTENTION, count, s, [&] { return launch_attention(aa, cfg.head_dim, s); });
+        if (rc) return rc;
       }
-      if (rc) return rc;
     }
-    if (deferred) {
-      L.q_obs = aa.q;
-      L.n_obs = n_obs;
-      L.unscored = kScoreProxy;
-    } else if (mode == kScoreKeydiff && defer) {
-      L.unscored = kScoreKeydiff;
-    } else if (mode == kScoreKeydiff) {
-      KeydiffArgs ka = keydiff_args(c, layer, L.count, n_tokens);
-      ka.g = one;
-      rc = launch(c, KVP_K_KEYDIFF, 1, s, [&] { return launch_keydiff(ka, cfg.head_dim, s); });
+    if (unscored == 0) {
+      ColsumArgs cs = colsum_args(c, first, cached, n_tokens, aa.n, aa.shift);
+      cs.g = group;
+      for (int i = 0; i < count; ++i) cs.q_layer[i] = aa.layer[i].q;
+      rc = launch(c, KVP_K_COLSUM, count, s, [&] { return launch_colsum(cs, cfg.head_dim, s); });
       if (rc) return rc;
-      L.n_partials = 1;
-    } else {
-      ColsumArgs cs = colsum_args(c, layer, L.count, n_tokens, aa.n, aa.shift);
-      cs.g = one;
-      cs.q_layer[0] = aa.q;
-      rc = launch(c, KVP_K_COLSUM, 1, s, [&] { return launch_colsum(cs, cfg.head_dim, s); });
-      if (rc) return rc;
-      L.n_partials = cs.n_partials;
+      n_partials = cs.n_partials;
     }
   }
 
-  L.state = PENDING;
-  L.t0 = token_begin; L.n = n_tokens;
-  L.k = aa.k_new; L.v = aa.v_new;
-  L.last_cand = L.count + n_tokens;
-  L.has_last = true;
-  c->set_owner[set_i] = layer;
+  for (int i = 0; i < count; ++i) {
+    Layer& L = c->layers[first + i];
+    L.n_partials = n_partials;
+    L.unscored = unscored;
+    if (unscored == kScoreProxy) {
+      L.q_obs = static_cast<const u16*>(q_obs[i]);
+      L.n_obs = n_obs;
+    }
+    L.state = PENDING;
+    L.last_cand = cached + n_tokens;
+    L.has_last = true;
+    c->set_owner[(first + i) % lay.n_sets] = first + i;
+  }
+  if (unscored != 0 && !defer) {
+    rc = score_deferred_layers(c, first, count, s);
+    if (rc) return rc;
+  }
   return KVP_OK;
+}
+
+// kvp_prefill_chunk and its variants: one layer
+static int prefill_impl(kvp_cache* c, int32_t layer, int32_t token_begin, int32_t n_tokens, const void* q,
+                        const void* k, const void* v, void* out, const void* q_obs, int32_t n_obs, int mode,
+                        void* stream, bool defer = false) {
+  const int rc = check_block(c, layer, token_begin, n_tokens, q, k, v, out, q_obs, n_obs, mode);
+  if (rc) return rc;
+  return prefill_layers(c, layer, 1, token_begin, n_tokens, &q, &k, &v, &out, &q_obs, n_obs, mode,
+                        static_cast<hipStream_t>(stream), defer);
 }
 
 }  // namespace
@@ -717,12 +723,19 @@ int kvp_prefill_block(kvp_cache* c, int32_t token_begin, int32_t n_tokens, const
     }
     int rc = KVP_OK;
     for (int layer = first; layer < last; ++layer) {
-      rc = prefill_impl(c, layer, token_begin, n_tokens, q[layer], k[layer], v[layer], out[layer],
-                        mode == kScoreProxy ? q_obs[layer] : nullptr, n_obs, mode, stream, mode != kScoreOwn);
+      rc = check_block(c, layer, token_begin, n_tokens, q[layer], k[layer], v[layer], out[layer],
+                       mode == kScoreProxy ? q_obs[layer] : nullptr, n_obs, mode);
       if (rc) {
-        last = layer;                            // the layers before it still get their compaction
+        last = layer;                            // the layers before it still go through
         break;
       }
+    }
+    // one attention launch for every run of layers with equally full caches (all of them, in a prefill)
+    for (int layer = first, run; layer < last; layer += run) {
+      for (run = 1; layer + run < last && c->layers[layer + run].count == c->layers[layer].count; ++run) {}
+      const int rc1 = prefill_layers(c, layer, run, token_begin, n_tokens, q + layer, k + layer, v + layer, out + layer,
+                                     mode == kScoreProxy ? q_obs + layer : nullptr, n_obs, mode, main, mode != kScoreOwn);
+      if (rc1) return rc1;
     }
     if (mode != kScoreOwn && last > first) {
       const int rc3 = score_deferred_layers(c, first, last - first, main);

@@ -34,49 +34,60 @@ constexpr size_t select_region_bytes(size_t cand_pad) {
   return (hist > lists ? hist : lists + 15) / 16 * 16;
 }
 
-// One block of one layer attending over cache U block (Eq. 1).
-struct AttnArgs {
-  const u16* q;        // [n, Hq, D]
-  const u16* k_new;    // [n, Hkv, D]
-  const u16* v_new;    // [n, Hkv, D]
-  u16* out;            // [n, Hq, D], or null: only the row statistics are wanted
-  const u16* k_cache;  // this layer: [Hkv, M, D]
-  const u16* v_cache;
-  float* lse2;         // [Hq, lse_stride]  log2-domain log-sum-exp of every row
-  float* partial;      // null, or [Hkv, n_partials, cand_stride]: the launch also leaves the column sums
-                       // of its softmax matrix (Eq. 4), one array per workgroup of a KV head
-  int n_partials, cand_stride;   // n_partials = query heads per KV head x n_row_tiles
-  int n, c, n_q_heads, n_kv_heads, budget, lse_stride;
-  int n_keys;          // block keys (k_new, v_new rows); the query rows are n
-  int shift;           // row r sees block key j iff j <= r + shift (0: causal block; >= n_keys: all)
-  int n_row_tiles, work_per_xcd, total_work;
-  int variant;         // tile shape, chosen by plan_attention
-  float scale_log2;    // softmax scale times log2(e)
-};
-
-// A launch of the selection and compaction kernels covers a group of consecutive layers that hold
-// the same block (same c, n, t0).  The pointers in SelectArgs and CompactArgs are those of the
-// group's FIRST layer; layer i of the group is reached through the strides below.
+// A launch covers a group of consecutive layers that hold the same block (same c, n, t0).  The cache
+// and scratch pointers in a kernel's arguments are those of the group's FIRST layer; layer i of the
+// group is reached through the strides below.
 constexpr int kMaxGroupLayers = 16;
-struct LayerGroup {
+struct GroupStrides {
   int n_layers;
   int first_set, n_sets;        // layer i uses scratch set (first_set + i) % n_sets
   long long set_stride;         // bytes between scratch sets
   long long kv_stride;          // bf16 elements between the K (or V) caches of consecutive layers
   long long meta_stride;        // elements between their token_idx (or weight) arrays
+};
+struct LayerGroup : GroupStrides {
   const u16* k_new[kMaxGroupLayers];   // the block's keys and values of every layer of the group
   const u16* v_new[kMaxGroupLayers];
 };
 
 #if defined(__HIPCC__)
-// the same pointer in scratch set (first_set + li) % n_sets instead of set first_set
+// the same pointer in scratch set (first_set + li) % n_sets instead of set first_set (a group has at most
+// n_sets layers: one subtraction wraps; pointer arithmetic, not integers: the compiler then still
+// knows that it points to global memory)
 template <class T>
-__device__ __forceinline__ T* in_set_of(T* p, const LayerGroup& g, int li) {
+__device__ __forceinline__ T* in_set_of(T* p, const GroupStrides& g, int li) {
   if (p == nullptr) return p;
-  const long long sets = (long long)((g.first_set + li) % g.n_sets) - g.first_set;
-  return reinterpret_cast<T*>(reinterpret_cast<uintptr_t>(p) + (uintptr_t)(sets * g.set_stride));
+  const int sets = g.first_set + li < g.n_sets ? li : li - g.n_sets;
+  return (T*)((char*)p + sets * g.set_stride);
 }
 #endif
+
+// One block of a group of layers attending over cache U block (Eq. 1); the layers of a group are
+// independent, and one launch for all of them fills the chip where a single layer's rows do not.
+struct AttnLayer {
+  const u16* q;        // [n, Hq, D]
+  const u16* k_new;    // [n_keys, Hkv, D]
+  const u16* v_new;
+  u16* out;            // [n, Hq, D], or null: only the row statistics are wanted
+};
+struct AttnArgs {
+  // Arguments are read from far memory at every launch, one 64-byte line at a time: what a workgroup
+  // needs first lies together, and so do the pointers of a layer.
+  int n, c, n_q_heads, n_kv_heads, budget, lse_stride;
+  int n_keys;          // block keys (k_new, v_new rows); the query rows are n
+  int shift;           // row r sees block key j iff j <= r + shift (0: causal block; >= n_keys: all)
+  int n_row_tiles, work_per_xcd, total_work;   // work items of one layer (grid y = layer)
+  int variant;         // tile shape, chosen by plan_attention
+  float scale_log2;    // softmax scale times log2(e)
+  int n_partials, cand_stride;   // n_partials = query heads per KV head x n_row_tiles
+  GroupStrides g;
+  const u16* k_cache;  // the group's first layer: [Hkv, M, D]
+  const u16* v_cache;
+  float* lse2;         // [Hq, lse_stride]  log2-domain log-sum-exp of every row (first layer's scratch set, like partial)
+  float* partial;      // null, or [Hkv, n_partials, cand_stride]: the launch also leaves the column sums
+                       // of its softmax matrix (Eq. 4), one array per workgroup of a KV head
+  AttnLayer layer[kMaxGroupLayers];
+};
 
 // Column sums of the softmax matrix (Eq. 4 summed over rows and over the query
 // heads of a KV group), one partial array per row split.
