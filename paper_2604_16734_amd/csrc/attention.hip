@@ -33,7 +33,7 @@
 // fewer than 1024 wave-sized row tiles.  Three shapes are built: 2 x 2 waves of
 // 64 rows (one wave per SIMD, 512 registers), 4 x 2 waves of 32 rows (two waves
 // per SIMD, 256 registers each; the fastest on the large shapes) and 2 x 2 waves
-// of 32 rows for blocks too small to fill the chip with 128-row workgroups.
+// of 32 rows.  Blocks too small to fill the chip with 128-row workgroups go to attention_split.hip.
 //
 // Schedule.  Matrix and vector work of one wave are made to overlap in program
 // order.  With S_X(t) = scores of block X of tile t, the loop body is
@@ -61,48 +61,13 @@
 #include <type_traits>
 
 #include "kvp_internal.h"
+#include "mfma_tools.h"
 
 namespace kvp {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
-typedef short i16x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
 constexpr float kRedoLog2 = 64.f;   // redo a row tile when a block maximum exceeds the reference by 2^64
-
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
-  f32x2 v = {lo, hi};
-  bf16x2 b = __builtin_convertvector(v, bf16x2);   // v_cvt_pk_bf16_f32, round to nearest even
-  return __builtin_bit_cast(unsigned, b);
-}
-
-// value of the same row held by the other half of the wave (lane ^ 32)
-__device__ __forceinline__ float max_with_other_half(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float sum_with_other_half(float x) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-__device__ __forceinline__ bf16x8 lds_read_b128(const u16* p) {
-  return *reinterpret_cast<const bf16x8*>(p);
-}
-// two transposing reads: keys k .. k+3 and k+8 .. k+11 of this lane's channel
-__device__ __forceinline__ bf16x8 lds_read_vt(const u16* p, int eight_rows) {
-  const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 __attribute__((address_space(3)))*)(p));
-  const i16x4 hi =
-      __builtin_amdgcn_ds_read_tr16_b64_v4i16((i16x4 __attribute__((address_space(3)))*)(p + eight_rows));
-  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-}
 
 template <int D, int QT, int QW, int KS>
 struct Shape {
@@ -197,11 +162,7 @@ attention_kernel(const AttnArgs a) {
   const int ld_sub = lane / S::kChunks, ld_pos = lane % S::kChunks;
   const int ld_row = S::kRowsPerLoad * wave + ld_sub;          // + kRowGroup j
   const int ld_chunk_k = ld_pos ^ (ld_row % S::kChunks);
-  // V rows are read four at a time by each half of a wave (transposing 8-byte reads, 64 bytes
-  // of each row): the swizzle sends those four 64-byte pieces to four different quarters of the
-  // 64 banks (D = 128: a row spans all banks; D = 64: rows r and r + 2 share their banks)
-  auto v_swizzle = [](int row) { return 4 * ((row % 4) >> (D == 64 ? 1 : 0)); };
-  const int ld_chunk_v = ld_pos ^ v_swizzle(ld_row);
+  const int ld_chunk_v = ld_pos ^ v_swizzle<D>(ld_row);
   // LDS destination of instruction j into `tile`, as the byte address M0 wants: wave-uniform and
   // all scalar arithmetic (the wave number is read into a scalar register once)
   const unsigned lds_base =
@@ -276,7 +237,7 @@ attention_kernel(const AttnArgs a) {
   int v_off[D / 32];
   {
     const int rsub = 4 * g + ((lane & 15) >> 2);
-    const int z = v_swizzle(rsub);
+    const int z = v_swizzle<D>(rsub);
 #pragma unroll
     for (int dt = 0; dt < D / 32; ++dt) {
       const int chunk = (4 * dt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ z;
@@ -986,17 +947,19 @@ hipError_t prepare_attention() {
   if ((e = prepare_shape<128, 1, 2, 2>()) != hipSuccess) return e;
   if ((e = prepare_shape<64, 2, 2, 2>()) != hipSuccess) return e;
   if ((e = prepare_shape<64, 1, 4, 2>()) != hipSuccess) return e;
-  return prepare_shape<64, 1, 2, 2>();
+  if ((e = prepare_shape<64, 1, 2, 2>()) != hipSuccess) return e;
+  return prepare_attention_split();
 }
 
 hipError_t launch_attention(const AttnArgs& a, int head_dim, hipStream_t s) {
+  if (a.variant == kAttnSplit32 || a.variant == kAttnSplit64) return launch_attention_split(a, head_dim, s);
   if (head_dim == 128) {
-    if (a.variant == 0) return launch_shape<128, 2, 2, 2>(a, s);
-    if (a.variant == 2) return launch_shape<128, 1, 4, 2>(a, s);
+    if (a.variant == kAttnWide4) return launch_shape<128, 2, 2, 2>(a, s);
+    if (a.variant == kAttnTile128) return launch_shape<128, 1, 4, 2>(a, s);
     return launch_shape<128, 1, 2, 2>(a, s);
   }
-  if (a.variant == 0) return launch_shape<64, 2, 2, 2>(a, s);
-  if (a.variant == 2) return launch_shape<64, 1, 4, 2>(a, s);
+  if (a.variant == kAttnWide4) return launch_shape<64, 2, 2, 2>(a, s);
+  if (a.variant == kAttnTile128) return launch_shape<64, 1, 4, 2>(a, s);
   return launch_shape<64, 1, 2, 2>(a, s);
 }
 

@@ -1,0 +1,449 @@
+// Attention of one block of queries over cache U block (Eq. 1) with its scores (Eq. 4), for blocks too
+// small to fill the chip with the tiles of attention.hip: the KEYS are split over the waves.
+//
+// A workgroup of eight waves takes 32 QW query rows of one head (QW = 1 or 2); the KS = 8 / QW waves
+// of a 32-row tile take every KS-th block of 32 keys.  The products are those of attention.hip
+// (S^T = K Q^T, O^T = V^T P^T, one query row per lane), but a wave works entirely by itself: its K
+// and V blocks go straight from global memory into two strips of LDS that belong to the wave, and there
+// is no barrier until the KS partial results of a row are added up.  What bounds a block of this
+// size is the chain of one workgroup -- launch, first keys from memory, the wave's share of the keys,
+// the merge, the second sweep -- and eight short chains replace two or four long ones.
+//
+// Everything comes through LDS, although a wave could load K and Q fragments straight into registers
+// in operand layout: there neighbouring lanes read different rows, and the address path of a CU takes
+// such a load at 16 bytes a clock, against 60 when four neighbouring lanes share 64 bytes (measured,
+// from L2).
+//
+// A wave's loop over its key blocks i:
+//   S = K(i) Q^T from the K strip, then the load of K(i + 1) into it; P = exp(S - m);
+//   O += P V(i) from the V strip, then the load of V(i + 1).
+// Two waves share a SIMD, out of step: one has matrix work while the other has vector work.
+//
+// Softmax reference.  A row's reference is the maximum of its first visible block; a later logit more
+// than 2^30 above it (fp32 has room for 2^127) sends the wave through a branch that brings O and the
+// row sum onto a new reference.  Ordinary logits never take it.
+//
+// Second sweep: as in attention.hip, S = Q K^T again with the final normalisers, one key per lane, one
+// partial array of column sums per workgroup.  Query fragments are, register for register, the A
+// operand of this product.
+//
+// plan.cpp has the rule that picks this kernel and what it measured against the tiles of attention.hip.
+#include <type_traits>
+
+#include "kvp_internal.h"
+#include "mfma_tools.h"
+
+namespace kvp {
+namespace {
+
+constexpr float kRescueLog2 = 30.f;
+
+template <int D, int QW>
+struct Split {
+  static constexpr int kWaves = 8;
+  static constexpr int KS = kWaves / QW;              // waves that share a 32-row tile
+  static constexpr int kThreads = 64 * kWaves;
+  static constexpr int kRows = 32 * QW;
+  static constexpr int kStrip = 32 * D;               // bf16 elements of a strip: 32 rows of K or V
+  static constexpr int kORow = D + 4;                 // floats of a partial output row, padded
+  static constexpr int kPartFloats = 32 * kORow;      // partial output of a wave
+  static constexpr int kStripBytes = 2 * kWaves * kStrip * 2;
+  static constexpr int kPartBytes = kWaves * kPartFloats * 4;
+  static constexpr int kMainBytes = kStripBytes > kPartBytes ? kStripBytes : kPartBytes;
+  static constexpr int kStatBytes = 2 * kWaves * 32 * 4;           // maximum and sum per wave and row
+  static constexpr int kQBytes = kRows * D * 2;       // the workgroup's query rows
+  static constexpr int kLdsBytes = kMainBytes + kStatBytes + kQBytes + kRows * 4;
+  static_assert(kLdsBytes <= 160 * 1024, "LDS of a CU");
+};
+
+template <int D, int QW>
+__global__ void __launch_bounds__((Split<D, QW>::kThreads))
+attention_split_kernel(const AttnArgs a) {
+  using S = Split<D, QW>;
+  constexpr int KS = S::KS;
+  constexpr int kNK = D / 16;                // K fragments (and MFMAs) of a 32-key block
+  constexpr int kND = D / 32;                // channel tiles of O
+  constexpr int kChunks = D / 8;             // 16-byte chunks per row
+  constexpr int kRowsPerLoad = 64 / kChunks; // rows one wave instruction brings in
+  constexpr int kLoads = 32 / kRowsPerLoad;  // instructions for a 32-row block
+  extern __shared__ __align__(16) unsigned char lds_raw[];
+  float* const stat_m = reinterpret_cast<float*>(lds_raw + S::kMainBytes);       // [kWaves][32]
+  float* const stat_l = stat_m + S::kWaves * 32;
+  u16* const q_lds = reinterpret_cast<u16*>(stat_l + S::kWaves * 32);            // [kRows][D], chunks swizzled like K's
+  float* const lse_lds = reinterpret_cast<float*>(q_lds + S::kRows * D);         // [kRows]
+
+  // XCD-aware order: consecutive work items (same KV head) land on one die
+  const int w = (blockIdx.x % kXcds) * a.work_per_xcd + blockIdx.x / kXcds;
+  if (w >= a.total_work) return;
+  const int li = blockIdx.y;
+  const u16* const q_rows = a.layer[li].q;
+  u16* const out_rows = a.layer[li].out;
+  float* const lse2 = in_set_of(a.lse2, a.g, li);
+  const int group = a.n_q_heads / a.n_kv_heads;
+  const int rt = a.n_row_tiles - 1 - (w % a.n_row_tiles);   // long rows first
+  const int h = w / a.n_row_tiles;
+  const int hk = h / group;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int qw = wave / KS, ks = wave % KS;
+  const int l32 = lane & 31;
+  const int g = lane >> 5;
+
+  const int n = a.n, c = a.c, shift = a.shift;
+  const int row_begin = rt * S::kRows;
+  const int q0 = row_begin + 32 * qw;                      // first query row of this wave
+  const u16* const kc = a.k_cache + (size_t)li * a.g.kv_stride + (size_t)hk * a.budget * D;
+  const u16* const vc = a.v_cache + (size_t)li * a.g.kv_stride + (size_t)hk * a.budget * D;
+  const u16* const kn = a.layer[li].k_new + (size_t)hk * D;
+  const u16* const vn = a.layer[li].v_new + (size_t)hk * D;
+  const int new_stride = a.n_kv_heads * D;
+  const float sl2 = a.scale_log2;
+
+  // ---- key blocks: 32 keys of the cache first, then those among the block's own keys (each part is cut
+  // into 32s by itself, so a block lies in one or the other)
+  const int c_blk = (c + 31) / 32;
+  struct Block {
+    bool cached;
+    int first, rows;                         // first row within the cache or the block's keys; real rows
+  };
+  auto block_of = [&](int b) __attribute__((always_inline)) -> Block {
+    const bool cached = b < c_blk;
+    const int first = 32 * (cached ? b : b - c_blk);
+    return Block{cached, first, min(32, (cached ? c : a.n_keys) - first)};
+  };
+
+  // ---- global memory -> LDS, 16 bytes per lane.  Instruction j brings in rows kRowsPerLoad j + (0 ..
+  // kRowsPerLoad - 1) of a 32-row strip; the 16-byte chunks of a row are XOR-swizzled on the way so that the
+  // fragment reads are free of bank conflicts (K and Q: by the row, V: v_swizzle).  Inline assembly for the
+  // reasons given in attention.hip; the waits are this kernel's own.
+  u16* const k_strip = reinterpret_cast<u16*>(lds_raw) + wave * S::kStrip;
+  u16* const v_strip = k_strip + S::kWaves * S::kStrip;
+  const unsigned lds_base =
+      __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) void*)lds_raw);
+  auto lds_addr = [&](const u16* p) __attribute__((always_inline)) -> unsigned {
+    return lds_base + 2u * (unsigned)(p - reinterpret_cast<u16*>(lds_raw));
+  };
+  auto load_row16 = [&](const u16* base, unsigned lane_bytes, unsigned to) __attribute__((always_inline)) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_bytes), "s"(base), "s"(to)
+                 : "m0", "memory");
+  };
+  const int ld_sub = lane / kChunks, ld_pos = lane % kChunks;
+  const int ld_chunk_k = ld_pos ^ ld_sub, ld_chunk_v = ld_pos ^ v_swizzle<D>(ld_sub);
+  // rows [0, rows) at `base`, `stride` elements apart; rows past the end: the last one again
+  auto load_strip = [&](const u16* base, int stride, int rows, u16* strip, bool is_v, int j) __attribute__((always_inline)) {
+    // row kRowsPerLoad j + ld_sub of the strip: its swizzle is the lane's, with bits of j where a row has 16 chunks
+    const int chunk = is_v ? ld_chunk_v : ld_chunk_k ^ ((kRowsPerLoad * j) % kChunks);
+    const int row = min(kRowsPerLoad * j + ld_sub, rows - 1);
+    load_row16(base, 2u * (unsigned)(row * stride + 8 * chunk), lds_addr(strip + j * kRowsPerLoad * D));
+  };
+  auto load_block = [&](const u16* cache, const u16* fresh, const Block& b, u16* strip, bool is_v) __attribute__((always_inline)) {
+    const int stride = b.cached ? D : new_stride;
+    const u16* const base = (b.cached ? cache : fresh) + (size_t)b.first * stride;
+    if (b.rows == 32) {
+      const unsigned lane_row = 2u * (unsigned)(ld_sub * stride);
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) {
+        const int chunk = is_v ? ld_chunk_v : ld_chunk_k ^ ((kRowsPerLoad * j) % kChunks);
+        load_row16(base + (size_t)(kRowsPerLoad * j * stride), lane_row + 16u * (unsigned)chunk, lds_addr(strip + j * kRowsPerLoad * D));
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < kLoads; ++j) load_strip(base, stride, b.rows, strip, is_v, j);
+    }
+  };
+  auto wait_older_than = [&](auto newest) __attribute__((always_inline)) {   // all but the `newest` latest loads have landed
+    constexpr int k = decltype(newest)::value;
+    static_assert(k <= 16, "fits the two fields of the wait");
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (k & 15) | (k >> 4 << 14));
+    asm volatile("" ::: "memory");
+  };
+  typedef std::integral_constant<int, 0> None;
+  typedef std::integral_constant<int, kLoads> OneBlock;
+  typedef std::integral_constant<int, 2 * kLoads> TwoBlocks;
+
+  // ---- per-lane LDS read offsets (bf16 elements), as in attention.hip
+  int k_off[kNK];
+#pragma unroll
+  for (int st = 0; st < kNK; ++st) k_off[st] = l32 * D + 8 * ((2 * st) ^ (g ^ (l32 % kChunks)));
+  int v_off[kND];
+  {
+    const int rsub = 4 * g + ((lane & 15) >> 2);
+#pragma unroll
+    for (int dt = 0; dt < kND; ++dt)
+      v_off[dt] = rsub * D + 8 * ((4 * dt + 2 * ((lane >> 4) & 1) + ((lane & 3) >> 1)) ^ v_swizzle<D>(rsub)) + 4 * (lane & 1);
+  }
+
+  // ---- first sweep
+  const int rows_end = min(n, q0 + 32);                    // = n for a tile past the end: computed, not stored
+  const int n_blk = c_blk + (min(a.n_keys, rows_end + shift) + 31) / 32;     // blocks some row of the tile sees
+  const int my_blk = n_blk > ks ? (n_blk - ks + KS - 1) / KS : 0;
+  auto mine = [&](int i) __attribute__((always_inline)) { return block_of(ks + KS * i); };
+
+  // the workgroup's query rows (each wave brings in its share), the wave's first block
+  for (int j = wave; j < QW * kLoads; j += S::kWaves) {
+    const int first_row = row_begin + 32 * (j / kLoads);       // rows past the block are computed, not stored
+    load_strip(q_rows + ((size_t)min(first_row, n - 1) * a.n_q_heads + h) * D, a.n_q_heads * D, max(min(32, n - first_row), 1),
+               q_lds + (j / kLoads) * S::kStrip, false, j % kLoads);
+  }
+  if (my_blk > 0) {
+    load_block(kc, kn, mine(0), k_strip, false);
+    load_block(vc, vn, mine(0), v_strip, true);
+    wait_older_than(TwoBlocks{});
+  } else {
+    wait_older_than(None{});
+  }
+  __builtin_amdgcn_s_barrier();              // the query rows are in LDS
+  asm volatile("" ::: "memory");
+  bf16x8 qf[kNK];
+#pragma unroll
+  for (int st = 0; st < kNK; ++st) qf[st] = lds_read_b128(q_lds + qw * S::kStrip + k_off[st]);
+  f32x16 o[kND];
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int dt = 0; dt < kND; ++dt) o[dt] = zero;
+  float m_ref = -INFINITY, l_run = 0.f;
+  const float rescue_raw = kRescueLog2 / sl2;              // the margin in units of the raw dot product
+
+  auto read_v = [&](int dt, int mm) __attribute__((always_inline)) {
+    return lds_read_vt(v_strip + v_off[dt] + 16 * mm * D, 8 * D);
+  };
+  auto p_frag = [](const unsigned (&p)[8], int mm) __attribute__((always_inline)) {
+    const u32x4 pw = {p[4 * mm], p[4 * mm + 1], p[4 * mm + 2], p[4 * mm + 3]};
+    return __builtin_bit_cast(bf16x8, pw);
+  };
+  for (int i = 0; i < my_blk; ++i) {
+    const Block b = mine(i);
+    const bool more = i + 1 < my_blk;
+    wait_older_than(OneBlock{});             // K(i) is in its strip; V(i) may still be on its way
+    f32x16 s;
+    bf16x8 kf[kNK];
+#pragma unroll
+    for (int st = 0; st < kNK; ++st) kf[st] = lds_read_b128(k_strip + k_off[st]);
+#pragma unroll
+    for (int st = 0; st < kNK; ++st) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st], qf[st], st == 0 ? zero : s, 0, 0, 0);
+    __builtin_amdgcn_s_waitcnt(0xC07F);      // the strip has been read
+    if (more) load_block(kc, kn, mine(i + 1), k_strip, false);
+    if (b.rows < 32 || (!b.cached && b.first + 31 > q0 + shift)) {         // some row may not see some key
+      const int last = b.cached ? b.rows - 1 : min(b.rows - 1, q0 + l32 + shift - b.first);
+      const int lim = last - 4 * g;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = (8 * (r >> 2) + (r & 3) <= lim) ? s[r] : -INFINITY;
+    }
+    float mx = s[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+    mx = max_with_other_half(mx);
+    if (__any(mx > m_ref + rescue_raw || (m_ref == -INFINITY && mx > -INFINITY))) {
+      const float m_new = fmaxf(m_ref, mx);
+      if (i > 0) {
+        const float f = m_ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_ref - m_new) * sl2);
+        l_run *= f;
+#pragma unroll
+        for (int dt = 0; dt < kND; ++dt)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[dt][r] *= f;
+      }
+      m_ref = m_new;
+    }
+    const float neg = -(m_ref == -INFINITY ? 0.f : m_ref) * sl2;
+    unsigned pw[8];
+    float sum = 0.f;
+    auto weigh_pair = [&](int k) __attribute__((always_inline)) {
+      const float p0 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * k], sl2, neg));
+      const float p1 = __builtin_amdgcn_exp2f(__builtin_fmaf(s[2 * k + 1], sl2, neg));
+      sum += p0 + p1;
+      pw[k] = pack_bf16(p0, p1);
+    };
+#pragma unroll
+    for (int k = 0; k < 4; ++k) weigh_pair(k);
+    if (more) wait_older_than(OneBlock{});   // V(i) is in its strip; K(i + 1) may still be on its way
+    else wait_older_than(None{});
+    bf16x8 vf[2 * kND];
+#pragma unroll
+    for (int dt = 0; dt < kND; ++dt) {
+      vf[dt] = read_v(dt, 0);
+      vf[kND + dt] = read_v(dt, 1);
+    }
+    // the products with the first sixteen keys run beside the exponentials of the other sixteen
+#pragma unroll
+    for (int dt = 0; dt < kND; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt], p_frag(pw, 0), o[dt], 0, 0, 0);
+#pragma unroll
+    for (int k = 4; k < 8; ++k) weigh_pair(k);
+#pragma unroll
+    for (int dt = 0; dt < kND; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kND + dt], p_frag(pw, 1), o[dt], 0, 0, 0);
+    l_run += sum;
+    __builtin_amdgcn_s_waitcnt(0xC07F);      // the strip has been read
+    if (more) load_block(vc, vn, mine(i + 1), v_strip, true);
+  }
+
+  // ---- merge the KS partial results of every row through LDS
+  l_run = sum_with_other_half(l_run);        // lanes l and l + 32 each summed half of the keys of a row
+  __syncthreads();                           // nobody needs the strips any more
+  {
+    float* const part_o = reinterpret_cast<float*>(lds_raw) + wave * S::kPartFloats + l32 * S::kORow + 4 * g;
+#pragma unroll
+    for (int dt = 0; dt < kND; ++dt)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        *reinterpret_cast<f32x4*>(part_o + 32 * dt + 8 * j) = f32x4{o[dt][4 * j], o[dt][4 * j + 1], o[dt][4 * j + 2], o[dt][4 * j + 3]};
+    if (g == 0) {
+      stat_m[wave * 32 + l32] = m_ref;
+      stat_l[wave * 32 + l32] = l_run;
+    }
+  }
+  const bool score = a.partial != nullptr;
+  __syncthreads();
+  {
+    constexpr int kPerRow = S::kThreads / S::kRows;        // threads that put a row together
+    constexpr int kCh = D / kPerRow;                       // channels of each
+    static_assert(kCh % 4 == 0, "four floats at a time");
+    const int row = tid / kPerRow, ch0 = (tid % kPerRow) * kCh;
+    const int first_wave = (row / 32) * KS, r = row % 32;
+    float m = -INFINITY;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) m = fmaxf(m, stat_m[(first_wave + s) * 32 + r]);
+    float f[KS], l = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      f[s] = __builtin_amdgcn_exp2f((stat_m[(first_wave + s) * 32 + r] - m) * sl2);    // 0 for a wave that saw nothing
+      l += stat_l[(first_wave + s) * 32 + r] * f[s];
+    }
+    const float inv = 1.f / l;
+    float acc[kCh];
+#pragma unroll
+    for (int k = 0; k < kCh; ++k) acc[k] = 0.f;
+#pragma unroll
+    for (int s = 0; s < KS; ++s) {
+      const float* const from = reinterpret_cast<const float*>(lds_raw) + (first_wave + s) * S::kPartFloats + r * S::kORow + ch0;
+#pragma unroll
+      for (int k = 0; k < kCh; k += 4) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(from + k);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[k + e] += f[s] * v[e];
+      }
+    }
+    const int orow = row_begin + row;
+    const float lse_row = m * sl2 + __builtin_log2f(l);
+    if (tid % kPerRow == 0) {
+      lse_lds[row] = lse_row;
+      if (orow < n) lse2[(size_t)h * a.lse_stride + orow] = lse_row;
+    }
+    if (orow < n && out_rows != nullptr) {
+      u16* const dst = out_rows + ((size_t)orow * a.n_q_heads + h) * D + ch0;
+#pragma unroll
+      for (int k = 0; k < kCh; k += 4) {
+        u32x2 pk;
+        pk.x = pack_bf16(acc[k] * inv, acc[k + 1] * inv);
+        pk.y = pack_bf16(acc[k + 2] * inv, acc[k + 3] * inv);
+        *reinterpret_cast<u32x2*>(dst + k) = pk;
+      }
+    }
+  }
+  if (!score) return;
+
+  // ---- second sweep: column sums (Eq. 4) of the workgroup's rows; wave w takes key blocks w, w + 8, ...,
+  // its two strips in turn
+  const int wg_rows_end = min(n, row_begin + S::kRows);
+  const int n_kb = c_blk + (min(a.n_keys, wg_rows_end + shift) + 31) / 32;   // blocks some row of the workgroup sees
+  __syncthreads();                           // the rows' statistics are in LDS, the partial outputs have been read
+  if (wave < n_kb) load_block(kc, kn, block_of(wave), k_strip, false);
+  bf16x8 qs[QW][kNK];
+#pragma unroll
+  for (int t = 0; t < QW; ++t)
+#pragma unroll
+    for (int st = 0; st < kNK; ++st) qs[t][st] = lds_read_b128(q_lds + t * S::kStrip + k_off[st]);
+  const int split = (h % group) * a.n_row_tiles + rt;
+  float* const part = in_set_of(a.partial, a.g, li) + ((size_t)hk * a.n_partials + split) * a.cand_stride;
+  float ls[QW][16];                          // register r is row 8 (r / 4) + 4 g + r % 4 of its tile
+#pragma unroll
+  for (int t = 0; t < QW; ++t)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(&lse_lds[32 * t + 8 * j + 4 * g]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ls[t][4 * j + e] = v[e];
+    }
+  auto weigh = [&](const f32x16 (&s)[QW], const Block& b) __attribute__((always_inline)) {
+    float sum[2] = {0.f, 0.f};
+    // every row sees every key and all are real
+    if (b.rows == 32 && (b.cached || b.first + 31 <= row_begin + shift) && row_begin + S::kRows <= n) {
+#pragma unroll
+      for (int t = 0; t < QW; ++t)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sum[r & 1] += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], sl2, -ls[t][r]));
+    } else {
+      // this lane's key counts for the row at offset off = 8 (r / 4) + r % 4 from row0 iff first <= off < rows left
+#pragma unroll
+      for (int t = 0; t < QW; ++t) {
+        const int row0 = row_begin + 32 * t + 4 * g;
+        const int first = b.cached ? 0 : max(b.first + l32 - shift - row0, 0);
+        const unsigned span = (unsigned)max(n - row0 - first, 0);
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], sl2, -ls[t][r]));
+          sum[r & 1] += (unsigned)(8 * (r >> 2) + (r & 3) - first) < span ? p : 0.f;
+        }
+      }
+    }
+    const float tot = sum_with_other_half(sum[0] + sum[1]);  // lanes l and l + 32 hold the two halves of the rows
+    if (g == 0 && l32 < b.rows) part[(b.cached ? 0 : c) + b.first + l32] = tot;
+  };
+  u16* strip = k_strip;
+  u16* other = v_strip;
+  for (int b = wave; b < n_kb; b += S::kWaves) {
+    if (b + S::kWaves < n_kb) {
+      load_block(kc, kn, block_of(b + S::kWaves), other, false);
+      wait_older_than(OneBlock{});
+    } else {
+      wait_older_than(None{});
+    }
+    bf16x8 kf[kNK];
+#pragma unroll
+    for (int st = 0; st < kNK; ++st) kf[st] = lds_read_b128(strip + k_off[st]);
+    f32x16 s[QW];
+#pragma unroll
+    for (int st = 0; st < kNK; ++st)
+#pragma unroll
+      for (int t = 0; t < QW; ++t)
+        s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qs[t][st], kf[st], st == 0 ? zero : s[t], 0, 0, 0);
+    weigh(s, block_of(b));
+    u16* const swap = strip;
+    strip = other;
+    other = swap;
+  }
+  // keys that none of this workgroup's rows see: zeros (the selection adds every partial array)
+  for (int k = 32 * (n_kb - c_blk) + tid; k < a.n_keys; k += S::kThreads) part[c + k] = 0.f;
+}
+
+template <int D, int QW>
+hipError_t launch_shape(const AttnArgs& a, hipStream_t s) {
+  using S = Split<D, QW>;
+  hipLaunchKernelGGL((attention_split_kernel<D, QW>), dim3(kXcds * a.work_per_xcd, a.g.n_layers), dim3(S::kThreads),
+                     S::kLdsBytes, s, a);
+  return hipGetLastError();
+}
+
+template <int D, int QW>
+hipError_t prepare_shape() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(attention_split_kernel<D, QW>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, Split<D, QW>::kLdsBytes);
+}
+
+}  // namespace
+
+hipError_t prepare_attention_split() {
+  hipError_t e;
+  if ((e = prepare_shape<128, 1>()) != hipSuccess) return e;
+  if ((e = prepare_shape<128, 2>()) != hipSuccess) return e;
+  if ((e = prepare_shape<64, 1>()) != hipSuccess) return e;
+  return prepare_shape<64, 2>();
+}
+
+hipError_t launch_attention_split(const AttnArgs& a, int head_dim, hipStream_t s) {
+  if (head_dim == 128) return a.variant == kAttnSplit32 ? launch_shape<128, 1>(a, s) : launch_shape<128, 2>(a, s);
+  return a.variant == kAttnSplit32 ? launch_shape<64, 1>(a, s) : launch_shape<64, 2>(a, s);
+}
+
+}  // namespace kvp

@@ -14,7 +14,9 @@ constexpr int kXcds = 8;            // MI355X: 8 accelerator dies, each with its
 constexpr int kNeighbours = 6;      // 4 in the plane + 2 in time
 
 // Sizes that the kernels and the host-side planning (plan.cpp) must agree on.
-constexpr int kAttnRowsOfShape[3] = {128, 64, 128};   // query rows per workgroup of the three attention shapes
+// Attention shapes: the three of attention.hip, then the two of attention_split.hip.
+enum { kAttnWide4 = 0, kAttnTile64 = 1, kAttnTile128 = 2, kAttnSplit32 = 3, kAttnSplit64 = 4 };
+constexpr int kAttnRowsOfShape[5] = {128, 64, 128, 32, 64};   // query rows per workgroup
 constexpr int kColsumWaves = 4;                 // waves per workgroup of the column-sum kernel
 constexpr int kColsumTargetWorkgroups = 512;    // two per CU, all resident: the launch is a single round
 constexpr int kColsumMaxRowSplits = 16;
@@ -224,6 +226,7 @@ struct CompactArgs {
 
 // launchers (each returns the hipError_t of the launch)
 hipError_t launch_attention(const AttnArgs& a, int head_dim, hipStream_t s);
+hipError_t launch_attention_split(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_colsum(const ColsumArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_select(const SelectArgs& a, int n_kv_heads, hipStream_t s);   // grid: heads x a.g.n_layers
 hipError_t launch_merge(const CompactArgs& a, hipStream_t s);
@@ -236,6 +239,7 @@ int rows_per_compact_block(int head_dim);
 void plan_attention(AttnArgs& a, int head_dim, int forced_shape);   // forced_shape < 0: chosen from the launch size
 int attention_max_partials(int group, int n_q_heads, int chunk_max);   // most partial score arrays per KV head a launch leaves
 constexpr int kMaxFusedPartials = 64;                   // beyond that the separate column-sum kernel scores
+hipError_t prepare_attention_split();
 hipError_t prepare_attention();   // function attributes on the current device; once per cache creation
 hipError_t prepare_select();
 void plan_colsum(ColsumArgs& a, int head_dim);

@@ -6,9 +6,21 @@
 namespace kvp {
 
 // ---- attention
-// eight waves x 32 rows (two waves per SIMD) when 128-row workgroups fill the chip, otherwise four
-// waves x 32 rows over 64-row workgroups
-static int shape_for(int n, int n_q_heads) { return ((n + 127) / 128) * n_q_heads >= 192 ? 2 : 1; }
+// 128-row workgroups of attention.hip when a layer's block has about one of them for every CU (from
+// three quarters on: every key tile then serves 128 rows, and the shape that splits the keys would need
+// three rounds of the chip); below that the split-key shapes of attention_split.hip: 32-row workgroups
+// while all of them fit on the chip at once, 64-row ones (half as many) beyond.  Per launch with scores,
+// against the four-wave 64-row tiles that used to serve these blocks:
+//   16/4 heads, d 64, 333 rows over 1444 keys   28.4 -> 13.2 us
+//   28/4 heads, d 128, 256 rows over 768 keys   22.7 ->  9.5 us (17.3 -> 9 without scores)
+//   32/32 heads, d 128, 128 rows over 384 keys  15.1 ->  7.6 us
+//   28/4 heads, d 128, 512 rows over 1536 keys  34.6 -> 26.5 us (64-row workgroups)
+// The choice depends on one layer's block alone, never on how many layers a launch takes, so that
+// grouped and single launches leave the same bits.
+static int shape_for(int n, int n_q_heads) {
+  if (((n + 127) / 128) * n_q_heads >= 192) return kAttnTile128;
+  return ((n + 31) / 32) * n_q_heads <= 256 ? kAttnSplit32 : kAttnSplit64;
+}
 
 // The most partial score arrays per KV head (query heads of the group x row tiles) that a block of
 // up to chunk_max rows leaves when the library picks the shape itself.  A forced shape may need

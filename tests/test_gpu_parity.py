@@ -117,6 +117,22 @@ def test_every_workgroup_shape_scores(variant, fused, hq, hkv, d, c, n, budget):
     cache.close()
 
 
+@pytest.mark.parametrize("hq,hkv,d,c,n", [
+    # keys split eight ways over 32-row tiles: fewer key blocks than waves, exactly as many, one more
+    (4, 2, 128, 0, 1), (4, 4, 64, 0, 31), (4, 2, 128, 0, 32), (4, 4, 64, 1, 33), (4, 2, 128, 223, 32),
+    (4, 2, 128, 224, 32), (4, 2, 64, 225, 64), (8, 2, 128, 31, 250), (6, 2, 64, 1025, 65),
+    # four ways over 64-row tiles: a last tile of one row, of 32, of 33, nothing cached
+    (28, 4, 128, 33, 321), (28, 4, 128, 300, 352), (16, 4, 64, 127, 545), (28, 4, 128, 0, 289)])
+def test_split_key_attention_edges(hq, hkv, d, c, n):
+    """Blocks too small to fill the chip, whose keys are split over the waves of a workgroup: outputs, and
+    the scores that the same launch leaves when the block does not fit."""
+    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, max(c, n // 2, 1), 600, seed=31 * c + n)
+    assert err <= U.OUT_TOL, err
+    scores_gpu, keep, dst = cache.debug_last(0)
+    U.check_scores(scores_gpu.cpu().numpy(), scores_ref, n * (hq // hkv))
+    cache.close()
+
+
 @pytest.mark.parametrize("fused", [1, 0])
 @pytest.mark.parametrize("hq,hkv,d,c,n,budget,chunk_max,scale", [
     (4, 4, 64, 128, 64, 128, 64, 0.0),
