@@ -3,13 +3,13 @@
 
 A "step" is one whole prefill of the workload: every block of the prefix
 through every layer, each as kvp_prefill_chunk (attention + scoring) followed
-by kvp_compact (select + merge + move), with Q, K, V of all layers already
+by kvp_compact (select, merge and move in one launch), with Q, K, V of all layers already
 resident in HBM.  The metric is prefill tokens/s at the fixed KV budget.
 
 Prints ONE JSON line.  `roofline` is for the attention kernel (the dominant
 one): algorithmic flops 4 d Hq (n c + n (n + 1) / 2) per launch over its HIP
 event time on the launching stream.  `rooflines` has an entry for every kernel
-of the path (scoring against its own MFMA flops; select, merge, move and the
+of the path (scoring against its own MFMA flops; the compaction, the append and the
 decode step against HBM, with the bytes taken from what this run's compactions
 actually did).  `attainable` holds what this GPU reaches on a register-resident
 bf16 MFMA loop and on a plain device copy, measured in the same run, and every
@@ -338,17 +338,17 @@ def bench_workload(wl, steps, warmup, device, threads, profile=True, streams=1, 
                 evicting_launches += 1
             c = min(wl.budget, c + n)
         appended *= wl.n_layers * prof_steps
-        select_bytes = select_bytes * wl.n_layers * prof_steps + done["moved_rows"] * 16 + done["merge_destinations"] * 32
         colsum_flops *= wl.n_layers * prof_steps
-        # a moved row: K and V read and written, token index and weight written, its plan entry read
-        move_bytes = (appended + done["moved_rows"]) * (4 * row + 8) + done["moved_rows"] * 16
-        # a merge: destination and sources read (K, V and weight), destination written, its plan entry read
-        merge_bytes = ((done["merge_destinations"] + done["merge_sources"]) * (2 * row + 4)
-                       + done["merge_destinations"] * (2 * row + 4 + 32))
+        # the compaction launch ("select") also moves and merges the rows.  A moved row: K and V read and written,
+        # token index and weight written; a merge: destination and sources read (K, V and weight),
+        # destination written.  The append launch ("move"): as a moved row.
+        select_bytes = (select_bytes * wl.n_layers * prof_steps + done["moved_rows"] * (4 * row + 8)
+                        + (done["merge_destinations"] + done["merge_sources"]) * (2 * row + 4)
+                        + done["merge_destinations"] * (2 * row + 4))
+        append_bytes = appended * (4 * row + 8)
         res["compaction_totals_per_step"] = {k: v // prof_steps for k, v in done.items()}
         res["compaction_totals_per_step"]["appended_rows"] = appended // prof_steps
-        res["hbm_bytes_per_step"] = {"select": select_bytes // prof_steps, "merge": merge_bytes // prof_steps,
-                                     "move": move_bytes // prof_steps}
+        res["hbm_bytes_per_step"] = {"select": select_bytes // prof_steps, "move": append_bytes // prof_steps}
         res["colsum_flops_per_step"] = colsum_flops // prof_steps
     cache.close()
     del data
@@ -492,7 +492,7 @@ def main():
                                "flops_per_launch", f / kern["colsum"]["launches_per_step"],
                                "the second QK^T sweep's own flops 2 d Hq (n c + n (n + 1) / 2); they are not "
                                "counted as algorithmic work of the path (see attention_plus_scoring_frac)"))
-    for name in ("select", "merge", "move"):
+    for name in ("select", "move"):
         if name in kern:
             b = main_res["hbm_bytes_per_step"][name]
             rooflines.append(entry(name, "hbm", b / (kern[name]["ms_per_step"] * 1e-3) / 1e9, "GB/s",
@@ -506,7 +506,7 @@ def main():
         if peaks:
             e["frac_of_attainable"] = round(dec["GBps_on_device"] / peaks["hbm_copy_GBps"], 4)
         rooflines.append(e)
-    compact_us = sum(kern[k]["ms_per_step"] for k in ("select", "merge", "move") if k in kern) * 1e3
+    compact_us = sum(kern[k]["ms_per_step"] for k in ("select", "move") if k in kern) * 1e3
     compact_bytes = sum(main_res["hbm_bytes_per_step"].values())
     line = {
         "metric": "prefill tokens/s at fixed KV budget (1 GPU)",

@@ -165,9 +165,8 @@ int kvp_compact(kvp_cache* cache, int32_t layer, const float* scores_override, v
  * moves up the stack (the cache needs one scratch set per layer that is pending
  * at a time), then this call once for all of them.  Layers that are in the same
  * state (same entry count, same block, scored the same way -- the case in a
- * prefill) are taken up to 16 at a time by ONE select, ONE merge and ONE move
- * launch, which fills the GPU where a single layer's KV heads cannot; others are
- * taken one by one.  The result is that of n_layers kvp_compact calls, bit for
+ * prefill) are taken up to 16 at a time by ONE launch, which fills the GPU
+ * where a single layer's KV heads cannot; others are taken one by one.  The result is that of n_layers kvp_compact calls, bit for
  * bit.  Every layer's k and v must still be valid.
  *   KVP_EINVAL  bad range;  KVP_ESTATE  a layer of the range is not PENDING
  * (both before anything is enqueued).  KVP_EDEVICE: a launch failed; the layers
@@ -183,8 +182,7 @@ int kvp_compact_layers(kvp_cache* cache, int32_t first_layer, int32_t n_layers, 
  * The layers go in groups (min(scratch_sets, 16) layers on one stream,
  * scratch_sets / 2 with a side stream), each kernel as ONE launch for the whole
  * group: the attention (which also scores by the block's own queries), the scoring
- * pass of proxy queries or of the keys, and the select, merge and move of the
- * compaction.  The results are those of the per-layer calls, bit for bit.
+ * pass of proxy queries or of the keys, and the compaction.  The results are those of the per-layer calls, bit for bit.
  * With side_stream NULL (or equal to stream) everything is enqueued on `stream`
  * in that order.  With another side_stream every kvp_compact goes there, beside
  * the attention of the layers that follow (in a model nothing after a layer's
@@ -320,7 +318,9 @@ enum {
 int kvp_debug_totals(kvp_cache* cache, const uint64_t** totals);
 
 /* Per-kernel timing with HIP events on the launching stream.  While enabled
- * every launch is bracketed by two events.  kvp_profile_read waits for the
+ * every launch is bracketed by two events.  A compaction that evicts is one launch
+ * (SELECT: it selects, merges and moves), an append is one (MOVE); MERGE has no
+ * launches of its own.  kvp_profile_read waits for the
  * recorded events, adds them up per kernel kind and clears them. */
 enum {
   KVP_K_ATTENTION = 0, KVP_K_COLSUM = 1, KVP_K_SELECT = 2, KVP_K_MERGE = 3,

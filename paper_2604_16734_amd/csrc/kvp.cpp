@@ -27,8 +27,7 @@ struct Layout {
   size_t segs_off, totals_off;
   // scratch, per set
   size_t set_off, set_bytes;
-  size_t lse_off, partial_off, scores_off, keep_off, dst_off, counts_off, moves_off, dsts_off,
-      stage_k_off, stage_v_off, stage_w_off;
+  size_t lse_off, partial_off, scores_off, keep_off, dst_off, sources_off, stage_k_off, stage_v_off, stage_w_off;
   int cand_stride, max_partials, n_sets;
   size_t total_bytes;
 };
@@ -72,22 +71,18 @@ Layout make_layout(const kvp_config& c) {
   }
   size_t s = 0;
   L.lse_off = s; s = align_up(s + (size_t)c.n_q_heads * B * 4);
-  // The partial score arrays and the staging rows of the compaction share their memory: the
-  // selection has read the last partial before the merge kernel (launched after it, on the same
-  // stream) writes the first staged row, and the next block's scoring pass writes partials only
-  // after the move kernel has read the last one (the scratch set is the layer's until then).
+  // The partial score arrays and the staging rows of the compaction do NOT share their memory: one
+  // launch reads the one and writes the other, and its workgroups run at their own pace.
   const size_t partial_bytes = align_up(H * L.max_partials * L.cand_stride * 4);
   const size_t stage_bytes = align_up(H * B * D * 2);
-  L.partial_off = s;
-  L.stage_k_off = s;
-  L.stage_v_off = s + stage_bytes;
-  s += partial_bytes > 2 * stage_bytes ? partial_bytes : 2 * stage_bytes;
+  L.partial_off = s; s += partial_bytes;
+  L.stage_k_off = s; s += stage_bytes;
+  L.stage_v_off = s; s += stage_bytes;
   L.scores_off = s; s = align_up(s + H * L.cand_stride * 4);
   L.keep_off = s; s = align_up(s + H * L.cand_stride);
   L.dst_off = s; s = align_up(s + H * L.cand_stride * 4);
-  L.counts_off = s; s = align_up(s + H * sizeof(HeadCounts));
-  L.moves_off = s; s = align_up(s + H * B * sizeof(MoveEntry));
-  L.dsts_off = s; s = align_up(s + H * B * sizeof(DstEntry));
+  L.sources_off = s;                 // source lists of the merge, for heads too large to keep them in LDS
+  if (M + B > 4 * (size_t)kSelectThreads) s = align_up(s + H * L.cand_stride * kNeighbours * 2);
   L.stage_w_off = s; s = align_up(s + H * B * 4);
   L.set_bytes = s;
   L.set_off = off;
@@ -206,7 +201,7 @@ LayerGroup make_group(const kvp_cache* c, int first, int count) {
 }
 
 // Alg. 1 lines 7-11 for `count` consecutive layers that hold the same block (same entries in the
-// cache, same tokens pending): one launch of each compaction kernel for all of them.
+// cache, same tokens pending): one launch for all of them.
 int run_compact(kvp_cache* c, int first, int count, const float* scores_override, hipStream_t s) {
   Layer& L = c->layers[first];
   const kvp_config& cfg = c->cfg;
@@ -214,66 +209,50 @@ int run_compact(kvp_cache* c, int first, int count, const float* scores_override
   unsigned char* set = c->set(first);
   const int cnt = L.count, n = L.n, M = cfg.budget;
 
-  const LayerGroup g = make_group(c, first, count);
-
-  CompactArgs ca{};
-  ca.g = g;
-  ca.k_cache = c->k_cache(first);
-  ca.v_cache = c->v_cache(first);
-  ca.token_idx = c->idx(first);
-  ca.weight = c->weight(first);
-  ca.counts = reinterpret_cast<HeadCounts*>(set + lay.counts_off);
-  ca.moves = reinterpret_cast<MoveEntry*>(set + lay.moves_off);
-  ca.dsts = reinterpret_cast<DstEntry*>(set + lay.dsts_off);
-  ca.stage_k = reinterpret_cast<u16*>(set + lay.stage_k_off);
-  ca.stage_v = reinterpret_cast<u16*>(set + lay.stage_v_off);
-  ca.stage_w = reinterpret_cast<float*>(set + lay.stage_w_off);
-  ca.c = cnt; ca.n = n; ca.t0 = L.t0; ca.budget = M;
-  ca.n_kv_heads = cfg.n_kv_heads; ca.head_dim = cfg.head_dim; ca.chunk_max = cfg.chunk_max;
-  const int rpb = rows_per_compact_block(cfg.head_dim);
+  LayerBlock blocks[kMaxGroupLayers];
+  for (int i = 0; i < count; ++i) blocks[i] = LayerBlock{c->layers[first + i].k, c->layers[first + i].v};
+  const GroupStrides g = make_group(c, first, count);
 
   if (cnt + n <= M) {
     // Alg. 1 line 8 is false: plain append
-    ca.identity = 1;
-    ca.blocks_per_head = (n + rpb - 1) / rpb;
+    CompactArgs ca{};
+    ca.g = g;
+    ca.k_cache = c->k_cache(first);
+    ca.v_cache = c->v_cache(first);
+    ca.token_idx = c->idx(first);
+    ca.weight = c->weight(first);
+    ca.c = cnt; ca.n = n; ca.t0 = L.t0; ca.budget = M;
+    ca.n_kv_heads = cfg.n_kv_heads; ca.head_dim = cfg.head_dim;
+    for (int i = 0; i < count; ++i) ca.layer[i] = blocks[i];
     return launch(c, KVP_K_MOVE, count, s, [&] { return launch_move(ca, s); });
   }
 
   SelectArgs sa{};
   sa.g = g;
-  sa.partial = scores_override ? nullptr : reinterpret_cast<const float*>(set + lay.partial_off);
+  sa.partial = reinterpret_cast<const float*>(set + lay.partial_off);
   sa.score_override = scores_override;
   sa.scores = reinterpret_cast<float*>(set + lay.scores_off);
   sa.keep = set + lay.keep_off;
   sa.dst = reinterpret_cast<int32_t*>(set + lay.dst_off);
   sa.token_idx = c->idx(first);
-  sa.counts = reinterpret_cast<HeadCounts*>(set + lay.counts_off);
-  sa.moves = reinterpret_cast<MoveEntry*>(set + lay.moves_off);
-  sa.dsts = reinterpret_cast<DstEntry*>(set + lay.dsts_off);
+  sa.weight = c->weight(first);
+  sa.k_cache = c->k_cache(first);
+  sa.v_cache = c->v_cache(first);
+  sa.sources = reinterpret_cast<u16*>(set + lay.sources_off);
+  sa.stage_k = reinterpret_cast<u16*>(set + lay.stage_k_off);
+  sa.stage_v = reinterpret_cast<u16*>(set + lay.stage_v_off);
+  sa.stage_w = reinterpret_cast<float*>(set + lay.stage_w_off);
   sa.segs = c->dev_segs();
   sa.totals = c->totals();
   sa.n_segs = (int)c->segs.size();
   sa.c = cnt; sa.n = n; sa.t0 = L.t0; sa.budget = M;
+  sa.n_kv_heads = cfg.n_kv_heads; sa.head_dim = cfg.head_dim;
   sa.cand_stride = lay.cand_stride; sa.chunk_max = cfg.chunk_max;
   sa.n_partials = L.n_partials;
   sa.merge = cfg.merge;
-  sa.items = (cnt + n + 1023) / 1024;
-  int ts = 2;
-  while (ts < 2 * (cnt + n)) ts <<= 1;
-  sa.table_size = ts;
-  int rc = launch(c, KVP_K_SELECT, count, s, [&] { return launch_select(sa, cfg.n_kv_heads, s); });
-  if (rc) return rc;
-
-  ca.identity = 0;
-  const int n_evict = cnt + n - M;
-  if (cfg.merge) {
-    const int max_dst = n_evict < cfg.chunk_max ? n_evict : cfg.chunk_max;
-    ca.blocks_per_head = (max_dst + rpb - 1) / rpb;
-    rc = launch(c, KVP_K_MERGE, count, s, [&] { return launch_merge(ca, s); });
-    if (rc) return rc;
-  }
-  ca.blocks_per_head = (n + rpb - 1) / rpb;
-  return launch(c, KVP_K_MOVE, count, s, [&] { return launch_move(ca, s); });
+  for (int i = 0; i < count; ++i) sa.layer[i] = blocks[i];
+  plan_select(sa);
+  return launch(c, KVP_K_SELECT, count, s, [&] { return launch_select(sa, cfg.n_kv_heads, s); });
 }
 
 // kvp_compact for layers [first, first + count): one group launch when they hold the same block,

@@ -21,20 +21,15 @@ constexpr int kColsumWaves = 4;                 // waves per workgroup of the co
 constexpr int kColsumTargetWorkgroups = 512;    // two per CU, all resident: the launch is a single round
 constexpr int kColsumMaxRowSplits = 16;
 constexpr int kSelectThreads = 1024;
-constexpr int kSelectCopies = 32;               // histogram replicas of the radix select
+constexpr int kSelectBins = 2048;               // histogram bins of the selection
+constexpr size_t kSelectLdsLimit = 156 * 1024;  // dynamic LDS of the compaction kernel, beside 3.5 KiB of static LDS
 constexpr int kRowstatBlockKeys = 256;          // keys per workgroup of the proxy row-statistics kernel
 constexpr int kKeydiffSliceKeys = 64;           // keys per workgroup of the key-sum kernel
 constexpr int kDecodeTile = 64;                 // keys per workgroup step of the decode kernel
 constexpr int kDecodeMaxSplits = 128;
 constexpr int kDecodeGroupLimit = 16;           // query heads per KV head the decode kernel is built for
 constexpr int kCompactThreads = 256;
-constexpr int kCompactTargetWorkgroups = 4096;  // a merge or move launch is capped at about this many workgroups
-
-// bytes of the select kernel's region that is first the radix histogram and then the compaction lists
-constexpr size_t select_region_bytes(size_t cand_pad) {
-  const size_t hist = (size_t)256 * kSelectCopies * 4, lists = cand_pad * 5;
-  return (hist > lists ? hist : lists + 15) / 16 * 16;
-}
+constexpr int kCompactTargetWorkgroups = 4096;  // an append launch is capped at about this many workgroups
 
 // A launch covers a group of consecutive layers that hold the same block (same c, n, t0).  The cache
 // and scratch pointers in a kernel's arguments are those of the group's FIRST layer; layer i of the
@@ -169,59 +164,49 @@ struct Seg {
   int begin, n, kind, gh, gw, planes, temporal;
 };
 
-// Per-head outputs of the select kernel, inputs of merge and move.
-struct HeadCounts {
-  int n_moves;   // kept block tokens = free slots filled
-  int n_dst;     // merge destinations that have at least one source
-  int pad0, pad1;
-};
-struct MoveEntry {
-  int pos;    // candidate position (>= c) of the kept block token
-  int slot;   // cache slot it goes to
-  int stage;  // index into the staging rows if the token is a merge destination, else -1
-  int pad;
-};
-struct DstEntry {
-  int pos;                  // candidate position of the destination
-  int n_src;
-  int src[kNeighbours];     // candidate positions of its sources
+struct LayerBlock {
+  const u16* k_new;             // [n, Hkv, D] the block's keys and values of one layer
+  const u16* v_new;
 };
 
-
+// Compaction of a group of layers whose block does not fit (select.hip); what a workgroup needs first lies
+// together, as in AttnArgs.
 struct SelectArgs {
-  LayerGroup g;
-  const float* partial;         // [Hkv, n_partials, cand_stride] or null when override is set
-  const float* score_override;  // [Hkv, n_cand] or null
+  int c, n, t0, budget, cand_stride, chunk_max, n_partials, merge;
+  int n_kv_heads, head_dim, n_segs;
+  int items;                    // candidates per thread
+  int direct;                   // the token table has one entry per token before t0, not a hash of them
+  int table_size;               // entries, a multiple of 8 (hash: a power of two >= 2 * (c + n))
+  int quads;                    // fours of neighbouring candidates
+  int width, groups;            // the threads sum the partial arrays as `groups` groups of `width`
+  GroupStrides g;
+  const float* partial;         // [Hkv, n_partials, cand_stride]
+  const float* score_override;  // [Hkv, n_cand] used instead, or null
+  int32_t* token_idx;           // the group's first layer: [Hkv, M]
+  float* weight;
   float* scores;                // [Hkv, cand_stride]   scores actually used
   uint8_t* keep;                // [Hkv, cand_stride]
   int32_t* dst;                 // [Hkv, cand_stride]
-  const int32_t* token_idx;     // this layer: [Hkv, M]
-  HeadCounts* counts;           // [Hkv]
-  MoveEntry* moves;             // [Hkv, chunk_max]
-  DstEntry* dsts;               // [Hkv, chunk_max]
   const Seg* segs;
+  u16* k_cache;                 // the group's first layer: [Hkv, M, D]
+  u16* v_cache;
+  u16* sources;                 // [Hkv, cand_stride, kNeighbours]: source lists that do not fit into LDS
+  u16* stage_k;                 // [Hkv, chunk_max, D]
+  u16* stage_v;
+  float* stage_w;               // [Hkv, chunk_max]
   unsigned long long* totals;   // [KVP_T_COUNT] running totals of the cache (kvp_debug_totals)
-  int n_segs;
-  int c, n, t0, budget, cand_stride, chunk_max, n_partials, merge;
-  int items;                    // candidates per thread
-  int table_size;               // power of two >= 2 * (c + n)
+  LayerBlock layer[kMaxGroupLayers];
 };
 
+// The append of a block that fits, for a group of layers (compact.hip).
 struct CompactArgs {
-  LayerGroup g;
-  u16* k_cache;            // the group's first layer
+  int c, n, t0, budget, n_kv_heads, head_dim;
+  GroupStrides g;
+  u16* k_cache;                 // the group's first layer
   u16* v_cache;
   int32_t* token_idx;
   float* weight;
-  const HeadCounts* counts;
-  const MoveEntry* moves;
-  const DstEntry* dsts;
-  u16* stage_k;            // [Hkv, chunk_max, D]
-  u16* stage_v;
-  float* stage_w;          // [Hkv, chunk_max]
-  int c, n, t0, budget, n_kv_heads, head_dim, chunk_max;
-  int identity;            // 1: plain append of all n tokens to slots c..c+n-1
-  int blocks_per_head;
+  LayerBlock layer[kMaxGroupLayers];
 };
 
 // launchers (each returns the hipError_t of the launch)
@@ -229,7 +214,6 @@ hipError_t launch_attention(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_attention_split(const AttnArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_colsum(const ColsumArgs& a, int head_dim, hipStream_t s);
 hipError_t launch_select(const SelectArgs& a, int n_kv_heads, hipStream_t s);   // grid: heads x a.g.n_layers
-hipError_t launch_merge(const CompactArgs& a, hipStream_t s);
 hipError_t launch_move(const CompactArgs& a, hipStream_t s);
 hipError_t launch_init(int32_t* token_idx, float* weight, size_t n_slots, const Seg* host_segs,
                        int n_segs, Seg* dev_segs, unsigned long long* totals, hipStream_t s);
@@ -244,6 +228,7 @@ hipError_t prepare_attention();   // function attributes on the current device; 
 hipError_t prepare_select();
 void plan_colsum(ColsumArgs& a, int head_dim);
 int colsum_max_partials(int group, int chunk_max);
-size_t select_lds_bytes(int n_cand, int items, int table_size);
+size_t select_lds_bytes(const SelectArgs& a);
+void plan_select(SelectArgs& a);
 
 }  // namespace kvp

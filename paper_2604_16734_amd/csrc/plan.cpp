@@ -85,10 +85,33 @@ void plan_colsum(ColsumArgs& a, int /*head_dim*/) {
 }
 
 
-// ---- selection
-size_t select_lds_bytes(int /*n_cand*/, int items, int table_size) {
-  const size_t cand_pad = (size_t)items * kSelectThreads;
-  return cand_pad * (4 + 4 + 1) + select_region_bytes(cand_pad) + (size_t)table_size * 2;
+// ---- selection and compaction
+// key, cnt, evicted, free_slot; the histogram; the token table; the source lists or, before them, the score
+// sums (up to 4096 candidates; beyond that the lists are in the scratch set and the sums lie elsewhere)
+size_t select_lds_bytes(const SelectArgs& a) {
+  const size_t cand_pad = (size_t)a.items * kSelectThreads;
+  const size_t lists = a.items > 4 ? 0 : cand_pad * kNeighbours * 2, sums = a.items > 4 ? 0 : (size_t)a.groups * a.quads * 16;
+  return cand_pad * (8 + 1 + 2 + 2) + kSelectBins * 4 + (size_t)a.table_size * 2 + (lists > sums ? lists : sums);
+}
+
+// A thread owns ceil(n_cand / 1024) neighbouring candidates.  For the sums of the partial arrays the threads
+// form groups of 64, 128 or 256 (the fewest that cover the candidates in fours, 256 at most) that take
+// every groups-th array, so that all of them have loads in flight whatever the number of candidates.
+// The token table has an entry for every token before the block where LDS has room for that.
+void plan_select(SelectArgs& a) {
+  const int n_cand = a.c + a.n;
+  a.items = (n_cand + kSelectThreads - 1) / kSelectThreads;
+  a.quads = (n_cand + 3) / 4;
+  a.width = a.items > 4 ? kSelectThreads : a.quads <= 64 ? 64 : a.quads <= 128 ? 128 : 256;
+  a.groups = a.score_override ? 1 : kSelectThreads / a.width;
+  if (a.groups > a.n_partials) a.groups = a.n_partials < 1 ? 1 : a.n_partials;
+  a.direct = 1;
+  a.table_size = ((a.t0 > n_cand ? a.t0 : n_cand) + 7) / 8 * 8;       // (it becomes the list of destinations, too)
+  if (!a.merge || select_lds_bytes(a) > kSelectLdsLimit) {
+    a.direct = 0;
+    a.table_size = 8;
+    while (a.merge && a.table_size < 2 * n_cand) a.table_size <<= 1;
+  }
 }
 
 // ---- compaction: row pairs (K row and V row of a slot, 16 bytes per lane) a workgroup carries

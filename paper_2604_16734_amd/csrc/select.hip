@@ -1,34 +1,61 @@
-// Per-head selection of the M candidates to keep (Alg. 1 lines 8-11, with the
-// rule of Sec. 3.2 that the lowest importance scores leave first), the slot
-// assignment of the kept block tokens, and the grid-neighbour merge plan.
+// Compaction of a layer's cache (Alg. 1 lines 8-11): per KV head the selection of the M candidates to keep
+// (the lowest importance scores leave first, Sec. 3.2), the slots of the kept block tokens, the
+// grid-neighbour merge of the evicted visual tokens, and the rows themselves, in place.
 //
-// One workgroup of 1024 threads per KV head; everything lives in LDS.
+// One workgroup of 1024 threads per KV head and layer does all of it.  A head's rows that change are few
+// (at 32/8 heads, 1024 new over 2048 cached: 175 merge destinations, 212 sources and 88 moved rows,
+// 0.4 MB), so one CU moves them in a few microseconds, and one launch replaces three whose
+// plans had to go through memory.  What bounds it is the chain of its phases: memory round trips,
+// LDS atomics, block scans, barriers.  With 16 layers in a launch the chains of 128 heads run side by
+// side.
+//   * scores: the partial column sums of a head are added up by groups of threads, sixteen bytes per
+//     load and sixteen loads in flight, each group every G-th array; the groups' sums meet in LDS, in a fixed order.
 //   * order: 64-bit key = (score as order-preserving u32) << 32 | ~token, so
 //     "higher score first, equal scores by lower token index" is "larger key
 //     first" and all keys are distinct: the kept set is unique.
-//   * the M-th largest key is found by an 8-bit radix select from the top
-//     byte down (at most 8 passes, early exit once the chosen bin holds one
-//     key).  Float scores share their top bits, so each histogram bin is
-//     replicated 32 times, indexed by lane, to spread LDS atomic contention.
+//   * the M-th largest key: one histogram of 2048 bins over the range the keys really span (a scale on
+//     float bits, so roughly logarithmic in the score), the bin that holds it, and then a ranking of
+//     the few keys in that bin by every wave for itself.  Should more than 64 keys share the bin
+//     (equal scores) the range shrinks to the bin and the histogram is taken again.
 //   * block-wide prefix sums rank the free slots and the kept block tokens;
 //     the k-th kept block token (ascending token index) gets the k-th free slot.
-//   * merge plan: a token -> position hash table over the cached tokens (block
-//     tokens map directly); every evicted visual candidate looks at its grid
-//     neighbours, takes the kept one with the largest key and counts itself in
-//     at that destination; a prefix sum numbers the destinations that were
-//     chosen, and the sources then write themselves into their destination's
-//     entry (the merge kernel sorts each entry, so the order they arrive in
-//     does not matter).
+//   * merge plan: a token -> position table over the cached tokens (block tokens map directly): one entry per
+//     token of the prefix so far where that fits into LDS (some tens of thousands), a hash table
+//     beyond.  Every evicted visual candidate looks at its grid neighbours, takes the kept one with the
+//     largest key and writes itself into that destination's list of at most six sources.
+//     (Walking the hash table was 3 of the 4.5 us of this phase: six chains of dependent LDS reads per lane,
+//     and the wave waits for its longest.)
+//   * merge: destination and sources of a row pair (the K row and the V row of one slot, 16 bytes per lane)
+//     are fetched together, four destinations in flight per group of lanes; sources are sorted by
+//     candidate position first, so that the fp32 sum is taken in one fixed order.  A destination in the
+//     cache is rewritten in place (no other row reads it: sources are evicted rows, destinations kept
+//     ones); one among the block's tokens goes to a staging row, because the slot it will get may
+//     still be a source.
+//   * move: kept block rows, or their staging rows, into the free slots.
+#include <type_traits>
+
 #include "kvp_internal.h"
 
 namespace kvp {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
 namespace {
 
 constexpr int kThreads = kSelectThreads;
 constexpr int kWaves = kThreads / 64;
 constexpr int kMaxItemsAny = KVP_MAX_CANDIDATES / kThreads;   // 8
-constexpr int kCopies = kSelectCopies;                     // histogram replicas
+constexpr int kBins = kSelectBins;
 constexpr unsigned kNone16 = 0xFFFFu;
+
+__device__ __forceinline__ float bf16_lo(unsigned x) { return __uint_as_float(x << 16); }
+__device__ __forceinline__ float bf16_hi(unsigned x) { return __uint_as_float(x & 0xFFFF0000u); }
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
+  f32x2 v = {lo, hi};
+  bf16x2 b = __builtin_convertvector(v, bf16x2);
+  return __builtin_bit_cast(unsigned, b);
+}
 
 __device__ __forceinline__ unsigned order_bits(float x) {
   if (x == 0.f) x = 0.f;   // -0 and +0 rank equal
@@ -37,7 +64,7 @@ __device__ __forceinline__ unsigned order_bits(float x) {
 }
 
 __device__ __forceinline__ unsigned long long make_key(unsigned ob, int tok) {
-  return ((unsigned long long)ob << 32) | (unsigned long long)(0xFFFFFFFFu - (unsigned)tok);
+  return ((unsigned long long)ob << 32) | (unsigned long long)~(unsigned)tok;
 }
 
 __device__ __forceinline__ unsigned hash_tok(int tok, unsigned mask) {
@@ -46,16 +73,42 @@ __device__ __forceinline__ unsigned hash_tok(int tok, unsigned mask) {
   return x & mask;
 }
 
+// Wave-wide scans and reductions on the DPP network (rows of 16 lanes, then across rows): a few cycles a
+// step, where a shuffle through LDS costs a hundred.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ unsigned dpp(unsigned identity, unsigned x) {
+  return (unsigned)__builtin_amdgcn_update_dpp((int)identity, (int)x, kCtrl, kRowMask, 0xF, false);
+}
+template <class Op>
+__device__ __forceinline__ unsigned wave_scan(unsigned x, unsigned identity, Op op) {     // inclusive
+  x = op(x, dpp<0x111, 0xF>(identity, x));   // row_shr 1, 2, 4, 8
+  x = op(x, dpp<0x112, 0xF>(identity, x));
+  x = op(x, dpp<0x114, 0xF>(identity, x));
+  x = op(x, dpp<0x118, 0xF>(identity, x));
+  x = op(x, dpp<0x142, 0xA>(identity, x));   // the last lane of a row into the next row (rows 1 and 3)
+  x = op(x, dpp<0x143, 0xC>(identity, x));   // the last lane of the first half into the second
+  return x;
+}
+struct Add { __device__ __forceinline__ unsigned operator()(unsigned a, unsigned b) const { return a + b; } };
+struct Min { __device__ __forceinline__ unsigned operator()(unsigned a, unsigned b) const { return a < b ? a : b; } };
+struct Max { __device__ __forceinline__ unsigned operator()(unsigned a, unsigned b) const { return a > b ? a : b; } };
+__device__ __forceinline__ unsigned last_lane(unsigned x) { return (unsigned)__builtin_amdgcn_readlane((int)x, 63); }
+
+// word of histogram bin b: bins 32 L .. 32 L + 31 are lane L's, and the lanes of a wave read four of theirs at a
+// time from consecutive 16-byte pieces (in bin order the pieces would lie 128 bytes apart, in two of the
+// sixteen bank groups: 2 us of the selection)
+__device__ __forceinline__ unsigned bin_word(unsigned b) { return ((b & 28u) << 6) | ((b >> 5) << 2) | (b & 3u); }
+static_assert(kBins == 32 * 64, "bin_word is a permutation of the bins");
+
 struct Lds {
-  unsigned* sc;       // [cand_pad] order-preserving score bits; later the ordinal of a merge destination
-  int* tok;           // [cand_pad]
-  unsigned char* keep;        // [cand_pad]; reused as per-destination fill counters
-  // one region, two lives: the radix histogram (256 x kCopies u32), then the compaction lists
-  unsigned* hist;
-  unsigned short* evicted;    // [cand_pad] positions of the evicted candidates, ascending
-  unsigned short* free_dst;   // [cand_pad] free slots by rank; then the destination of the e-th evicted
+  unsigned long long* key;    // [cand_pad] low word ~token, high word order-preserving score bits; at the end the
+                              // high word is the staging row of a destination
   unsigned* cnt;              // [cand_pad / 4] one byte per candidate: sources that chose it
-  unsigned* table;    // token -> position of the cached tokens: table_size u16, open addressing
+  unsigned short* evicted;    // [cand_pad] positions of the evicted candidates; later those of the moved rows
+  unsigned short* free_slot;  // [cand_pad] free slots by rank
+  unsigned* hist;             // [kBins]
+  unsigned* table;    // token -> position of the cached tokens, u16; later the destinations
+  float* sums;        // [groups][4 * quads] sums of the partial arrays by group
 };
 
 __device__ __forceinline__ void table_insert(unsigned* words, unsigned mask, int tok, unsigned pos) {
@@ -78,11 +131,12 @@ __device__ __forceinline__ unsigned table_entry(const Lds& l, unsigned h) {
   return (l.table[h >> 1] >> ((h & 1u) * 16u)) & 0xFFFFu;
 }
 
-// position of cached token `tok`, or -1, when its home slot `h` holds `e` and that is not it
-__device__ __forceinline__ int probe_on(const Lds& l, unsigned mask, int tok, unsigned h, unsigned e) {
+// position of cached token `tok`, or -1
+__device__ __forceinline__ int probe(const Lds& l, unsigned mask, int tok) {
+  unsigned h = hash_tok(tok, mask), e = table_entry(l, h);
   for (;;) {
     if (e == kNone16) return -1;
-    if (l.tok[e] == tok) return (int)e;
+    if ((unsigned)l.key[e] == ~(unsigned)tok) return (int)e;
     h = (h + 1) & mask;
     e = table_entry(l, h);
   }
@@ -127,233 +181,237 @@ __device__ __forceinline__ bool neighbours(const SegL* segs, int n_segs, int tok
   return false;
 }
 
-// kMaxItems: candidates a thread can own (4 covers up to 4096 candidates and halves the registers
-// of the batched loads; 8 covers the limit)
-template <int kMaxItems>
+// One row pair of `D` channels: 2 D / 8 lanes of 16 bytes, K row then V row.
+template <int D>
+struct Lanes {
+  static constexpr int kPerRow = D / 8;
+  static constexpr int kPerPair = 2 * kPerRow;
+  static constexpr int kPairs = kThreads / kPerPair;   // row pairs the workgroup carries at a time
+};
+
+// kMaxItems: candidates a thread can own (4 covers up to 4096 candidates, with the source lists in LDS;
+// 8 covers the limit, with the source lists in the scratch set)
+template <int D, int kMaxItems>
 __global__ void __launch_bounds__(kThreads)
-select_kernel(const SelectArgs a_first) {
-  // grid (KV heads, layers of the group): this workgroup's layer
-  SelectArgs a = a_first;
-  {
-    const int li = blockIdx.y;
-    a.partial = in_set_of(a.partial, a.g, li);
-    a.scores = in_set_of(a.scores, a.g, li);
-    a.keep = in_set_of(a.keep, a.g, li);
-    a.dst = in_set_of(a.dst, a.g, li);
-    a.counts = in_set_of(a.counts, a.g, li);
-    a.moves = in_set_of(a.moves, a.g, li);
-    a.dsts = in_set_of(a.dsts, a.g, li);
-    a.token_idx += (long long)li * a.g.meta_stride;
-  }
+compact_kernel(const SelectArgs a) {
+  constexpr bool kListsInLds = kMaxItems <= 4;
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  __shared__ unsigned long long s_threshold;
-  __shared__ unsigned s_digit, s_want, s_bin_count;
-  __shared__ unsigned s_bin[256];
-  __shared__ unsigned s_wave_tot[kWaves], s_wave_ev[kWaves];
-  __shared__ unsigned s_wave_diff[2 * kWaves];
+  __shared__ unsigned long long s_members[64];
+  __shared__ unsigned s_n_members, s_n_dst, s_n_src;
+  __shared__ unsigned s_wave_tot[kWaves], s_wave_ev[kWaves], s_wave_min[kWaves], s_wave_max[kWaves];
   __shared__ SegL s_segs[KVP_MAX_SEGMENTS];
 
-  const int hk = blockIdx.x;
+  const int hk = blockIdx.x, li = blockIdx.y;          // grid (KV heads, layers of the group)
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = a.c, n = a.n, n_cand = c + n, budget = a.budget;
   const int items = a.items;
   const int cand_pad = items * kThreads;
   const unsigned mask = (unsigned)a.table_size - 1u;
+  int* const token_idx = a.token_idx + (long long)li * a.g.meta_stride + (size_t)hk * budget;
+  float* const weight = a.weight + (long long)li * a.g.meta_stride + (size_t)hk * budget;
 
   Lds l;
+  unsigned short* sources;                             // [candidate][kNeighbours]
   {
     unsigned char* p = lds_raw;
-    l.sc = reinterpret_cast<unsigned*>(p); p += (size_t)cand_pad * 4;
-    l.tok = reinterpret_cast<int*>(p); p += (size_t)cand_pad * 4;
-    l.keep = p; p += (size_t)cand_pad;
-    l.hist = reinterpret_cast<unsigned*>(p);
-    l.evicted = reinterpret_cast<unsigned short*>(p);
-    l.free_dst = reinterpret_cast<unsigned short*>(p + (size_t)cand_pad * 2);
-    l.cnt = reinterpret_cast<unsigned*>(p + (size_t)cand_pad * 4);
-    p += select_region_bytes(cand_pad);
-    l.table = reinterpret_cast<unsigned*>(p);
+    l.key = reinterpret_cast<unsigned long long*>(p); p += (size_t)cand_pad * 8;
+    l.cnt = reinterpret_cast<unsigned*>(p); p += (size_t)cand_pad;
+    l.evicted = reinterpret_cast<unsigned short*>(p); p += (size_t)cand_pad * 2;
+    l.free_slot = reinterpret_cast<unsigned short*>(p); p += (size_t)cand_pad * 2;
+    l.hist = reinterpret_cast<unsigned*>(p); p += kBins * 4;
+    l.table = reinterpret_cast<unsigned*>(p); p += (size_t)a.table_size * 2;
+    if constexpr (kListsInLds) {
+      l.sums = reinterpret_cast<float*>(p);            // dead when the lists begin
+      sources = reinterpret_cast<unsigned short*>(p);
+    } else {
+      l.sums = reinterpret_cast<float*>(l.evicted);    // one group; dead when those lists begin
+      sources = in_set_of(a.sources, a.g, li) + (size_t)hk * a.cand_stride * kNeighbours;
+    }
   }
+  unsigned* const key_words = reinterpret_cast<unsigned*>(l.key);
+  unsigned short* const direct = reinterpret_cast<unsigned short*>(l.table);
 
-  // ---- token indices, the token -> position table of the cached ones, and the scores (sum of
-  // the partial column sums in a fixed order).  Thread t takes candidates t, t + 1024, ...; the
-  // loads of a batch of partials of all of them are in flight together, and the first batch is
-  // on its way while the table is filled.
-  float* scores = a.scores + (size_t)hk * a.cand_stride;
+  // ---- token indices, the token -> position table of the cached ones, and the sums of the partial arrays:
+  // the threads are `groups` groups of `width`; thread t adds up the fours of neighbouring candidates
+  // t % width, + width, ... over the arrays t / width, + groups, ...
   {
     int tokv[kMaxItems];
 #pragma unroll
     for (int i = 0; i < kMaxItems; ++i) {
       const int p = tid + i * kThreads;
       tokv[i] = 0;
-      if (i < items && p < n_cand) tokv[i] = p < c ? a.token_idx[(size_t)hk * budget + p] : a.t0 + (p - c);
+      if (i < items && p < n_cand) tokv[i] = p < c ? token_idx[p] : a.t0 + (p - c);
     }
-    float acc[kMaxItems];
-#pragma unroll
-    for (int i = 0; i < kMaxItems; ++i) acc[i] = 0.f;
-    const float* part = a.partial + (size_t)hk * a.n_partials * a.cand_stride;
-    constexpr int kBatch = kMaxItems <= 4 ? 8 : 4;             // partials fetched together
-    const int n_rounds = a.score_override ? 0 : (a.n_partials + kBatch - 1) / kBatch;
-    float v[kBatch][kMaxItems];
-    auto fetch = [&](int round) __attribute__((always_inline)) {
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const int j = min(kBatch * round + u, a.n_partials - 1);      // a surplus slot repeats the last partial
-#pragma unroll
-        for (int i = 0; i < kMaxItems; ++i)
-          if (i < items) v[u][i] = part[(size_t)j * a.cand_stride + min(tid + i * kThreads, n_cand - 1)];
+    for (int i = tid; i < kBins; i += kThreads) l.hist[i] = 0u;
+    if (tid == 0) { s_n_members = 0u; s_n_dst = 0u; s_n_src = 0u; }
+    if (a.merge) {
+      for (int i = tid; i < a.table_size / 8; i += kThreads)
+        reinterpret_cast<uint4*>(l.table)[i] = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
+      for (int i = tid; i < cand_pad / 4; i += kThreads) l.cnt[i] = 0u;
+      if (tid < a.n_segs) {
+        const Seg g = a.segs[tid];
+        SegL sl;
+        sl.begin = g.begin; sl.n = g.n; sl.kind = g.kind; sl.gh = g.gh; sl.gw = g.gw;
+        sl.planes = g.planes; sl.temporal = g.temporal;
+        sl.per = g.gh * g.gw;
+        sl.inv_per = sl.per > 0 ? 1.f / (float)sl.per : 0.f;
+        sl.inv_gw = g.gw > 0 ? 1.f / (float)g.gw : 0.f;
+        s_segs[tid] = sl;
       }
-    };
-    auto add = [&](int round) __attribute__((always_inline)) {
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u)
-#pragma unroll
-        for (int i = 0; i < kMaxItems; ++i)
-          if (i < items && kBatch * round + u < a.n_partials) acc[i] += v[u][i];
-    };
-    if (n_rounds > 0) fetch(0);
+    }
     if (a.score_override) {
+      for (int p = tid; p < n_cand; p += kThreads) l.sums[p] = a.score_override[(size_t)hk * n_cand + p];
+    } else {
+      const int grp = tid / a.width, quad0 = tid % a.width;              // width is a power of two
+      const int n_arrays = grp < a.groups ? (a.n_partials - grp + a.groups - 1) / a.groups : 0;
+      // a scalar base per array, a lane offset that never changes
+      const float* const part = in_set_of(a.partial, a.g, li) + (size_t)hk * a.n_partials * a.cand_stride;
+      const unsigned lane_off = (unsigned)(grp * a.cand_stride + 4 * quad0);
+      auto sum_arrays = [&](auto passes, auto batch) __attribute__((always_inline)) {
+        constexpr int kPasses = decltype(passes)::value, kBatch = decltype(batch)::value;
+        float4 acc[kPasses];
+#pragma unroll
+        for (int s = 0; s < kPasses; ++s) acc[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int first = 0; first < n_arrays; first += kBatch) {
+          float4 v[kBatch][kPasses];
+#pragma unroll
+          for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+            for (int s = 0; s < kPasses; ++s) {
+              v[u][s] = make_float4(0.f, 0.f, 0.f, 0.f);
+              if (first + u < n_arrays && quad0 + s * a.width < a.quads)
+                v[u][s] = *reinterpret_cast<const float4*>(part + (size_t)((first + u) * a.groups * a.cand_stride + 4 * s * a.width) + lane_off);
+            }
+#pragma unroll
+          for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+            for (int s = 0; s < kPasses; ++s) {
+              acc[s].x += v[u][s].x; acc[s].y += v[u][s].y; acc[s].z += v[u][s].z; acc[s].w += v[u][s].w;
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < kPasses; ++s)
+          if (n_arrays > 0 && quad0 + s * a.width < a.quads)
+            *reinterpret_cast<float4*>(l.sums + (size_t)(grp * a.quads + quad0 + s * a.width) * 4) = acc[s];
+      };
+      if constexpr (kMaxItems > 4) {
+        sum_arrays(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
+      } else {
+        if (a.quads <= a.width) sum_arrays(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
+        else sum_arrays(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kMaxItems; ++i) {
+      const int p = tid + i * kThreads;
+      if (i < items && p < n_cand) key_words[2 * p] = ~(unsigned)tokv[i];
+    }
+    __syncthreads();
+    if (a.merge) {
 #pragma unroll
       for (int i = 0; i < kMaxItems; ++i) {
         const int p = tid + i * kThreads;
-        if (i < items && p < n_cand) acc[i] = a.score_override[(size_t)hk * n_cand + p];
-      }
-    }
-    for (int i = tid; i < a.table_size / 2; i += kThreads) l.table[i] = 0xFFFFFFFFu;
-    if (tid < a.n_segs) {
-      const Seg g = a.segs[tid];
-      SegL sl;
-      sl.begin = g.begin; sl.n = g.n; sl.kind = g.kind; sl.gh = g.gh; sl.gw = g.gw;
-      sl.planes = g.planes; sl.temporal = g.temporal;
-      sl.per = g.gh * g.gw;
-      sl.inv_per = sl.per > 0 ? 1.f / (float)sl.per : 0.f;
-      sl.inv_gw = g.gw > 0 ? 1.f / (float)g.gw : 0.f;
-      s_segs[tid] = sl;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kMaxItems; ++i) {
-      const int p = tid + i * kThreads;
-      if (i < items && p < n_cand) {
-        l.tok[p] = tokv[i];
-        if (a.merge && p < c) table_insert(l.table, mask, tokv[i], (unsigned)p);
-      }
-    }
-    for (int round = 0; round < n_rounds; ++round) {
-      add(round);
-      if (round + 1 < n_rounds) fetch(round + 1);
-    }
-#pragma unroll
-    for (int i = 0; i < kMaxItems; ++i) {
-      const int p = tid + i * kThreads;
-      if (i < items && p < n_cand) {
-        scores[p] = acc[i];
-        l.sc[p] = order_bits(acc[i]);
+        if (i < items && p < c) {
+          if (a.direct) direct[tokv[i]] = (unsigned short)p;
+          else table_insert(l.table, mask, tokv[i], (unsigned)p);
+        }
       }
     }
   }
-  __syncthreads();
 
   // ---- own candidates, blocked: thread t owns positions [t * items, (t + 1) * items)
+  float* const scores = in_set_of(a.scores, a.g, li) + (size_t)hk * a.cand_stride;
   unsigned long long key[kMaxItems];
   bool valid[kMaxItems];
+  unsigned ob_min = 0xFFFFFFFFu, ob_max = 0u;
 #pragma unroll
   for (int i = 0; i < kMaxItems; ++i) {
     const int p = tid * items + i;
     valid[i] = i < items && p < n_cand;
-    key[i] = valid[i] ? make_key(l.sc[p], l.tok[p]) : 0ull;
-  }
-
-  // ---- radix select of the budget-th largest key, eight bits at a time, starting at the highest
-  // bit in which any two keys differ (float scores share their sign and most of the exponent,
-  // and digits spent on a common prefix would tell nothing apart)
-  // (the bits in which some key differs from candidate 0 are the bits in which any two differ)
-  const unsigned long long ref = make_key(l.sc[0], l.tok[0]);
-  unsigned diff_hi = 0, diff_lo = 0;
-#pragma unroll
-  for (int i = 0; i < kMaxItems; ++i)
+    key[i] = 0ull;
     if (valid[i]) {
-      diff_hi |= (unsigned)((key[i] ^ ref) >> 32);
-      diff_lo |= (unsigned)(key[i] ^ ref);
+      float s = l.sums[p];
+      for (int grp = 1; grp < a.groups; ++grp) s += l.sums[(size_t)grp * a.quads * 4 + p];
+      scores[p] = s;
+      const unsigned ob = order_bits(s);
+      key[i] = ((unsigned long long)ob << 32) | key_words[2 * p];
+      key_words[2 * p + 1] = ob;
+      ob_min = min(ob_min, ob);
+      ob_max = max(ob_max, ob);
     }
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    diff_hi |= __shfl_xor(diff_hi, off, 64);
-    diff_lo |= __shfl_xor(diff_lo, off, 64);
   }
-  if (lane == 0) { s_wave_diff[2 * wave] = diff_hi; s_wave_diff[2 * wave + 1] = diff_lo; }
+  ob_min = last_lane(wave_scan(ob_min, 0xFFFFFFFFu, Min{}));
+  ob_max = last_lane(wave_scan(ob_max, 0u, Max{}));
+  if (lane == 0) { s_wave_min[wave] = ob_min; s_wave_max[wave] = ob_max; }
   __syncthreads();
 #pragma unroll
-  for (int w2 = 0; w2 < kWaves; ++w2) { diff_hi |= s_wave_diff[2 * w2]; diff_lo |= s_wave_diff[2 * w2 + 1]; }
-  const unsigned long long diff = ((unsigned long long)diff_hi << 32) | diff_lo;
-  int top = diff ? 64 - __builtin_clzll(diff) : 0;             // bits [0, top) are still undecided
-  unsigned long long prefix = top >= 64 ? 0ull : (ref >> top) << top;
-  unsigned want = (unsigned)budget;
-  bool found_unique = false;
-  while (top > 0 && !found_unique) {
-    const int width = top < 8 ? top : 8;
-    const int lo = top - width;
-    for (int i = tid; i < 256 * kCopies; i += kThreads) l.hist[i] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kMaxItems; ++i) {
-      if (!valid[i]) continue;
-      const bool match = top >= 64 || (key[i] >> top) == (prefix >> top);
-      if (match)
-        atomicAdd(&l.hist[(unsigned)((key[i] >> lo) & ((1u << width) - 1u)) * kCopies + (lane & (kCopies - 1))], 1u);
-    }
-    __syncthreads();
-    {  // bin totals: 4 threads per bin, 8 replicas each, taken in an order that keeps the 64 lanes
-       // of a wave on 64 different banks (bin b, replica r is word 32 b + r)
-      const int bin = tid >> 2, part = tid & 3;
-      unsigned t = 0;
-#pragma unroll
-      for (int k = 0; k < kCopies / 4; ++k)
-        t += l.hist[bin * kCopies + ((4 * (bin >> 1) + part + 4 * k) & (kCopies - 1))];
-      t += __shfl_xor(t, 1, 64);
-      t += __shfl_xor(t, 2, 64);
-      if (part == 0) s_bin[bin] = t;
-    }
-    __syncthreads();
-    if (wave == 0) {
-      // lane L owns bins 4L .. 4L+3; suffix sums count the keys in higher bins
-      unsigned cnt[4];
-#pragma unroll
-      for (int b = 0; b < 4; ++b) cnt[b] = s_bin[4 * lane + b];
-      const unsigned mine = cnt[0] + cnt[1] + cnt[2] + cnt[3];
-      unsigned suf = mine;
-#pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const unsigned v = __shfl_down(suf, off, 64);
-        if (lane + off < 64) suf += v;
-      }
-      unsigned above = suf - mine;
-#pragma unroll
-      for (int b = 3; b >= 0; --b) {
-        if (above < want && want <= above + cnt[b]) {
-          s_digit = 4 * lane + b;
-          s_want = want - above;
-          s_bin_count = cnt[b];
-        }
-        above += cnt[b];
-      }
-    }
-    __syncthreads();
-    prefix |= (unsigned long long)s_digit << lo;
-    want = s_want;
-    if (s_bin_count == 1) {
-      // the bin holds exactly the key we are after
+  for (int w2 = 0; w2 < kWaves; ++w2) { ob_min = min(ob_min, s_wave_min[w2]); ob_max = max(ob_max, s_wave_max[w2]); }
+
+  // ---- the budget-th largest key
+  unsigned long long threshold;
+  {
+    unsigned long long lo = (unsigned long long)ob_min << 32;           // every key of interest is in [lo, lo + (kBins << shift))
+    const unsigned long long span = (((unsigned long long)ob_max << 32) | 0xFFFFFFFFull) - lo;
+    constexpr int kBinBits = 11;
+    static_assert((1 << kBinBits) == kBins, "bins");
+    int shift = max(0, 64 - (int)__builtin_clzll(span) - kBinBits);
+    unsigned want = (unsigned)budget, in_bin = 0;
+    for (;;) {
 #pragma unroll
       for (int i = 0; i < kMaxItems; ++i)
-        if (valid[i] && (key[i] >> lo) == (prefix >> lo)) s_threshold = key[i];
-      found_unique = true;
+        if (valid[i] && key[i] >= lo) {
+          const unsigned long long bin = (key[i] - lo) >> shift;
+          if (bin < (unsigned long long)kBins) atomicAdd(&l.hist[bin_word((unsigned)bin)], 1u);
+        }
+      __syncthreads();
+      // every wave finds the bin for itself: lane L adds up bins 32 L .. 32 L + 31, a scan over the lanes finds
+      // the lane with the wanted key, and a second one, of that lane's bins, the bin
+      unsigned mine = 0;
+#pragma unroll
+      for (int b = 0; b < kBins / 64; b += 4) {
+        const uint4 v = *reinterpret_cast<const uint4*>(&l.hist[64 * b + 4 * lane]);
+        mine += v.x + v.y + v.z + v.w;
+      }
+      const unsigned upto = wave_scan(mine, 0u, Add{});
+      const unsigned above = last_lane(upto) - upto;                 // keys in the bins of higher lanes
+      const int owner = __builtin_ctzll(__ballot(above < want && want <= above + mine));
+      want -= (unsigned)__builtin_amdgcn_readlane((int)above, owner);
+      const unsigned one = lane < 32 ? l.hist[bin_word(32u * (unsigned)owner + (unsigned)lane)] : 0u;
+      const unsigned upto1 = wave_scan(one, 0u, Add{});
+      const unsigned above1 = last_lane(upto1) - upto1;
+      const int from = __builtin_ctzll(__ballot(above1 < want && want <= above1 + one));
+      const unsigned digit = 32u * (unsigned)owner + (unsigned)from;
+      want -= (unsigned)__builtin_amdgcn_readlane((int)above1, from);
+      in_bin = (unsigned)__builtin_amdgcn_readlane((int)one, from);
+      lo += (unsigned long long)digit << shift;
+      if (in_bin <= 64u) break;
+      // more than a wave can rank: look into this bin alone (with shift 0 a bin holds one key: keys are distinct)
+      shift = max(0, shift - kBinBits);
+      __syncthreads();                                 // everybody has read the histogram
+      for (int i = tid; i < kBins; i += kThreads) l.hist[i] = 0u;
+      __syncthreads();
     }
+#pragma unroll
+    for (int i = 0; i < kMaxItems; ++i)
+      if (valid[i] && key[i] >= lo && ((key[i] - lo) >> shift) == 0ull) s_members[atomicAdd(&s_n_members, 1u)] = key[i];
     __syncthreads();
-    top = lo;
+    const unsigned long long k = lane < (int)in_bin ? s_members[lane] : 0ull;
+    unsigned rank = 0;
+    for (unsigned i = 0; i < in_bin; i += 4) {             // (four reads in flight; past the end: zeros or old keys, not counted)
+      unsigned long long other[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) other[u] = s_members[i + u];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) rank += i + u < in_bin && other[u] > k ? 1u : 0u;
+    }
+    const int from = __builtin_ctzll(__ballot(lane < (int)in_bin && rank == want - 1u));
+    threshold = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(k >> 32), from) << 32) |
+                (unsigned)__builtin_amdgcn_readlane((int)(unsigned)k, from);
   }
-  const unsigned long long threshold = found_unique ? s_threshold : prefix;
 
-  // ---- keep flags; rank the free slots, the kept block tokens and the evicted candidates.
-  // (The histogram is dead from here on: its memory now holds the lists.)
+  // ---- keep flags; rank the free slots, the kept block tokens and the evicted candidates
+  uint8_t* const keep_out = in_set_of(a.keep, a.g, li) + (size_t)hk * a.cand_stride;
+  int32_t* const dst_out = in_set_of(a.dst, a.g, li) + (size_t)hk * a.cand_stride;
   bool keep[kMaxItems];
   unsigned n_free = 0, n_new = 0, n_ev = 0;
 #pragma unroll
@@ -361,197 +419,288 @@ select_kernel(const SelectArgs a_first) {
     const int p = tid * items + i;
     keep[i] = valid[i] && key[i] >= threshold;
     if (valid[i]) {
-      l.keep[p] = keep[i];
-      a.keep[(size_t)hk * a.cand_stride + p] = keep[i];
-      a.dst[(size_t)hk * a.cand_stride + p] = -1;
+      keep_out[p] = keep[i];
+      if (!a.merge || keep[i]) dst_out[p] = -1;        // an evicted candidate's is written by the merge plan
       if (p < budget && (p >= c || !keep[i])) ++n_free;
       if (p >= c && keep[i]) ++n_new;
       if (!keep[i]) ++n_ev;
     }
   }
-  unsigned packed = n_free | (n_new << 16);
-  unsigned incl = packed, incl_ev = n_ev;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned v = __shfl_up(incl, off, 64);
-    const unsigned ve = __shfl_up(incl_ev, off, 64);
-    if (lane >= off) { incl += v; incl_ev += ve; }
-  }
+  const unsigned packed = n_free | (n_new << 16);
+  const unsigned incl = wave_scan(packed, 0u, Add{}), incl_ev = wave_scan(n_ev, 0u, Add{});
   if (lane == 63) { s_wave_tot[wave] = incl; s_wave_ev[wave] = incl_ev; }
-  for (int i = tid; i < cand_pad / 4; i += kThreads) l.cnt[i] = 0u;
   __syncthreads();
   unsigned base = incl - packed, base_ev = incl_ev - n_ev;
   unsigned total = 0, total_ev = 0;
+#pragma unroll
   for (int w2 = 0; w2 < kWaves; ++w2) {
     const unsigned t = s_wave_tot[w2], te = s_wave_ev[w2];
     if (w2 < wave) { base += t; base_ev += te; }
     total += t; total_ev += te;
   }
-  unsigned base_free = base & 0xFFFFu, base_new = base >> 16;
-  const unsigned total_new = total >> 16;
-  int rank_new[kMaxItems];
+  unsigned base_free = base & 0xFFFFu;
+  const unsigned base_new = base >> 16, total_new = total >> 16;
 #pragma unroll
   for (int i = 0; i < kMaxItems; ++i) {
     const int p = tid * items + i;
-    rank_new[i] = -1;
     if (valid[i]) {
-      if (p < budget && (p >= c || !keep[i])) l.free_dst[base_free++] = (unsigned short)p;
-      if (p >= c && keep[i]) rank_new[i] = (int)base_new++;
+      if (p < budget && (p >= c || !keep[i])) l.free_slot[base_free++] = (unsigned short)p;
       if (!keep[i]) l.evicted[base_ev++] = (unsigned short)p;
     }
   }
   __syncthreads();
-  MoveEntry* moves = a.moves + (size_t)hk * a.chunk_max;
+
+  using L = Lanes<D>;
+  const int sub = tid % L::kPerPair;
+  const bool is_v = sub >= L::kPerRow;
+  const int piece = sub % L::kPerRow;
+  // (both candidates of a choice are formed outside of it: a load of an argument whose address depends on a
+  // per-lane condition would push the arguments to memory)
+  u16* const k_cache = a.k_cache;
+  u16* const v_cache = a.v_cache;
+  const u16* const k_new = a.layer[li].k_new;
+  const u16* const v_new = a.layer[li].v_new;
+  u16* const stage_k = in_set_of(a.stage_k, a.g, li);
+  u16* const stage_v = in_set_of(a.stage_v, a.g, li);
+  u16* const cache = (is_v ? v_cache : k_cache) + (long long)li * a.g.kv_stride + (size_t)hk * budget * D + 8 * piece;
+  const u16* const fresh = (is_v ? v_new : k_new) + (size_t)hk * D + 8 * piece;
+  const int fresh_stride = a.n_kv_heads * D;
+  u16* const staged = (is_v ? stage_v : stage_k) + (size_t)hk * a.chunk_max * D + 8 * piece;
+  float* const staged_w = in_set_of(a.stage_w, a.g, li) + (size_t)hk * a.chunk_max;
+
+  if (a.merge) {
+    // ---- merge plan: the e-th evicted candidate (thread e, e + 1024, ...) picks its best kept
+    // grid neighbour and enters itself there
+    for (unsigned e = tid; e < total_ev; e += kThreads) {
+      const int p = l.evicted[e];
+      int best = -1;
+      int nb[kNeighbours];
+      if (neighbours(s_segs, a.n_segs, (int)~key_words[2 * p], nb)) {
+        int r[kNeighbours];              // a token of the block sits at a known position, one after it nowhere
 #pragma unroll
-  for (int i = 0; i < kMaxItems; ++i) {
-    if (rank_new[i] >= 0) {
-      MoveEntry e;
-      e.pos = tid * items + i;
-      e.slot = l.free_dst[rank_new[i]];
-      e.stage = -1;
-      e.pad = 0;
-      moves[rank_new[i]] = e;
+        for (int j = 0; j < kNeighbours; ++j) {
+          const bool cached = nb[j] >= 0 && nb[j] < a.t0;
+          if (a.direct) {
+            const unsigned e = direct[cached ? nb[j] : 0];
+            r[j] = cached && e != kNone16 ? (int)e : -1;
+          } else {
+            r[j] = cached ? probe(l, mask, nb[j]) : -1;
+          }
+          if (nb[j] >= a.t0 && nb[j] < a.t0 + n) r[j] = c + (nb[j] - a.t0);
+        }
+        unsigned long long kr[kNeighbours], best_key = 0;
+#pragma unroll
+        for (int j = 0; j < kNeighbours; ++j) kr[j] = l.key[max(r[j], 0)];
+#pragma unroll
+        for (int j = 0; j < kNeighbours; ++j)
+          if (r[j] >= 0 && kr[j] >= threshold && (best < 0 || kr[j] > best_key)) { best = r[j]; best_key = kr[j]; }
+      }
+      dst_out[p] = best;
+      if (best >= 0) {
+        const unsigned old = atomicAdd(&l.cnt[best >> 2], 1u << (8 * (best & 3)));
+        sources[best * kNeighbours + ((old >> (8 * (best & 3))) & 0xFFu)] = (unsigned short)p;
+      }
+    }
+    __syncthreads();
+  }
+
+  // ---- the destinations that were chosen, in any order (which staging row one gets is nobody's
+  // business), and the block rows to move, by rank
+  unsigned short* const dests = reinterpret_cast<unsigned short*>(l.table);
+  unsigned short* const moved = l.evicted;
+  {
+    unsigned n_src_mine = 0, rank = base_new;
+#pragma unroll
+    for (int i = 0; i < kMaxItems; ++i) {
+      if (!valid[i]) continue;
+      const int p = tid * items + i;
+      if (p >= c && keep[i]) moved[rank++] = (unsigned short)p;
+      if (a.merge) {
+        const unsigned k = (l.cnt[p >> 2] >> (8 * (p & 3))) & 0xFFu;
+        if (k) {
+          n_src_mine += k;
+          const unsigned at = atomicAdd(&s_n_dst, 1u);
+          dests[at] = (unsigned short)p;
+          key_words[2 * p + 1] = at;
+        }
+      }
+    }
+    if (n_src_mine) atomicAdd(&s_n_src, n_src_mine);
+  }
+  __syncthreads();
+
+  if (a.merge) {
+    const int n_dst = (int)s_n_dst;
+    auto row_at = [&](int pos) __attribute__((always_inline)) {
+      return *reinterpret_cast<const uint4*>(pos < c ? cache + (size_t)pos * D : fresh + (size_t)(pos - c) * fresh_stride);
+    };
+    auto weight_at = [&](int pos) __attribute__((always_inline)) { return pos < c ? weight[pos] : 1.f; };
+    // sources of destination p in ascending position, unused entries last
+    auto sorted_sources = [&](int p, int n_src, int (&pos)[kNeighbours]) __attribute__((always_inline)) {
+#pragma unroll
+      for (int k = 0; k < kNeighbours; ++k) pos[k] = k < n_src ? (int)sources[p * kNeighbours + k] : 0x7FFFFFFF;
+#pragma unroll
+      for (int pass = 0; pass < kNeighbours; ++pass)
+#pragma unroll
+        for (int k = pass & 1; k + 1 < kNeighbours; k += 2) {
+          const int lo = min(pos[k], pos[k + 1]), hi = max(pos[k], pos[k + 1]);
+          pos[k] = lo; pos[k + 1] = hi;
+        }
+    };
+    // The destination and its first two sources, which is all that most have, are fetched for four
+    // destinations at a time; further sources follow when the destination's turn has come.
+    constexpr int kFlight = 4, kEarly = 2;
+    for (int at0 = tid / L::kPerPair; at0 < n_dst; at0 += kFlight * L::kPairs) {
+      int pos[kFlight], n_src[kFlight];
+      float wt[kFlight][kEarly + 1];
+      uint4 rows[kFlight][kEarly + 1];
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) {
+        const int at = at0 + u * L::kPairs;
+        pos[u] = 0; n_src[u] = 0;
+#pragma unroll
+        for (int k = 0; k <= kEarly; ++k) { wt[u][k] = 0.f; rows[u][k] = make_uint4(0u, 0u, 0u, 0u); }
+        if (at < n_dst) {
+          const int p = dests[at];
+          int from[kNeighbours];
+          pos[u] = p;
+          n_src[u] = (int)((l.cnt[p >> 2] >> (8 * (p & 3))) & 0xFFu);
+          sorted_sources(p, n_src[u], from);
+          rows[u][0] = row_at(p);
+          wt[u][0] = weight_at(p);
+#pragma unroll
+          for (int k = 0; k < kEarly; ++k)
+            if (k < n_src[u]) { rows[u][k + 1] = row_at(from[k]); wt[u][k + 1] = weight_at(from[k]); }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) {
+        const int at = at0 + u * L::kPairs;
+        if (at >= n_dst) continue;
+        const int p = pos[u];
+        float sum_w = wt[u][0];
+        float acc[8];
+        {
+          const unsigned w[4] = {rows[u][0].x, rows[u][0].y, rows[u][0].z, rows[u][0].w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            acc[2 * k] = wt[u][0] * bf16_lo(w[k]);
+            acc[2 * k + 1] = wt[u][0] * bf16_hi(w[k]);
+          }
+        }
+        auto add = [&](const uint4& row, float wgt) __attribute__((always_inline)) {
+          sum_w += wgt;
+          const unsigned w[4] = {row.x, row.y, row.z, row.w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            acc[2 * k] = __builtin_fmaf(wgt, bf16_lo(w[k]), acc[2 * k]);
+            acc[2 * k + 1] = __builtin_fmaf(wgt, bf16_hi(w[k]), acc[2 * k + 1]);
+          }
+        };
+#pragma unroll
+        for (int k = 0; k < kEarly; ++k)
+          if (k < n_src[u]) add(rows[u][k + 1], wt[u][k + 1]);
+        if (n_src[u] > kEarly) {
+          int from[kNeighbours];
+          sorted_sources(p, n_src[u], from);
+          uint4 late[kNeighbours - kEarly];
+          float late_w[kNeighbours - kEarly];
+#pragma unroll
+          for (int k = kEarly; k < kNeighbours; ++k) {
+            late[k - kEarly] = make_uint4(0u, 0u, 0u, 0u);
+            late_w[k - kEarly] = 0.f;
+            if (k < n_src[u]) { late[k - kEarly] = row_at(from[k]); late_w[k - kEarly] = weight_at(from[k]); }
+          }
+#pragma unroll
+          for (int k = kEarly; k < kNeighbours; ++k)
+            if (k < n_src[u]) add(late[k - kEarly], late_w[k - kEarly]);
+        }
+        uint4 res;
+        res.x = pack_bf16(acc[0] / sum_w, acc[1] / sum_w);
+        res.y = pack_bf16(acc[2] / sum_w, acc[3] / sum_w);
+        res.z = pack_bf16(acc[4] / sum_w, acc[5] / sum_w);
+        res.w = pack_bf16(acc[6] / sum_w, acc[7] / sum_w);
+        if (p < c) {
+          *reinterpret_cast<uint4*>(cache + (size_t)p * D) = res;
+          if (sub == 0) weight[p] = sum_w;
+        } else {
+          *reinterpret_cast<uint4*>(staged + (size_t)at * D) = res;
+          if (sub == 0) staged_w[at] = sum_w;
+        }
+      }
+    }
+    __syncthreads();                                   // sources have been read, staging rows written
+  }
+
+  // ---- kept block rows into the free slots, eight per group of lanes in flight
+  {
+    constexpr int kFlight = 8;
+    for (int i0 = tid / L::kPerPair; i0 < (int)total_new; i0 += kFlight * L::kPairs) {
+      uint4 row[kFlight];
+      float wt[kFlight];
+      int pos[kFlight];
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) {
+        const int i = i0 + u * L::kPairs;
+        row[u] = make_uint4(0u, 0u, 0u, 0u);
+        wt[u] = 1.f;
+        pos[u] = 0;
+        if (i < (int)total_new) {
+          const int p = moved[i];
+          const bool merged = a.merge && ((l.cnt[p >> 2] >> (8 * (p & 3))) & 0xFFu) != 0u;
+          const int at = merged ? (int)key_words[2 * p + 1] : 0;
+          pos[u] = p;
+          row[u] = *reinterpret_cast<const uint4*>(merged ? staged + (size_t)at * D : fresh + (size_t)(p - c) * fresh_stride);
+          if (merged) wt[u] = staged_w[at];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kFlight; ++u) {
+        const int i = i0 + u * L::kPairs;
+        if (i < (int)total_new) {
+          const int slot = l.free_slot[i];
+          *reinterpret_cast<uint4*>(cache + (size_t)slot * D) = row[u];
+          if (sub == 0) {
+            token_idx[slot] = a.t0 + (pos[u] - c);
+            weight[slot] = wt[u];
+          }
+        }
+      }
     }
   }
+  // running totals for the benchmark's byte counts (integer atomics: the order does not matter)
   if (tid == 0) {
-    a.counts[hk].n_moves = (int)total_new;
     atomicAdd(&a.totals[KVP_T_EVICTING_HEADS], 1ull);
     atomicAdd(&a.totals[KVP_T_MOVED_ROWS], (unsigned long long)total_new);
-  }
-
-  if (!a.merge) {
-    if (tid == 0) a.counts[hk].n_dst = 0;
-    return;
-  }
-  __syncthreads();                       // the free list has been consumed: it now takes destinations
-
-  // ---- merge plan: the e-th evicted candidate (thread e, e + 1024, ...) picks its best kept
-  // grid neighbour and counts itself in there
-  for (unsigned e = tid; e < total_ev; e += kThreads) {
-    const int p = l.evicted[e];
-    const int tokp = l.tok[p];
-    int best = -1;
-    int nb[kNeighbours];
-    if (neighbours(s_segs, a.n_segs, tokp, nb)) {
-      // first probe of all neighbours at once; a token of the block sits at a known position
-      unsigned h[kNeighbours], ent[kNeighbours];
-      bool in_block[kNeighbours];
-#pragma unroll
-      for (int j = 0; j < kNeighbours; ++j) {
-        in_block[j] = nb[j] >= a.t0 && nb[j] < a.t0 + n;
-        h[j] = hash_tok(nb[j] < 0 ? 0 : nb[j], mask);
-        ent[j] = table_entry(l, h[j]);
-      }
-      int r[kNeighbours];
-      int tk[kNeighbours];
-#pragma unroll
-      for (int j = 0; j < kNeighbours; ++j) {
-        r[j] = in_block[j] ? c + (nb[j] - a.t0) : (ent[j] == kNone16 ? -1 : (int)ent[j]);
-        tk[j] = r[j] >= 0 ? l.tok[r[j]] : -1;
-      }
-#pragma unroll
-      for (int j = 0; j < kNeighbours; ++j) {
-        if (nb[j] < 0) r[j] = -1;
-        else if (!in_block[j] && r[j] >= 0 && tk[j] != nb[j]) r[j] = probe_on(l, mask, nb[j], h[j], ent[j]);
-      }
-      unsigned kp[kNeighbours], sc[kNeighbours];
-#pragma unroll
-      for (int j = 0; j < kNeighbours; ++j) {
-        kp[j] = r[j] >= 0 ? l.keep[r[j]] : 0u;
-        sc[j] = r[j] >= 0 ? l.sc[r[j]] : 0u;
-      }
-      unsigned long long best_key = 0;
-#pragma unroll
-      for (int j = 0; j < kNeighbours; ++j) {
-        if (!kp[j]) continue;
-        const unsigned long long kr = make_key(sc[j], nb[j]);
-        if (best < 0 || kr > best_key) { best = r[j]; best_key = kr; }
-      }
-    }
-    l.free_dst[e] = best >= 0 ? (unsigned short)best : (unsigned short)kNone16;
-    if (best >= 0) {
-      a.dst[(size_t)hk * a.cand_stride + p] = best;
-      atomicAdd(&l.cnt[best >> 2], 1u << (8 * (best & 3)));
+    if (a.merge) {
+      atomicAdd(&a.totals[KVP_T_MERGE_SOURCES], (unsigned long long)s_n_src);
+      atomicAdd(&a.totals[KVP_T_MERGE_DESTINATIONS], (unsigned long long)s_n_dst);
     }
   }
-  __syncthreads();
-  // number the destinations that were chosen, in candidate order; the ordinal of a destination
-  // goes where its score bits were (nobody reads those any more)
-  unsigned* fill = reinterpret_cast<unsigned*>(l.keep);     // the keep flags have been consumed
-  unsigned n_mine = 0;
-  unsigned cnt_of[kMaxItems];
-#pragma unroll
-  for (int i = 0; i < kMaxItems; ++i) {
-    const int p = tid * items + i;
-    cnt_of[i] = valid[i] ? (l.cnt[p >> 2] >> (8 * (p & 3))) & 0xFFu : 0u;
-    n_mine += cnt_of[i] ? 1u : 0u;
-  }
-  unsigned incl2 = n_mine;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const unsigned v = __shfl_up(incl2, off, 64);
-    if (lane >= off) incl2 += v;
-  }
-  if (lane == 63) s_wave_tot[wave] = incl2;
-  for (int i = tid; i < cand_pad / 4; i += kThreads) fill[i] = 0u;
-  __syncthreads();
-  unsigned ord = incl2 - n_mine, n_dst = 0;
-  for (int w2 = 0; w2 < kWaves; ++w2) {
-    const unsigned t = s_wave_tot[w2];
-    if (w2 < wave) ord += t;
-    n_dst += t;
-  }
-  DstEntry* dsts = a.dsts + (size_t)hk * a.chunk_max;
-#pragma unroll
-  for (int i = 0; i < kMaxItems; ++i) {
-    if (!cnt_of[i]) continue;
-    const int p = tid * items + i;
-    l.sc[p] = ord;
-    dsts[ord].pos = p;
-    dsts[ord].n_src = (int)cnt_of[i];
-    if (rank_new[i] >= 0) moves[rank_new[i]].stage = (int)ord;
-    ++ord;
-  }
-  __syncthreads();
-  // every source writes itself into its destination's entry
-  unsigned n_src_mine = 0;
-  for (unsigned e = tid; e < total_ev; e += kThreads) {
-    const unsigned d = l.free_dst[e];
-    if (d == kNone16) continue;
-    const unsigned old = atomicAdd(&fill[d >> 2], 1u << (8 * (d & 3)));
-    const unsigned k = (old >> (8 * (d & 3))) & 0xFFu;
-    dsts[l.sc[d]].src[k] = l.evicted[e];
-    ++n_src_mine;
-  }
-  if (tid == 0) a.counts[hk].n_dst = (int)n_dst;
-  // running totals for the benchmark's byte counts (integer atomics: the order does not matter)
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) n_src_mine += __shfl_xor(n_src_mine, off, 64);
-  if (lane == 0 && n_src_mine) atomicAdd(&a.totals[KVP_T_MERGE_SOURCES], (unsigned long long)n_src_mine);
-  if (tid == 0) atomicAdd(&a.totals[KVP_T_MERGE_DESTINATIONS], (unsigned long long)n_dst);
+}
+
+template <int D>
+hipError_t launch_head_dim(const SelectArgs& a, int n_kv_heads, hipStream_t s) {
+  const size_t lds = select_lds_bytes(a);
+  const dim3 grid(n_kv_heads, a.g.n_layers);
+  if (a.items <= 4) hipLaunchKernelGGL((compact_kernel<D, 4>), grid, dim3(kThreads), lds, s, a);
+  else hipLaunchKernelGGL((compact_kernel<D, kMaxItemsAny>), grid, dim3(kThreads), lds, s, a);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_select(const SelectArgs& a, int n_kv_heads, hipStream_t s) {
-  const size_t lds = select_lds_bytes(a.c + a.n, a.items, a.table_size);
-  const dim3 grid(n_kv_heads, a.g.n_layers);
-  if (a.items <= 4) hipLaunchKernelGGL(select_kernel<4>, grid, dim3(kThreads), lds, s, a);
-  else hipLaunchKernelGGL(select_kernel<kMaxItemsAny>, grid, dim3(kThreads), lds, s, a);
-  return hipGetLastError();
+  return a.head_dim == 128 ? launch_head_dim<128>(a, n_kv_heads, s) : launch_head_dim<64>(a, n_kv_heads, s);
 }
 
-// Allows both kernels the dynamic LDS of the largest head they can be given (the attribute
+// Allows the kernels the dynamic LDS of the largest head they can be given (the attribute
 // belongs to the function on the current device: called at cache creation).
 hipError_t prepare_select() {
-  const int sizes[2] = {4, kMaxItemsAny};
-  const void* fns[2] = {reinterpret_cast<const void*>(select_kernel<4>),
-                        reinterpret_cast<const void*>(select_kernel<kMaxItemsAny>)};
-  for (int i = 0; i < 2; ++i) {
-    int ts = 2;
-    while (ts < 2 * sizes[i] * kThreads) ts <<= 1;
-    const size_t lds = select_lds_bytes(sizes[i] * kThreads, sizes[i], ts);
-    hipError_t e = hipFuncSetAttribute(fns[i], hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  for (const void* fn : {reinterpret_cast<const void*>(compact_kernel<64, 4>), reinterpret_cast<const void*>(compact_kernel<128, 4>),
+                         reinterpret_cast<const void*>(compact_kernel<64, kMaxItemsAny>),
+                         reinterpret_cast<const void*>(compact_kernel<128, kMaxItemsAny>)}) {
+    const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSelectLdsLimit);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

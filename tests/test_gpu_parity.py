@@ -425,6 +425,43 @@ def test_odd_sizes_lockstep():
         cache.close()
 
 
+@pytest.mark.parametrize("d,c,n,budget,t0,levels", [
+    (64, 700, 324, 700, 700, 5),          # 1024 candidates, one per thread; hundreds of equal scores at the threshold
+    (128, 700, 325, 650, 30000, 40),      # one more; a token table with an entry per token of a long prefix
+    (64, 900, 1100, 1000, 60000, 9),      # a prefix too long for that: the hash table
+    (128, 3000, 1096, 3000, 3000, 3),     # 4096 candidates, the most with source lists in LDS
+    (64, 3000, 1097, 3100, 90000, 100000)])   # one more
+def test_compaction_edges(d, c, n, budget, t0, levels):
+    """Selection, merge plan and rows at the edges of the compaction kernel's ranges: candidates per thread,
+    more equal scores than a wave can rank, the two kinds of token table."""
+    hkv, gh, gw = 2, 16, 16
+    rng = np.random.default_rng(c + n)
+    planes = (t0 + n) // (gh * gw) + 1
+    segs = (Segment(0, planes * gh * gw, 1, gh, gw, planes, 1),)
+    cache = K.Cache(1, hkv, hkv, d, budget, max(n, c), segs, merge=True, device=DEV)
+    oc = O.LayerCache(hkv, d, budget, segs, True)
+    kb0, vb0 = _rand_bits(rng, (c, hkv, d)), _rand_bits(rng, (c, hkv, d))
+    k0, v0 = O.bf16_bits_to_f64(kb0), O.bf16_bits_to_f64(vb0)
+    keep = min(c, budget)
+    # cached tokens from the last few thousand before the block, in any slot order
+    oc.idx = np.stack([rng.choice(np.arange(max(0, t0 - 4 * c), t0), size=keep, replace=False) for _ in range(hkv)])
+    oc.w = rng.integers(1, 4, size=(hkv, keep))
+    oc.K, oc.V, oc.count = k0[:keep].transpose(1, 0, 2).copy(), v0[:keep].transpose(1, 0, 2).copy(), keep
+    U.upload_state(cache, 0, oc)
+    cache.set_state(0, keep, t0)
+    qb, kb, vb = _rand_bits(rng, (n, hkv, d)), _rand_bits(rng, (n, hkv, d)), _rand_bits(rng, (n, hkv, d))
+    scores = (rng.integers(0, levels, size=(hkv, keep + n)).astype(np.float32) + 1) / 7
+    cache.prefill_chunk(0, t0, U.bits_to_torch(qb), U.bits_to_torch(kb), U.bits_to_torch(vb))
+    cache.compact(0, torch.from_numpy(scores).to(DEV))
+    rec = oc.compact(t0, O.bf16_bits_to_f64(kb), O.bf16_bits_to_f64(vb), scores)
+    used, kept, dst = cache.debug_last(0)
+    assert np.array_equal(used.cpu().numpy(), scores)
+    assert np.array_equal(kept.cpu().numpy().astype(bool), rec["keep"])
+    assert np.array_equal(dst.cpu().numpy().astype(np.int64), rec["dst"])
+    assert U.compare_state(cache, 0, oc) > 0
+    cache.close()
+
+
 def test_maximum_candidates_lockstep():
     """budget + block at the library's limit (8192 candidates per head): the select kernel's
     eight-candidates-per-thread shape, its largest LDS layout, 2048-row blocks."""
