@@ -3,22 +3,27 @@
 // keys and values of the tokens generated so far, the current one included (the
 // "tail", which the caller keeps).
 //
-// Bound by HBM: every cached K and V row is read once per KV head and serves
-// the G query heads of its group.  A single query row gives the block attention
-// kernel nothing to spread, so the keys are spread instead: a workgroup takes
-// 64 keys of one KV head at a time.  Its 256 threads fetch the 64 K rows and the
-// 64 V rows with fully coalesced 16-byte loads, all in flight at once (a thread
-// holds one 8-channel piece of 64 * 8 / 256 rows of each), so a tile costs one
-// trip to memory.  Then
-//   scores   each thread dots its pieces with the G queries; the pieces of a row
-//            sit in neighbouring lanes and are added by butterflies;
-//   softmax  one wave per query head: maximum and sum over the 64 keys, merged
-//            into the running statistics of the workgroup (kept in LDS);
-//   values   each thread scales its V pieces by the weights of its rows.
-// After its last tile the workgroup adds the threads' pieces (butterflies, then
-// LDS across waves) and leaves (max, sum, unnormalised output) per query head; a
-// second small kernel folds the workgroups' partials in a fixed order and rounds
-// once to bfloat16.
+// Bound by latency long before HBM: 2049 keys of eight KV heads are 8.4 MB, a microsecond and a half of
+// memory bandwidth, and a launch costs more than that.  So a thread has all its loads in flight
+// together (one trip to memory), everything that crosses lanes goes over the DPP network or the
+// lane-swap instructions instead of through LDS (butterflies by shuffle were half of the 11 us a step
+// used to take), and waves meet once or twice.
+//
+// A thread holds one 8-channel piece of some K rows and of the same V rows, with coalesced 16-byte loads.
+//   scores   it dots its pieces with the query; the pieces of a row sit in neighbouring lanes and are
+//            added on the DPP network, so that every lane of a row knows its logit;
+//   weights  every lane then has the exponentials of its own rows, against a maximum of the wave or the
+//            workgroup;
+//   values   it scales its V pieces; the sums over the rows of a wave are taken pairwise by lane swaps (a
+//            swap and an addition halve two values at once), those over the waves through LDS.
+// Two ways to spread the work:
+//   few keys (up to 640 at head dimension 128): one workgroup of 1024 threads per QUERY head takes all of
+//            them and writes the result, one launch.  (A CU takes 64 bytes a clock from L2: beyond
+//            about 700 keys that costs more than the second launch below.)  10.2 -> 6 us per layer at
+//            32/32 heads, 265 keys;
+//   else     a workgroup of 256 threads takes 64 keys of one KV head at a time for all G query heads of
+//            the group and leaves (unnormalised output, maximum, sum) per query head; a second kernel
+//            folds the workgroups' partials in a fixed order and rounds once to bfloat16.
 #include <mutex>
 
 #include "kvp_internal.h"
@@ -32,9 +37,9 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / 64;
+constexpr int kHeadThreads = 1024;   // of the one-workgroup-per-query-head kernel
 constexpr int kTile = kDecodeTile;   // keys per workgroup step
 constexpr int kGroupLimit = kDecodeGroupLimit;   // query heads per KV head
-constexpr int kMaxSplits = kDecodeMaxSplits;
 
 __device__ __forceinline__ float bf16_lo(unsigned x) { return __uint_as_float(x << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned x) { return __uint_as_float(x & 0xFFFF0000u); }
@@ -49,7 +54,137 @@ __device__ __forceinline__ const u16* row_of(const u16* cache, const u16* tail, 
   return j < c ? cache + ((size_t)hk * budget + j) * D : tail + ((size_t)(j - c) * n_kv_heads + hk) * D;
 }
 
-// grid (n_splits, Hkv).  G = query heads per KV head, at most GM (the compiled bound, which
+template <int kCtrl>
+__device__ __forceinline__ float dpp(float x) {
+  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), kCtrl, 0xF, 0xF, false));
+}
+// sum over the kPieces (8 or 16) neighbouring lanes that hold a row, in all of them
+template <int kPieces>
+__device__ __forceinline__ float row_sum(float x) {
+  x += dpp<0xB1>(x);                             // lane ^ 1
+  x += dpp<0x4E>(x);                             // lane ^ 2
+  x += dpp<0x141>(x);                            // the other four of eight lanes
+  if constexpr (kPieces == 16) x += dpp<0x140>(x);   // the other eight of sixteen
+  return x;
+}
+// The lane swaps exchange the upper half (16: the odd rows of sixteen lanes) of the first operand with the lower half
+// (the even rows) of the second.
+template <int kLanes>
+__device__ __forceinline__ void swap_lanes(float& x, float& y) {
+  const unsigned a = __float_as_uint(x), b = __float_as_uint(y);
+  if constexpr (kLanes == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+    x = __uint_as_float(r[0]); y = __uint_as_float(r[1]);
+  } else {
+    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+    x = __uint_as_float(r[0]); y = __uint_as_float(r[1]);
+  }
+}
+template <class Op>
+__device__ __forceinline__ float over_rows(float x, Op op, bool eight_lanes) {    // over the rows of a wave, in all lanes
+  if (eight_lanes) x = op(x, dpp<0x128>(x));     // rows of eight lanes: the other one of the sixteen
+  float y = x;
+  swap_lanes<16>(x, y);
+  x = op(x, y);
+  y = x;
+  swap_lanes<32>(x, y);
+  return op(x, y);
+}
+struct Max { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
+struct Sum { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
+
+// Sums of v[0 .. N - 1] over the rows of a wave; lanes 16 r .. 16 r + 15 (r = 0 .. 3) end up with those of
+// v[r N / 4 .. (r + 1) N / 4 - 1], in v[0 .. N / 4 - 1].
+template <int kPieces, int N>
+__device__ __forceinline__ void sum_rows(float (&v)[N]) {
+#pragma unroll
+  for (int i = 0; i < N / 2; ++i) { swap_lanes<32>(v[i], v[i + N / 2]); v[i] += v[i + N / 2]; }
+#pragma unroll
+  for (int i = 0; i < N / 4; ++i) { swap_lanes<16>(v[i], v[i + N / 4]); v[i] += v[i + N / 4]; }
+  if constexpr (kPieces == 8) {
+#pragma unroll
+    for (int i = 0; i < N / 4; ++i) v[i] += dpp<0x128>(v[i]);
+  }
+}
+
+__device__ __forceinline__ u16 round_bf16(float r) {
+  unsigned u = __float_as_uint(r);               // round to nearest even
+  u += 0x7FFFu + ((u >> 16) & 1u);
+  return (u16)(u >> 16);
+}
+
+__device__ __forceinline__ float dot8(const uint4 k, const float (&q)[8]) {
+  float kx[8];
+  unpack8(k, kx);
+  float s = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) s = __builtin_fmaf(kx[e], q[e], s);
+  return s;
+}
+
+// ---- one workgroup per query head, all keys, no partial results; kLoads rows per thread
+template <int D, int kLoads>
+__global__ void __launch_bounds__(kHeadThreads)
+decode_head_kernel(const DecodeArgs a) {
+  constexpr int kPieces = D / 8, kRows = kHeadThreads / kPieces, kHeadWaves = kHeadThreads / 64;
+  __shared__ float s_m[kHeadWaves], s_l[kHeadWaves];
+  __shared__ __align__(16) float s_o[kHeadWaves][D];
+  // neighbouring workgroups take different KV heads: a KV head's query heads share the L2 of one or two dies
+  const int hk = blockIdx.x % a.n_kv_heads, h = hk * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int piece = tid % kPieces, sub = tid / kPieces;
+  const int n_keys = a.c + a.n_tail;
+  uint4 kw[kLoads], vw[kLoads];
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) {
+    const int j = min(kRows * i + sub, n_keys - 1);
+    kw[i] = *reinterpret_cast<const uint4*>(row_of(a.k_cache, a.k_tail, hk, a.n_kv_heads, j, a.c, a.budget, D) + 8 * piece);
+  }
+  float qx[8];
+  unpack8(*reinterpret_cast<const uint4*>(a.q + (size_t)h * D + 8 * piece), qx);
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) {
+    const int j = min(kRows * i + sub, n_keys - 1);
+    vw[i] = *reinterpret_cast<const uint4*>(row_of(a.v_cache, a.v_tail, hk, a.n_kv_heads, j, a.c, a.budget, D) + 8 * piece);
+  }
+  float s[kLoads], mx = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) {
+    s[i] = row_sum<kPieces>(dot8(kw[i], qx));
+    s[i] = kRows * i + sub < n_keys ? s[i] : -INFINITY;
+    mx = fmaxf(mx, s[i]);
+  }
+  mx = over_rows(mx, Max{}, kPieces == 8);
+  if (lane == 0) s_m[wave] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < kHeadWaves; ++w) mx = fmaxf(mx, s_m[w]);         // finite: there is at least one key
+  float o[8], l = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = 0.f;
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) {
+    const float p = __builtin_amdgcn_exp2f((s[i] - mx) * a.scale_log2);      // 0 for a key past the end
+    l += p;
+    float vx[8];
+    unpack8(vw[i], vx);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = __builtin_fmaf(p, vx[e], o[e]);
+  }
+  l = over_rows(l, Sum{}, kPieces == 8);
+  sum_rows<kPieces, 8>(o);                       // lanes 16 r ..: channels 2 r, 2 r + 1 of the piece
+  if (lane % 16 < kPieces) *reinterpret_cast<float2*>(&s_o[wave][8 * piece + 2 * (lane / 16)]) = make_float2(o[0], o[1]);
+  if (lane == 0) s_l[wave] = l;
+  __syncthreads();
+  if (tid < D) {
+    float num = 0.f, den = 0.f;
+#pragma unroll
+    for (int w = 0; w < kHeadWaves; ++w) { num += s_o[w][tid]; den += s_l[w]; }
+    a.out[(size_t)h * D + tid] = round_bf16(num / den);
+  }
+}
+
+// ---- grid (n_splits, Hkv).  G = query heads per KV head, at most GM (the compiled bound, which
 // sizes the register arrays; queries beyond G read as zero and their results are dropped).
 template <int D, int GM>
 __global__ void __launch_bounds__(kThreads)
@@ -57,9 +192,8 @@ decode_kernel(const DecodeArgs a) {
   constexpr int kPieces = D / 8;                 // 16-byte pieces per row
   constexpr int kRowsPerLoad = kThreads / kPieces;
   constexpr int kLoads = kTile / kRowsPerLoad;   // rows of a tile a thread holds a piece of
-  __shared__ float s_s[GM][kTile];               // logits of the tile, then its weights
-  __shared__ float s_m[GM], s_l[GM], s_f[GM];    // running maximum, running sum, rescale factor of this tile
-  __shared__ float s_o[kWaves][GM][D];
+  __shared__ float s_m[kWaves][GM], s_l[kWaves][GM];
+  __shared__ __align__(16) float s_o[kWaves][GM][D];
   const int split = blockIdx.x, hk = blockIdx.y;
   const int G = a.n_q_heads / a.n_kv_heads;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -67,169 +201,171 @@ decode_kernel(const DecodeArgs a) {
   const int n_keys = a.c + a.n_tail;
   const int n_tiles = (n_keys + kTile - 1) / kTile;
 
-  if (tid < GM) { s_m[tid] = -INFINITY; s_l[tid] = 0.f; }
-  float o[GM][8];
+  float o[8 * GM], m[GM], l[GM];                 // of this wave's rows; l of this lane's
 #pragma unroll
-  for (int g = 0; g < GM; ++g)
+  for (int g = 0; g < GM; ++g) {
+    m[g] = -INFINITY;
+    l[g] = 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) o[g][e] = 0.f;
-
+    for (int e = 0; e < 8; ++e) o[8 * g + e] = 0.f;
+  }
   for (int tile = split; tile < n_tiles; tile += a.n_splits) {
-    // ---- fetch: every K and V piece of the tile, all loads in flight together
+    // every K and V piece of the tile, all loads in flight together
     uint4 kw[kLoads], vw[kLoads];
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
       const int j = min(tile * kTile + kRowsPerLoad * i + sub, n_keys - 1);
       kw[i] = *reinterpret_cast<const uint4*>(row_of(a.k_cache, a.k_tail, hk, a.n_kv_heads, j, a.c, a.budget, D) + 8 * piece);
+    }
+    uint4 qw[GM];
+#pragma unroll
+    for (int g = 0; g < GM; ++g) {
+      qw[g] = make_uint4(0u, 0u, 0u, 0u);
+      if (g < G) qw[g] = *reinterpret_cast<const uint4*>(a.q + ((size_t)hk * G + g) * D + 8 * piece);
+    }
+#pragma unroll
+    for (int i = 0; i < kLoads; ++i) {
+      const int j = min(tile * kTile + kRowsPerLoad * i + sub, n_keys - 1);
       vw[i] = *reinterpret_cast<const uint4*>(row_of(a.v_cache, a.v_tail, hk, a.n_kv_heads, j, a.c, a.budget, D) + 8 * piece);
     }
-    // ---- scores
-    float s[kLoads][GM];
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i)
-#pragma unroll
-      for (int g = 0; g < GM; ++g) s[i][g] = 0.f;
+    float p[GM][kLoads];
 #pragma unroll
     for (int g = 0; g < GM; ++g) {
-      if (g < G) {
-        float qx[8];
-        unpack8(*reinterpret_cast<const uint4*>(a.q + ((size_t)hk * G + g) * D + 8 * piece), qx);
-#pragma unroll
-        for (int i = 0; i < kLoads; ++i) {
-          float kx[8];
-          unpack8(kw[i], kx);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) s[i][g] = __builtin_fmaf(kx[e], qx[e], s[i][g]);
-        }
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < kLoads; ++i)
-#pragma unroll
-      for (int g = 0; g < GM; ++g) {
-#pragma unroll
-        for (int off = 1; off < kPieces; off <<= 1) s[i][g] += __shfl_xor(s[i][g], off, 64);
-      }
-    if (piece == 0) {
+      if (g >= G) continue;
+      float qx[8];
+      unpack8(qw[g], qx);
+      float mx = m[g];
 #pragma unroll
       for (int i = 0; i < kLoads; ++i) {
-        const int r = kRowsPerLoad * i + sub;
-        const bool live = tile * kTile + r < n_keys;
-#pragma unroll
-        for (int g = 0; g < GM; ++g) s_s[g][r] = live ? s[i][g] : -INFINITY;
+        p[g][i] = row_sum<kPieces>(dot8(kw[i], qx));
+        p[g][i] = tile * kTile + kRowsPerLoad * i + sub < n_keys ? p[g][i] : -INFINITY;
+        mx = fmaxf(mx, p[g][i]);
       }
-    }
-    __syncthreads();
-    // ---- softmax statistics: wave w takes query heads w, w + 4, ...
-    for (int g = wave; g < G; g += kWaves) {
-      const float x = s_s[g][lane];
-      float mx = x;
+      mx = over_rows(mx, Max{}, kPieces == 8);
+      const float m_use = mx == -INFINITY ? 0.f : mx;      // all of this wave's keys so far lie past the end
+      const float f = __builtin_amdgcn_exp2f((m[g] - m_use) * a.scale_log2);    // 0 on the first tile
+      l[g] *= f;
 #pragma unroll
-      for (int off = 1; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-      const float m_old = s_m[g];
-      const float m_new = fmaxf(m_old, mx);            // finite: a tile holds at least one key
-      const float p = __builtin_amdgcn_exp2f((x - m_new) * a.scale_log2);   // 0 for a key past the end
-      float sum = p;
+      for (int e = 0; e < 8; ++e) o[8 * g + e] *= f;
 #pragma unroll
-      for (int off = 1; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
-      const float f = __builtin_amdgcn_exp2f((m_old - m_new) * a.scale_log2);   // 0 on the first tile
-      s_s[g][lane] = p;
-      if (lane == 0) { s_m[g] = m_new; s_l[g] = s_l[g] * f + sum; s_f[g] = f; }
-    }
-    __syncthreads();
-    // ---- values
-#pragma unroll
-    for (int g = 0; g < GM; ++g) {
-      if (g < G) {
-        const float f = s_f[g];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[g][e] *= f;
+      for (int i = 0; i < kLoads; ++i) {
+        p[g][i] = __builtin_amdgcn_exp2f((p[g][i] - m_use) * a.scale_log2);     // 0 for a key past the end
+        l[g] += p[g][i];
       }
+      m[g] = mx;
     }
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
       float vx[8];
       unpack8(vw[i], vx);
-      const int r = kRowsPerLoad * i + sub;
 #pragma unroll
       for (int g = 0; g < GM; ++g) {
-        if (g < G) {
-          const float p = s_s[g][r];
+        if (g >= G) continue;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) o[g][e] = __builtin_fmaf(p, vx[e], o[g][e]);
-        }
+        for (int e = 0; e < 8; ++e) o[8 * g + e] = __builtin_fmaf(p[g][i], vx[e], o[8 * g + e]);
       }
     }
-    // the next tile's logits overwrite s_s only after its own barrier-free score phase:
-    // every thread must be done reading the weights first
-    __syncthreads();
   }
-  // ---- add the pieces: rows of one wave by butterflies, waves through LDS
+  // ---- rows of a wave, then the waves
 #pragma unroll
-  for (int g = 0; g < GM; ++g)
+  for (int g = 0; g < GM; ++g) {
+    if (g >= G) continue;
+    l[g] = over_rows(l[g], Sum{}, kPieces == 8);
+    if (lane == 0) { s_m[wave][g] = m[g]; s_l[wave][g] = l[g]; }
+  }
+  sum_rows<kPieces, 8 * GM>(o);                  // lanes 16 r ..: query heads r GM / 4 .. (r + 1) GM / 4 - 1
+  if (lane % 16 < kPieces) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
+    for (int k = 0; k < GM / 4; ++k)
 #pragma unroll
-      for (int off = kPieces; off < 64; off <<= 1) o[g][e] += __shfl_xor(o[g][e], off, 64);
-    }
-  if (lane < kPieces) {
-#pragma unroll
-    for (int g = 0; g < GM; ++g)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s_o[wave][g][8 * piece + e] = o[g][e];
+      for (int e = 0; e < 8; e += 4)
+        *reinterpret_cast<float4*>(&s_o[wave][(lane / 16) * (GM / 4) + k][8 * piece + e]) =
+            make_float4(o[8 * k + e], o[8 * k + e + 1], o[8 * k + e + 2], o[8 * k + e + 3]);
   }
   __syncthreads();
   for (int i = tid; i < G * D; i += kThreads) {
     const int g = i / D, ch = i % D;
-    float sum = 0.f;
+    float mm = s_m[0][g];
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) sum += s_o[w][g][ch];
+    for (int w = 1; w < kWaves; ++w) mm = fmaxf(mm, s_m[w][g]);          // finite: a tile holds at least one key
+    float num = 0.f, den = 0.f;
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const float f = __builtin_amdgcn_exp2f((s_m[w][g] - mm) * a.scale_log2);
+      num = __builtin_fmaf(s_o[w][g][ch], f, num);
+      den = __builtin_fmaf(s_l[w][g], f, den);
+    }
     float* part = a.partial + (((size_t)hk * G + g) * a.n_splits + split) * (D + 2);
-    part[ch] = sum;
-    if (ch == 0) { part[D] = s_m[g]; part[D + 1] = s_l[g]; }
+    part[ch] = num;
+    if (ch == 0) { part[D] = mm; part[D + 1] = den; }
   }
 }
 
-// grid (Hq); kFoldLanes threads per channel, each folding every kFoldLanes-th partial, so
-// that the loads of a thread do not depend on one another and a handful are in flight at once
-constexpr int kFoldLanes = 4;
+// ---- grid (Hq); kFoldLanes threads per channel, each folding every kFoldLanes-th partial.  The outputs, maxima and
+// sums of a batch of them are in flight together: one trip to memory up to 48 partials.
+constexpr int kFoldLanes = 4, kFoldBatch = 12;
 template <int D>
 __global__ void __launch_bounds__(kFoldLanes * D)
 decode_fold_kernel(const DecodeArgs a) {
-  __shared__ float s_w[kMaxSplits];            // rescale factor of every partial
-  __shared__ float s_mm[kMaxSplits];
-  __shared__ float s_acc[kFoldLanes][D + 1];   // per lane group: channels, then the sum
+  __shared__ float s_o[kFoldLanes][D], s_m[kFoldLanes], s_l[kFoldLanes];
   const int h = blockIdx.x, tid = threadIdx.x;
   const int ch = tid % D, grp = tid / D;
-  const float* part = a.partial + (size_t)h * a.n_splits * (D + 2);
-  if (tid < a.n_splits) s_mm[tid] = part[(size_t)tid * (D + 2) + D];
-  __syncthreads();
-  float mm = -INFINITY;
-  for (int s = 0; s < a.n_splits; ++s) mm = fmaxf(mm, s_mm[s]);
-  if (tid < a.n_splits) s_w[tid] = __builtin_amdgcn_exp2f((s_mm[tid] - mm) * a.scale_log2);
-  __syncthreads();
-  float oo = 0.f, ll = 0.f;
-#pragma unroll 8
-  for (int s = grp; s < a.n_splits; s += kFoldLanes) {
-    oo = __builtin_fmaf(part[(size_t)s * (D + 2) + ch], s_w[s], oo);
-    if (ch == 0) ll = __builtin_fmaf(part[(size_t)s * (D + 2) + D + 1], s_w[s], ll);
+  const float* const part = a.partial + (size_t)h * a.n_splits * (D + 2);
+  float m = -INFINITY, o = 0.f, l = 0.f;
+  for (int first = grp; first < a.n_splits; first += kFoldLanes * kFoldBatch) {
+    float po[kFoldBatch], pm[kFoldBatch], pl[kFoldBatch];
+#pragma unroll
+    for (int u = 0; u < kFoldBatch; ++u) {
+      const int s = first + kFoldLanes * u;
+      // (past the end: the last one again, with weight 0; a load under a condition would be waited for on the spot)
+      const float* const from = part + (size_t)min(s, a.n_splits - 1) * (D + 2);
+      po[u] = from[ch]; pm[u] = from[D]; pl[u] = from[D + 1];
+    }
+#pragma unroll
+    for (int u = 0; u < kFoldBatch; ++u)
+      if (first + kFoldLanes * u >= a.n_splits) pm[u] = -INFINITY;
+    float mx = m;
+#pragma unroll
+    for (int u = 0; u < kFoldBatch; ++u) mx = fmaxf(mx, pm[u]);
+    const float f0 = __builtin_amdgcn_exp2f((m - mx) * a.scale_log2);    // 0 on the first batch
+    o *= f0;
+    l *= f0;
+#pragma unroll
+    for (int u = 0; u < kFoldBatch; ++u) {
+      const float f = __builtin_amdgcn_exp2f((pm[u] - mx) * a.scale_log2);
+      o = __builtin_fmaf(po[u], f, o);
+      l = __builtin_fmaf(pl[u], f, l);
+    }
+    m = mx;
   }
-  s_acc[grp][ch] = oo;
-  if (ch == 0) s_acc[grp][D] = ll;
+  s_o[grp][ch] = o;
+  if (ch == 0) { s_m[grp] = m; s_l[grp] = l; }
   __syncthreads();
   if (grp == 0) {
-    float o_sum = 0.f, l_sum = 0.f;
+    float mm = s_m[0];
 #pragma unroll
-    for (int g = 0; g < kFoldLanes; ++g) { o_sum += s_acc[g][ch]; l_sum += s_acc[g][D]; }
-    const float r = o_sum / l_sum;
-    unsigned u = __float_as_uint(r);          // round to nearest even
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    a.out[(size_t)h * D + ch] = (u16)(u >> 16);
+    for (int k = 1; k < kFoldLanes; ++k) mm = fmaxf(mm, s_m[k]);
+    float num = 0.f, den = 0.f;
+#pragma unroll
+    for (int k = 0; k < kFoldLanes; ++k) {
+      const float f = __builtin_amdgcn_exp2f((s_m[k] - mm) * a.scale_log2);    // 0 for a group without partials
+      num = __builtin_fmaf(s_o[k][ch], f, num);
+      den = __builtin_fmaf(s_l[k], f, den);
+    }
+    a.out[(size_t)h * D + ch] = round_bf16(num / den);
   }
 }
 
 template <int D>
 hipError_t launch_for(const DecodeArgs& a, hipStream_t s) {
+  // few keys: one launch (10 rows per thread at most)
+  constexpr int kRows = kHeadThreads / (D / 8);
+  const long long n_keys = (long long)a.c + a.n_tail;
+  if (n_keys <= 10 * kRows) {
+    if (n_keys <= 4 * kRows) hipLaunchKernelGGL((decode_head_kernel<D, 4>), dim3(a.n_q_heads), dim3(kHeadThreads), 0, s, a);
+    else hipLaunchKernelGGL((decode_head_kernel<D, 10>), dim3(a.n_q_heads), dim3(kHeadThreads), 0, s, a);
+    return hipGetLastError();
+  }
   const dim3 grid(a.n_splits, a.n_kv_heads);
   const int group = a.n_q_heads / a.n_kv_heads;
   if (group <= 4) hipLaunchKernelGGL((decode_kernel<D, 4>), grid, dim3(kThreads), 0, s, a);

@@ -142,6 +142,8 @@ hipError_t launch_keydiff(KeydiffArgs a, int head_dim, hipStream_t s);
 
 // One decode step of one layer (decode.hip).
 struct DecodeArgs {
+  int c, n_tail, n_q_heads, n_kv_heads, budget, n_splits;
+  float scale_log2;
   const u16* q;        // [Hq, D]
   const u16* k_tail;   // [n_tail, Hkv, D]
   const u16* v_tail;
@@ -149,8 +151,6 @@ struct DecodeArgs {
   const u16* k_cache;  // this layer: [Hkv, M, D]
   const u16* v_cache;
   float* partial;      // [Hq, n_splits, D + 2] scratch: unnormalised output, maximum, sum
-  int c, n_tail, n_q_heads, n_kv_heads, budget, n_splits;
-  float scale_log2;
 };
 int decode_max_group();
 int decode_splits(long long n_keys, int head_dim, size_t scratch_floats, int n_q_heads);

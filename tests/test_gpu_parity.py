@@ -292,6 +292,28 @@ def test_decode_step(hq, hkv, d, c, n_tail, budget, chunk_max, scale):
     cache.close()
 
 
+@pytest.mark.parametrize("hq,hkv,d,n_keys", [
+    # one workgroup per query head: edges of its four and ten rows per thread, and the first keys beyond
+    (8, 2, 128, 255), (8, 2, 128, 257), (7, 7, 128, 640), (7, 1, 128, 641), (4, 4, 64, 513), (12, 4, 64, 1280), (12, 4, 64, 1281),
+    # partial results: a workgroup whose last waves have no key, more than 48 partials to fold
+    (10, 1, 128, 705), (4, 4, 64, 64 * 49 + 1)])
+def test_decode_step_edges(hq, hkv, d, n_keys):
+    rng = np.random.default_rng(n_keys)
+    c = n_keys - 5
+    cache = K.Cache(1, hq, hkv, d, c, 64, [Segment(0, 100000, 0)], device=DEV)
+    oc = O.LayerCache(hkv, d, c)
+    kb0, vb0 = _rand_bits(rng, (c, hkv, d)), _rand_bits(rng, (c, hkv, d))
+    oc.compact(0, O.bf16_bits_to_f64(kb0), O.bf16_bits_to_f64(vb0), np.zeros((hkv, c), dtype=np.float32))
+    U.upload_state(cache, 0, oc)
+    cache.set_state(0, c, c)
+    qb, kb, vb = _rand_bits(rng, (hq, d), 2.0), _rand_bits(rng, (5, hkv, d)), _rand_bits(rng, (5, hkv, d))
+    _, _, k_all, v_all = oc.candidates(c, O.bf16_bits_to_f64(kb), O.bf16_bits_to_f64(vb))
+    ref = O.decode_step(O.bf16_bits_to_f64(qb), k_all, v_all)
+    out = cache.decode_step(0, U.bits_to_torch(qb), U.bits_to_torch(kb), U.bits_to_torch(vb))
+    assert U.out_rel_err(U.torch_bf16_to_f64(out), ref) <= 5e-3      # fp32 throughout: the rounding of the output to bf16 alone
+    cache.close()
+
+
 def test_decode_step_after_prefill():
     """Prefill a layer block by block, then generate three tokens over what it kept."""
     wl = get_workload("tiled_image")
