@@ -14,10 +14,16 @@
 // such a load at 16 bytes a clock, against 60 when four neighbouring lanes share 64 bytes (measured,
 // from L2).
 //
-// A wave's loop over its key blocks i:
+// A wave's loop over its key blocks i, with one row tile per workgroup:
 //   S = K(i) Q^T from the K strip, then the load of K(i + 1) into it; P = exp(S - m);
 //   O += P V(i) from the V strip, then the load of V(i + 1).
-// Two waves share a SIMD, out of step: one has matrix work while the other has vector work.
+// With two row tiles (one from the front of the head, one from the back, for equal work) the waves of a pair need the
+// same blocks: one wave of the pair brings in K and the other V, a round ahead, with one barrier per round.
+// (A software pipeline as in attention.hip -- S(i + 1) and P(i - 1) V(i - 1) among the exponentials of block i --
+// was built and measured slower: a round of two waves per SIMD takes the sum of their matrix and vector time
+// either way, and the pipeline works out one block more per wave.  So was a touch of all the head's cache lines up
+// front: the blocks do not wait for memory.)
+// Two waves share a SIMD: one has matrix work while the other has vector work.
 //
 // Softmax reference.  A row's reference is the maximum of its first visible block; a later logit more
 // than 2^30 above it (fp32 has room for 2^127) sends the wave through a branch that brings O and the
@@ -92,8 +98,13 @@ attention_split_kernel(const AttnArgs a) {
   const int g = lane >> 5;
 
   const int n = a.n, c = a.c, shift = a.shift;
-  const int row_begin = rt * S::kRows;
-  const int q0 = row_begin + 32 * qw;                      // first query row of this wave
+  // Row tiles.  Two of a workgroup are one from the front of the head and one from the back, so that all workgroups see
+  // about as many keys; and since waves w and w + 4 share a SIMD, the late tile's wave has the SIMD to itself
+  // when the early tile has run out of visible keys.
+  auto tile_row = [&](int t) __attribute__((always_inline)) {
+    return 32 * (QW == 1 || t == 0 ? rt : 2 * a.n_row_tiles - 1 - rt);
+  };
+  const int q0 = tile_row(qw);                             // first query row of this wave
   const u16* const kc = a.k_cache + (size_t)li * a.g.kv_stride + (size_t)hk * a.budget * D;
   const u16* const vc = a.v_cache + (size_t)li * a.g.kv_stride + (size_t)hk * a.budget * D;
   const u16* const kn = a.layer[li].k_new + (size_t)hk * D;
@@ -176,18 +187,35 @@ attention_split_kernel(const AttnArgs a) {
   }
 
   // ---- first sweep
-  const int rows_end = min(n, q0 + 32);                    // = n for a tile past the end: computed, not stored
+  const int rows_end = min(n, q0 + 32);
   const int n_blk = c_blk + (min(a.n_keys, rows_end + shift) + 31) / 32;     // blocks some row of the tile sees
-  const int my_blk = n_blk > ks ? (n_blk - ks + KS - 1) / KS : 0;
+  const int my_blk = q0 < n && n_blk > ks ? (n_blk - ks + KS - 1) / KS : 0;   // (a tile may lie past the end)
   auto mine = [&](int i) __attribute__((always_inline)) { return block_of(ks + KS * i); };
+  const int wg_rows_end = min(n, tile_row(QW - 1) + 32);
+  const int n_kb = c_blk + (min(a.n_keys, wg_rows_end + shift) + 31) / 32;   // blocks some row of the workgroup sees
+  // Two row tiles share their blocks: the waves (0, ks) and (1, ks) bring in K and V of block (ks, i) for both, a
+  // round of KS blocks ahead, into the half of the strips that the round before has left.
+  constexpr bool kShared = QW == 2;
+  auto round_strip = [&](int i, bool is_v) __attribute__((always_inline)) {
+    return reinterpret_cast<u16*>(lds_raw) + ((i & 1) * S::kWaves + (is_v ? KS : 0) + ks) * S::kStrip;
+  };
+  auto load_round = [&](int i) __attribute__((always_inline)) {
+    if (ks + KS * i >= n_kb) return;
+    if (qw == 0) load_block(kc, kn, mine(i), round_strip(i, false), false);
+    else load_block(vc, vn, mine(i), round_strip(i, true), true);
+  };
 
   // the workgroup's query rows (each wave brings in its share), the wave's first block
   for (int j = wave; j < QW * kLoads; j += S::kWaves) {
-    const int first_row = row_begin + 32 * (j / kLoads);       // rows past the block are computed, not stored
+    const int first_row = tile_row(j / kLoads);                // rows past the block are computed, not stored
     load_strip(q_rows + ((size_t)min(first_row, n - 1) * a.n_q_heads + h) * D, a.n_q_heads * D, max(min(32, n - first_row), 1),
                q_lds + (j / kLoads) * S::kStrip, false, j % kLoads);
   }
-  if (my_blk > 0) {
+  if constexpr (kShared) {
+    load_round(0);
+    if (ks < n_kb) wait_older_than(OneBlock{});
+    else wait_older_than(None{});
+  } else if (my_blk > 0) {
     load_block(kc, kn, mine(0), k_strip, false);
     load_block(vc, vn, mine(0), v_strip, true);
     wait_older_than(TwoBlocks{});
@@ -206,25 +234,20 @@ attention_split_kernel(const AttnArgs a) {
   float m_ref = -INFINITY, l_run = 0.f;
   const float rescue_raw = kRescueLog2 / sl2;              // the margin in units of the raw dot product
 
-  auto read_v = [&](int dt, int mm) __attribute__((always_inline)) {
-    return lds_read_vt(v_strip + v_off[dt] + 16 * mm * D, 8 * D);
-  };
   auto p_frag = [](const unsigned (&p)[8], int mm) __attribute__((always_inline)) {
     const u32x4 pw = {p[4 * mm], p[4 * mm + 1], p[4 * mm + 2], p[4 * mm + 3]};
     return __builtin_bit_cast(bf16x8, pw);
   };
-  for (int i = 0; i < my_blk; ++i) {
+  // block i of this wave, K and V in LDS; k_read runs when K has been read, v_wait before V is
+  auto attend = [&](int i, const u16* k_from, const u16* v_from, auto&& k_read, auto&& v_wait) __attribute__((always_inline)) {
     const Block b = mine(i);
-    const bool more = i + 1 < my_blk;
-    wait_older_than(OneBlock{});             // K(i) is in its strip; V(i) may still be on its way
     f32x16 s;
     bf16x8 kf[kNK];
 #pragma unroll
-    for (int st = 0; st < kNK; ++st) kf[st] = lds_read_b128(k_strip + k_off[st]);
+    for (int st = 0; st < kNK; ++st) kf[st] = lds_read_b128(k_from + k_off[st]);
 #pragma unroll
     for (int st = 0; st < kNK; ++st) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st], qf[st], st == 0 ? zero : s, 0, 0, 0);
-    __builtin_amdgcn_s_waitcnt(0xC07F);      // the strip has been read
-    if (more) load_block(kc, kn, mine(i + 1), k_strip, false);
+    k_read();
     if (b.rows < 32 || (!b.cached && b.first + 31 > q0 + shift)) {         // some row may not see some key
       const int last = b.cached ? b.rows - 1 : min(b.rows - 1, q0 + l32 + shift - b.first);
       const int lim = last - 4 * g;
@@ -258,13 +281,12 @@ attention_split_kernel(const AttnArgs a) {
     };
 #pragma unroll
     for (int k = 0; k < 4; ++k) weigh_pair(k);
-    if (more) wait_older_than(OneBlock{});   // V(i) is in its strip; K(i + 1) may still be on its way
-    else wait_older_than(None{});
+    v_wait();
     bf16x8 vf[2 * kND];
 #pragma unroll
     for (int dt = 0; dt < kND; ++dt) {
-      vf[dt] = read_v(dt, 0);
-      vf[kND + dt] = read_v(dt, 1);
+      vf[dt] = lds_read_vt(v_from + v_off[dt], 8 * D);
+      vf[kND + dt] = lds_read_vt(v_from + v_off[dt] + 16 * D, 8 * D);
     }
     // the products with the first sixteen keys run beside the exponentials of the other sixteen
 #pragma unroll
@@ -274,8 +296,32 @@ attention_split_kernel(const AttnArgs a) {
 #pragma unroll
     for (int dt = 0; dt < kND; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kND + dt], p_frag(pw, 1), o[dt], 0, 0, 0);
     l_run += sum;
-    __builtin_amdgcn_s_waitcnt(0xC07F);      // the strip has been read
-    if (more) load_block(vc, vn, mine(i + 1), v_strip, true);
+  };
+  if constexpr (kShared) {
+    const int n_rounds = (n_kb + KS - 1) / KS;
+    for (int i = 0; i < n_rounds; ++i) {
+      wait_older_than(None{});               // this wave's share of round i has landed
+      __builtin_amdgcn_s_barrier();          // everybody's has, and everybody is done with round i - 1
+      asm volatile("" ::: "memory");
+      load_round(i + 1);
+      if (i < my_blk) attend(i, round_strip(i, false), round_strip(i, true), [] {}, [] {});
+    }
+  } else {
+    for (int i = 0; i < my_blk; ++i) {
+      const bool more = i + 1 < my_blk;
+      wait_older_than(OneBlock{});           // K(i) is in its strip; V(i) may still be on its way
+      attend(i, k_strip, v_strip,
+             [&]() __attribute__((always_inline)) {
+               __builtin_amdgcn_s_waitcnt(0xC07F);         // the strip has been read
+               if (more) load_block(kc, kn, mine(i + 1), k_strip, false);
+             },
+             [&]() __attribute__((always_inline)) {
+               if (more) wait_older_than(OneBlock{});      // V(i) is in its strip; K(i + 1) may still be on its way
+               else wait_older_than(None{});
+             });
+      __builtin_amdgcn_s_waitcnt(0xC07F);    // the strip has been read
+      if (more) load_block(vc, vn, mine(i + 1), v_strip, true);
+    }
   }
 
   // ---- merge the KS partial results of every row through LDS
@@ -324,7 +370,7 @@ attention_split_kernel(const AttnArgs a) {
         for (int e = 0; e < 4; ++e) acc[k + e] += f[s] * v[e];
       }
     }
-    const int orow = row_begin + row;
+    const int orow = tile_row(row / 32) + row % 32;
     const float lse_row = m * sl2 + __builtin_log2f(l);
     if (tid % kPerRow == 0) {
       lse_lds[row] = lse_row;
@@ -345,8 +391,6 @@ attention_split_kernel(const AttnArgs a) {
 
   // ---- second sweep: column sums (Eq. 4) of the workgroup's rows; wave w takes key blocks w, w + 8, ...,
   // its two strips in turn
-  const int wg_rows_end = min(n, row_begin + S::kRows);
-  const int n_kb = c_blk + (min(a.n_keys, wg_rows_end + shift) + 31) / 32;   // blocks some row of the workgroup sees
   __syncthreads();                           // the rows' statistics are in LDS, the partial outputs have been read
   if (wave < n_kb) load_block(kc, kn, block_of(wave), k_strip, false);
   bf16x8 qs[QW][kNK];
@@ -365,53 +409,66 @@ attention_split_kernel(const AttnArgs a) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) ls[t][4 * j + e] = v[e];
     }
-  auto weigh = [&](const f32x16 (&s)[QW], const Block& b) __attribute__((always_inline)) {
-    float sum[2] = {0.f, 0.f};
-    // every row sees every key and all are real
-    if (b.rows == 32 && (b.cached || b.first + 31 <= row_begin + shift) && row_begin + S::kRows <= n) {
-#pragma unroll
-      for (int t = 0; t < QW; ++t)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sum[r & 1] += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], sl2, -ls[t][r]));
-    } else {
-      // this lane's key counts for the row at offset off = 8 (r / 4) + r % 4 from row0 iff first <= off < rows left
-#pragma unroll
-      for (int t = 0; t < QW; ++t) {
-        const int row0 = row_begin + 32 * t + 4 * g;
-        const int first = b.cached ? 0 : max(b.first + l32 - shift - row0, 0);
-        const unsigned span = (unsigned)max(n - row0 - first, 0);
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], sl2, -ls[t][r]));
-          sum[r & 1] += (unsigned)(8 * (r >> 2) + (r & 3) - first) < span ? p : 0.f;
-        }
-      }
-    }
-    const float tot = sum_with_other_half(sum[0] + sum[1]);  // lanes l and l + 32 hold the two halves of the rows
-    if (g == 0 && l32 < b.rows) part[(b.cached ? 0 : c) + b.first + l32] = tot;
-  };
+  // The wave's blocks from b up to `end`, by row tiles T0 .. QW - 1 (those before T0 see none of them); returns its first
+  // block after those.  (No software pipeline: with the exponentials of one block among the matrix instructions of the
+  // next it was a few per cent slower; the two waves of a SIMD fill each other's gaps.)
   u16* strip = k_strip;
   u16* other = v_strip;
-  for (int b = wave; b < n_kb; b += S::kWaves) {
-    if (b + S::kWaves < n_kb) {
-      load_block(kc, kn, block_of(b + S::kWaves), other, false);
-      wait_older_than(OneBlock{});
-    } else {
-      wait_older_than(None{});
+  auto sweep = [&](int b, int end, auto tiles_from) __attribute__((always_inline)) -> int {
+    constexpr int T0 = decltype(tiles_from)::value;
+    for (; b < end; b += S::kWaves) {
+      if (b + S::kWaves < n_kb) {
+        load_block(kc, kn, block_of(b + S::kWaves), other, false);
+        wait_older_than(OneBlock{});
+      } else {
+        wait_older_than(None{});
+      }
+      bf16x8 kf[kNK];
+#pragma unroll
+      for (int st = 0; st < kNK; ++st) kf[st] = lds_read_b128(strip + k_off[st]);
+      f32x16 s[QW];
+#pragma unroll
+      for (int st = 0; st < kNK; ++st)
+#pragma unroll
+        for (int t = T0; t < QW; ++t)
+          s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qs[t][st], kf[st], st == 0 ? zero : s[t], 0, 0, 0);
+      const Block kb = block_of(b);
+      float sum[2] = {0.f, 0.f};
+      // every row sees every key and all are real
+      if (kb.rows == 32 && (kb.cached || kb.first + 31 <= tile_row(T0) + shift) && tile_row(QW - 1) + 32 <= n) {
+#pragma unroll
+        for (int t = T0; t < QW; ++t)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) sum[r & 1] += __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], sl2, -ls[t][r]));
+      } else {
+        // this lane's key counts for the row at offset off = 8 (r / 4) + r % 4 from row0 iff first <= off < rows left
+#pragma unroll
+        for (int t = T0; t < QW; ++t) {
+          const int row0 = tile_row(t) + 4 * g;
+          const int first = kb.cached ? 0 : max(kb.first + l32 - shift - row0, 0);
+          const unsigned span = (unsigned)max(n - row0 - first, 0);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const float p = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][r], sl2, -ls[t][r]));
+            sum[r & 1] += (unsigned)(8 * (r >> 2) + (r & 3) - first) < span ? p : 0.f;
+          }
+        }
+      }
+      const float tot = sum_with_other_half(sum[0] + sum[1]);  // lanes l and l + 32 hold the two halves of the rows
+      if (g == 0 && l32 < kb.rows) part[(kb.cached ? 0 : c) + kb.first + l32] = tot;
+      u16* const swap = strip;
+      strip = other;
+      other = swap;
     }
-    bf16x8 kf[kNK];
-#pragma unroll
-    for (int st = 0; st < kNK; ++st) kf[st] = lds_read_b128(strip + k_off[st]);
-    f32x16 s[QW];
-#pragma unroll
-    for (int st = 0; st < kNK; ++st)
-#pragma unroll
-      for (int t = 0; t < QW; ++t)
-        s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qs[t][st], kf[st], st == 0 ? zero : s[t], 0, 0, 0);
-    weigh(s, block_of(b));
-    u16* const swap = strip;
-    strip = other;
-    other = swap;
+    return b;
+  };
+  if constexpr (QW == 1) {
+    sweep(wave, n_kb, std::integral_constant<int, 0>{});
+  } else {
+    // blocks that rows of both tiles see, then those that only the late tile's do
+    const int n_both = c_blk + (min(a.n_keys, min(n, tile_row(0) + 32) + shift) + 31) / 32;
+    const int b = sweep(wave, min(n_both, n_kb), std::integral_constant<int, 0>{});
+    sweep(b, n_kb, std::integral_constant<int, 1>{});
   }
   // keys that none of this workgroup's rows see: zeros (the selection adds every partial array)
   for (int k = 32 * (n_kb - c_blk) + tid; k < a.n_keys; k += S::kThreads) part[c + k] = 0.f;
