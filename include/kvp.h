@@ -286,7 +286,9 @@ int kvp_set_score_sweep(kvp_cache* cache, int32_t fused);
  * with its scores still to come; kvp_compact or kvp_compact_layers launches them
  * first -- kvp_compact_layers for up to 16 layers of the range per launch, which
  * is what makes it worth while: these passes are launch-sized for one layer.
- * The result is the same bit for bit.  While a layer waits, its q_obs (and, as
+ * The result is the same bit for bit.  (A head with few candidates, up to 1024 at
+ * head_dim 128 and 2048 at 64, is always scored by its keys inside the compaction
+ * launch.)  While a layer waits, its q_obs (and, as
  * always, its k and v) must stay valid, and kvp_debug_last has nothing to show
  * for it.  kvp_prefill_block does the same by itself and ignores this setting. */
 int kvp_set_deferred_scoring(kvp_cache* cache, int32_t on);

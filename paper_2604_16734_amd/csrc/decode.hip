@@ -27,6 +27,7 @@
 #include <mutex>
 
 #include "kvp_internal.h"
+#include "lane_tools.h"
 
 // Scratch of kvp_decode_step_static (the entry point for callers that cannot allocate): the
 // partial results of the step, KVP_STATIC_SCRATCH_BYTES per GPU, held until the process ends.
@@ -41,70 +42,10 @@ constexpr int kHeadThreads = 1024;   // of the one-workgroup-per-query-head kern
 constexpr int kTile = kDecodeTile;   // keys per workgroup step
 constexpr int kGroupLimit = kDecodeGroupLimit;   // query heads per KV head
 
-__device__ __forceinline__ float bf16_lo(unsigned x) { return __uint_as_float(x << 16); }
-__device__ __forceinline__ float bf16_hi(unsigned x) { return __uint_as_float(x & 0xFFFF0000u); }
-__device__ __forceinline__ void unpack8(const uint4 w, float (&x)[8]) {
-  x[0] = bf16_lo(w.x); x[1] = bf16_hi(w.x); x[2] = bf16_lo(w.y); x[3] = bf16_hi(w.y);
-  x[4] = bf16_lo(w.z); x[5] = bf16_hi(w.z); x[6] = bf16_lo(w.w); x[7] = bf16_hi(w.w);
-}
-
 // key j of the list: cache slot j for j < c, then the tail rows
 __device__ __forceinline__ const u16* row_of(const u16* cache, const u16* tail, int hk, int n_kv_heads, int j, int c,
                                              int budget, int D) {
   return j < c ? cache + ((size_t)hk * budget + j) * D : tail + ((size_t)(j - c) * n_kv_heads + hk) * D;
-}
-
-template <int kCtrl>
-__device__ __forceinline__ float dpp(float x) {
-  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), kCtrl, 0xF, 0xF, false));
-}
-// sum over the kPieces (8 or 16) neighbouring lanes that hold a row, in all of them
-template <int kPieces>
-__device__ __forceinline__ float row_sum(float x) {
-  x += dpp<0xB1>(x);                             // lane ^ 1
-  x += dpp<0x4E>(x);                             // lane ^ 2
-  x += dpp<0x141>(x);                            // the other four of eight lanes
-  if constexpr (kPieces == 16) x += dpp<0x140>(x);   // the other eight of sixteen
-  return x;
-}
-// The lane swaps exchange the upper half (16: the odd rows of sixteen lanes) of the first operand with the lower half
-// (the even rows) of the second.
-template <int kLanes>
-__device__ __forceinline__ void swap_lanes(float& x, float& y) {
-  const unsigned a = __float_as_uint(x), b = __float_as_uint(y);
-  if constexpr (kLanes == 32) {
-    const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
-    x = __uint_as_float(r[0]); y = __uint_as_float(r[1]);
-  } else {
-    const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
-    x = __uint_as_float(r[0]); y = __uint_as_float(r[1]);
-  }
-}
-template <class Op>
-__device__ __forceinline__ float over_rows(float x, Op op, bool eight_lanes) {    // over the rows of a wave, in all lanes
-  if (eight_lanes) x = op(x, dpp<0x128>(x));     // rows of eight lanes: the other one of the sixteen
-  float y = x;
-  swap_lanes<16>(x, y);
-  x = op(x, y);
-  y = x;
-  swap_lanes<32>(x, y);
-  return op(x, y);
-}
-struct Max { __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); } };
-struct Sum { __device__ __forceinline__ float operator()(float a, float b) const { return a + b; } };
-
-// Sums of v[0 .. N - 1] over the rows of a wave; lanes 16 r .. 16 r + 15 (r = 0 .. 3) end up with those of
-// v[r N / 4 .. (r + 1) N / 4 - 1], in v[0 .. N / 4 - 1].
-template <int kPieces, int N>
-__device__ __forceinline__ void sum_rows(float (&v)[N]) {
-#pragma unroll
-  for (int i = 0; i < N / 2; ++i) { swap_lanes<32>(v[i], v[i + N / 2]); v[i] += v[i + N / 2]; }
-#pragma unroll
-  for (int i = 0; i < N / 4; ++i) { swap_lanes<16>(v[i], v[i + N / 4]); v[i] += v[i + N / 4]; }
-  if constexpr (kPieces == 8) {
-#pragma unroll
-    for (int i = 0; i < N / 4; ++i) v[i] += dpp<0x128>(v[i]);
-  }
 }
 
 __device__ __forceinline__ u16 round_bf16(float r) {
@@ -154,7 +95,7 @@ decode_head_kernel(const DecodeArgs a) {
     s[i] = kRows * i + sub < n_keys ? s[i] : -INFINITY;
     mx = fmaxf(mx, s[i]);
   }
-  mx = over_rows(mx, Max{}, kPieces == 8);
+  mx = over_rows(mx, FloatMax{}, kPieces == 8);
   if (lane == 0) s_m[wave] = mx;
   __syncthreads();
 #pragma unroll
@@ -171,7 +112,7 @@ decode_head_kernel(const DecodeArgs a) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] = __builtin_fmaf(p, vx[e], o[e]);
   }
-  l = over_rows(l, Sum{}, kPieces == 8);
+  l = over_rows(l, FloatSum{}, kPieces == 8);
   sum_rows<kPieces, 8>(o);                       // lanes 16 r ..: channels 2 r, 2 r + 1 of the piece
   if (lane % 16 < kPieces) *reinterpret_cast<float2*>(&s_o[wave][8 * piece + 2 * (lane / 16)]) = make_float2(o[0], o[1]);
   if (lane == 0) s_l[wave] = l;
@@ -241,7 +182,7 @@ decode_kernel(const DecodeArgs a) {
         p[g][i] = tile * kTile + kRowsPerLoad * i + sub < n_keys ? p[g][i] : -INFINITY;
         mx = fmaxf(mx, p[g][i]);
       }
-      mx = over_rows(mx, Max{}, kPieces == 8);
+      mx = over_rows(mx, FloatMax{}, kPieces == 8);
       const float m_use = mx == -INFINITY ? 0.f : mx;      // all of this wave's keys so far lie past the end
       const float f = __builtin_amdgcn_exp2f((m[g] - m_use) * a.scale_log2);    // 0 on the first tile
       l[g] *= f;
@@ -270,7 +211,7 @@ decode_kernel(const DecodeArgs a) {
 #pragma unroll
   for (int g = 0; g < GM; ++g) {
     if (g >= G) continue;
-    l[g] = over_rows(l[g], Sum{}, kPieces == 8);
+    l[g] = over_rows(l[g], FloatSum{}, kPieces == 8);
     if (lane == 0) { s_m[wave][g] = m[g]; s_l[wave][g] = l[g]; }
   }
   sum_rows<kPieces, 8 * GM>(o);                  // lanes 16 r ..: query heads r GM / 4 .. (r + 1) GM / 4 - 1

@@ -250,6 +250,7 @@ int run_compact(kvp_cache* c, int first, int count, const float* scores_override
   sa.cand_stride = lay.cand_stride; sa.chunk_max = cfg.chunk_max;
   sa.n_partials = L.n_partials;
   sa.merge = cfg.merge;
+  sa.keydiff = scores_override == nullptr && L.unscored == kScoreKeydiff;
   for (int i = 0; i < count; ++i) sa.layer[i] = blocks[i];
   plan_select(sa);
   return launch(c, KVP_K_SELECT, count, s, [&] { return launch_select(sa, cfg.n_kv_heads, s); });
@@ -258,14 +259,15 @@ int run_compact(kvp_cache* c, int first, int count, const float* scores_override
 // kvp_compact for layers [first, first + count): one group launch when they hold the same block,
 // one layer at a time otherwise.  Every layer must be PENDING.
 int compact_layers(kvp_cache* c, int first, int count, const float* scores_override, hipStream_t s) {
-  // (a scoring pass that was put off is the caller's to launch first: score_deferred_layers)
+  // (a scoring pass that was put off is the caller's to launch first: score_deferred_layers; what is still unscored
+  // then is scored by the compaction kernel)
   for (int i = 0; i < count; ++i)
-    if (c->layers[first + i].state != PENDING || c->layers[first + i].unscored != 0) return KVP_ESTATE;
+    if (c->layers[first + i].state != PENDING || c->layers[first + i].unscored == kScoreProxy) return KVP_ESTATE;
   bool same = count <= kMaxGroupLayers && (scores_override == nullptr || count == 1);
   const Layer& A = c->layers[first];
   for (int i = 1; i < count && same; ++i) {
     const Layer& B = c->layers[first + i];
-    same = B.count == A.count && B.n == A.n && B.t0 == A.t0 && B.n_partials == A.n_partials;
+    same = B.count == A.count && B.n == A.n && B.t0 == A.t0 && B.n_partials == A.n_partials && B.unscored == A.unscored;
   }
   if (!same) {
     if (scores_override != nullptr) return KVP_EINVAL;
@@ -281,6 +283,7 @@ int compact_layers(kvp_cache* c, int first, int count, const float* scores_overr
     Layer& L = c->layers[first + i];
     L.count = L.count + L.n <= c->cfg.budget ? L.count + L.n : c->cfg.budget;
     L.state = READY;
+    L.unscored = 0;
     L.next_token = L.t0 + L.n;
     c->set_owner[(first + i) % c->lay.n_sets] = -1;
   }
@@ -449,7 +452,8 @@ static int score_deferred_layers(kvp_cache* c, int first, int count, hipStream_t
   const kvp_config& cfg = c->cfg;
   for (int done = 0; done < count;) {
     Layer& A = c->layers[first + done];
-    if (A.unscored == 0) {          // scored inside prefill_layers already (nothing to evict, or a long list)
+    // scored inside prefill_layers already (nothing to evict, or a long list), or left to the compaction kernel
+    if (A.unscored == 0 || (A.unscored == kScoreKeydiff && keydiff_in_compaction(A.count + A.n, cfg.head_dim))) {
       ++done;
       continue;
     }

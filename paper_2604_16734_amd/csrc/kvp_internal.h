@@ -22,6 +22,7 @@ constexpr int kColsumTargetWorkgroups = 512;    // two per CU, all resident: the
 constexpr int kColsumMaxRowSplits = 16;
 constexpr int kSelectThreads = 1024;
 constexpr int kSelectBins = 2048;               // histogram bins of the selection
+constexpr int kKeydiffRowsPerThread = 16;       // keys a thread of the compaction kernel can hold a piece of
 constexpr size_t kSelectLdsLimit = 156 * 1024;  // dynamic LDS of the compaction kernel, beside 3.5 KiB of static LDS
 constexpr int kRowstatBlockKeys = 256;          // keys per workgroup of the proxy row-statistics kernel
 constexpr int kKeydiffSliceKeys = 64;           // keys per workgroup of the key-sum kernel
@@ -178,6 +179,7 @@ struct SelectArgs {
   int direct;                   // the token table has one entry per token before t0, not a hash of them
   int table_size;               // entries, a multiple of 8 (hash: a power of two >= 2 * (c + n))
   int quads;                    // fours of neighbouring candidates
+  int keydiff;                  // 1: the kernel scores by the keys alone itself, there are no partial arrays
   int width, groups;            // the threads sum the partial arrays as `groups` groups of `width`
   GroupStrides g;
   const float* partial;         // [Hkv, n_partials, cand_stride]
@@ -230,5 +232,6 @@ void plan_colsum(ColsumArgs& a, int head_dim);
 int colsum_max_partials(int group, int chunk_max);
 size_t select_lds_bytes(const SelectArgs& a);
 void plan_select(SelectArgs& a);
+bool keydiff_in_compaction(int n_cand, int head_dim);
 
 }  // namespace kvp

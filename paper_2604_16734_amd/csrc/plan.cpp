@@ -90,7 +90,8 @@ void plan_colsum(ColsumArgs& a, int /*head_dim*/) {
 // sums (up to 4096 candidates; beyond that the lists are in the scratch set and the sums lie elsewhere)
 size_t select_lds_bytes(const SelectArgs& a) {
   const size_t cand_pad = (size_t)a.items * kSelectThreads;
-  const size_t lists = a.items > 4 ? 0 : cand_pad * kNeighbours * 2, sums = a.items > 4 ? 0 : (size_t)a.groups * a.quads * 16;
+  const size_t lists = a.items > 4 ? 0 : cand_pad * kNeighbours * 2, 
+               sums = a.items > 4 ? 0 : (size_t)a.groups * a.quads * 16 + (a.keydiff ? (kSelectThreads / 64 + 1) * (size_t)a.head_dim * 4 : 0);
   return cand_pad * (8 + 1 + 2 + 2) + kSelectBins * 4 + (size_t)a.table_size * 2 + (lists > sums ? lists : sums);
 }
 
@@ -103,7 +104,7 @@ void plan_select(SelectArgs& a) {
   a.items = (n_cand + kSelectThreads - 1) / kSelectThreads;
   a.quads = (n_cand + 3) / 4;
   a.width = a.items > 4 ? kSelectThreads : a.quads <= 64 ? 64 : a.quads <= 128 ? 128 : 256;
-  a.groups = a.score_override ? 1 : kSelectThreads / a.width;
+  a.groups = a.score_override || a.keydiff ? 1 : kSelectThreads / a.width;
   if (a.groups > a.n_partials) a.groups = a.n_partials < 1 ? 1 : a.n_partials;
   a.direct = 1;
   a.table_size = ((a.t0 > n_cand ? a.t0 : n_cand) + 7) / 8 * 8;       // (it becomes the list of destinations, too)
@@ -112,6 +113,11 @@ void plan_select(SelectArgs& a) {
     a.table_size = 8;
     while (a.merge && a.table_size < 2 * n_cand) a.table_size <<= 1;
   }
+}
+
+// Keys that the threads of one workgroup can hold in registers: the compaction then scores by the keys alone itself.
+bool keydiff_in_compaction(int n_cand, int head_dim) {
+  return n_cand <= kKeydiffRowsPerThread * (kSelectThreads / (head_dim / 8));
 }
 
 // ---- compaction: row pairs (K row and V row of a slot, 16 bytes per lane) a workgroup carries

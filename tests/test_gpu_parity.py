@@ -447,6 +447,21 @@ def test_odd_sizes_lockstep():
         cache.close()
 
 
+@pytest.mark.parametrize("hq,hkv,d,c,n", [(2, 2, 128, 200, 55), (2, 1, 128, 700, 324), (2, 1, 128, 700, 325), (4, 2, 64, 100, 413),
+                                          (2, 1, 64, 1500, 548), (2, 1, 64, 1500, 549)])
+def test_keydiff_scored_by_the_compaction_edges(hq, hkv, d, c, n):
+    """Scores by the keys alone inside the compaction launch: its four and sixteen rows per thread, and the first
+    heads that are too large for it."""
+    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, c, 600, seed=c + n, keydiff=True)
+    scores_gpu, keep, _ = cache.debug_last(0)
+    got = scores_gpu.cpu().numpy().astype(np.float64)
+    assert np.abs(got - scores_ref).max() <= 2e-5
+    tok = np.concatenate([oc.idx, np.broadcast_to(np.arange(c, c + n), (hkv, n))], axis=1)
+    for hk in range(hkv):
+        assert np.array_equal(keep.cpu().numpy()[hk].astype(bool), O.select_keep(scores_gpu.cpu().numpy()[hk], tok[hk], c))
+    cache.close()
+
+
 @pytest.mark.parametrize("d,c,n,budget,t0,levels", [
     (64, 700, 324, 700, 700, 5),          # 1024 candidates, one per thread; hundreds of equal scores at the threshold
     (128, 700, 325, 650, 30000, 40),      # one more; a token table with an entry per token of a long prefix
