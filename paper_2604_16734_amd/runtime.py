@@ -38,46 +38,46 @@ class Prefill:
         if self.overlap and (int(cache.cfg.scratch_sets) or 1) < 2:
             raise ValueError("overlap needs a cache created with scratch_sets >= 2")
         self.side = torch.cuda.Stream(device=cache.device) if self.overlap else None
+        self._pointers = B.ctypes.c_void_p * n_layers
 
     def _streams(self):
-        main = self.torch.cuda.current_stream(self.cache.device).cuda_stream
-        return main, (self.side.cuda_stream if self.side is not None else None)
+        return self.cache._stream(), (self.side.cuda_stream if self.side is not None else None)
 
     def block(self, t0, qkv_of_layer, out_of_layer=None, obs_of_layer=None, keydiff=False):
         """One block of the prefix through all layers.  `qkv_of_layer(l)` gives the block's
         (q, k, v) of layer l, `out_of_layer(l)` the tensor the attention output goes to (or None).
         The candidates are scored by the block's own queries, or by the proxy queries
         `obs_of_layer(l)`, or (`keydiff`) by the keys alone.  Returns the list of outputs."""
-        cache, torch = self.cache, self.torch
-        bf = torch.bfloat16
-        qs, ks, vs, outs, obs = [], [], [], [], []
-        n = None
+        cache, bf, ptr = self.cache, self.torch.bfloat16, self.cache._ptr
+        new = self._pointers
+        qp, kp, vp, op, obs_p = new(), new(), new(), new(), new()
+        held, outs = [], []      # everything the kernels read stays alive until they are enqueued
+        n, n_obs = None, 0
         for layer in range(self.n_layers):
             q, k, v = qkv_of_layer(layer)
-            n = q.shape[0]
-            assert q.shape == (n, cache.cfg.n_q_heads, cache.cfg.head_dim)
-            assert k.shape == v.shape == (n, cache.cfg.n_kv_heads, cache.cfg.head_dim)
             out = out_of_layer(layer) if out_of_layer else None
-            if out is None:
-                out = torch.empty_like(q)
-            assert out.shape == q.shape
-            qs.append(q); ks.append(k); vs.append(v); outs.append(out)
+            n, qp[layer], kp[layer], vp[layer], op[layer], out = cache._prefill_args(q, k, v, out)
+            outs.append(out)
+            held.append((q, k, v))
             if obs_of_layer is not None and not keydiff:
                 o = obs_of_layer(layer)
-                assert o.shape[1:] == q.shape[1:] and (not obs or o.shape[0] == obs[0].shape[0])
-                obs.append(o)
-        scoring = B.KVP_SCORE_KEYDIFF if keydiff else (B.KVP_SCORE_PROXY if obs else B.KVP_SCORE_OWN)
-        ptr = lambda ts: [cache._ptr(t, bf) for t in ts]
+                assert o.shape[1:] == q.shape[1:] and (not layer or o.shape[0] == n_obs)
+                n_obs = o.shape[0]
+                obs_p[layer] = ptr(o, bf)
+                held.append((o,))
+        proxy = obs_of_layer is not None and not keydiff
+        scoring = B.KVP_SCORE_KEYDIFF if keydiff else (B.KVP_SCORE_PROXY if proxy else B.KVP_SCORE_OWN)
         main, side = self._streams()
-        rc = B.kvp_prefill_block(cache.handle, t0, n, ptr(qs), ptr(ks), ptr(vs), ptr(outs), scoring,
-                                 ptr(obs) if obs else None, obs[0].shape[0] if obs else 0, main, side)
+        rc = cache._lib.kvp_prefill_block(cache.handle, t0, n, qp, kp, vp, op, scoring, obs_p if proxy else None,
+                                          n_obs, main, side)
         B._check(rc, "kvp_prefill_block")
         if self.side is not None:
             # the compactions just enqueued on the side stream read the block's K and V after this
             # call returns: tell torch's allocator, so that memory the caller drops now is not
             # handed out again before the side stream is done with it
-            for t in ks + vs:
-                t.record_stream(self.side)
+            for t in held:
+                for kv in t[1:]:
+                    kv.record_stream(self.side)
         return outs
 
     def finish(self):
