@@ -19,8 +19,10 @@
 // Two ways to spread the work:
 //   few keys (up to 640 at head dimension 128): one workgroup of 1024 threads per QUERY head takes all of
 //            them and writes the result, one launch.  (A CU takes 64 bytes a clock from L2: beyond
-//            about 700 keys that costs more than the second launch below.)  10.2 -> 6 us per layer at
-//            32/32 heads, 265 keys;
+//            about 700 keys that costs more than the second launch below.)  The kernel is built for each
+//            number of rows a thread may hold, one to ten: rows past the end are loaded again at full price,
+//            so a step takes the fewest that cover its keys.  10.3 -> 5.4 us per layer at 32/32 heads, 265 keys
+//            (6.4 with ten rows per thread), 15.2 -> 6.0 at 28/4 heads, 553 keys;
 //   else     a workgroup of 256 threads takes 64 keys of one KV head at a time for all G query heads of
 //            the group and leaves (unnormalised output, maximum, sum) per query head; a second kernel
 //            folds the workgroups' partials in a fixed order and rounds once to bfloat16.
@@ -297,16 +299,20 @@ decode_fold_kernel(const DecodeArgs a) {
   }
 }
 
+// few keys: one launch, as many rows per thread as the keys need
+constexpr int kHeadLoads = 10;
+template <int D> constexpr int kHeadRows = kHeadThreads / (D / 8);
+template <int D, int kLoads = 1>
+hipError_t launch_head(const DecodeArgs& a, hipStream_t s) {
+  if constexpr (kLoads < kHeadLoads)
+    if (a.c + a.n_tail > kLoads * kHeadRows<D>) return launch_head<D, kLoads + 1>(a, s);
+  hipLaunchKernelGGL((decode_head_kernel<D, kLoads>), dim3(a.n_q_heads), dim3(kHeadThreads), 0, s, a);
+  return hipGetLastError();
+}
+
 template <int D>
 hipError_t launch_for(const DecodeArgs& a, hipStream_t s) {
-  // few keys: one launch (10 rows per thread at most)
-  constexpr int kRows = kHeadThreads / (D / 8);
-  const long long n_keys = (long long)a.c + a.n_tail;
-  if (n_keys <= 10 * kRows) {
-    if (n_keys <= 4 * kRows) hipLaunchKernelGGL((decode_head_kernel<D, 4>), dim3(a.n_q_heads), dim3(kHeadThreads), 0, s, a);
-    else hipLaunchKernelGGL((decode_head_kernel<D, 10>), dim3(a.n_q_heads), dim3(kHeadThreads), 0, s, a);
-    return hipGetLastError();
-  }
+  if ((long long)a.c + a.n_tail <= kHeadLoads * kHeadRows<D>) return launch_head<D>(a, s);
   const dim3 grid(a.n_splits, a.n_kv_heads);
   const int group = a.n_q_heads / a.n_kv_heads;
   if (group <= 4) hipLaunchKernelGGL((decode_kernel<D, 4>), grid, dim3(kThreads), 0, s, a);

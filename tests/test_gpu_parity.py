@@ -293,8 +293,8 @@ def test_decode_step(hq, hkv, d, c, n_tail, budget, chunk_max, scale):
 
 
 @pytest.mark.parametrize("hq,hkv,d,n_keys", [
-    # one workgroup per query head: edges of its four and ten rows per thread, and the first keys beyond
-    (8, 2, 128, 255), (8, 2, 128, 257), (7, 7, 128, 640), (7, 1, 128, 641), (4, 4, 64, 513), (12, 4, 64, 1280), (12, 4, 64, 1281),
+    # one workgroup per query head: edges of its rows per thread, and the first keys beyond
+    (8, 2, 128, 64), (8, 2, 128, 65), (8, 2, 128, 255), (8, 2, 128, 257), (7, 7, 128, 640), (7, 1, 128, 641), (4, 4, 64, 513), (12, 4, 64, 1280), (12, 4, 64, 1281),
     # partial results: a workgroup whose last waves have no key, more than 48 partials to fold
     (10, 1, 128, 705), (4, 4, 64, 64 * 49 + 1)])
 def test_decode_step_edges(hq, hkv, d, n_keys):
