@@ -416,7 +416,7 @@ static RowstatArgs rowstat_args(kvp_cache* c, int layer, int count, int n_tokens
   return ra;
 }
 
-static ColsumArgs colsum_args(kvp_cache* c, int layer, int count, int n_tokens, int n_rows, int shift) {
+static ColsumArgs colsum_args(kvp_cache* c, int layer, int n_layers, int count, int n_tokens, int n_rows, int shift) {
   const kvp_config& cfg = c->cfg;
   const Layout& lay = c->lay;
   unsigned char* set = c->set(layer);
@@ -429,7 +429,7 @@ static ColsumArgs colsum_args(kvp_cache* c, int layer, int count, int n_tokens, 
   cs.n_q_heads = cfg.n_q_heads; cs.n_kv_heads = cfg.n_kv_heads;
   cs.budget = cfg.budget; cs.lse_stride = cfg.chunk_max; cs.cand_stride = lay.cand_stride;
   cs.scale_log2 = c->scale * 1.4426950408889634f;
-  plan_colsum(cs, cfg.head_dim);
+  plan_colsum(cs, n_layers);
   return cs;
 }
 
@@ -473,10 +473,10 @@ static int score_deferred_layers(kvp_cache* c, int first, int count, hipStream_t
       if (rc) return rc;
     } else {
       RowstatArgs ra = rowstat_args(c, layer, A.count, A.n, A.n_obs);
-      ColsumArgs cs = colsum_args(c, layer, A.count, A.n, A.n_obs, A.n);
+      ColsumArgs cs = colsum_args(c, layer, m, A.count, A.n, A.n_obs, A.n);
       ra.g = g;
       cs.g = g;
-      for (int i = 0; i < m; ++i) ra.q_layer[i] = cs.q_layer[i] = c->layers[layer + i].q_obs;
+      for (int i = 0; i < m; ++i) ra.layer[i] = cs.layer[i] = ScoreLayer{c->layers[layer + i].q_obs, g.k_new[i]};
       int rc = launch(c, KVP_K_ROWSTAT, m, s, [&] { return launch_rowstat(ra, cfg.head_dim, s); });
       if (rc) return rc;
       rc = launch(c, KVP_K_COLSUM, m, s, [&] { return launch_colsum(cs, cfg.head_dim, s); });
@@ -576,9 +576,9 @@ static int prefill_layers(kvp_cache* c, int first, int count, int32_t token_begi
       }
     }
     if (unscored == 0) {
-      ColsumArgs cs = colsum_args(c, first, cached, n_tokens, aa.n, aa.shift);
+      ColsumArgs cs = colsum_args(c, first, count, cached, n_tokens, aa.n, aa.shift);
       cs.g = group;
-      for (int i = 0; i < count; ++i) cs.q_layer[i] = aa.layer[i].q;
+      for (int i = 0; i < count; ++i) cs.layer[i] = ScoreLayer{aa.layer[i].q, group.k_new[i]};
       rc = launch(c, KVP_K_COLSUM, count, s, [&] { return launch_colsum(cs, cfg.head_dim, s); });
       if (rc) return rc;
       n_partials = cs.n_partials;

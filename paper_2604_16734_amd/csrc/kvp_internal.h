@@ -90,41 +90,46 @@ struct AttnArgs {
 // Column sums of the softmax matrix (Eq. 4 summed over rows and over the query
 // heads of a KV group), one partial array per row split.
 constexpr int kColsumMaxKvBlocks = 64;
+struct ScoreLayer {
+  const u16* q;        // [n, Hq, D]
+  const u16* k_new;    // [n_keys, Hkv, D]
+};
 struct ColsumArgs {
-  // One launch scores a group of layers (grid y = layer): layer i of the group reads its queries
-  // from q_layer[i], the block's keys from g.k_new[i], the cache g.kv_stride elements further on
-  // per layer, and its statistics and partials from scratch set (g.first_set + i) % g.n_sets.
-  LayerGroup g;
-  const u16* q_layer[kMaxGroupLayers];
-  const u16* k_cache;  // of the group's first layer
-  const float* lse2;   // in the first layer's scratch set, like partial
-  float* partial;      // [Hkv, n_partials, cand_stride]
+  // One launch scores a group of layers (grid y = layer): layer i of the group reads the cache
+  // g.kv_stride elements further on per layer, and its statistics and partials from scratch set
+  // (g.first_set + i) % g.n_sets.  In the order of AttnArgs.
   int n, c, n_q_heads, n_kv_heads, budget, lse_stride, cand_stride;
   int n_keys, shift;   // as in AttnArgs
   int n_kv_blocks;     // blocks of 256 * subtiles keys
   int n_partials;      // the most row splits any key block has; every key gets that many partials
   int subtiles;        // 32-key subtiles per wave, chosen by plan_colsum
-  int wgs_per_head;    // = split_prefix[n_kv_blocks]
+  int splits_per_wg;   // row splits a workgroup takes one after the other; more than one only where all blocks have as many
+  int wgs_per_head;    // = split_prefix[n_kv_blocks] where that is one
   int work_per_xcd, total_work;
   float scale_log2;
+  GroupStrides g;
+  const u16* k_cache;  // of the group's first layer
+  const float* lse2;   // in the first layer's scratch set, like partial
+  float* partial;      // [Hkv, n_partials, cand_stride]
   // workgroups [split_prefix[k], split_prefix[k + 1]) of a head share key block k and split the
   // 32-row query tiles that see it evenly among themselves
   int split_prefix[kColsumMaxKvBlocks + 1];
+  ScoreLayer layer[kMaxGroupLayers];
 };
 
 // Row statistics of a short list of proxy queries over all candidates (rowstat.hip).
 struct RowstatArgs {
-  LayerGroup g;        // a group of layers per launch, as in ColsumArgs; g.k_new[i]: [n_keys, Hkv, D]
-  const u16* q_layer[kMaxGroupLayers];   // [n, Hq, D] proxy queries of every layer of the group
-  const u16* k_cache;  // the group's first layer: [Hkv, M, D]
-  float* lse2;         // [Hq, lse_stride] out
-  float* part_m;       // [Hq, n, n_kv_blocks] scratch: row maximum per key block (raw logits)
-  float* part_l;       // [Hq, n, n_kv_blocks] scratch: sum of exp2 against that maximum
   int n, c, n_keys, n_q_heads, n_kv_heads, budget, lse_stride;
   int n_kv_blocks;     // set by launch_rowstat, like the next two
   int items_per_wg;    // (query head, 32-row tile) items a workgroup takes
   int item_splits;     // workgroups that share the items of a KV head
   float scale_log2;
+  GroupStrides g;      // a group of layers per launch, as in ColsumArgs
+  const u16* k_cache;  // the group's first layer: [Hkv, M, D]
+  float* lse2;         // [Hq, lse_stride] out
+  float* part_m;       // [n_kv_blocks, Hq, n] scratch: row maximum per key block (raw logits)
+  float* part_l;       // [n_kv_blocks, Hq, n] scratch: sum of exp2 against that maximum
+  ScoreLayer layer[kMaxGroupLayers];   // q: the proxy queries
 };
 int rowstat_key_blocks(int n_cand);
 hipError_t launch_rowstat(RowstatArgs a, int head_dim, hipStream_t s);
@@ -228,7 +233,7 @@ constexpr int kMaxFusedPartials = 64;                   // beyond that the separ
 hipError_t prepare_attention_split();
 hipError_t prepare_attention();   // function attributes on the current device; once per cache creation
 hipError_t prepare_select();
-void plan_colsum(ColsumArgs& a, int head_dim);
+void plan_colsum(ColsumArgs& a, int n_layers);
 int colsum_max_partials(int group, int chunk_max);
 size_t select_lds_bytes(const SelectArgs& a);
 void plan_select(SelectArgs& a);

@@ -48,37 +48,54 @@ void plan_attention(AttnArgs& a, int /*head_dim*/, int forced_shape) {
 // ---- column sums
 int colsum_max_partials(int /*group*/, int /*chunk_max*/) { return kColsumMaxRowSplits; }
 
-void plan_colsum(ColsumArgs& a, int /*head_dim*/) {
+// Key blocks of 32 * nt * kColsumWaves keys, each with as many row splits as it takes to give a workgroup `tau` of the
+// query tiles that see it.
+static void colsum_work(ColsumArgs& a, int nt, int tau) {
+  const int n_qt = (a.n + 31) / 32;
+  const int block_keys = 32 * nt * kColsumWaves;
+  a.subtiles = nt;
+  a.n_kv_blocks = (a.c + a.n_keys + block_keys - 1) / block_keys;
+  int total = 0, most = 0;
+  for (int k = 0; k < a.n_kv_blocks; ++k) {
+    const int blk0 = k * block_keys;
+    const int first_tile = blk0 - a.c > a.shift ? (blk0 - a.c - a.shift) / 32 : 0;
+    const int visible = n_qt - first_tile > 0 ? n_qt - first_tile : 1;
+    const int splits = (visible + tau - 1) / tau;
+    a.split_prefix[k] = total;
+    total += splits;
+    most = splits > most ? splits : most;
+  }
+  a.split_prefix[a.n_kv_blocks] = total;
+  a.wgs_per_head = total;
+  a.n_partials = most;
+}
+
+void plan_colsum(ColsumArgs& a, int n_layers) {
   const int n_cand = a.c + a.n_keys;
   const int n_qt = (a.n + 31) / 32;
   // 64 keys per wave, or 32 when that is what it takes to spread a small launch over the chip
-  int nt = 2;
-  {
-    const int blocks = (n_cand + 64 * kColsumWaves - 1) / (64 * kColsumWaves);
-    const int splits = n_qt < kColsumMaxRowSplits ? n_qt : kColsumMaxRowSplits;
-    if (a.n_kv_heads * blocks * splits < kColsumTargetWorkgroups / 2) nt = 1;
-  }
-  a.subtiles = nt;
-  const int block_keys = 32 * nt * kColsumWaves;
-  a.n_kv_blocks = (n_cand + block_keys - 1) / block_keys;
-  // tiles per workgroup: the fewest that keep the launch within one round (and the row splits of
+  const int wide_blocks = (n_cand + 64 * kColsumWaves - 1) / (64 * kColsumWaves) * a.n_kv_heads;
+  const int most_splits = n_qt < kColsumMaxRowSplits ? n_qt : kColsumMaxRowSplits;
+  const int nt = wide_blocks * most_splits < kColsumTargetWorkgroups / 2 ? 1 : 2;
+  // tiles per row split: the fewest that keep the launch within one round (and the row splits of
   // a block within the partial count)
   int tau = (n_qt + kColsumMaxRowSplits - 1) / kColsumMaxRowSplits;
   for (;; ++tau) {
-    int total = 0, most = 0;
-    for (int k = 0; k < a.n_kv_blocks; ++k) {
-      const int blk0 = k * block_keys;
-      const int first_tile = blk0 - a.c > a.shift ? (blk0 - a.c - a.shift) / 32 : 0;
-      const int visible = n_qt - first_tile > 0 ? n_qt - first_tile : 1;
-      const int splits = (visible + tau - 1) / tau;
-      a.split_prefix[k] = total;
-      total += splits;
-      most = splits > most ? splits : most;
-    }
-    a.split_prefix[a.n_kv_blocks] = total;
-    a.wgs_per_head = total;
-    a.n_partials = most;
-    if (total * a.n_kv_heads <= kColsumTargetWorkgroups || tau >= n_qt) break;
+    colsum_work(a, nt, tau);
+    if (a.wgs_per_head * a.n_kv_heads <= kColsumTargetWorkgroups || tau >= n_qt) break;
+  }
+  // A launch for several layers has workgroups enough without the row splits, and a workgroup pays for its keys
+  // as much as for two or three of its steps.  Grouped and single launches must leave the same bits, so the
+  // sums stay cut where they are: a workgroup takes several splits one after the other, and 64 keys per wave.
+  // Only for proxy queries, where every split of every key block has as much work.
+  a.splits_per_wg = 1;
+  if (a.shift >= a.n_keys && n_layers > 1) {
+    const int splits = a.n_partials;
+    if (nt == 1 && wide_blocks * splits * n_layers >= kColsumTargetWorkgroups) colsum_work(a, 2, tau);
+    const int all = a.n_kv_blocks * a.n_kv_heads * n_layers;
+    while (a.splits_per_wg < splits && all * ((splits + a.splits_per_wg) / (a.splits_per_wg + 1)) >= kColsumTargetWorkgroups)
+      ++a.splits_per_wg;
+    a.wgs_per_head = a.n_kv_blocks * ((splits + a.splits_per_wg - 1) / a.splits_per_wg);
   }
   a.total_work = a.wgs_per_head * a.n_kv_heads;
   a.work_per_xcd = (a.total_work + kXcds - 1) / kXcds;

@@ -13,34 +13,48 @@
 // partials of all key blocks, in a fixed order, into the statistic the scoring
 // kernel reads.  Every candidate is visible to every proxy query (the prompt
 // follows the visual tokens), so there is no mask beyond the end of the keys.
+//
+// Bound by the vector unit (maximum, difference, scale, exponential, sum: 22 cycles per logit and SIMD
+// against 8 of the matrix pipe).  What it must avoid is fetching operands in operand layout, where
+// neighbouring lanes read different rows: that runs at 16 bytes a clock, a quarter of a CU's path, and with
+// every wave fetching every query tile by itself it was two thirds of the time.  Keys and queries
+// therefore come through LDS in whole rows, the queries once per workgroup: 72 -> 48 us for 16 layers of 32/8
+// heads, d 128, 64 queries over 3072 keys (without the fetch of the keys 36, without the matrix products 37, without the
+// exponentials 44), 44 -> 28 us for 8 layers of 28/4 heads, 128 queries over 1536.  Products of the next item among the
+// exponentials of this one, two waves per SIMD instead of four: the same times.
+#include <type_traits>
+
 #include "kvp_internal.h"
+#include "mfma_tools.h"
 
 namespace kvp {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kWaves = 4;
+constexpr int kThreads = 64 * kWaves;
 constexpr int kSub = 2;                        // 32-key subtiles per wave
 constexpr int kWaveKeys = 32 * kSub;
-constexpr int kBlockKeys = 4 * kWaveKeys;
+constexpr int kBlockKeys = kWaves * kWaveKeys;
+constexpr int kRing = 4;                       // query tiles in LDS: the pair in use and the pair in flight
+constexpr int kStats = 4;                      // items whose statistics wait in LDS: the pair in work and the pair being folded
 static_assert(kBlockKeys == kRowstatBlockKeys, "the host plans with this block size");
 
-__device__ __forceinline__ float other_half(float x) { return __shfl_xor(x, 32, 64); }
-
 // grid (key blocks, KV heads x item splits, layers of the group).  An item is one 32-row tile of
-// one query head of the KV group; a workgroup keeps its 256 keys in registers (A operand: a wave
-// its 64) and takes `items_per_wg` items one after the other, the query fragments of the next
-// item on their way while the current one is worked on: every key is fetched once per workgroup
-// instead of once per item.
+// one query head of the KV group; a workgroup takes `items_per_wg` of them, in pairs.
 template <int D>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kThreads, 4)
 rowstat_kernel(const RowstatArgs a) {
-  __shared__ float s_m[2][4][32], s_l[2][4][32];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int kChunks = D / 8;                   // 16-byte chunks per row
+  constexpr int kTile = 32 * D;
+  constexpr int kRowsPerLoad = 64 / kChunks;       // rows one wave instruction brings in
+  constexpr int kLoads = 32 / kRowsPerLoad;        // instructions for 32 rows
+  __shared__ __align__(1024) u16 q_lds[kRing][kTile];        // (and, before the first of them, each wave's keys)
+  auto& k_lds = q_lds;
+  static_assert(kRing >= kWaves);
+  __shared__ float s_m[kStats][kWaves][32], s_l[kStats][kWaves][32];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
   const int group = a.n_q_heads / a.n_kv_heads;
   const int kb = blockIdx.x, li = blockIdx.z;
@@ -49,101 +63,182 @@ rowstat_kernel(const RowstatArgs a) {
   const int n_items = group * n_rt;
   const int item0 = isplit * a.items_per_wg, item1 = min(n_items, item0 + a.items_per_wg);
   if (item0 >= item1) return;
-  const u16* const q_rows = a.q_layer[li];
-  const u16* const k_new = a.g.k_new[li];
+  const u16* const q_rows = a.layer[li].q;
+  const u16* const k_new = a.layer[li].k_new;
   const u16* const k_cache = a.k_cache + (long long)li * a.g.kv_stride;
   float* const part_m = in_set_of(a.part_m, a.g, li);
   float* const part_l = in_set_of(a.part_l, a.g, li);
   const int c = a.c, n_cand = a.c + a.n_keys;
   const int key0 = kb * kBlockKeys + wave * kWaveKeys;
+  const float sl2 = a.scale_log2;
+
+  // global memory -> LDS, 16 bytes per lane, as inline assembly (the compiler would make every later LDS
+  // read wait for a load it knows about); row r keeps its chunk ch at ch ^ (r % kChunks), so
+  // that the fragment reads are free of bank conflicts
+  auto load16 = [&](const u16* src, const u16* to) __attribute__((always_inline)) {
+    const unsigned dst = __builtin_amdgcn_readfirstlane((unsigned)(size_t)(__attribute__((address_space(3))) const void*)to);
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(dst) : "m0", "memory");
+  };
+  const int ld_sub = lane / kChunks, ld_pos = lane % kChunks;
+  // the query tile of item `i` (past the last one: that again), shared out among the waves
+  auto issue_item = [&](int i) __attribute__((always_inline)) {
+    const int item = min(i, item1 - 1);
+    const int h = hk * group + item / n_rt, rt = item % n_rt;
+#pragma unroll
+    for (int j = 0; j < kLoads / kWaves; ++j) {
+      const int first = kRowsPerLoad * (wave + kWaves * j);
+      const int row = first + ld_sub;
+      load16(q_rows + ((size_t)min(32 * rt + row, a.n - 1) * a.n_q_heads + h) * D + 8 * (ld_pos ^ (row % kChunks)),
+             &q_lds[(i - item0) % kRing][first * D]);
+    }
+  };
+  static_assert(kLoads % kWaves == 0, "every wave brings in as much of a query tile");
+  int off[D / 16];             // fragment st of row l32: chunk 2 st + g
+#pragma unroll
+  for (int st = 0; st < D / 16; ++st) off[st] = l32 * D + 8 * ((2 * st + g) ^ (l32 % kChunks));
 
   // A operand: subtile t of this wave is keys key0 + 32 t + (0..31); lane holds K[key][16 s + 8 g .. + 7]
   bf16x8 kf[kSub][D / 16];
 #pragma unroll
   for (int t = 0; t < kSub; ++t) {
-    const int kv = min(key0 + 32 * t + l32, n_cand - 1);
-    const u16* src = (kv < c ? k_cache + ((size_t)hk * a.budget + kv) * D
-                             : k_new + ((size_t)(kv - c) * a.n_kv_heads + hk) * D) + 8 * g;
 #pragma unroll
-    for (int st = 0; st < D / 16; ++st)
-      kf[t][st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(src + 16 * st));
+    for (int j = 0; j < kLoads; ++j) {
+      const int row = kRowsPerLoad * j + ld_sub;
+      const int kv = min(key0 + 32 * t + row, n_cand - 1);
+      const u16* src = kv < c ? k_cache + ((size_t)hk * a.budget + kv) * D : k_new + ((size_t)(kv - c) * a.n_kv_heads + hk) * D;
+      load16(src + 8 * (ld_pos ^ (row % kChunks)), &k_lds[wave][kRowsPerLoad * j * D]);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int st = 0; st < D / 16; ++st) kf[t][st] = lds_read_b128(&k_lds[wave][off[st]]);
+    // the strip is read before the next keys are on their way into it
+#pragma unroll
+    for (int st = 0; st < D / 16; ++st) asm volatile("" : "+v"(kf[t][st]));
   }
-  // B operand of item i: lane holds Q[32 rt + l32][16 s + 8 g .. + 7] of head hk group + i / n_rt
-  auto load_q = [&](bf16x8 (&qf)[D / 16], int item) __attribute__((always_inline)) {
-    const int h = hk * group + item / n_rt, rt = item % n_rt;
-    const int row = min(32 * rt + l32, a.n - 1);
-    const u16* src = q_rows + ((size_t)row * a.n_q_heads + h) * D + 8 * g;
+  __syncthreads();             // everybody has its keys
+  issue_item(item0);
+  issue_item(item0 + 1);
+
+  // S^T of the query tile in ring buffer BUF, subtile t: rows = keys, columns = the 32 query rows
+  auto logits = [&](int buf, f32x16 (&s)[kSub]) __attribute__((always_inline)) {
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int st = 0; st < D / 16; ++st) qf[st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(src + 16 * st));
+    for (int st = 0; st < D / 16; ++st) {
+      const bf16x8 qf = lds_read_b128(&q_lds[buf][off[st]]);
+#pragma unroll
+      for (int t = 0; t < kSub; ++t) s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t][st], qf, st == 0 ? zero : s[t], 0, 0, 0);
+    }
   };
-  auto one_item = [&](const bf16x8 (&qf)[D / 16], int item, int buf) __attribute__((always_inline)) {
-    // S^T subtile t: rows = keys, columns = the 32 query rows
-    float m = -INFINITY, l = 0.f;
-    f32x16 s[kSub];
+  // A vector instruction may read the result of a 32x32x16 matrix instruction only twelve wait states after it
+  // was issued, and nobody counts those across a branch: the distance is paid at the end of the block.
+  auto settle = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 7\n\ts_nop 3");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // (maximum, sum of exp2) of every row over this wave's keys, for item `i`.  `cut`: some of the keys lie past the end.
+  auto statistics = [&](const f32x16 (&s_in)[kSub], int i, auto cut) __attribute__((always_inline)) {
+    f32x16 s[kSub] = {s_in[0], s_in[1]};
+    float mx[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
 #pragma unroll
     for (int t = 0; t < kSub; ++t) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[t][r] = 0.f;
-#pragma unroll
-      for (int st = 0; st < D / 16; ++st) s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t][st], qf[st], s[t], 0, 0, 0);
       // accumulator register r of lane group g is key 8 (r / 4) + 4 g + r % 4 of the subtile
       const int left = n_cand - (key0 + 32 * t) - 4 * g;      // keys of this lane's list that exist
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        if (8 * (r >> 2) + (r & 3) >= left) s[t][r] = -INFINITY;
-        m = fmaxf(m, s[t][r]);
-      }
+      for (int r = 0; r < 16; ++r)
+        if (decltype(cut)::value && 8 * (r >> 2) + (r & 3) >= left) s[t][r] = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16; r += 2) mx[r / 2 % 4] = fmaxf(fmaxf(mx[r / 2 % 4], s[t][r]), s[t][r + 1]);
     }
-    m = fmaxf(m, other_half(m));               // lanes l and l + 32 hold the two halves of a row's keys
-    const float m_use = m == -INFINITY ? 0.f : m;
+    // lanes l and l + 32 hold the two halves of a row's keys
+    const float m = max_with_other_half(fmaxf(fmaxf(mx[0], mx[1]), fmaxf(mx[2], mx[3])));
+    const float m_use = decltype(cut)::value && m == -INFINITY ? 0.f : m;
+    float l = 0.f;
 #pragma unroll
     for (int t = 0; t < kSub; ++t)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) l += __builtin_amdgcn_exp2f((s[t][r] - m_use) * a.scale_log2);
-    l += other_half(l);
-    if (g == 0) { s_m[buf][wave][l32] = m; s_l[buf][wave][l32] = l; }
-    __syncthreads();             // one barrier per item: the next item writes the other buffer
-    if (tid < 32) {
-      float mm = s_m[buf][0][tid];
+      for (int r = 0; r < 16; ++r) l += __builtin_amdgcn_exp2f((s[t][r] - m_use) * sl2);
+    const float sum = sum_with_other_half(l);
+    const int at = i - item0;
+    s_m[at % kStats][wave][l32] = m;           // (both halves write the same)
+    s_l[at % kStats][wave][l32] = sum;
+  };
+  // the four waves' pairs of the items `first`, `first + 1`
+  auto fold = [&](int first) __attribute__((always_inline)) {
+    const int row_of = tid & 31, item = first + (tid >> 5);
+    if (first < item0 || tid >= 64 || item >= item1) return;
+    const int at = (item - item0) % kStats;
+    float mm = s_m[at][0][row_of];
 #pragma unroll
-      for (int w = 1; w < 4; ++w) mm = fmaxf(mm, s_m[buf][w][tid]);
-      const float mu = mm == -INFINITY ? 0.f : mm;
-      float ll = 0.f;
+    for (int w = 1; w < kWaves; ++w) mm = fmaxf(mm, s_m[at][w][row_of]);       // finite: a block holds at least one key
+    float ll = 0.f;
 #pragma unroll
-      for (int w = 0; w < 4; ++w) ll += s_l[buf][w][tid] * __builtin_amdgcn_exp2f((s_m[buf][w][tid] - mu) * a.scale_log2);
-      const int h = hk * group + item / n_rt, rt = item % n_rt;
-      const int row = 32 * rt + tid;
-      if (row < a.n) {
-        const size_t at = ((size_t)h * a.n + row) * a.n_kv_blocks + kb;
-        part_m[at] = mm;
-        part_l[at] = ll;
-      }
+    for (int w = 0; w < kWaves; ++w) ll += s_l[at][w][row_of] * __builtin_amdgcn_exp2f((s_m[at][w][row_of] - mm) * sl2);
+    const int h = hk * group + item / n_rt, row = 32 * (item % n_rt) + row_of;
+    if (row < a.n) {
+      const size_t to = ((size_t)kb * a.n_q_heads + h) * a.n + row;
+      part_m[to] = mm;
+      part_l[to] = ll;
     }
   };
-  bf16x8 qa[D / 16], qb[D / 16];
-  load_q(qa, item0);
-  for (int item = item0; item < item1; item += 2) {
-    load_q(qb, min(item + 1, item1 - 1));
-    one_item(qa, item, 0);
-    load_q(qa, min(item + 2, item1 - 1));
-    if (item + 1 < item1) one_item(qb, item + 1, 1);
-  }
+  // One barrier per pair of items: this wave's share of the pair from item i on has landed and everybody is
+  // through with the pair before: its buffers take the next pair, and its statistics are folded.
+  auto publish = [&](int i) __attribute__((always_inline)) {
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    issue_item(i + 2);
+    issue_item(i + 3);
+    fold(i - 2);
+  };
+  auto all_items = [&](auto cut) __attribute__((always_inline)) {
+    for (int i = item0; i < item1; ++i) {
+      if ((i - item0) % 2 == 0) publish(i);
+      f32x16 s[kSub];
+      logits((i - item0) % kRing, s);
+      statistics(s, i, cut);
+    }
+  };
+  if (key0 + kWaveKeys <= n_cand) all_items(std::false_type{});
+  else all_items(std::true_type{});
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  fold(item0 + (item1 - 1 - item0) / 2 * 2);
 }
 
-// lse2[h][row] from the partials of all key blocks, folded in block order
-__global__ void rowstat_fold_kernel(const RowstatArgs a) {
+// lse2[h][row] from the partials of all key blocks, folded in block order; kFoldBatch of them are on their way together
+constexpr int kFoldBatch = 16;
+__global__ void __launch_bounds__(256)
+rowstat_fold_kernel(const RowstatArgs a) {
   // grid (blocks of 256 rows, layers of the group)
   const int i = blockIdx.x * blockDim.x + threadIdx.x, li = blockIdx.y;
-  if (i >= a.n_q_heads * a.n) return;
-  const float* const part_m = in_set_of(a.part_m, a.g, li);
-  const float* const part_l = in_set_of(a.part_l, a.g, li);
+  const int rows = a.n_q_heads * a.n;
+  if (i >= rows) return;
+  const float* const part_m = in_set_of(a.part_m, a.g, li) + i;
+  const float* const part_l = in_set_of(a.part_l, a.g, li) + i;
+  // two passes over the partials, the maximum first; up to a batch of them stays in registers for the second
+  float pm[kFoldBatch], pl[kFoldBatch], m = -INFINITY, l = 0.f;
+  auto fetch = [&](int first) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < kFoldBatch; ++u) {
+      // (past the end: the last one again, with weight 0; a load under a condition would be waited for on the spot)
+      const size_t at = (size_t)min(first + u, a.n_kv_blocks - 1) * rows;
+      pm[u] = part_m[at];
+      pl[u] = part_l[at];
+    }
+  };
+  for (int first = 0; first < a.n_kv_blocks; first += kFoldBatch) {
+    fetch(first);
+#pragma unroll
+    for (int u = 0; u < kFoldBatch; ++u) m = fmaxf(m, pm[u]);
+  }
+  for (int first = 0; first < a.n_kv_blocks; first += kFoldBatch) {
+    if (a.n_kv_blocks > kFoldBatch) fetch(first);
+#pragma unroll
+    for (int u = 0; u < kFoldBatch; ++u) {
+      const float f = __builtin_amdgcn_exp2f((pm[u] - m) * a.scale_log2);
+      l = __builtin_fmaf(pl[u], first + u < a.n_kv_blocks ? f : 0.f, l);
+    }
+  }
   const int h = i / a.n, row = i % a.n;
-  const size_t at = ((size_t)h * a.n + row) * a.n_kv_blocks;
-  float mm = -INFINITY;
-  for (int b = 0; b < a.n_kv_blocks; ++b) mm = fmaxf(mm, part_m[at + b]);
-  float ll = 0.f;
-  for (int b = 0; b < a.n_kv_blocks; ++b) ll += part_l[at + b] * __builtin_amdgcn_exp2f((part_m[at + b] - mm) * a.scale_log2);
-  in_set_of(a.lse2, a.g, li)[(size_t)h * a.lse_stride + row] = mm * a.scale_log2 + __builtin_log2f(ll);
+  in_set_of(a.lse2, a.g, li)[(size_t)h * a.lse_stride + row] = m * a.scale_log2 + __builtin_log2f(l);
 }
 
 }  // namespace
@@ -151,12 +246,19 @@ __global__ void rowstat_fold_kernel(const RowstatArgs a) {
 hipError_t launch_rowstat(RowstatArgs a, int head_dim, hipStream_t s) {
   a.n_kv_blocks = rowstat_key_blocks(a.c + a.n_keys);
   if (a.g.n_layers < 1 || a.g.n_layers > kMaxGroupLayers) return hipErrorInvalidValue;
-  // items (32-row tiles x query heads of a KV group) per workgroup: as many as still leave about
-  // two workgroups per compute unit
+  // Items (32-row tiles x query heads of a KV group) per workgroup: a workgroup's keys cost it as much as about six
+  // items, and up to two workgroups per CU more of them cost nothing.
   const int n_items = (a.n_q_heads / a.n_kv_heads) * ((a.n + 31) / 32);
-  const long long units = (long long)n_items * a.n_kv_blocks * a.n_kv_heads * a.g.n_layers;
-  long long per = units / 512;
-  a.items_per_wg = (int)(per < 1 ? 1 : per > n_items ? n_items : per);
+  const long long blocks = (long long)a.n_kv_blocks * a.n_kv_heads * a.g.n_layers;
+  long long best = 0;
+  for (int splits = 1; splits <= n_items; ++splits) {
+    const int per = (n_items + splits - 1) / splits;
+    const long long workgroups = blocks * splits, cost = (workgroups < 512 ? 512 : workgroups) * (per + 6);
+    if (splits == 1 || cost < best) {
+      best = cost;
+      a.items_per_wg = per;
+    }
+  }
   a.item_splits = (n_items + a.items_per_wg - 1) / a.items_per_wg;
   if ((long long)a.n_kv_heads * a.item_splits > 65535) return hipErrorInvalidValue;
   const dim3 grid(a.n_kv_blocks, a.n_kv_heads * a.item_splits, a.g.n_layers);

@@ -735,6 +735,28 @@ def test_compact_layers_is_the_per_layer_compaction(name, layers, scoring):
                                y.view(torch.int16) if y.dtype == torch.bfloat16 else y)
 
 
+@pytest.mark.parametrize("layers,hq,hkv,d,c,n,n_obs", [
+    # three row splits of a key block per workgroup; two and then one; a last split of a single row tile more
+    (16, 8, 8, 64, 700, 300, 75), (12, 8, 8, 64, 700, 300, 75), (16, 6, 2, 128, 1793, 256, 193)])
+def test_grouped_proxy_scores_edges(layers, hq, hkv, d, c, n, n_obs):
+    """Workgroups of a grouped scoring launch take several row splits in turn: the scores are those
+    of the launches for one layer, bit for bit (and those are checked against the oracle)."""
+    gen = torch.Generator(device=DEV).manual_seed(c + n_obs)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device=DEV).to(torch.bfloat16)
+    data = [(draw(c + n, hq, d), draw(c + n, hkv, d), draw(c + n, hkv, d), draw(n_obs, hq, d)) for _ in range(layers)]
+    scores = []
+    for grouped in (False, True):
+        cache = K.Cache(layers, hq, hkv, d, c, max(c, n), [Segment(0, c + n, 0)], scratch_sets=layers, device=DEV)
+        cache.set_deferred_scoring(int(grouped))
+        for t0, m in ((0, c), (c, n)):
+            for l, (q, k, v, o) in enumerate(data):
+                cache.prefill_chunk_proxy(l, t0, q[t0:t0 + m], k[t0:t0 + m], v[t0:t0 + m], o)
+            cache.compact_layers(0, layers)
+        scores.append([cache.debug_last(l)[0].clone() for l in range(layers)])
+        cache.close()
+    assert all(torch.equal(x, y) for x, y in zip(*scores))
+
+
 def test_bench_launch_configuration_changes_nothing():
     """bench.py's default order at its own shape: everything in line on one stream, sixteen scratch
     sets, so that select, merge and move go out once per sixteen layers of long_video.  The first
