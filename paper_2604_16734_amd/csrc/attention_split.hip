@@ -23,7 +23,13 @@
 // was built and measured slower: a round of two waves per SIMD takes the sum of their matrix and vector time
 // either way, and the pipeline works out one block more per wave.  So was a touch of all the head's cache lines up
 // front: the blocks do not wait for memory.)
-// Two waves share a SIMD: one has matrix work while the other has vector work.
+// Two waves share a SIMD: one has matrix work while the other has vector work.  They start together and would stay
+// in step, both at the same kind of work; a wave therefore raises its priority once its products S are on their way and
+// lowers it at the end of the block, so that the one that is ahead stays ahead (16/4 heads, d 64, 333 rows over 1444
+// keys: 13.6 -> 13.3 us; 28/4 heads, d 128, 256 rows over 768 keys: 9.3 -> 9.0 us per layer of a grouped launch;
+// 28/4 heads, 512 rows over 1536 keys, second sweep only: 26.1 -> 25.7 us).  Not with two row tiles in the first sweep,
+// whose barrier per round keeps the waves together anyhow.  Leaving out the maximum of every later block, with a
+// check of the row sums instead, was slower (25.7 -> 26.7 us): the waves of a SIMD fall into step again.
 //
 // Softmax reference.  A row's reference is the maximum of its first visible block; a later logit more
 // than 2^30 above it (fp32 has room for 2^127) sends the wave through a branch that brings O and the
@@ -247,6 +253,7 @@ attention_split_kernel(const AttnArgs a) {
     for (int st = 0; st < kNK; ++st) kf[st] = lds_read_b128(k_from + k_off[st]);
 #pragma unroll
     for (int st = 0; st < kNK; ++st) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st], qf[st], st == 0 ? zero : s, 0, 0, 0);
+    if constexpr (!kShared) __builtin_amdgcn_s_setprio(1);
     k_read();
     if (b.rows < 32 || (!b.cached && b.first + 31 > q0 + shift)) {         // some row may not see some key
       const int last = b.cached ? b.rows - 1 : min(b.rows - 1, q0 + l32 + shift - b.first);
@@ -296,6 +303,7 @@ attention_split_kernel(const AttnArgs a) {
 #pragma unroll
     for (int dt = 0; dt < kND; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kND + dt], p_frag(pw, 1), o[dt], 0, 0, 0);
     l_run += sum;
+    if constexpr (!kShared) __builtin_amdgcn_s_setprio(0);
   };
   if constexpr (kShared) {
     const int n_rounds = (n_kb + KS - 1) / KS;
@@ -432,6 +440,7 @@ attention_split_kernel(const AttnArgs a) {
 #pragma unroll
         for (int t = T0; t < QW; ++t)
           s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qs[t][st], kf[st], st == 0 ? zero : s[t], 0, 0, 0);
+      __builtin_amdgcn_s_setprio(1);
       const Block kb = block_of(b);
       float sum[2] = {0.f, 0.f};
       // every row sees every key and all are real
@@ -456,6 +465,7 @@ attention_split_kernel(const AttnArgs a) {
       }
       const float tot = sum_with_other_half(sum[0] + sum[1]);  // lanes l and l + 32 hold the two halves of the rows
       if (g == 0 && l32 < kb.rows) part[(kb.cached ? 0 : c) + kb.first + l32] = tot;
+      __builtin_amdgcn_s_setprio(0);
       u16* const swap = strip;
       strip = other;
       other = swap;
