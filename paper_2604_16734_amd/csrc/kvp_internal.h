@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "key_range.h"
 #include "kvp.h"
 
 namespace kvp {
@@ -21,7 +22,6 @@ constexpr int kColsumWaves = 4;                 // waves per workgroup of the co
 constexpr int kColsumTargetWorkgroups = 512;    // two per CU, all resident: the launch is a single round
 constexpr int kColsumMaxRowSplits = 16;
 constexpr int kSelectThreads = 1024;
-constexpr int kSelectBins = 2048;               // histogram bins of the selection
 constexpr int kKeydiffRowsPerThread = 16;       // keys a thread of the compaction kernel can hold a piece of
 constexpr size_t kSelectLdsLimit = 156 * 1024;  // dynamic LDS of the compaction kernel, beside 3.5 KiB of static LDS
 constexpr int kRowstatBlockKeys = 256;          // keys per workgroup of the proxy row-statistics kernel

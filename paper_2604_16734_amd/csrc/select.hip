@@ -19,7 +19,7 @@
 //   * the M-th largest key: one histogram of 2048 bins over the range the keys really span (a scale on
 //     float bits, so roughly logarithmic in the score), the bin that holds it, and then a ranking of
 //     the few keys in that bin by every wave for itself.  Should more than 64 keys share the bin
-//     (equal scores) the range shrinks to the bin and the histogram is taken again.
+//     (equal scores) the range shrinks to the bin and the histogram is taken again (key_range.h).
 //   * block-wide prefix sums rank the free slots and the kept block tokens;
 //     the k-th kept block token (ascending token index) gets the k-th free slot.
 //   * merge plan: a token -> position table over the cached tokens (block tokens map directly): one entry per
@@ -422,19 +422,12 @@ compact_kernel(const SelectArgs a) {
   // ---- the budget-th largest key
   unsigned long long threshold;
   {
-    unsigned long long lo = (unsigned long long)ob_min << 32;           // every key of interest is in [lo, lo + (kBins << shift))
-    const unsigned long long span = (((unsigned long long)ob_max << 32) | 0xFFFFFFFFull) - lo;
-    constexpr int kBinBits = 11;
-    static_assert((1 << kBinBits) == kBins, "bins");
-    int shift = max(0, 64 - (int)__builtin_clzll(span) - kBinBits);
+    KeyRange range = KeyRange::over(ob_min, ob_max);
     unsigned want = (unsigned)budget, in_bin = 0;
     for (;;) {
 #pragma unroll
       for (int i = 0; i < kMaxItems; ++i)
-        if (valid[i] && key[i] >= lo) {
-          const unsigned long long bin = (key[i] - lo) >> shift;
-          if (bin < (unsigned long long)kBins) atomicAdd(&l.hist[bin_word((unsigned)bin)], 1u);
-        }
+        if (unsigned bin; valid[i] && range.holds(key[i], bin)) atomicAdd(&l.hist[bin_word(bin)], 1u);
       __syncthreads();
       // every wave finds the bin for itself: lane L adds up bins 32 L .. 32 L + 31, a scan over the lanes finds
       // the lane with the wanted key, and a second one, of that lane's bins, the bin
@@ -455,17 +448,17 @@ compact_kernel(const SelectArgs a) {
       const unsigned digit = 32u * (unsigned)owner + (unsigned)from;
       want -= (unsigned)__builtin_amdgcn_readlane((int)above1, from);
       in_bin = (unsigned)__builtin_amdgcn_readlane((int)one, from);
-      lo += (unsigned long long)digit << shift;
+      range.enter(digit);
       if (in_bin <= 64u) break;
       // more than a wave can rank: look into this bin alone (with shift 0 a bin holds one key: keys are distinct)
-      shift = max(0, shift - kBinBits);
+      range.divide();
       __syncthreads();                                 // everybody has read the histogram
       for (int i = tid; i < kBins; i += kThreads) l.hist[i] = 0u;
       __syncthreads();
     }
 #pragma unroll
     for (int i = 0; i < kMaxItems; ++i)
-      if (valid[i] && key[i] >= lo && ((key[i] - lo) >> shift) == 0ull) s_members[atomicAdd(&s_n_members, 1u)] = key[i];
+      if (unsigned bin; valid[i] && range.holds(key[i], bin)) s_members[atomicAdd(&s_n_members, 1u)] = key[i];
     __syncthreads();
     const unsigned long long k = lane < (int)in_bin ? s_members[lane] : 0ull;
     unsigned rank = 0;

@@ -499,6 +499,49 @@ def test_compaction_edges(d, c, n, budget, t0, levels):
     cache.close()
 
 
+def _compact_on_given_scores(d, c, n, budget, t0, segs, tokens, scores):
+    """A cache preloaded with `tokens` [2, c], one block of n tokens, a compaction on `scores`: the caches of the library
+    and of the oracle, kept set, merge plan, token indices, weights and rows compared."""
+    hkv = 2
+    rng = np.random.default_rng(c + n)
+    cache = K.Cache(1, hkv, hkv, d, budget, n, segs, merge=True, device=DEV)
+    oc = O.LayerCache(hkv, d, budget, segs, True)
+    oc.idx, oc.count = np.asarray(tokens, dtype=np.int64), c
+    oc.w = rng.integers(1, 4, size=(hkv, c))
+    oc.K, oc.V = (O.bf16_bits_to_f64(_rand_bits(rng, (hkv, c, d))) for _ in range(2))
+    U.upload_state(cache, 0, oc)
+    cache.set_state(0, c, t0)
+    qb, kb, vb = (_rand_bits(rng, (n, hkv, d)) for _ in range(3))
+    cache.prefill_chunk(0, t0, U.bits_to_torch(qb), U.bits_to_torch(kb), U.bits_to_torch(vb))
+    cache.compact(0, torch.from_numpy(scores).to(DEV))
+    rec = oc.compact(t0, O.bf16_bits_to_f64(kb), O.bf16_bits_to_f64(vb), scores)
+    used, kept, dst = cache.debug_last(0)
+    assert np.array_equal(used.cpu().numpy(), scores)
+    assert np.array_equal(kept.cpu().numpy().astype(bool), rec["keep"])
+    assert np.array_equal(dst.cpu().numpy().astype(np.int64), rec["dst"])
+    merged = U.compare_state(cache, 0, oc)
+    return cache, merged
+
+
+@pytest.mark.parametrize("d,c,n,budget,t0", [(128, 2048, 1024, 2048, 2048),     # the bench shape
+                                             (64, 1536, 512, 1536, 1536), (64, 512, 256, 512, 700), (64, 4100, 200, 4100, 5000)])
+@pytest.mark.parametrize("kind", ["equal", "half_zero", "zeros"])
+def test_selection_among_equal_scores(kind, d, c, n, budget, t0):
+    """Hundreds of equal scores around the threshold, all of them or beside ordinary ones: as many are kept as the budget
+    says, the lower token indices."""
+    rng = np.random.default_rng(c)
+    gh, gw = 16, 16
+    planes = (t0 + n) // (gh * gw) + 1
+    tokens = np.stack([rng.permutation(t0)[:c] for _ in range(2)])
+    scores = np.full((2, c + n), 0.75 if kind == "equal" else 0.0, dtype=np.float32)
+    if kind == "half_zero":
+        some = rng.permutation(c + n)[:(c + n) // 2]
+        scores[:, some] = 4 * rng.random((2, len(some)), dtype=np.float32)
+    cache, merged = _compact_on_given_scores(d, c, n, budget, t0, (Segment(0, planes * gh * gw, 1, gh, gw, planes, 1),), tokens, scores)
+    assert merged > 0
+    cache.close()
+
+
 def test_maximum_candidates_lockstep():
     """budget + block at the library's limit (8192 candidates per head): the select kernel's
     eight-candidates-per-thread shape, its largest LDS layout, 2048-row blocks."""

@@ -1,0 +1,20 @@
+"""The selection's search for the budget-th largest key (csrc/key_range.h), run on the CPU as the kernel runs it and
+compared with a sort: equal scores, zeros beside ordinary scores, few levels, tokens across multiples of 1024, and every
+width of the first histogram's bins."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+def test_key_search_finds_the_key_a_sort_finds(tmp_path):
+    exe = str(tmp_path / "key_search")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-g", "-fsanitize=address,undefined", "-fno-sanitize-recover=undefined",
+                    "-static-libasan", "-I", os.path.join(os.path.dirname(HERE), "paper_2604_16734_amd", "csrc"),
+                    os.path.join(HERE, "host_asan", "key_search.cpp"), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-3000:] + r.stderr
