@@ -263,7 +263,9 @@ int kvp_decode_step_static(kvp_cache* cache, int32_t layer, const void* q, const
 
 /* Resume: declare that the caller has written `count` valid slots per head
  * into the layer's K, V, token_idx and weight (through the kvp_view pointers)
- * and that the next block starts at `next_token`.  Layer becomes READY. */
+ * and that the next block starts at `next_token`.  Layer becomes READY.  A slot
+ * whose token index is negative or not below the block that evicts is kept or
+ * evicted like any other, but no evicted token is merged into it. */
 int kvp_set_state(kvp_cache* cache, int32_t layer, int32_t count, int32_t next_token);
 
 /* Tuning and test aid: force one of the attention kernel's three workgroup shapes

@@ -384,8 +384,9 @@ compact_kernel(const SelectArgs a) {
       for (int i = 0; i < kMaxItems; ++i) {
         const int p = tid + i * kThreads;
         if (i < items && p < c) {
-          if (a.direct) direct[tokv[i]] = (unsigned short)p;
-          else table_insert(l.table, mask, tokv[i], (unsigned)p);
+          // (a cache that was loaded from outside may hold any token index: one that is not below t0 has no entry)
+          if (!a.direct) table_insert(l.table, mask, tokv[i], (unsigned)p);
+          else if ((unsigned)tokv[i] < (unsigned)a.t0) direct[tokv[i]] = (unsigned short)p;
         }
       }
     }

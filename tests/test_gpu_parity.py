@@ -542,6 +542,26 @@ def test_selection_among_equal_scores(kind, d, c, n, budget, t0):
     cache.close()
 
 
+@pytest.mark.parametrize("d,c,n,t0", [(64, 700, 324, 700),         # the table has an entry per token before the block
+                                      (128, 900, 1100, 60000)])     # a hash table
+def test_cached_tokens_that_the_block_does_not_follow(d, c, n, t0):
+    """A cache written from outside (kvp_set_state) whose token indices are not all below the block: they compete like
+    any other, and the compaction stays inside its memory."""
+    rng = np.random.default_rng(t0)
+    gh, gw = 16, 16
+    planes = (t0 + n) // (gh * gw) + 1
+    n_vis = planes * gh * gw
+    segs = (Segment(0, n_vis, 1, gh, gw, planes, 1), Segment(n_vis, 100000, 0))
+    tokens = np.stack([rng.permutation(t0)[:c] for _ in range(2)])
+    late = rng.permutation(c)[:c // 3]
+    tokens[:, late] = n_vis + rng.permutation(100000)[:len(late)]          # text: nothing to merge, on either side
+    scores = rng.random((2, c + n), dtype=np.float32)
+    tokens[:, late[0]], scores[:, late[0]] = -1, 2.0                       # (kept: the oracle has no place for an evicted one)
+    cache, merged = _compact_on_given_scores(d, c, n, c, t0, segs, tokens, scores)
+    assert merged > 0
+    cache.close()
+
+
 def test_maximum_candidates_lockstep():
     """budget + block at the library's limit (8192 candidates per head): the select kernel's
     eight-candidates-per-thread shape, its largest LDS layout, 2048-row blocks."""
