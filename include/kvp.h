@@ -265,7 +265,10 @@ int kvp_decode_step_static(kvp_cache* cache, int32_t layer, const void* q, const
  * into the layer's K, V, token_idx and weight (through the kvp_view pointers)
  * and that the next block starts at `next_token`.  Layer becomes READY.  A slot
  * whose token index is negative or not below the block that evicts is kept or
- * evicted like any other, but no evicted token is merged into it. */
+ * evicted like any other, but takes no part in merging.  The token indices of a
+ * head should differ from each other: of slots that share one, one at most is
+ * merged, and slots that share score and token index with the last candidate that
+ * fits all stay (the block tokens with the highest indices then find no slot). */
 int kvp_set_state(kvp_cache* cache, int32_t layer, int32_t count, int32_t next_token);
 
 /* Tuning and test aid: force one of the attention kernel's three workgroup shapes

@@ -15,7 +15,8 @@
 //     load and sixteen loads in flight, each group every G-th array; the groups' sums meet in LDS, in a fixed order.
 //   * order: 64-bit key = (score as order-preserving u32) << 32 | ~token, so
 //     "higher score first, equal scores by lower token index" is "larger key
-//     first" and all keys are distinct: the kept set is unique.
+//     first" and all keys are distinct: the kept set is unique.  (Token indices that a caller wrote, kvp_set_state, may
+//     repeat; the kernel then still ends and stays inside its memory.)
 //   * the M-th largest key: one histogram of 2048 bins over the range the keys really span (a scale on
 //     float bits, so roughly logarithmic in the score), the bin that holds it, and then a ranking of
 //     the few keys in that bin by every wave for itself.  Should more than 64 keys share the bin
@@ -450,29 +451,37 @@ compact_kernel(const SelectArgs a) {
       want -= (unsigned)__builtin_amdgcn_readlane((int)above1, from);
       in_bin = (unsigned)__builtin_amdgcn_readlane((int)one, from);
       range.enter(digit);
-      if (in_bin <= 64u) break;
-      // more than a wave can rank: look into this bin alone (with shift 0 a bin holds one key: keys are distinct)
+      // (one key to a bin and still more than 64 of them: cached slots that share score and token index)
+      if (in_bin <= 64u || range.shift == 0) break;
+      // more than a wave can rank: look into this bin alone
       range.divide();
       __syncthreads();                                 // everybody has read the histogram
       for (int i = tid; i < kBins; i += kThreads) l.hist[i] = 0u;
       __syncthreads();
     }
+    if (in_bin > 64u) {
+      threshold = range.lo;
+    } else {
 #pragma unroll
-    for (int i = 0; i < kMaxItems; ++i)
-      if (unsigned bin; valid[i] && range.holds(key[i], bin)) s_members[atomicAdd(&s_n_members, 1u)] = key[i];
-    __syncthreads();
-    const unsigned long long k = lane < (int)in_bin ? s_members[lane] : 0ull;
-    unsigned rank = 0;
-    for (unsigned i = 0; i < in_bin; i += 4) {             // (four reads in flight; past the end: zeros or old keys, not counted)
-      unsigned long long other[4];
+      for (int i = 0; i < kMaxItems; ++i)
+        if (unsigned bin; valid[i] && range.holds(key[i], bin)) s_members[atomicAdd(&s_n_members, 1u)] = key[i];
+      __syncthreads();
+      const unsigned long long k = lane < (int)in_bin ? s_members[lane] : 0ull;
+      unsigned rank = 0;
+      for (unsigned i = 0; i < in_bin; i += 4) {             // (four reads in flight; past the end: zeros or old keys, not counted)
+        unsigned long long other[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) other[u] = s_members[i + u];
+        for (int u = 0; u < 4; ++u) other[u] = s_members[i + u];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) rank += i + u < in_bin && other[u] > k ? 1u : 0u;
+        for (int u = 0; u < 4; ++u) rank += i + u < in_bin && other[u] > k ? 1u : 0u;
+      }
+      // (members that are equal share the rank of the first of them: the last rank up to the wanted one that there is)
+      unsigned long long at = 0ull;
+      for (unsigned r = want; at == 0ull && r > 0u; --r) at = __ballot(lane < (int)in_bin && rank == r - 1u);
+      const int from = __builtin_ctzll(at);
+      threshold = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(k >> 32), from) << 32) |
+                  (unsigned)__builtin_amdgcn_readlane((int)(unsigned)k, from);
     }
-    const int from = __builtin_ctzll(__ballot(lane < (int)in_bin && rank == want - 1u));
-    threshold = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(k >> 32), from) << 32) |
-                (unsigned)__builtin_amdgcn_readlane((int)(unsigned)k, from);
   }
 
   // ---- keep flags; rank the free slots, the kept block tokens and the evicted candidates
@@ -505,7 +514,10 @@ compact_kernel(const SelectArgs a) {
     total += t; total_ev += te;
   }
   unsigned base_free = base & 0xFFFFu;
-  const unsigned base_new = base >> 16, total_new = total >> 16;
+  const unsigned base_new = base >> 16;
+  // (distinct keys: as many slots as new rows.  Slots that share a key with the threshold all stay, and the last of the
+  // block's rows find no slot.)
+  const unsigned total_new = min(total >> 16, total & 0xFFFFu);
 #pragma unroll
   for (int i = 0; i < kMaxItems; ++i) {
     const int p = tid * items + i;
@@ -539,9 +551,17 @@ compact_kernel(const SelectArgs a) {
     // grid neighbour and enters itself there
     for (unsigned e = tid; e < total_ev; e += kThreads) {
       const int p = l.evicted[e];
+      const int tok = (int)~key_words[2 * p];
       int best = -1;
       int nb[kNeighbours];
-      if (neighbours(s_segs, a.n_segs, (int)~key_words[2 * p], nb)) {
+      if (neighbours(s_segs, a.n_segs, tok, nb)) {
+        // of cached slots that share a token index the one in the table merges: a destination then has at most
+        // one source per neighbour, which is what its list has room for
+        int self = p;
+        if (p < c) {
+          if (!a.direct) self = probe(l, mask, tok);
+          else self = (unsigned)tok < (unsigned)a.t0 ? (int)direct[tok] : -1;
+        }
         int r[kNeighbours];              // a token of the block sits at a known position, one after it nowhere
 #pragma unroll
         for (int j = 0; j < kNeighbours; ++j) {
@@ -560,6 +580,7 @@ compact_kernel(const SelectArgs a) {
 #pragma unroll
         for (int j = 0; j < kNeighbours; ++j)
           if (r[j] >= 0 && kr[j] >= threshold && (best < 0 || kr[j] > best_key)) { best = r[j]; best_key = kr[j]; }
+        if (self != p) best = -1;
       }
       dst_out[p] = best;
       if (best >= 0) {

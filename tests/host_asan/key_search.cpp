@@ -49,8 +49,15 @@ static bool right(const std::vector<Key>& keys, unsigned budget, const std::stri
     want -= above;
     in_bin = hist[digit];
     range.enter((unsigned)digit);
-    if (in_bin <= 64u) break;
+    if (in_bin <= 64u || range.shift == 0) break;
     range.divide();
+  }
+  if (in_bin > 64u) {                      // equal keys, as only a cache written from outside has them
+    std::vector<Key> sorted = keys;
+    std::sort(sorted.rbegin(), sorted.rend());
+    if (range.lo == sorted[budget - 1]) return true;
+    std::printf("%s: another key\n", what.c_str());
+    return false;
   }
   std::vector<Key> members;
   for (Key k : keys)
@@ -98,6 +105,13 @@ int main() {
       check(keys([&](unsigned) { return (float)(1 + rng() % (unsigned)levels) / 7.f; }), s.budget, at + ", " + std::to_string(levels) + " levels");
     check(keys([&](unsigned) { return -uniform(rng); }), s.budget, at + ", negative");
     check(keys([&](unsigned i) { return i % 3 ? -0.f : 0.f; }), s.budget, at + ", both zeros");
+    // token indices that repeat: in pairs, in forties, by the hundred, all the same
+    for (unsigned copies : {2u, 40u, 100u, s.n})
+      for (int levels : {1, 3}) {
+        std::vector<Key> k(s.n);
+        for (unsigned i = 0; i < s.n; ++i) k[i] = key_of((float)(1 + rng() % (unsigned)levels), s.token0 + i / copies);
+        check(k, s.budget, at + ", tokens " + std::to_string(copies) + " times");
+      }
     // scores that span 2^j steps of the float scale: the first shift is 21 + j, every one from 21 to 53 - with the
     // threshold among equal scores at the bottom, in the middle and at the top
     for (int j = 0; j <= 32; ++j)

@@ -562,6 +562,59 @@ def test_cached_tokens_that_the_block_does_not_follow(d, c, n, t0):
     cache.close()
 
 
+@pytest.mark.parametrize("t0", [1000, 60000])                 # the two kinds of token table
+@pytest.mark.parametrize("copies", [2, 40, 300])
+def test_cached_tokens_that_repeat(copies, t0):
+    """A cache written from outside whose token indices repeat is no valid state: the compaction still ends, stays inside
+    its memory, keeps what is ordinary about the case, and merges one of the slots that share a token."""
+    hkv, d, c, n = 2, 64, 1000, 300
+    rng = np.random.default_rng(copies)
+    gh, gw = 16, 16
+    planes = (t0 + n) // (gh * gw) + 1
+    segs = (Segment(0, planes * gh * gw, 1, gh, gw, planes, 1),)
+    bits = [_rand_bits(rng, shape) for shape in [(hkv, c, d)] * 2 + [(n, hkv, d)] * 3]
+    at = 8 * gw + 8                                           # a token with five neighbours before the block
+    first = [at - 1, at + 1, at - gw, at + gw, at + gh * gw]
+    others = np.setdiff1d(np.arange(t0), first + [at])
+    tok = np.concatenate([first, np.full(copies, at), rng.permutation(others)[:c]])[:c]
+    assert len(tok) == c
+    for kind in ("evicted", "threshold"):
+        scores = 0.5 + rng.random((hkv, c + n), dtype=np.float32) / 4
+        scores[:, :5] = 1.0
+        if kind == "evicted":
+            scores[:, 5:5 + copies] = 0.25
+        else:                     # room for half of the copies, ten free slots for copies / 2 + 10 rows of the block
+            scores[:, 5:5 + copies] = 0.5
+            scores[:, c - 10:] = 0.25
+            scores[:, c:c + copies // 2 + 10] = 0.9
+        cache = K.Cache(1, hkv, hkv, d, c, n, segs, merge=True, device=DEV)
+        k, v, idx, w, _, _ = cache.decode_ready(0)
+        k.copy_(U.bits_to_torch(bits[0]))
+        v.copy_(U.bits_to_torch(bits[1]))
+        idx.copy_(torch.from_numpy(np.stack([tok] * hkv).astype(np.int32)))
+        w.fill_(1.0)
+        cache.set_state(0, c, t0)
+        cache.prefill_chunk(0, t0, *(U.bits_to_torch(x) for x in bits[2:]))
+        cache.compact(0, torch.from_numpy(scores).to(DEV))
+        torch.cuda.synchronize()
+        assert cache.guards_intact()
+        _, kept, dst = (x.cpu().numpy() for x in cache.debug_last(0))
+        idx, w = idx.cpu().numpy(), w.cpu().numpy()
+        order = ~np.concatenate([tok, np.arange(t0, t0 + n)]).astype(np.uint32)
+        for hk in range(hkv):
+            keys = (scores[hk].view(np.uint32).astype(np.uint64) << np.uint64(32)) | order.astype(np.uint64)
+            want = keys >= np.sort(keys)[n]                   # the c largest of c + n, and what equals the smallest of them
+            assert np.array_equal(kept[hk].astype(bool), want)
+            assert np.array_equal(idx[hk][want[:c]], tok[want[:c]])                    # kept slots keep their tokens
+            assert sorted(idx[hk][~want[:c]]) == (t0 + np.flatnonzero(want[c:]))[:(~want[:c]).sum()].tolist()
+            assert (w[hk] >= 1).all() and w[hk].max() <= 7
+            if kind == "evicted":
+                copies_of = np.flatnonzero(tok == at)
+                evicted = copies_of[~want[copies_of]]
+                assert (dst[hk][evicted] >= 0).sum() == 1 and set(dst[hk][evicted]) <= {-1, 0, 1, 2, 3, 4}
+        cache.close()
+
+
 def test_maximum_candidates_lockstep():
     """budget + block at the library's limit (8192 candidates per head): the select kernel's
     eight-candidates-per-thread shape, its largest LDS layout, 2048-row blocks."""
