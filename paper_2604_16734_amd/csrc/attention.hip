@@ -734,7 +734,7 @@ attention_kernel(const AttnArgs a) {
     // blocks of 32 keys that some row of the workgroup sees
     const int n_kb = (min(n_cand, c + wg_rows_end + shift) + 31) / 32;
     const int split = (h % group) * a.n_row_tiles + rt;
-    float* const part = in_set_of(a.partial, a.g, li) + ((size_t)hk * a.n_partials + split) * a.cand_stride;
+    float* const part = in_set_of(a.partial, a.g, li) + (size_t)hk * a.partial_stride + (size_t)split * a.cand_stride;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
     auto load_keys = [&](bf16x8 (&kf)[kNK], int kbi) __attribute__((always_inline)) {

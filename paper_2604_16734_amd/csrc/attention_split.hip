@@ -407,7 +407,7 @@ attention_split_kernel(const AttnArgs a) {
 #pragma unroll
     for (int st = 0; st < kNK; ++st) qs[t][st] = lds_read_b128(q_lds + t * S::kStrip + k_off[st]);
   const int split = (h % group) * a.n_row_tiles + rt;
-  float* const part = in_set_of(a.partial, a.g, li) + ((size_t)hk * a.n_partials + split) * a.cand_stride;
+  float* const part = in_set_of(a.partial, a.g, li) + (size_t)hk * a.partial_stride + (size_t)split * a.cand_stride;
   float ls[QW][16];                          // register r is row 8 (r / 4) + 4 g + r % 4 of its tile
 #pragma unroll
   for (int t = 0; t < QW; ++t)

@@ -297,7 +297,7 @@ colsum_kernel(const ColsumArgs a) {
 
   // lanes l and l + 32 hold the two halves of the rows of one key column
   auto store_sums = [&](int split_i) __attribute__((always_inline)) {
-    float* dstp = partial + ((size_t)hk * a.n_partials + split_i) * a.cand_stride;
+    float* dstp = partial + (size_t)hk * a.partial_stride + (size_t)split_i * a.cand_stride;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
       const float mine = colacc[t][0] + colacc[t][1];
@@ -354,7 +354,7 @@ colsum_kernel(const ColsumArgs a) {
   // a key block with fewer row splits than the launch's partial count leaves the rest at zero
   if (split_end == splits) {
     for (int p = splits + g; p < a.n_partials; p += 2) {
-      float* z = partial + ((size_t)hk * a.n_partials + p) * a.cand_stride;
+      float* z = partial + (size_t)hk * a.partial_stride + (size_t)p * a.cand_stride;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
         const int kv = key0 + 32 * t + l32;

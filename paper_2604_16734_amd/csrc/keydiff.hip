@@ -61,7 +61,7 @@ keydiff_sum_kernel(const KeydiffArgs a) {
     float t = 0.f;
 #pragma unroll
     for (int r = 0; r < kRowsAtOnce; ++r) t += s_part[r][threadIdx.x];
-    in_set_of(a.sums, a.g, li)[((size_t)hk * a.n_slices + slice) * D + threadIdx.x] = t;
+    in_set_of(a.sums, a.g, li)[(size_t)hk * a.head_stride + slice * D + threadIdx.x] = t;
   }
 }
 
@@ -74,7 +74,7 @@ keydiff_score_kernel(const KeydiffArgs a) {
   __shared__ float s_fold[kFold][D];
   __shared__ float s_mu2;
   const int hk = blockIdx.y, li = blockIdx.z;
-  const float* const sums = in_set_of(a.sums, a.g, li);
+  const float* const sums = in_set_of(a.sums, a.g, li) + (size_t)hk * a.head_stride;
   const int n_cand = a.c + a.n_keys;
   // this thread's piece of its key first: the load is on its way while the anchor is folded
   constexpr int kPer = D / 4;                      // channels per lane: a quarter of a key
@@ -93,7 +93,7 @@ keydiff_score_kernel(const KeydiffArgs a) {
     const int s0 = part * per, s1 = min(a.n_slices, s0 + per);
     float t = 0.f;
 #pragma unroll 8
-    for (int s2 = s0; s2 < s1; ++s2) t += sums[((size_t)hk * a.n_slices + s2) * D + ch];
+    for (int s2 = s0; s2 < s1; ++s2) t += sums[s2 * D + ch];
     s_fold[part][ch] = t;
   }
   __syncthreads();
@@ -129,7 +129,7 @@ keydiff_score_kernel(const KeydiffArgs a) {
   dot += __shfl_xor(dot, 1, 64); k2 += __shfl_xor(k2, 1, 64);
   dot += __shfl_xor(dot, 2, 64); k2 += __shfl_xor(k2, 2, 64);
   if (quarter == 0 && kv < n_cand)
-    in_set_of(a.scores, a.g, li)[(size_t)hk * a.cand_stride + kv] = -dot / (sqrtf(k2) * sqrtf(s_mu2));
+    in_set_of(a.scores, a.g, li)[(size_t)hk * a.head_stride + kv] = -dot / (sqrtf(k2) * sqrtf(s_mu2));
 }
 
 }  // namespace

@@ -77,13 +77,13 @@ struct AttnArgs {
   int n_row_tiles, work_per_xcd, total_work;   // work items of one layer (grid y = layer)
   int variant;         // tile shape, chosen by plan_attention
   float scale_log2;    // softmax scale times log2(e)
-  int n_partials, cand_stride;   // n_partials = query heads per KV head x n_row_tiles
+  int partial_stride, cand_stride;   // floats from a KV head's partial arrays to the next head's, and from array to array
   GroupStrides g;
   const u16* k_cache;  // the group's first layer: [Hkv, M, D]
   const u16* v_cache;
   float* lse2;         // [Hq, lse_stride]  log2-domain log-sum-exp of every row (first layer's scratch set, like partial)
-  float* partial;      // null, or [Hkv, n_partials, cand_stride]: the launch also leaves the column sums
-                       // of its softmax matrix (Eq. 4), one array per workgroup of a KV head
+  float* partial;      // null, or [Hkv][query heads of the group x n_row_tiles][candidates], strides above: the launch
+                       // also leaves the column sums of its softmax matrix (Eq. 4), one array per workgroup of a KV head
   AttnLayer layer[kMaxGroupLayers];
 };
 
@@ -98,7 +98,7 @@ struct ColsumArgs {
   // One launch scores a group of layers (grid y = layer): layer i of the group reads the cache
   // g.kv_stride elements further on per layer, and its statistics and partials from scratch set
   // (g.first_set + i) % g.n_sets.  In the order of AttnArgs.
-  int n, c, n_q_heads, n_kv_heads, budget, lse_stride, cand_stride;
+  int n, c, n_q_heads, n_kv_heads, budget, lse_stride, partial_stride, cand_stride;
   int n_keys, shift;   // as in AttnArgs
   int n_kv_blocks;     // blocks of 256 * subtiles keys
   int n_partials;      // the most row splits any key block has; every key gets that many partials
@@ -110,7 +110,7 @@ struct ColsumArgs {
   GroupStrides g;
   const u16* k_cache;  // of the group's first layer
   const float* lse2;   // in the first layer's scratch set, like partial
-  float* partial;      // [Hkv, n_partials, cand_stride]
+  float* partial;      // [Hkv][n_partials][candidates], strides as in AttnArgs
   // workgroups [split_prefix[k], split_prefix[k + 1]) of a head share key block k and split the
   // 32-row query tiles that see it evenly among themselves
   int split_prefix[kColsumMaxKvBlocks + 1];
@@ -138,9 +138,9 @@ hipError_t launch_rowstat(RowstatArgs a, int head_dim, hipStream_t s);
 struct KeydiffArgs {
   LayerGroup g;        // a group of layers per launch (grid z); g.k_new[i]: [n_keys, Hkv, D]
   const u16* k_cache;  // the group's first layer: [Hkv, M, D]
-  float* sums;         // [Hkv, n_slices, D] scratch: column sums of the keys, one per slice
-  float* scores;       // [Hkv, cand_stride] out (both in the first layer's scratch set)
-  int c, n_keys, n_kv_heads, budget, cand_stride;
+  float* sums;         // [Hkv][n_slices][D] scratch: column sums of the keys, one per slice
+  float* scores;       // [Hkv][candidates] out (both in the first layer's scratch set, heads head_stride floats apart)
+  int c, n_keys, n_kv_heads, budget, head_stride;
   int n_slices, keys_per_block;   // set by launch_keydiff
 };
 int keydiff_slices(int n_cand);
@@ -178,7 +178,7 @@ struct LayerBlock {
 // Compaction of a group of layers whose block does not fit (select.hip); what a workgroup needs first lies
 // together, as in AttnArgs.
 struct SelectArgs {
-  int c, n, t0, budget, cand_stride, chunk_max, n_partials, merge;
+  int c, n, t0, budget, partial_stride, cand_stride, chunk_max, n_partials, merge;
   int n_kv_heads, head_dim, n_segs;
   int items;                    // candidates per thread
   int direct;                   // the token table has one entry per token before t0, not a hash of them
@@ -187,7 +187,7 @@ struct SelectArgs {
   int keydiff;                  // 1: the kernel scores by the keys alone itself, there are no partial arrays
   int width, groups;            // the threads sum the partial arrays as `groups` groups of `width`
   GroupStrides g;
-  const float* partial;         // [Hkv, n_partials, cand_stride]
+  const float* partial;         // [Hkv][n_partials][candidates], strides as in AttnArgs
   const float* score_override;  // [Hkv, n_cand] used instead, or null
   int32_t* token_idx;           // the group's first layer: [Hkv, M]
   float* weight;
@@ -198,8 +198,7 @@ struct SelectArgs {
   u16* k_cache;                 // the group's first layer: [Hkv, M, D]
   u16* v_cache;
   u16* sources;                 // [Hkv, cand_stride, kNeighbours]: source lists that do not fit into LDS
-  u16* stage_k;                 // [Hkv, chunk_max, D]
-  u16* stage_v;
+  u16* stage;                   // K, then V [chunk_max, D] of every head, over that head's partial arrays
   float* stage_w;               // [Hkv, chunk_max]
   unsigned long long* totals;   // [KVP_T_COUNT] running totals of the cache (kvp_debug_totals)
   LayerBlock layer[kMaxGroupLayers];

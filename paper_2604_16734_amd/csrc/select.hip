@@ -34,7 +34,7 @@
 //     candidate position first, so that the fp32 sum is taken in one fixed order.  A destination in the
 //     cache is rewritten in place (no other row reads it: sources are evicted rows, destinations kept
 //     ones); one among the block's tokens goes to a staging row, because the slot it will get may
-//     still be a source.
+//     still be a source.  The staging rows lie over the head's own partial arrays, read by then.
 //   * move: kept block rows, or their staging rows, into the free slots.
 #include <type_traits>
 
@@ -338,7 +338,7 @@ compact_kernel(const SelectArgs a) {
       const int grp = tid / a.width, quad0 = tid % a.width;              // width is a power of two
       const int n_arrays = grp < a.groups ? (a.n_partials - grp + a.groups - 1) / a.groups : 0;
       // a scalar base per array, a lane offset that never changes
-      const float* const part = in_set_of(a.partial, a.g, li) + (size_t)hk * a.n_partials * a.cand_stride;
+      const float* const part = in_set_of(a.partial, a.g, li) + (size_t)hk * a.partial_stride;
       const unsigned lane_off = (unsigned)(grp * a.cand_stride + 4 * quad0);
       auto sum_arrays = [&](auto passes, auto batch) __attribute__((always_inline)) {
         constexpr int kPasses = decltype(passes)::value, kBatch = decltype(batch)::value;
@@ -538,12 +538,12 @@ compact_kernel(const SelectArgs a) {
   u16* const v_cache = a.v_cache;
   const u16* const k_new = a.layer[li].k_new;
   const u16* const v_new = a.layer[li].v_new;
-  u16* const stage_k = in_set_of(a.stage_k, a.g, li);
-  u16* const stage_v = in_set_of(a.stage_v, a.g, li);
+  u16* const stage_k = in_set_of(a.stage, a.g, li) + 2 * (size_t)hk * a.partial_stride;
+  u16* const stage_v = stage_k + (size_t)a.chunk_max * D;
   u16* const cache = (is_v ? v_cache : k_cache) + (long long)li * a.g.kv_stride + (size_t)hk * budget * D + 8 * piece;
   const u16* const fresh = (is_v ? v_new : k_new) + (size_t)hk * D + 8 * piece;
   const int fresh_stride = a.n_kv_heads * D;
-  u16* const staged = (is_v ? stage_v : stage_k) + (size_t)hk * a.chunk_max * D + 8 * piece;
+  u16* const staged = (is_v ? stage_v : stage_k) + 8 * piece;
   float* const staged_w = in_set_of(a.stage_w, a.g, li) + (size_t)hk * a.chunk_max;
 
   if (a.merge) {

@@ -47,6 +47,20 @@ def test_persistent_bytes_follow_eq2():
         assert total2 >= total
 
 
+def test_scratch_set_holds_partial_scores_or_staging_rows_not_both():
+    """The benchmark's shape, sixteen scratch sets.  A set: a statistic per query row; per KV head the K and V staging rows
+    of a block, or its partial score arrays (at most 40 of 3072 floats here: the smaller of the two), in the same
+    place; score, keep flag and destination per candidate and a weight per staging row; each part rounded up to 256 bytes."""
+    wl = get_workload("long_video")
+    cand = wl.budget + wl.chunk
+    staging = 2 * wl.chunk * wl.head_dim * 2
+    assert 40 * cand * 4 < staging
+    bound = wl.n_q_heads * wl.chunk * 4 + wl.n_kv_heads * (staging + cand * (4 + 1 + 4) + wl.chunk * 4) + 7 * 256
+    cfg1, cfg16 = _cfg(wl, sets=1), _cfg(wl, sets=16)
+    assert K.kvp_cache_bytes(cfg16) - K.kvp_cache_bytes(cfg1) <= 15 * bound
+    assert K.kvp_cache_bytes(cfg16) - K.kvp_persistent_bytes(cfg16) <= 76 * 2 ** 20
+
+
 @pytest.mark.parametrize("field,value", [
     ("n_layers", 0), ("n_q_heads", 5), ("n_kv_heads", 0), ("head_dim", 96), ("budget", 0),
     ("chunk_max", 0), ("merge", 2), ("scratch_sets", -1), ("flags", 8), ("softmax_scale", -1.0),
