@@ -183,6 +183,9 @@ int kvp_compact_layers(kvp_cache* cache, int32_t first_layer, int32_t n_layers, 
  * scratch_sets / 2 with a side stream), each kernel as ONE launch for the whole
  * group: the attention (which also scores by the block's own queries), the scoring
  * pass of proxy queries or of the keys, and the compaction.  The results are those of the per-layer calls, bit for bit.
+ * Layers may depend on each other through these tensors (one `out` for all of them, the out of a layer as a later
+ * one's q): attention launches then take fewer layers, and a layer whose out overlaps an earlier one's k, v or
+ * q_obs starts a group of its own.
  * With side_stream NULL (or equal to stream) everything is enqueued on `stream`
  * in that order.  With another side_stream every kvp_compact goes there, beside
  * the attention of the layers that follow (in a model nothing after a layer's

@@ -604,6 +604,33 @@ static int prefill_layers(kvp_cache* c, int first, int count, int32_t token_begi
   return KVP_OK;
 }
 
+// The tensors of one block, for all layers, by their device addresses: which layers may share a launch.
+struct BlockTensors {
+  const void* const* q;
+  const void* const* k;
+  const void* const* v;
+  void* const* out;
+  const void* const* q_obs;             // null without proxy queries
+  size_t q_bytes, kv_bytes, obs_bytes;  // of one layer
+
+  static bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x && y && x < y + b_bytes && y < x + a_bytes;
+  }
+  // The attention of layer j (i < j) has to come after that of layer i: it reads or writes what the other writes, or
+  // writes what the other reads.
+  bool attention_in_order(int i, int j) const {
+    return overlap(out[i], q_bytes, out[j], q_bytes) || overlap(out[i], q_bytes, q[j], q_bytes) ||
+           overlap(out[i], q_bytes, k[j], kv_bytes) || overlap(out[i], q_bytes, v[j], kv_bytes) ||
+           overlap(out[j], q_bytes, q[i], q_bytes);
+  }
+  // It has to come after the scoring and the compaction of layer i, too: it writes over what those read.
+  bool after_compaction(int i, int j) const {
+    return overlap(out[j], q_bytes, k[i], kv_bytes) || overlap(out[j], q_bytes, v[i], kv_bytes) ||
+           (q_obs != nullptr && overlap(out[j], q_bytes, q_obs[i], obs_bytes));
+  }
+};
+
 // kvp_prefill_chunk and its variants: one layer
 static int prefill_impl(kvp_cache* c, int32_t layer, int32_t token_begin, int32_t n_tokens, const void* q,
                         const void* k, const void* v, void* out, const void* q_obs, int32_t n_obs, int mode,
@@ -690,8 +717,14 @@ int kvp_prefill_block(kvp_cache* c, int32_t token_begin, int32_t n_tokens, const
     c->set_last_group.assign(n_sets, -1);
   }
   const int mode = scoring == KVP_SCORE_PROXY ? kScoreProxy : scoring == KVP_SCORE_KEYDIFF ? kScoreKeydiff : kScoreOwn;
-  for (int first = 0; first < n_layers; first += group) {
-    int last = std::min(n_layers, first + group);
+  const size_t q_row = (size_t)c->cfg.n_q_heads * c->cfg.head_dim * 2, kv_row = (size_t)c->cfg.n_kv_heads * c->cfg.head_dim * 2;
+  const BlockTensors of{q, k, v, out, mode == kScoreProxy ? q_obs : nullptr, n_tokens * q_row, n_tokens * kv_row, n_obs * q_row};
+  for (int first = 0, last; first < n_layers; first = last) {
+    last = std::min(n_layers, first + group);
+    // a layer that writes over what the compaction of an earlier one reads starts a group of its own
+    for (int layer = first + 1; layer < last; ++layer)
+      for (int earlier = first; earlier < layer; ++earlier)
+        if (of.after_compaction(earlier, layer)) last = layer;
     if (two) {
       // A scratch set must have been released by the compaction that used it last; the side
       // stream is in order, so the latest such group covers the others, and with them the
@@ -712,9 +745,14 @@ int kvp_prefill_block(kvp_cache* c, int32_t token_begin, int32_t n_tokens, const
         break;
       }
     }
-    // one attention launch for every run of layers with equally full caches (all of them, in a prefill)
+    // one attention launch for every run of layers with equally full caches (all of them, in a prefill) that are
+    // independent of each other
     for (int layer = first, run; layer < last; layer += run) {
-      for (run = 1; layer + run < last && c->layers[layer + run].count == c->layers[layer].count; ++run) {}
+      for (run = 1; layer + run < last; ++run) {
+        bool joins = c->layers[layer + run].count == c->layers[layer].count;
+        for (int i = layer; joins && i < layer + run; ++i) joins = !of.attention_in_order(i, layer + run);
+        if (!joins) break;
+      }
       const int rc1 = prefill_layers(c, layer, run, token_begin, n_tokens, q + layer, k + layer, v + layer, out + layer,
                                      mode == kScoreProxy ? q_obs + layer : nullptr, n_obs, mode, main, mode != kScoreOwn);
       if (rc1) return rc1;

@@ -1,12 +1,14 @@
 // Drives the C ABI of the host-only sanitized build through the dry-run cases of the Python host
 // tests: configuration and segment validation, sizes, the per-layer state machine over all five
 // workloads and all three ways of scoring, kvp_prefill_block in groups, the decode entry points
-// and their limits.  Exits 0 when every check holds; the sanitizers abort on any invalid access.
+// and their limits; and, with the launches recorded, kvp_prefill_block over layers that depend on each other.  Exits 0 when every check holds; the sanitizers abort on any invalid access.
 #include <cstdio>
 #include <cstdlib>
+#include <string>
 #include <vector>
 
 #include "kvp.h"
+#include "stubs.h"
 
 #define CHECK(cond)                                                            \
   do {                                                                         \
@@ -43,7 +45,104 @@ static std::vector<kvp_segment> segments_of(const Shape& s) {
           kvp_segment{nvis, s.n_text, KVP_TEXT, 0, 0, 0, 0}};
 }
 
+// kvp_prefill_block on a cache that is no dry run, every launch recorded: layers whose tensors are independent share
+// launches, layers that depend on each other go in their order.  The addresses are never looked at.
+static void check_dependent_layers() {
+  const Shape s{"block", 8, 8, 2, 64, 32, 64, 4, 4, 40, 1, 32};
+  const std::vector<kvp_segment> segs = segments_of(s);
+  kvp_config cfg = config_of(s, s.layers);
+  cfg.flags = 0;
+  const size_t q_bytes = (size_t)s.chunk * s.hq * s.d * 2, kv_bytes = (size_t)s.chunk * s.hkv * s.d * 2;
+  auto at = [](size_t bytes) { return reinterpret_cast<void*>((size_t)0x100000000 + bytes); };
+  auto launches = [&](int scoring, auto&& change) {
+    std::vector<Launch> seen;
+    recorded = &seen;
+    kvp_cache* c = nullptr;
+    CHECK(kvp_init_cache(&cfg, segs.data(), 2, at(0), (size_t)1 << 40, nullptr, &c) == KVP_OK && c);
+    for (int l = 0; l < s.layers; ++l) CHECK(kvp_set_state(c, l, s.budget, s.budget) == KVP_OK);       // the block evicts
+    std::vector<const void*> q(s.layers), k(s.layers), v(s.layers), obs(s.layers);
+    std::vector<void*> out(s.layers);
+    for (int l = 0; l < s.layers; ++l) {               // neighbours in memory, without a byte in common
+      const size_t base = (size_t)(l + 1) << 30;
+      q[l] = at(base); k[l] = at(base + q_bytes); v[l] = at(base + q_bytes + kv_bytes);
+      out[l] = at(base + q_bytes + 2 * kv_bytes); obs[l] = at(base + 2 * q_bytes + 2 * kv_bytes);
+    }
+    change(q, k, v, out, obs);
+    CHECK(kvp_prefill_block(c, s.budget, s.chunk, q.data(), k.data(), v.data(), out.data(), scoring, obs.data(), s.chunk,
+                            nullptr, nullptr) == KVP_OK);
+    for (int l = 0; l < s.layers; ++l) {
+      kvp_view vw{};
+      CHECK(kvp_decode_ready(c, l, &vw) == KVP_OK && vw.next_token == s.budget + s.chunk);
+    }
+    kvp_free_cache(c);
+    recorded = nullptr;
+    std::string all;
+    for (const Launch& x : seen) all += std::string(x.kernel) + std::to_string(x.layers) + " ";
+    return all;
+  };
+  auto times = [](int n, const std::string& what) {
+    std::string all;
+    for (int i = 0; i < n; ++i) all += what;
+    return all;
+  };
+#define EXPECT(got, want)                                                                                       \
+  do {                                                                                                          \
+    const std::string g = (got), w = (want);                                                                    \
+    if (g != w) {                                                                                               \
+      std::fprintf(stderr, "%s:%d: launches\n  %s\nexpected\n  %s\n", __FILE__, __LINE__, g.c_str(), w.c_str()); \
+      std::exit(1);                                                                                             \
+    }                                                                                                           \
+  } while (0)
+  const int own = KVP_SCORE_OWN;
+  EXPECT(launches(own, [](auto&, auto&, auto&, auto&, auto&) {}), "attention8 select8 ");
+  // one out for all layers; two in turn
+  EXPECT(launches(own, [](auto&, auto&, auto&, auto& out, auto&) { for (void*& o : out) o = out[0]; }), times(8, "attention1 ") + "select8 ");
+  EXPECT(launches(own, [](auto&, auto&, auto&, auto& out, auto&) { for (int l = 2; l < 8; ++l) out[l] = out[l % 2]; }),
+         times(4, "attention2 ") + "select8 ");
+  // a layer's out is the next one's q, or the last byte of its k
+  EXPECT(launches(own, [](auto& q, auto&, auto&, auto& out, auto&) { for (int l = 1; l < 8; ++l) q[l] = out[l - 1]; }),
+         times(8, "attention1 ") + "select8 ");
+  EXPECT(launches(own, [&](auto&, auto& k, auto&, auto& out, auto&) { k[3] = static_cast<char*>(out[2]) - kv_bytes + 1; }),
+         "attention3 attention5 select8 ");
+  // a layer's out overwrites what an earlier layer's attention has read
+  EXPECT(launches(own, [](auto& q, auto&, auto&, auto& out, auto&) { out[5] = const_cast<void*>(q[1]); }), "attention5 attention3 select8 ");
+  // ... or what its compaction has yet to read
+  EXPECT(launches(own, [](auto&, auto& k, auto&, auto& out, auto&) { out[5] = const_cast<void*>(k[1]); }),
+         "attention5 select5 attention3 select3 ");
+  EXPECT(launches(own, [&](auto&, auto&, auto& v, auto& out, auto&) {
+           for (int l = 1; l < 8; ++l) out[l] = static_cast<char*>(const_cast<void*>(v[l - 1])) + kv_bytes - 1;
+         }), times(8, "attention1 select1 "));
+  // ... or its scoring pass
+  EXPECT(launches(KVP_SCORE_PROXY, [](auto&, auto&, auto&, auto&, auto&) {}), "attention8 rowstat8 colsum8 select8 ");
+  EXPECT(launches(KVP_SCORE_PROXY, [](auto&, auto&, auto&, auto& out, auto& obs) { out[4] = const_cast<void*>(obs[1]); }),
+         times(2, "attention4 rowstat4 colsum4 select4 "));
+  EXPECT(launches(own, [](auto&, auto&, auto&, auto& out, auto& obs) { out[4] = const_cast<void*>(obs[1]); }), "attention8 select8 ");
+  // an error in a later group: the layers before it have gone through
+  {
+    std::vector<Launch> seen;
+    recorded = &seen;
+    kvp_cache* c = nullptr;
+    CHECK(kvp_init_cache(&cfg, segs.data(), 2, at(0), (size_t)1 << 40, nullptr, &c) == KVP_OK && c);
+    for (int l = 0; l < s.layers; ++l) CHECK(kvp_set_state(c, l, 0, 0) == KVP_OK);
+    std::vector<const void*> in(s.layers, at(0));
+    std::vector<void*> out(s.layers);
+    for (int l = 0; l < s.layers; ++l) out[l] = at((size_t)(l + 1) << 30);
+    out[3] = at(0);
+    in[6] = nullptr;
+    CHECK(kvp_prefill_block(c, 0, s.chunk, in.data(), in.data(), in.data(), out.data(), own, nullptr, 0, nullptr, nullptr) == KVP_EINVAL);
+    for (int l = 0; l < s.layers; ++l) {
+      kvp_view vw{};
+      CHECK(kvp_decode_ready(c, l, &vw) == KVP_OK && vw.next_token == (l < 6 ? s.chunk : 0));
+    }
+    for (int n_tokens : {0, -5, s.chunk + 1})
+      CHECK(kvp_prefill_block(c, s.chunk, n_tokens, in.data(), in.data(), in.data(), out.data(), own, nullptr, 0, nullptr, nullptr) == KVP_EINVAL);
+    kvp_free_cache(c);
+    recorded = nullptr;
+  }
+}
+
 int main() {
+  check_dependent_layers();
   CHECK(kvp_strerror(KVP_OK) && kvp_strerror(-77));
   for (const Shape& s : kShapes) {
     const std::vector<kvp_segment> segs = segments_of(s);

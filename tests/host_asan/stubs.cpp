@@ -1,32 +1,42 @@
-// Host-only build of libkvp's state machine: the kernel launchers are replaced by stubs (a dry-run
-// cache never calls them), everything else -- validation, layout, the per-layer state machine,
-// the launch planning of plan.cpp -- is the real code, compiled with -fsanitize=address,undefined.
+// Host-only build of libkvp's state machine: the kernel launchers are replaced by stubs, everything else --
+// validation, layout, the per-layer state machine, the launch planning of plan.cpp -- is the real code, compiled
+// with -fsanitize=address,undefined.  A dry-run cache never calls a launcher.  While the driver records, the launchers
+// note what they would launch, for how many layers; otherwise they refuse.
 #include "kvp_internal.h"
+#include "stubs.h"
+
+std::vector<Launch>* recorded = nullptr;
+
+namespace {
+hipError_t note(const char* kernel, int layers) {
+  if (!recorded) return hipErrorNotSupported;
+  recorded->push_back(Launch{kernel, layers});
+  return hipSuccess;
+}
+hipError_t note_nothing() { return recorded ? hipSuccess : hipErrorNotSupported; }
+}  // namespace
 
 namespace kvp {
 
-hipError_t launch_attention(const AttnArgs&, int, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_colsum(const ColsumArgs&, int, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_select(const SelectArgs&, int, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_merge(const CompactArgs&, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_move(const CompactArgs&, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_init(int32_t*, float*, size_t, const Seg*, int, Seg*, unsigned long long*, hipStream_t) {
-  return hipErrorNotSupported;
-}
-hipError_t launch_rowstat(RowstatArgs, int, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_keydiff(KeydiffArgs, int, hipStream_t) { return hipErrorNotSupported; }
-hipError_t launch_decode(const DecodeArgs&, int, hipStream_t) { return hipErrorNotSupported; }
+hipError_t launch_attention(const AttnArgs& a, int, hipStream_t) { return note("attention", a.g.n_layers); }
+hipError_t launch_colsum(const ColsumArgs& a, int, hipStream_t) { return note("colsum", a.g.n_layers); }
+hipError_t launch_select(const SelectArgs& a, int, hipStream_t) { return note("select", a.g.n_layers); }
+hipError_t launch_move(const CompactArgs& a, hipStream_t) { return note("move", a.g.n_layers); }
+hipError_t launch_init(int32_t*, float*, size_t, const Seg*, int, Seg*, unsigned long long*, hipStream_t) { return note_nothing(); }
+hipError_t launch_rowstat(RowstatArgs a, int, hipStream_t) { return note("rowstat", a.g.n_layers); }
+hipError_t launch_keydiff(KeydiffArgs a, int, hipStream_t) { return note("keydiff", a.g.n_layers); }
+hipError_t launch_decode(const DecodeArgs&, int, hipStream_t) { return note("decode", 1); }
 hipError_t decode_static_scratch(float** ptr, size_t* n_floats) {
   *ptr = nullptr;
   *n_floats = 0;
-  return hipErrorNotSupported;
+  return note_nothing();
 }
-hipError_t prepare_attention() { return hipErrorNotSupported; }
-hipError_t prepare_select() { return hipErrorNotSupported; }
+hipError_t prepare_attention() { return note_nothing(); }
+hipError_t prepare_select() { return note_nothing(); }
 
 }  // namespace kvp
 
-// the HIP runtime calls kvp.cpp makes (events, stream waits): never reached by a dry-run cache
+// the HIP runtime calls kvp.cpp makes (events, stream waits): never reached, neither by a dry-run cache nor on one stream
 extern "C" {
 hipError_t hipEventCreate(hipEvent_t*) { return hipErrorNotSupported; }
 hipError_t hipEventCreateWithFlags(hipEvent_t*, unsigned) { return hipErrorNotSupported; }

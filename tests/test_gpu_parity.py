@@ -955,6 +955,45 @@ def test_layerwise_driver_matches_the_block_driver(scoring):
                                y.view(torch.int16) if y.dtype == torch.bfloat16 else y)
 
 
+@pytest.mark.parametrize("streams", [1, 2])
+@pytest.mark.parametrize("kind", ["one_out", "chain"])
+def test_block_driver_with_layers_that_depend_on_each_other(kind, streams):
+    """kvp_prefill_block over layers that share one output buffer, or whose queries are the output of the layer before:
+    caches and outputs are those of the calls one by one."""
+    wl = get_workload("tiled_image")
+    layers, hq, hkv, d = 6, wl.n_q_heads, wl.n_kv_heads, wl.head_dim
+    data = [tuple(U.bits_to_torch(x) for x in layer_inputs(wl, l)) for l in range(layers)]
+    ranges = chunk_ranges(wl.n_tokens, wl.chunk)[:6]                  # two that append, four that evict
+    results = []
+    for grouped in (False, True):
+        cache = K.Cache(layers, hq, hkv, d, wl.budget, wl.chunk, wl.segments, merge=True, scratch_sets=4, device=DEV)
+        outs = [torch.zeros((wl.chunk, hq, d), dtype=torch.bfloat16, device=DEV) for _ in range(layers)]
+        if kind == "one_out":
+            outs = [outs[0]] * layers
+        driver = K.Prefill(cache, layers, overlap=streams == 2)
+        seen = []
+        for t0, n in ranges:
+            def qkv(l):
+                q, k, v = (x[t0:t0 + n] for x in data[l])
+                return (outs[l - 1][:n] if kind == "chain" and l else q), k, v
+            if grouped:
+                driver.block(t0, qkv, lambda l: outs[l][:n])
+            else:
+                for l in range(layers):
+                    cache.prefill_chunk(l, t0, *qkv(l), out=outs[l][:n])
+                    cache.compact(l)
+            seen.append(outs[-1].clone())
+        driver.finish()
+        for l in range(layers):
+            k, v, idx, w, count, _ = cache.decode_ready(l)
+            seen += [k[:, :count].clone(), v[:, :count].clone(), idx[:, :count].clone(), w[:, :count].clone()]
+        torch.cuda.synchronize()
+        results.append(seen)
+        cache.close()
+    bits = lambda t: t.view(torch.int16) if t.dtype == torch.bfloat16 else t
+    assert all(torch.equal(bits(x), bits(y)) for x, y in zip(*results))
+
+
 def test_real_cache_refuses_null_tensors():
     """A cache on a live allocation (not a dry run) returns KVP_EINVAL for a null tensor before it
     enqueues anything, and stays usable."""
