@@ -30,10 +30,16 @@ if ROOT not in sys.path:
 
 PEAK_BF16_TFLOPS = 2500.0     # MI355X dense bf16 MFMA, vendor figure
 PEAK_HBM_GBS = 8000.0         # MI355X HBM3E, vendor figure
-# HBM bytes per attention launch (fetch + write) at the long_video steady state, from the
-# rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs summarised in profiles/ (launch-weighted mean,
-# counters scaled by what they read for a plain 256 MiB copy); None for a workload not measured
-ATTENTION_TRAFFIC_BYTES = {"long_video": 52326293}
+# HBM bytes per attention launch (fetch + write) over the long_video prefill, from the rocprofv3 --pmc FETCH_SIZE /
+# WRITE_SIZE runs summarised in profiles/ (launch-weighted mean, counters scaled by what they read for a plain 256 MiB
+# copy), and the layers a launch of those runs covered: (layers, bytes)
+ATTENTION_TRAFFIC = {"long_video": (16, 830826395)}
+
+
+def attention_traffic(workload, layers_per_launch):
+    """The stored HBM bytes of an attention launch; None for a workload, or a number of layers per launch, not measured."""
+    layers, nbytes = ATTENTION_TRAFFIC.get(workload, (None, None))
+    return nbytes if layers == layers_per_launch else None
 
 
 def attention_flops(wl, t0_n_pairs):
@@ -410,7 +416,7 @@ def main():
                          "launches (measured faster); 2: those compactions on a second stream beside the next "
                          "group's attention")
     ap.add_argument("--scratch-sets", type=int, default=16,
-                    help="scratch sets of the cache: one select/merge/move launch covers a group of layers, "
+                    help="scratch sets of the cache: a launch covers a group of layers, "
                          "sets / 2 of them with two streams (two events between the streams per group), "
                          "min(sets, 16) with one")
     ap.add_argument("--n-obs", type=int, default=64,
@@ -535,9 +541,11 @@ def main():
             "peak": PEAK_BF16_TFLOPS,
             "unit": "TFLOP/s",
             "frac": round(achieved / PEAK_BF16_TFLOPS, 4),
-            "traffic": ATTENTION_TRAFFIC_BYTES.get(wl.name),
+            "layers_per_launch": att["layers_per_launch"],
+            "traffic": attention_traffic(wl.name, att["layers_per_launch"]),
             "traffic_source": "stored figure from the rocprofv3 --pmc runs summarised under profiles/ "
-                              "(FETCH_SIZE and WRITE_SIZE scaled by a plain copy); not measured by this run",
+                              "(FETCH_SIZE and WRITE_SIZE scaled by a plain copy), for a launch of as many layers; "
+                              "not measured by this run",
             "avg_launch_us": round(att["avg_us"], 2),
             "flops_per_launch": main_res["attention_flops_per_launch"],
             "attention_plus_scoring_tflops": round(main_res["attention_plus_scoring_tflops"], 2),
