@@ -1,11 +1,20 @@
-// Sums and maxima across the lanes of a wave when kPieces = D / 8 neighbouring lanes hold a row of D channels in 16-byte
+// bf16 values two to a register.  Sums and maxima across the lanes of a wave when kPieces = D / 8 neighbouring lanes hold a row of D channels in 16-byte
 // pieces: on the DPP network and by lane swaps, never through LDS.
 #pragma once
 #include "kvp_internal.h"
 
 namespace kvp {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
 namespace {
 
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
+  f32x2 v = {lo, hi};
+  bf16x2 b = __builtin_convertvector(v, bf16x2);   // v_cvt_pk_bf16_f32, round to nearest even
+  return __builtin_bit_cast(unsigned, b);
+}
 __device__ __forceinline__ float bf16_lo(unsigned x) { return __uint_as_float(x << 16); }
 __device__ __forceinline__ float bf16_hi(unsigned x) { return __uint_as_float(x & 0xFFFF0000u); }
 __device__ __forceinline__ void unpack8(const uint4 w, float (&x)[8]) {

@@ -1,25 +1,18 @@
 // Vector types and small device helpers shared by the MFMA kernels of attention.
 #pragma once
 #include "kvp_internal.h"
+#include "lane_tools.h"
 
 namespace kvp {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 
 namespace {
-
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
-  f32x2 v = {lo, hi};
-  bf16x2 b = __builtin_convertvector(v, bf16x2);   // v_cvt_pk_bf16_f32, round to nearest even
-  return __builtin_bit_cast(unsigned, b);
-}
 
 // value of the same row held by the other half of the wave (lane ^ 32)
 __device__ __forceinline__ float max_with_other_half(float x) {

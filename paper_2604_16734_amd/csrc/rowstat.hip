@@ -129,13 +129,6 @@ rowstat_kernel(const RowstatArgs a) {
       for (int t = 0; t < kSub; ++t) s[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[t][st], qf, st == 0 ? zero : s[t], 0, 0, 0);
     }
   };
-  // A vector instruction may read the result of a 32x32x16 matrix instruction only twelve wait states after it
-  // was issued, and nobody counts those across a branch: the distance is paid at the end of the block.
-  auto settle = [&]() __attribute__((always_inline)) {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 7\n\ts_nop 3");
-    __builtin_amdgcn_sched_barrier(0);
-  };
   // (maximum, sum of exp2) of every row over this wave's keys, for item `i`.  `cut`: some of the keys lie past the end.
   auto statistics = [&](const f32x16 (&s_in)[kSub], int i, auto cut) __attribute__((always_inline)) {
     f32x16 s[kSub] = {s_in[0], s_in[1]};

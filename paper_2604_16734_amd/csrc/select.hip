@@ -43,8 +43,6 @@
 
 namespace kvp {
 
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
@@ -55,20 +53,10 @@ constexpr int kMaxItemsAny = KVP_MAX_CANDIDATES / kThreads;   // 8
 constexpr int kBins = kSelectBins;
 constexpr unsigned kNone16 = 0xFFFFu;
 
-__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
-  f32x2 v = {lo, hi};
-  bf16x2 b = __builtin_convertvector(v, bf16x2);
-  return __builtin_bit_cast(unsigned, b);
-}
-
 __device__ __forceinline__ unsigned order_bits(float x) {
   if (x == 0.f) x = 0.f;   // -0 and +0 rank equal
   const unsigned u = __float_as_uint(x);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
-}
-
-__device__ __forceinline__ unsigned long long make_key(unsigned ob, int tok) {
-  return ((unsigned long long)ob << 32) | (unsigned long long)~(unsigned)tok;
 }
 
 __device__ __forceinline__ unsigned hash_tok(int tok, unsigned mask) {
