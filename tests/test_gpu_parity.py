@@ -254,6 +254,41 @@ def test_runaway_logits_take_the_careful_path(hq, hkv, d, c, n):
     cache.close()
 
 
+@pytest.mark.parametrize("hq,hkv,d,c,n", [
+    (4, 2, 128, 700, 150), (16, 4, 64, 1111, 333),       # 32-row workgroups, the keys split eight ways
+    (28, 4, 128, 0, 352), (28, 4, 128, 1025, 321), (16, 4, 64, 700, 545),      # 64-row workgroups, four ways
+    (32, 8, 128, 1536, 1024)])                           # 128-row workgroups
+def test_scores_after_runaway_logits(hq, hkv, d, c, n):
+    """Logits that climb by hundreds of nats along the keys, in a block that evicts: a row's softmax reference moves in
+    every key block of a wave, and the scores come from the normalisers that this leaves."""
+    from kvp_workload import f32_to_bf16_bits
+    rng = np.random.default_rng(d + c + n)
+    budget = max(c, n // 2)
+    cache = K.Cache(1, hq, hkv, d, budget, n, [Segment(0, 100000, 0)], merge=False, device=DEV)
+    tot = c + n
+    # raw products up to 32 d: fp32 sums of them are off by 8 half units in the last place at most, 2e-4 nats
+    ramp = 8.0 * np.arange(tot, dtype=np.float32)[:, None, None] / tot
+    kb = f32_to_bf16_bits(ramp + 0.05 * rng.standard_normal((tot, hkv, d)).astype(np.float32))
+    vb = _rand_bits(rng, (tot, hkv, d))
+    qb = f32_to_bf16_bits(4.0 + 0.05 * rng.standard_normal((n, hq, d)).astype(np.float32))
+    q64, k64, v64 = (O.bf16_bits_to_f64(x) for x in (qb, kb, vb))
+    oc = O.LayerCache(hkv, d, budget)
+    if c:
+        oc.compact(0, k64[:c], v64[:c], np.zeros((hkv, c), dtype=np.float32))
+    U.upload_state(cache, 0, oc)
+    cache.set_state(0, c, c)
+    out_ref, scores_ref = oc.attend(c, q64, k64[c:], v64[c:])
+    out = cache.prefill_chunk(0, c, U.bits_to_torch(qb), U.bits_to_torch(kb[c:]), U.bits_to_torch(vb[c:]))
+    cache.compact(0)
+    assert U.out_rel_err(U.torch_bf16_to_f64(out), out_ref) <= U.OUT_TOL
+    scores, kept, _ = (x.cpu().numpy() for x in cache.debug_last(0))
+    U.check_scores(scores, scores_ref, n * (hq // hkv))
+    tok = np.concatenate([oc.idx, np.broadcast_to(np.arange(c, tot), (hkv, n))], axis=1)
+    for hk in range(hkv):
+        assert np.array_equal(kept[hk].astype(bool), O.select_keep(scores[hk], tok[hk], budget))
+    cache.close()
+
+
 @pytest.mark.parametrize("hq,hkv,d,c,n_tail,budget,chunk_max,scale", [
     (4, 4, 64, 0, 1, 256, 64, 0.0),          # nothing cached: the current token alone
     (4, 2, 128, 63, 1, 256, 64, 0.0),        # exactly one 64-key group
