@@ -124,7 +124,8 @@ int kvp_init_cache(const kvp_config* cfg, const kvp_segment* segs, int32_t n_seg
  * Row r attends to every cached entry and to block keys 0..r.  Scores (the
  * softmax weights summed over the block's rows and over the query heads that
  * share a KV head) are left in the layer's scratch set.  k and v must stay
- * valid, in stream order, until kvp_compact for this layer has been enqueued.
+ * valid, in stream order, until kvp_compact for this layer has been enqueued;
+ * out overlaps none of q, k and v (q is read again after out has been written).
  * token_begin must be the layer's next unseen token; 1 <= n_tokens <= chunk_max. */
 int kvp_prefill_chunk(kvp_cache* cache, int32_t layer, int32_t token_begin, int32_t n_tokens,
                       const void* q, const void* k, const void* v, void* out, void* stream);
@@ -166,8 +167,9 @@ int kvp_compact(kvp_cache* cache, int32_t layer, const float* scores_override, v
  * at a time), then this call once for all of them.  Layers that are in the same
  * state (same entry count, same block, scored the same way -- the case in a
  * prefill) are taken up to 16 at a time by ONE launch, which fills the GPU
- * where a single layer's KV heads cannot; others are taken one by one.  The result is that of n_layers kvp_compact calls, bit for
- * bit.  Every layer's k and v must still be valid.
+ * where a single layer's KV heads cannot; others are taken one by one.  The
+ * result is that of n_layers kvp_compact calls, bit for bit.  Every layer's k
+ * and v must still be valid.
  *   KVP_EINVAL  bad range;  KVP_ESTATE  a layer of the range is not PENDING
  * (both before anything is enqueued).  KVP_EDEVICE: a launch failed; the layers
  * of the groups launched before it are READY, the rest still PENDING. */
@@ -182,7 +184,8 @@ int kvp_compact_layers(kvp_cache* cache, int32_t first_layer, int32_t n_layers, 
  * The layers go in groups (min(scratch_sets, 16) layers on one stream,
  * scratch_sets / 2 with a side stream), each kernel as ONE launch for the whole
  * group: the attention (which also scores by the block's own queries), the scoring
- * pass of proxy queries or of the keys, and the compaction.  The results are those of the per-layer calls, bit for bit.
+ * pass of proxy queries or of the keys, and the compaction.  The results are those
+ * of the per-layer calls, bit for bit.
  * Layers may depend on each other through these tensors (one `out` for all of them, the out of a layer as a later
  * one's q): attention launches then take fewer layers, and a layer whose out overlaps an earlier one's k, v or
  * q_obs starts a group of its own.
@@ -274,10 +277,11 @@ int kvp_decode_step_static(kvp_cache* cache, int32_t layer, const void* q, const
  * fits all stay (the block tokens with the highest indices then find no slot). */
 int kvp_set_state(kvp_cache* cache, int32_t layer, int32_t count, int32_t next_token);
 
-/* Tuning and test aid: force one of the attention kernel's three workgroup shapes
- * for every later kvp_prefill_chunk of this cache (0: four waves of 64 rows,
- * 1: four waves of 32 rows, 2: eight waves of 32 rows), or -1 to let the library
- * choose from the launch size again (the default).  Results are the same to
+/* Tuning and test aid: force one of three workgroup shapes on the attention of
+ * every later block of this cache (0: four waves of 64 rows, 1: four waves of 32
+ * rows, 2: eight waves of 32 rows), or -1 to let the library choose from the
+ * block's size again (the default: shape 2 for large blocks, and for small ones
+ * one of two shapes that cannot be forced, whose waves share a row's keys).  Results are the same to
  * rounding; only speed differs.  KVP_EINVAL for any other value. */
 int kvp_set_attention_shape(kvp_cache* cache, int32_t shape);
 

@@ -30,10 +30,10 @@
 // every staged key tile.  A wave takes 64 keys of each tile as two 32-key
 // blocks X and Y; the KS partial results of a row are merged through LDS at the
 // end.  The split keeps all 1024 SIMDs busy when a block of the prefix has
-// fewer than 1024 wave-sized row tiles.  Three shapes are built: 2 x 2 waves of
-// 64 rows (one wave per SIMD, 512 registers), 4 x 2 waves of 32 rows (two waves
-// per SIMD, 256 registers each; the fastest on the large shapes) and 2 x 2 waves
-// of 32 rows.  Blocks too small to fill the chip with 128-row workgroups go to attention_split.hip.
+// fewer than 1024 wave-sized row tiles.  The library picks 4 x 2 waves of 32 rows (two
+// waves per SIMD, 256 registers each); blocks too small to fill the chip with its 128-row workgroups
+// go to attention_split.hip.  2 x 2 waves of 64 rows (one wave per SIMD, 512 registers) and 2 x 2 waves of 32 rows
+// run where a caller forces them (kvp_set_attention_shape).
 //
 // Schedule.  Matrix and vector work of one wave are made to overlap in program
 // order.  With S_X(t) = scores of block X of tile t, the loop body is
@@ -56,8 +56,8 @@
 // Layers.  One launch takes the block of up to sixteen layers (grid y), for callers that have them
 // all in hand (kvp_prefill_block).  One layer's block is 96 to 256 workgroups, a single round of the
 // chip at best: every launch pays the dispatch, the first tiles and the wait for its slowest
-// workgroup, and small blocks leave CUs idle.  Per layer: 22.7 -> 9.9 us at 28/4 heads, 256 rows over
-// 768 keys (8 layers per launch), 72 -> 65 us at 32/8 heads, 1024 rows over 3072 keys (16 layers).
+// workgroup, and small blocks leave CUs idle.  Per layer, scores included: 77 -> 72 us at 32/8 heads, d 128,
+// 1024 rows over 3072 keys (16 layers per launch).
 #include <type_traits>
 
 #include "kvp_internal.h"

@@ -2,6 +2,10 @@
 // observation queries): score_j = sum over rows r and over the query heads of
 // the KV group of softmax(S)[r, j].
 //
+// The scores of a block's own queries come out of the attention launch; this kernel serves proxy queries, blocks whose
+// attention workgroups would leave more than 64 partial arrays per KV head, and callers that switch the
+// attention launch's score sweep off.
+//
 // A column sum mixes rows whose softmax normalisers are only known once the
 // row has seen its last key, so it cannot ride along with the online softmax
 // of the attention kernel.  This kernel takes the finished row statistics
@@ -11,7 +15,7 @@
 // operand, for every query head of the KV group in turn.  In the accumulator
 // layout a lane then holds one key column, so the column sum is a plain
 // per-lane running add and nothing is reduced across lanes until the very end.
-// No atomics: every row split writes its own partial array and the select
+// No atomics: every row split writes its own partial array and the compaction
 // kernel adds them in a fixed order.
 //
 // Inside a wave the work is software-pipelined: the MFMAs of query tile i run

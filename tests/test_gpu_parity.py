@@ -75,9 +75,9 @@ def _attention_case(hq, hkv, d, c, n, budget, chunk_max, seed, scale=0.0, n_obs=
     (2, 1, 128, 100, 1, 4096, 64),      # a single row
     (8, 2, 128, 193, 150, 4096, 256),   # cache not tile aligned, ragged rows, several key tiles
     (4, 4, 64, 70, 129, 4096, 256),     # head_dim 64, ragged
-    (32, 8, 128, 512, 256, 4096, 256),  # rows-64 variant
-    (32, 8, 128, 640, 1024, 4096, 1024),  # rows-128 variant, diagonal over many tiles
-    (28, 4, 128, 300, 512, 4096, 512),  # group of 7
+    (32, 8, 128, 512, 256, 4096, 256),  # 32-row workgroups, as many as CUs
+    (32, 8, 128, 640, 1024, 4096, 1024),  # 128-row workgroups, diagonal over many tiles
+    (28, 4, 128, 300, 512, 4096, 512),  # 64-row workgroups, group of 7
 ])
 def test_attention_outputs(hq, hkv, d, c, n, budget, chunk_max):
     """Eq. 1 alone: c + n <= budget in every case here, so nothing is scored or evicted and the
@@ -94,8 +94,8 @@ def test_attention_outputs(hq, hkv, d, c, n, budget, chunk_max):
 @pytest.mark.parametrize("variant", [0, 1, 2])
 @pytest.mark.parametrize("hq,hkv,d,c,n", [(8, 2, 128, 193, 300), (4, 4, 64, 70, 200), (4, 2, 128, 0, 129)])
 def test_every_workgroup_shape(variant, hq, hkv, d, c, n):
-    # the library picks the attention workgroup shape from the launch size; the tuning call
-    # forces each compiled shape in turn so that none goes untested
+    # the library picks the attention workgroup shape from the launch size; the tuning call forces the three shapes of
+    # attention.hip in turn (the two that split the keys are picked by size: test_split_key_attention_edges)
     cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, 4096, 512, seed=7 * c + n + variant,
                                                     attention_shape=variant)
     assert err <= U.OUT_TOL, err
@@ -106,7 +106,7 @@ def test_every_workgroup_shape(variant, hq, hkv, d, c, n):
 @pytest.mark.parametrize("variant", [0, 1, 2])
 @pytest.mark.parametrize("hq,hkv,d,c,n,budget", [(8, 2, 128, 300, 200, 300), (4, 4, 64, 130, 190, 200), (6, 2, 128, 0, 129, 64)])
 def test_every_workgroup_shape_scores(variant, fused, hq, hkv, d, c, n, budget):
-    """Each workgroup shape, scoring inside the attention launch (its second sweep) or with the
+    """Each workgroup shape of attention.hip, scoring inside the attention launch (its second sweep) or with the
     separate column-sum kernel reading the row statistics it leaves: scores and the selection made
     from them, with the shape forced."""
     cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, budget, 256, seed=11 + variant,
@@ -910,7 +910,7 @@ def test_grouped_proxy_scores_edges(layers, hq, hkv, d, c, n, n_obs):
 
 def test_bench_launch_configuration_changes_nothing():
     """bench.py's default order at its own shape: everything in line on one stream, sixteen scratch
-    sets, so that select, merge and move go out once per sixteen layers of long_video.  The first
+    sets, so that attention and compaction go out once per sixteen layers of long_video.  The first
     five blocks (two that only append, three that evict) of sixteen layers must leave the caches
     and outputs of the layer-by-layer order with one scratch set, bit for bit."""
     wl = get_workload("long_video")
