@@ -85,10 +85,16 @@ struct Shape {
   static constexpr int kMergeBytes = (KS - 1) * QW * kMergeFloats * 4;
   static constexpr int kStripRow = 2 * D + 16;        // bytes of an output row staged in LDS, padded
   static constexpr int kEpilogueBytes = kMergeBytes + QW * 32 * kStripRow;
-  static constexpr int kMainBytes = kTileBytes > kEpilogueBytes ? kTileBytes : kEpilogueBytes;
-  // behind the tiles, for the score sweep: the finished row statistics of the workgroup's rows
+  // at the end of the tile buffers, when the tiles are done with: the finished row statistics of the workgroup's
+  // rows for the score sweep, and before them a word per wave (does it want its rows redone)
   static constexpr int kScoreBytes = QW * QT * 32 * 4;
-  static constexpr int kLdsBytes = kMainBytes + kScoreBytes;
+  static constexpr int kFlagBytes = kWaves * 4;
+  static_assert(kEpilogueBytes + kScoreBytes + kFlagBytes <= kTileBytes, "room for the statistics");
+  // and the key strips of the score sweep, one block of 32 keys per wave, at the front
+  static constexpr int kStrip = 32 * D;
+  static_assert(kWaves * kStrip * 2 + kScoreBytes + kFlagBytes <= kTileBytes, "strips and statistics");
+  static constexpr int kQBytes = kRows * D * 2;       // behind the tiles: the workgroup's query rows, for both sweeps
+  static constexpr int kLdsBytes = kTileBytes + kQBytes;
   static_assert(kLdsBytes <= 160 * 1024, "LDS of a CU");
   static_assert(kWaves == 4 || kWaves == 8, "four or eight waves per workgroup");
   static_assert(kTk == 128, "the staging map assumes 128-key tiles");
@@ -102,7 +108,9 @@ attention_kernel(const AttnArgs a) {
   extern __shared__ __align__(16) unsigned char lds_raw[];
   u16* const lds_k = reinterpret_cast<u16*>(lds_raw);              // [2][kTile]
   u16* const lds_v = lds_k + 2 * S::kTile;                         // [2][kTile]
-  float* const lse_lds = reinterpret_cast<float*>(lds_raw + S::kMainBytes);   // [QW][QT][32]
+  u16* const q_lds = lds_v + 2 * S::kTile;                         // [QW][QT][32][D], chunks swizzled like K's
+  float* const lse_lds = reinterpret_cast<float*>(lds_raw + S::kTileBytes - S::kScoreBytes);   // [QW][QT][32]
+  unsigned* const flag_lds = reinterpret_cast<unsigned*>(lse_lds) - S::kWaves;
 
   // XCD-aware order: consecutive work items (same KV head) land on one die
   const int xcd = blockIdx.x % kXcds;
@@ -248,22 +256,24 @@ attention_kernel(const AttnArgs a) {
   // ================================================================ fast path
   bool redo = false;
   {
-    // ---- Q fragments: B operand, lane holds Q[q0 + 32 t + l32][16 s + 8 g .. + 7]
-    bf16x8 qf[QT][D / 16];
+    // ---- the workgroup's query rows, whole rows into LDS (they stay there for the second sweep), and the first
+    // tiles behind them: one trip to memory for all.  (The fragments straight from memory in operand layout, where
+    // neighbouring lanes read different rows, go through the CU's address path at a quarter of its rate, and the tiles
+    // had to wait for them.)  Entry to the first tile's products at 32/8 heads, d 128, 1024 rows: 5.5 -> 4.6 us.
+    constexpr int kQLoads = S::kRows / S::kRowGroup;
+    static_assert(32 % S::kRowsPerLoad == 0 && S::kRows % S::kRowGroup == 0, "whole loads per row tile");
 #pragma unroll
-    for (int t = 0; t < QT; ++t) {
-      const int row = min(q0 + 32 * t + l32, n - 1);     // rows past the block are computed, not stored
-      const u16* src = q_rows + ((size_t)row * a.n_q_heads + h) * D + 8 * g;
-#pragma unroll
-      for (int s = 0; s < D / 16; ++s)
-        qf[t][s] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(src + 16 * s));
+    for (int j = 0; j < kQLoads; ++j) {
+      const int r0 = S::kRowGroup * j + S::kRowsPerLoad * wave_s;        // first row of this load; 32-row tiles in a row
+      const int ti = r0 / 32, r = r0 % 32 + ld_sub;
+      const int row = min(first_row_of(ti / QT) + 32 * (ti % QT) + r, n - 1);   // rows past the block are computed, not stored
+      load16(q_rows + ((size_t)row * a.n_q_heads + h) * D + 8 * (ld_pos ^ (r % S::kChunks)),
+             lds_base + 2u * (unsigned)((int)(q_lds - lds_k) + r0 * D));
     }
-    // Make the compiler finish these loads here.  Left pending, it would wait for them inside the
-    // loop, at a point where the hand-issued tile loads are in flight, and drain those as well.
-#pragma unroll
-    for (int t = 0; t < QT; ++t)
-#pragma unroll
-      for (int s = 0; s < D / 16; ++s) asm volatile("" ::"v"(qf[t][s]));
+    issue_any(kc, kn, lds_k, 0, ld_chunk_k);
+    issue_any(vc, vn, lds_v, 0, ld_chunk_v);
+    issue_any(kc, kn, lds_k + S::kTile, 1, ld_chunk_k);
+    bf16x8 qf[QT][D / 16];        // Q fragments: B operand, lane holds Q[q0 + 32 t + l32][16 s + 8 g .. + 7]
     f32x16 o[QT][D / 32];
     float m_ref[QT], l_run[QT];
 #pragma unroll
@@ -388,21 +398,24 @@ attention_kernel(const AttnArgs a) {
       for (int t = 0; t < QT; ++t) l_run[t] += sum[t];
     };
 
-    // ---- prologue: K(0), K(1), V(0) into LDS, S_X(0) computed
+    // ---- prologue: Q and K(0) in LDS, S_X(0) computed (V(0) and K(1) may still be on their way: the first
+    // body waits for them)
     f32x16 sx[QT], sy[QT];
     unsigned px[QT][8], py[QT][8];
 #pragma unroll
     for (int t = 0; t < QT; ++t)
 #pragma unroll
       for (int r = 0; r < 8; ++r) { px[t][r] = 0u; py[t][r] = 0u; }
-    issue_any(kc, kn, lds_k, 0, ld_chunk_k);
-    issue_any(vc, vn, lds_v, 0, ld_chunk_v);
-    issue_any(kc, kn, lds_k + S::kTile, 1, ld_chunk_k);
     // V buffer 1 is read as "V(-1)" with P = 0 in the first phase: make it finite
     for (int i = tid; i < S::kTile / 8; i += kThreads)
       reinterpret_cast<u32x4*>(lds_v + S::kTile)[i] = u32x4{0u, 0u, 0u, 0u};
-    wait_loads();
+    static_assert(2 * S::kLoadsPerWave < 32, "fits the two fields of the wait");
+    __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * S::kLoadsPerWave & 15) | (2 * S::kLoadsPerWave >> 4 << 14));
     __syncthreads();
+#pragma unroll
+    for (int t = 0; t < QT; ++t)
+#pragma unroll
+      for (int s = 0; s < D / 16; ++s) qf[t][s] = lds_read_b128(q_lds + (qw * QT + t) * 32 * D + k_off[s]);
     {
       // S_X(0) without anything to overlap with
 #pragma unroll
@@ -521,7 +534,12 @@ attention_kernel(const AttnArgs a) {
     // pushed the row sum past 2^64 (or to infinity or NaN)
 #pragma unroll
     for (int tq = 0; tq < QT; ++tq) redo |= !(l_run[tq] <= 0x1p64f);
-    redo = __syncthreads_or(redo) != 0;     // workgroup-uniform; also: everybody is done with the tiles
+    if (__any(redo)) redo = true;
+    if (lane == 0) flag_lds[wave] = redo ? 1u : 0u;
+    __syncthreads();               // (the tiles were done with before the barrier above)
+    redo = false;                  // workgroup-uniform from here on
+#pragma unroll
+    for (int w2 = 0; w2 < S::kWaves; ++w2) redo |= flag_lds[w2] != 0u;
 
     if (!redo) {
       // lanes l and l + 32 each summed half of the keys of a row
@@ -709,7 +727,7 @@ attention_kernel(const AttnArgs a) {
   // ================================================================ scores
   // Eq. 4 needs every row's FINAL normaliser, so the column sums are a second sweep over the
   // workgroup's keys, now that its rows have their log-sum-exp.  The roles change: the workgroup's
-  // query rows go into LDS once (row tiles of 32), and every wave takes every kWaves-th block of
+  // query rows are in LDS (row tiles of 32), and every wave takes every kWaves-th block of
   // 32 keys and keeps it in registers as the B operand while the row tiles pass by as the A
   // operand.  S = Q K^T then has one KEY column per lane and 16 rows of it in the lane's
   // registers: exp2(S - lse) is the exact softmax weight, the column sum is a running add inside
@@ -722,27 +740,52 @@ attention_kernel(const AttnArgs a) {
     constexpr int kRowTiles = QW * QT;
     static_assert(kRowTiles % 2 == 0, "the two accumulator sets alternate over the row tiles");
     __syncthreads();               // the statistics are in LDS; nobody needs the tile buffers any more
-    // ---- the workgroup's query rows, swizzled like a K tile (chunk ch of row r at ch ^ (r % kChunks)):
-    // row tile i holds rows first_row_of(i / QT) + 32 (i % QT) + 0..31, as lse_lds does
-    u16* const q_lds = lds_k;
-    for (int idx = tid; idx < kRowTiles * 32 * S::kChunks; idx += kThreads) {
-      const int ch = idx % S::kChunks, r = (idx / S::kChunks) % 32, ti = idx / (S::kChunks * 32);
-      const int row = min(first_row_of(ti / QT) + 32 * (ti % QT) + r, n - 1);
-      const u32x4 v = *reinterpret_cast<const u32x4*>(q_rows + ((size_t)row * a.n_q_heads + h) * D + 8 * ch);
-      *reinterpret_cast<u32x4*>(q_lds + (ti * 32 + r) * D + 8 * (ch ^ (r % S::kChunks))) = v;
-    }
     // blocks of 32 keys that some row of the workgroup sees
     const int n_kb = (min(n_cand, c + wg_rows_end + shift) + 31) / 32;
     const int split = (h % group) * a.n_row_tiles + rt;
     float* const part = in_set_of(a.partial, a.g, li) + (size_t)hk * a.partial_stride + (size_t)split * a.cand_stride;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-    auto load_keys = [&](bf16x8 (&kf)[kNK], int kbi) __attribute__((always_inline)) {
-      const int kv = min(kbi * 32 + l32, n_cand - 1);            // past the end: any real row, never stored
-      const u16* src = (kv < c ? kc + (size_t)kv * D : kn + (size_t)(kv - c) * new_stride) + 8 * g;
+    // ---- a wave's key blocks come in whole rows through a strip of LDS of its own: block i + 1 is on its way into
+    // it while block i is worked on from registers.  (In operand layout straight from memory they took a CU's address
+    // path at a quarter of its rate.  Statistics to the last sum, 32/8 heads, 1024 rows over 3072 keys: 27.3 -> 24.5 us,
+    // a quarter of that from the query rows that are there already; a prefill of 16640 tokens through 32
+    // such layers 36.3 -> 35.1 ms.)
+    u16* const k_strip = lds_k + wave_s * S::kStrip;
+    constexpr int kStripLoads = 32 / S::kRowsPerLoad;
+    const int strip_chunk = ld_pos ^ ld_sub;           // of load 0; load j: bits of j where a row has 16 chunks
+    const unsigned lane_cache = 2u * (unsigned)(ld_sub * D + 8 * strip_chunk);
+    const unsigned lane_new = 2u * (unsigned)(ld_sub * new_stride + 8 * strip_chunk);
+    auto load_keys = [&](int kbi) __attribute__((always_inline)) {
+      const int kb0 = kbi * 32;
+      const bool cached = kb0 + 32 <= c;
+      if (cached || (kb0 >= c && kb0 + 32 <= n_cand)) {
+        const int stride = cached ? D : new_stride;
+        const u16* const base = cached ? kc + (size_t)kb0 * D : kn + (size_t)(kb0 - c) * new_stride;
+        const unsigned lane_off = cached ? lane_cache : lane_new;
 #pragma unroll
-      for (int st = 0; st < kNK; ++st)
-        kf[st] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(src + 16 * st));
+        for (int j = 0; j < kStripLoads; ++j)
+          load16_scalar_base(base + (size_t)(S::kRowsPerLoad * j) * stride, lane_off ^ (16u * ((S::kRowsPerLoad * j) % S::kChunks)),
+                             lds_base + 2u * (unsigned)((int)(k_strip - lds_k) + S::kRowsPerLoad * j * D));
+      } else {
+#pragma unroll
+        for (int j = 0; j < kStripLoads; ++j) {
+          const int kv = min(kb0 + S::kRowsPerLoad * j + ld_sub, n_cand - 1);      // past the end: any real row, never stored
+          const u16* src = kv < c ? kc + (size_t)kv * D : kn + (size_t)(kv - c) * new_stride;
+          load16(src + 8 * (strip_chunk ^ ((S::kRowsPerLoad * j) % S::kChunks)),
+                 lds_base + 2u * (unsigned)((int)(k_strip - lds_k) + S::kRowsPerLoad * j * D));
+        }
+      }
+    };
+    // the block in the strip into registers, the next one on its way
+    auto next_keys = [&](bf16x8 (&kf)[kNK], int next_kbi) __attribute__((always_inline)) {
+      wait_loads();
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int st = 0; st < kNK; ++st) kf[st] = lds_read_b128(k_strip + k_off[st]);
+#pragma unroll
+      for (int st = 0; st < kNK; ++st) asm volatile("" : "+v"(kf[st]));      // the strip has been read
+      if (next_kbi < n_kb) load_keys(next_kbi);
     };
     // The scale behind an opaque copy for every variant of the stage below, made here, where all
     // lanes are active: the variants then share no subexpression, and the compiler cannot lift the
@@ -897,24 +940,16 @@ attention_kernel(const AttnArgs a) {
       carry = acc;
       carry_kb = kbi;
     };
-    // This wave's key blocks are wave, wave + kWaves, ...; two register sets take turns, the block
-    // after the current one is on its way while the current one is worked on (a third set, two
-    // blocks ahead, was tried: it spills and is slower).  The fetches are unconditional (past the
-    // wave's last block they read it again): the compiler counts the loads in flight to place its
-    // waits, and a fetch that may or may not have been issued would make it wait for the newest one.
-    bf16x8 kfa[kNK], kfb[kNK];
-    const int last_kb = max(n_kb - 1, 0);
-    load_keys(kfa, min(wave_s, last_kb));
-    __syncthreads();               // the query rows are in LDS
-    for (int kbi = wave_s; kbi < n_kb; kbi += 2 * S::kWaves) {
-      load_keys(kfb, min(kbi + S::kWaves, last_kb));
-      do_block(kfa, kbi);
-      load_keys(kfa, min(kbi + 2 * S::kWaves, last_kb));
-      if (kbi + S::kWaves < n_kb) do_block(kfb, kbi + S::kWaves);
+    // This wave's key blocks are wave, wave + kWaves, ...
+    bf16x8 kf[kNK];
+    if (wave_s < n_kb) load_keys(wave_s);
+    for (int kbi = wave_s; kbi < n_kb; kbi += S::kWaves) {
+      next_keys(kf, kbi + S::kWaves);
+      do_block(kf, kbi);
     }
     if (carry_kb >= 0) {
       // the last slot of the last block: its logits are in the second accumulator set
-      const float got = slot(sb, sa, q_lds, kfa, false);
+      const float got = slot(sb, sa, q_lds, kf, false);
       store_block(carry_kb, carry + got);
     }
     // keys that none of this workgroup's rows see: zeros (the selection adds every partial array)

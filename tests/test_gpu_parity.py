@@ -117,6 +117,21 @@ def test_every_workgroup_shape_scores(variant, fused, hq, hkv, d, c, n, budget):
     cache.close()
 
 
+@pytest.mark.parametrize("variant", [0, 1, 2])
+@pytest.mark.parametrize("hq,hkv,d,c,n", [
+    # key blocks of 32: all of the cache, one that holds cached and new keys, a last one of one key, fewer than waves
+    (4, 2, 128, 256, 160), (4, 2, 128, 255, 161), (4, 4, 64, 257, 128), (4, 2, 64, 33, 32), (4, 2, 128, 0, 33)])
+def test_score_sweep_key_blocks(variant, hq, hkv, d, c, n):
+    """The second sweep of attention.hip fetches a block of keys in whole rows, by one base address where the block lies in
+    the cache or among the new keys entirely, row by row otherwise: scores at the edges of the two."""
+    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, max(c, n // 2), 192, seed=17 * c + n + variant,
+                                                    attention_shape=variant)
+    assert err <= U.OUT_TOL, err
+    scores_gpu, keep, dst = cache.debug_last(0)
+    U.check_scores(scores_gpu.cpu().numpy(), scores_ref, n * (hq // hkv))
+    cache.close()
+
+
 @pytest.mark.parametrize("hq,hkv,d,c,n", [
     # keys split eight ways over 32-row tiles: fewer key blocks than waves, exactly as many, one more
     (4, 2, 128, 0, 1), (4, 4, 64, 0, 31), (4, 2, 128, 0, 32), (4, 4, 64, 1, 33), (4, 2, 128, 223, 32),
