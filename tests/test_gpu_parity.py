@@ -148,6 +148,22 @@ def test_split_key_attention_edges(hq, hkv, d, c, n):
     cache.close()
 
 
+@pytest.mark.parametrize("scale", [0.0, 2.0])      # 2: logits of hundreds, so that references move in later blocks
+@pytest.mark.parametrize("hq,hkv,d,c,n", [
+    # 32-row workgroups of eight waves: 1 to 8 key blocks per wave whose weights stay in registers (up to 6 at d 128),
+    # and one more, for which the scores take a second sweep; one row past a tile, a last block of one key
+    (4, 2, 128, 100, 33), (4, 2, 128, 481, 33), (4, 2, 128, 705, 32), (8, 2, 128, 930, 65), (4, 2, 128, 1216, 33),
+    (4, 2, 128, 1472, 33), (4, 2, 128, 1473, 33), (4, 4, 64, 450, 33), (4, 2, 64, 704, 33), (4, 2, 64, 960, 64),
+    (4, 2, 64, 1217, 1), (4, 2, 64, 1472, 33), (4, 2, 64, 1985, 33), (4, 2, 64, 1985, 65)])
+def test_scores_from_kept_weights(hq, hkv, d, c, n, scale):
+    """Scores out of the weights that a wave of the split-key kernel holds, for every number of blocks it is built for."""
+    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, c, 96, seed=13 * c + n, scale=scale)
+    assert err <= U.OUT_TOL, err
+    scores_gpu, keep, dst = cache.debug_last(0)
+    U.check_scores(scores_gpu.cpu().numpy(), scores_ref, n * (hq // hkv))
+    cache.close()
+
+
 @pytest.mark.parametrize("fused", [1, 0])
 @pytest.mark.parametrize("hq,hkv,d,c,n,budget,chunk_max,scale", [
     (4, 4, 64, 128, 64, 128, 64, 0.0),
