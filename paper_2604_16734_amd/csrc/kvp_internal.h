@@ -21,8 +21,8 @@ constexpr int kAttnRowsOfShape[5] = {128, 64, 128, 32, 64};   // query rows per 
 constexpr int kColsumWaves = 4;                 // waves per workgroup of the column-sum kernel
 constexpr int kColsumTargetWorkgroups = 512;    // two per CU, all resident: the launch is a single round
 constexpr int kColsumMaxRowSplits = 16;
-constexpr int kSelectThreads = 1024;
-constexpr int kKeydiffRowsPerThread = 16;       // keys a thread of the compaction kernel can hold a piece of
+constexpr int kSelectThreads = 1024;            // the most of the compaction kernel
+constexpr int kKeydiffRowsPerThread = 16;       // keys a thread of it can hold a piece of (twice as many where it has half the threads)
 constexpr size_t kSelectLdsLimit = 156 * 1024;  // dynamic LDS of the compaction kernel, beside 3.5 KiB of static LDS
 constexpr int kRowstatBlockKeys = 256;          // keys per workgroup of the proxy row-statistics kernel
 constexpr int kKeydiffSliceKeys = 64;           // keys per workgroup of the key-sum kernel
@@ -180,6 +180,7 @@ struct LayerBlock {
 struct SelectArgs {
   int c, n, t0, budget, partial_stride, cand_stride, chunk_max, n_partials, merge;
   int n_kv_heads, head_dim, n_segs;
+  int threads;                  // of a workgroup: 512 or 1024
   int items;                    // candidates per thread
   int direct;                   // the token table has one entry per token before t0, not a hash of them
   int table_size;               // entries, a multiple of 8 (hash: a power of two >= 2 * (c + n))

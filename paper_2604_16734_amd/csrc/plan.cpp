@@ -106,22 +106,28 @@ void plan_colsum(ColsumArgs& a, int n_layers) {
 // key, cnt, evicted, free_slot; the histogram; the token table; the source lists or, before them, the score
 // sums (up to 4096 candidates; beyond that the lists are in the scratch set and the sums lie elsewhere)
 size_t select_lds_bytes(const SelectArgs& a) {
-  const size_t cand_pad = (size_t)a.items * kSelectThreads;
+  const size_t cand_pad = (size_t)a.items * a.threads;
   const size_t lists = a.items > 4 ? 0 : cand_pad * kNeighbours * 2, 
-               sums = a.items > 4 ? 0 : (size_t)a.groups * a.quads * 16 + (a.keydiff ? (kSelectThreads / 64 + 1) * (size_t)a.head_dim * 4 : 0);
+               sums = a.items > 4 ? 0 : (size_t)a.groups * a.quads * 16 + (a.keydiff ? (a.threads / 64 + 1) * (size_t)a.head_dim * 4 : 0);
   return cand_pad * (8 + 1 + 2 + 2) + kSelectBins * 4 + (size_t)a.table_size * 2 + (lists > sums ? lists : sums);
 }
 
-// A thread owns ceil(n_cand / 1024) neighbouring candidates.  For the sums of the partial arrays the threads
+// A workgroup has 512 threads up to 2048 candidates (four to a thread), 1024 beyond.  Most of its phases are what every wave
+// does for itself (scans, the search of the histogram) on four SIMDs, so that fewer waves are done sooner, until there are
+// too few for the rows.  Per launch with 512 threads, with 1024: 4 heads of d 64, 192 candidates 10.2, 11.4 us; 4 heads of
+// d 128, 768 candidates, scored by the keys 14.0, 14.5 us; with 256 threads 10.8 and 14.1 us, and 8 layers of 768
+// candidates 3 us more than with 512.
+// A thread owns ceil(n_cand / threads) neighbouring candidates.  For the sums of the partial arrays the threads
 // form groups of 64, 128 or 256 (the fewest that cover the candidates in fours, 256 at most) that take
 // every groups-th array, so that all of them have loads in flight whatever the number of candidates.
 // The token table has an entry for every token before the block where LDS has room for that.
 void plan_select(SelectArgs& a) {
   const int n_cand = a.c + a.n;
-  a.items = (n_cand + kSelectThreads - 1) / kSelectThreads;
+  a.threads = n_cand <= 2048 ? 512 : kSelectThreads;
+  a.items = (n_cand + a.threads - 1) / a.threads;
   a.quads = (n_cand + 3) / 4;
-  a.width = a.items > 4 ? kSelectThreads : a.quads <= 64 ? 64 : a.quads <= 128 ? 128 : 256;
-  a.groups = a.score_override || a.keydiff ? 1 : kSelectThreads / a.width;
+  a.width = a.items > 4 ? a.threads : a.quads <= 64 ? 64 : a.quads <= 128 ? 128 : 256;
+  a.groups = a.score_override || a.keydiff ? 1 : a.threads / a.width;
   if (a.groups > a.n_partials) a.groups = a.n_partials < 1 ? 1 : a.n_partials;
   a.direct = 1;
   a.table_size = ((a.t0 > n_cand ? a.t0 : n_cand) + 7) / 8 * 8;       // (it becomes the list of destinations, too)

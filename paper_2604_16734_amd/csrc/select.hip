@@ -2,13 +2,13 @@
 // (the lowest importance scores leave first, Sec. 3.2), the slots of the kept block tokens, the
 // grid-neighbour merge of the evicted visual tokens, and the rows themselves, in place.
 //
-// One workgroup of 1024 threads per KV head and layer does all of it.  A head's rows that change are few
+// One workgroup of 512 or 1024 threads (plan.cpp) per KV head and layer does all of it.  A head's rows that change are few
 // (at 32/8 heads, 1024 new over 2048 cached: 175 merge destinations, 212 sources and 88 moved rows,
 // 0.4 MB), so one CU moves them in a few microseconds, and one launch replaces three whose
 // plans had to go through memory.  What bounds it is the chain of its phases: memory round trips,
 // LDS atomics, block scans, barriers.  With 16 layers in a launch the chains of 128 heads run side by
 // side.
-//   * scores by the keys alone, for up to 16 rows per thread (1024 candidates at head dimension 128): the workgroup
+//   * scores by the keys alone, for up to 16 or 32 rows per thread (1024 candidates at head dimension 128): the workgroup
 //     reads the head's keys once, keeps them in registers, adds them up to the anchor and takes every key's
 //     cosine with it -- a launch pair of 9 us otherwise (keydiff.hip, which serves larger heads).
 //   * other scores: the partial column sums of a head are added up by groups of threads, sixteen bytes per
@@ -47,9 +47,7 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
-constexpr int kThreads = kSelectThreads;
-constexpr int kWaves = kThreads / 64;
-constexpr int kMaxItemsAny = KVP_MAX_CANDIDATES / kThreads;   // 8
+constexpr int kMaxItemsAny = KVP_MAX_CANDIDATES / kSelectThreads;   // 8
 constexpr int kBins = kSelectBins;
 constexpr unsigned kNone16 = 0xFFFFu;
 
@@ -174,7 +172,7 @@ __device__ __forceinline__ bool neighbours(const SegL* segs, int n_segs, int tok
 }
 
 // One row pair of `D` channels: 2 D / 8 lanes of 16 bytes, K row then V row.
-template <int D>
+template <int D, int kThreads>
 struct Lanes {
   static constexpr int kPerRow = D / 8;
   static constexpr int kPerPair = 2 * kPerRow;
@@ -183,9 +181,10 @@ struct Lanes {
 
 // kMaxItems: candidates a thread can own (4 covers up to 4096 candidates, with the source lists in LDS;
 // 8 covers the limit, with the source lists in the scratch set)
-template <int D, int kMaxItems>
+template <int D, int kMaxItems, int kThreads>
 __global__ void __launch_bounds__(kThreads)
 compact_kernel(const SelectArgs a) {
+  constexpr int kWaves = kThreads / 64;
   constexpr bool kListsInLds = kMaxItems <= 4;
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ unsigned long long s_members[64];
@@ -318,10 +317,12 @@ compact_kernel(const SelectArgs a) {
         }
       };
       const int passes = (n_cand + kRows - 1) / kRows;
-      if (passes <= 4) score_keys(std::integral_constant<int, 4>{});
-      else if (passes <= 8) score_keys(std::integral_constant<int, 8>{});
-      else if (passes <= 12) score_keys(std::integral_constant<int, 12>{});
-      else score_keys(std::integral_constant<int, kKeydiffRowsPerThread>{});
+      // (512 threads hold twice the rows each, with twice the registers)
+      constexpr int kRowsEach = kKeydiffRowsPerThread * (kSelectThreads / kThreads);
+      if (passes <= kRowsEach / 4) score_keys(std::integral_constant<int, kRowsEach / 4>{});
+      else if (passes <= kRowsEach / 2) score_keys(std::integral_constant<int, kRowsEach / 2>{});
+      else if (passes <= 3 * kRowsEach / 4) score_keys(std::integral_constant<int, 3 * kRowsEach / 4>{});
+      else score_keys(std::integral_constant<int, kRowsEach>{});
     } else {
       const int grp = tid / a.width, quad0 = tid % a.width;              // width is a power of two
       const int n_arrays = grp < a.groups ? (a.n_partials - grp + a.groups - 1) / a.groups : 0;
@@ -516,7 +517,7 @@ compact_kernel(const SelectArgs a) {
   }
   __syncthreads();
 
-  using L = Lanes<D>;
+  using L = Lanes<D, kThreads>;
   const int sub = tid % L::kPerPair;
   const bool is_v = sub >= L::kPerRow;
   const int piece = sub % L::kPerRow;
@@ -758,8 +759,9 @@ template <int D>
 hipError_t launch_head_dim(const SelectArgs& a, int n_kv_heads, hipStream_t s) {
   const size_t lds = select_lds_bytes(a);
   const dim3 grid(n_kv_heads, a.g.n_layers);
-  if (a.items <= 4) hipLaunchKernelGGL((compact_kernel<D, 4>), grid, dim3(kThreads), lds, s, a);
-  else hipLaunchKernelGGL((compact_kernel<D, kMaxItemsAny>), grid, dim3(kThreads), lds, s, a);
+  if (a.items > 4) hipLaunchKernelGGL((compact_kernel<D, kMaxItemsAny, 1024>), grid, dim3(1024), lds, s, a);
+  else if (a.threads == 1024) hipLaunchKernelGGL((compact_kernel<D, 4, 1024>), grid, dim3(1024), lds, s, a);
+  else hipLaunchKernelGGL((compact_kernel<D, 4, 512>), grid, dim3(512), lds, s, a);
   return hipGetLastError();
 }
 
@@ -772,9 +774,10 @@ hipError_t launch_select(const SelectArgs& a, int n_kv_heads, hipStream_t s) {
 // Allows the kernels the dynamic LDS of the largest head they can be given (the attribute
 // belongs to the function on the current device: called at cache creation).
 hipError_t prepare_select() {
-  for (const void* fn : {reinterpret_cast<const void*>(compact_kernel<64, 4>), reinterpret_cast<const void*>(compact_kernel<128, 4>),
-                         reinterpret_cast<const void*>(compact_kernel<64, kMaxItemsAny>),
-                         reinterpret_cast<const void*>(compact_kernel<128, kMaxItemsAny>)}) {
+  for (const void* fn : {reinterpret_cast<const void*>(compact_kernel<64, 4, 512>), reinterpret_cast<const void*>(compact_kernel<128, 4, 512>),
+                         reinterpret_cast<const void*>(compact_kernel<64, 4, 1024>), reinterpret_cast<const void*>(compact_kernel<128, 4, 1024>),
+                         reinterpret_cast<const void*>(compact_kernel<64, kMaxItemsAny, 1024>),
+                         reinterpret_cast<const void*>(compact_kernel<128, kMaxItemsAny, 1024>)}) {
     const hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSelectLdsLimit);
     if (e != hipSuccess) return e;
   }

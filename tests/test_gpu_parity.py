@@ -589,6 +589,20 @@ def _compact_on_given_scores(d, c, n, budget, t0, segs, tokens, scores):
     return cache, merged
 
 
+@pytest.mark.parametrize("d,c,n", [(64, 3, 1), (128, 400, 112), (64, 400, 113), (128, 1500, 548), (64, 1500, 549)])
+@pytest.mark.parametrize("t0", [2000, 70000])                 # the two kinds of token table
+def test_compaction_workgroup_sizes(d, c, n, t0):
+    """The smallest head, one candidate per thread of 512 and one more, the most candidates that 512 threads take (four
+    each) and one more."""
+    planes = (t0 + n) // 256 + 1
+    rng = np.random.default_rng(t0 + c + n)
+    tokens = np.stack([rng.choice(np.arange(t0 - min(t0, 2 * c), t0), size=c, replace=False) for _ in range(2)])
+    scores = (rng.integers(0, 50, size=(2, c + n)).astype(np.float32) + 1) / 7
+    cache, merged = _compact_on_given_scores(d, c, n, c, t0, (Segment(0, planes * 256, 1, 16, 16, planes, 1),), tokens, scores)
+    assert merged > 0 or c < 100
+    cache.close()
+
+
 @pytest.mark.parametrize("d,c,n,budget,t0", [(128, 2048, 1024, 2048, 2048),     # the bench shape
                                              (64, 1536, 512, 1536, 1536), (64, 512, 256, 512, 700), (64, 4100, 200, 4100, 5000)])
 @pytest.mark.parametrize("kind", ["equal", "half_zero", "zeros"])
