@@ -112,18 +112,20 @@ attention_kernel(const AttnArgs a) {
   float* const lse_lds = reinterpret_cast<float*>(lds_raw + S::kTileBytes - S::kScoreBytes);   // [QW][QT][32]
   unsigned* const flag_lds = reinterpret_cast<unsigned*>(lse_lds) - S::kWaves;
 
+  const int li = blockIdx.y;                         // layer of the group
+  const u16* const q_rows = a.layer[li].q;
+  u16* const out_rows = a.layer[li].out;
+  have_arguments(q_rows, out_rows, a.layer[li].k_new, a.layer[li].v_new, a.k_cache, a.v_cache, a.lse2, a.partial, a.g.first_set,
+                 a.g.n_sets, a.g.set_stride, a.g.kv_stride, a.n, a.c, a.work_per_xcd, a.total_work, a.tiles_magic, a.group_magic);
   // XCD-aware order: consecutive work items (same KV head) land on one die
   const int xcd = blockIdx.x % kXcds;
   const int w = xcd * a.work_per_xcd + blockIdx.x / kXcds;
   if (w >= a.total_work) return;
-  const int li = blockIdx.y;                         // layer of the group
-  const u16* const q_rows = a.layer[li].q;
-  u16* const out_rows = a.layer[li].out;
   float* const lse2 = in_set_of(a.lse2, a.g, li);
-  const int group = a.n_q_heads / a.n_kv_heads;
-  const int rt = a.n_row_tiles - 1 - (w % a.n_row_tiles);   // long rows first
-  const int h = w / a.n_row_tiles;
-  const int hk = h / group;
+  const int group = a.group;
+  const int h = (int)quotient((unsigned)w, a.tiles_magic);
+  const int rt = a.n_row_tiles - 1 - (w - h * a.n_row_tiles);    // long rows first
+  const int hk = (int)quotient((unsigned)h, a.group_magic);
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -742,7 +744,7 @@ attention_kernel(const AttnArgs a) {
     __syncthreads();               // the statistics are in LDS; nobody needs the tile buffers any more
     // blocks of 32 keys that some row of the workgroup sees
     const int n_kb = (min(n_cand, c + wg_rows_end + shift) + 31) / 32;
-    const int split = (h % group) * a.n_row_tiles + rt;
+    const int split = (h - hk * group) * a.n_row_tiles + rt;
     float* const part = in_set_of(a.partial, a.g, li) + (size_t)hk * a.partial_stride + (size_t)split * a.cand_stride;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 

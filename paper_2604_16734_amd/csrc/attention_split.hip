@@ -116,17 +116,19 @@ attention_split_kernel(const AttnArgs a) {
   u16* const q_lds = reinterpret_cast<u16*>(stat_l + S::kWaves * 32);            // [kRows][D], chunks swizzled like K's
   float* const lse_lds = reinterpret_cast<float*>(q_lds + S::kRows * D);         // [kRows]
 
-  // XCD-aware order: consecutive work items (same KV head) land on one die
-  const int w = (blockIdx.x % kXcds) * a.work_per_xcd + blockIdx.x / kXcds;
-  if (w >= a.total_work) return;
   const int li = blockIdx.y;
   const u16* const q_rows = a.layer[li].q;
   u16* const out_rows = a.layer[li].out;
+  have_arguments(q_rows, out_rows, a.layer[li].k_new, a.layer[li].v_new, a.k_cache, a.v_cache, a.lse2, a.partial, a.g.first_set,
+                 a.g.n_sets, a.g.set_stride, a.g.kv_stride, a.n, a.c, a.work_per_xcd, a.total_work, a.tiles_magic, a.group_magic);
+  // XCD-aware order: consecutive work items (same KV head) land on one die
+  const int w = (blockIdx.x % kXcds) * a.work_per_xcd + blockIdx.x / kXcds;
+  if (w >= a.total_work) return;
   float* const lse2 = in_set_of(a.lse2, a.g, li);
-  const int group = a.n_q_heads / a.n_kv_heads;
-  const int rt = a.n_row_tiles - 1 - (w % a.n_row_tiles);   // long rows first
-  const int h = w / a.n_row_tiles;
-  const int hk = h / group;
+  const int group = a.group;
+  const int h = (int)quotient((unsigned)w, a.tiles_magic);
+  const int rt = a.n_row_tiles - 1 - (w - h * a.n_row_tiles);    // long rows first
+  const int hk = (int)quotient((unsigned)h, a.group_magic);
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -441,7 +443,7 @@ attention_split_kernel(const AttnArgs a) {
     }
   }
   if (!score) return;
-  const int split = (h % group) * a.n_row_tiles + rt;
+  const int split = (h - hk * group) * a.n_row_tiles + rt;
   float* const part = in_set_of(a.partial, a.g, li) + (size_t)hk * a.partial_stride + (size_t)split * a.cand_stride;
   // keys that none of this workgroup's rows see: zeros (the selection adds every partial array)
   for (int k = 32 * (n_kb - c_blk) + tid; k < a.n_keys; k += S::kThreads) part[c + k] = 0.f;

@@ -67,18 +67,20 @@ colsum_kernel(const ColsumArgs a) {
   __shared__ __align__(256) float lse_lds[kStatRing][64];
   __shared__ __align__(1024) u16 k_lds[W][kTile];
 
+  // grid y: the layer of the group
+  const int li = blockIdx.y;
+  have_arguments(a.layer[li].q, a.layer[li].k_new, a.k_cache, a.lse2, a.partial, a.g.first_set, a.g.n_sets, a.g.set_stride, a.g.kv_stride,
+                 a.n, a.c, a.budget, a.work_per_xcd, a.total_work, a.wgs_per_head, a.splits_per_wg, a.group);
   const int xcd = blockIdx.x % kXcds;
   const int w = xcd * a.work_per_xcd + blockIdx.x / kXcds;
   if (w >= a.total_work) return;
-  // grid y: the layer of the group
-  const int li = blockIdx.y;
   const u16* const q_rows = a.layer[li].q;
   const u16* const k_new = a.layer[li].k_new;
   const u16* const k_cache = a.k_cache + (long long)li * a.g.kv_stride;
   const float* const lse2 = in_set_of(a.lse2, a.g, li);
   float* const partial = in_set_of(a.partial, a.g, li);
-  const int hk = w / a.wgs_per_head;
-  const int rem = w % a.wgs_per_head;
+  const int hk = (int)quotient((unsigned)w, a.wgs_magic);
+  const int rem = w - hk * a.wgs_per_head;
   // its key block, and its row splits [split, split_end) of the block's `splits`
   int kvb = 0, split, split_end, splits;
   if (a.splits_per_wg == 1) {
@@ -93,7 +95,7 @@ colsum_kernel(const ColsumArgs a) {
     split = rem % per_block * a.splits_per_wg;
     split_end = min(splits, split + a.splits_per_wg);
   }
-  const int group = a.n_q_heads / a.n_kv_heads;
+  const int group = a.group;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform: branches on it are scalar

@@ -44,11 +44,20 @@ constexpr int kHeadThreads = 1024;   // of the one-workgroup-per-query-head kern
 constexpr int kTile = kDecodeTile;   // keys per workgroup step
 constexpr int kGroupLimit = kDecodeGroupLimit;   // query heads per KV head
 
-// key j of the list: cache slot j for j < c, then the tail rows
-__device__ __forceinline__ const u16* row_of(const u16* cache, const u16* tail, int hk, int n_kv_heads, int j, int c,
-                                             int budget, int D) {
-  return j < c ? cache + ((size_t)hk * budget + j) * D : tail + ((size_t)(j - c) * n_kv_heads + hk) * D;
-}
+// a piece of key or value j of a KV head's list: cache slot j for j < c, then the tail rows
+template <int D, class Offset>
+struct Rows {
+  const u16* cached;
+  const u16* tail;
+  unsigned tail_bytes;
+  int c;
+  __device__ __forceinline__ Rows(const u16* cache, const u16* tail_rows, const DecodeArgs& a, int hk, int piece)
+      : cached(cache + (size_t)hk * a.budget * D + 8 * piece), tail(tail_rows + (size_t)hk * D + 8 * piece),
+        tail_bytes(2u * (unsigned)(a.n_kv_heads * D)), c(a.c) {}
+  __device__ __forceinline__ uint4 load(int j) const {
+    return *reinterpret_cast<const uint4*>(row_of_two<Offset>(cached, 2u * D, tail, tail_bytes, j, c));
+  }
+};
 
 __device__ __forceinline__ u16 round_bf16(float r) {
   unsigned u = __float_as_uint(r);               // round to nearest even
@@ -72,24 +81,23 @@ decode_head_kernel(const DecodeArgs a) {
   constexpr int kPieces = D / 8, kRows = kHeadThreads / kPieces, kHeadWaves = kHeadThreads / 64;
   __shared__ float s_m[kHeadWaves], s_l[kHeadWaves];
   __shared__ __align__(16) float s_o[kHeadWaves][D];
-  // neighbouring workgroups take different KV heads: a KV head's query heads share the L2 of one or two dies
-  const int hk = blockIdx.x % a.n_kv_heads, h = hk * (a.n_q_heads / a.n_kv_heads) + blockIdx.x / a.n_kv_heads;
+  have_arguments(a.q, a.k_tail, a.v_tail, a.out, a.k_cache, a.v_cache, a.c, a.n_tail, a.n_kv_heads, a.budget, a.group, a.scale_log2);
+  // grid (KV heads, query heads of one): neighbouring workgroups take different KV heads, and a KV head's query heads share
+  // the L2 of one or two dies
+  const int hk = blockIdx.x, h = hk * a.group + blockIdx.y;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int piece = tid % kPieces, sub = tid / kPieces;
   const int n_keys = a.c + a.n_tail;
   uint4 kw[kLoads], vw[kLoads];
+  const uint4 qw = *reinterpret_cast<const uint4*>(a.q + (size_t)h * D + 8 * piece);
+  const Rows<D, unsigned> k_rows(a.k_cache, a.k_tail, a, hk, piece), v_rows(a.v_cache, a.v_tail, a, hk, piece);
 #pragma unroll
-  for (int i = 0; i < kLoads; ++i) {
-    const int j = min(kRows * i + sub, n_keys - 1);
-    kw[i] = *reinterpret_cast<const uint4*>(row_of(a.k_cache, a.k_tail, hk, a.n_kv_heads, j, a.c, a.budget, D) + 8 * piece);
-  }
+  for (int i = 0; i < kLoads; ++i) kw[i] = k_rows.load(min(kRows * i + sub, n_keys - 1));
+#pragma unroll
+  for (int i = 0; i < kLoads; ++i) vw[i] = v_rows.load(min(kRows * i + sub, n_keys - 1));
+  __builtin_amdgcn_sched_barrier(0);             // all loads on their way before the first is waited for
   float qx[8];
-  unpack8(*reinterpret_cast<const uint4*>(a.q + (size_t)h * D + 8 * piece), qx);
-#pragma unroll
-  for (int i = 0; i < kLoads; ++i) {
-    const int j = min(kRows * i + sub, n_keys - 1);
-    vw[i] = *reinterpret_cast<const uint4*>(row_of(a.v_cache, a.v_tail, hk, a.n_kv_heads, j, a.c, a.budget, D) + 8 * piece);
-  }
+  unpack8(qw, qx);
   float s[kLoads], mx = -INFINITY;
 #pragma unroll
   for (int i = 0; i < kLoads; ++i) {
@@ -137,13 +145,16 @@ decode_kernel(const DecodeArgs a) {
   constexpr int kLoads = kTile / kRowsPerLoad;   // rows of a tile a thread holds a piece of
   __shared__ float s_m[kWaves][GM], s_l[kWaves][GM];
   __shared__ __align__(16) float s_o[kWaves][GM][D];
+  have_arguments(a.q, a.k_tail, a.v_tail, a.partial, a.k_cache, a.v_cache, a.c, a.n_tail, a.n_kv_heads, a.budget, a.group, a.n_splits,
+                 a.scale_log2);
   const int split = blockIdx.x, hk = blockIdx.y;
-  const int G = a.n_q_heads / a.n_kv_heads;
+  const int G = a.group;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int piece = tid % kPieces, sub = tid / kPieces;
   const int n_keys = a.c + a.n_tail;
   const int n_tiles = (n_keys + kTile - 1) / kTile;
 
+  const Rows<D, unsigned long long> k_rows(a.k_cache, a.k_tail, a, hk, piece), v_rows(a.v_cache, a.v_tail, a, hk, piece);
   float o[8 * GM], m[GM], l[GM];                 // of this wave's rows; l of this lane's
 #pragma unroll
   for (int g = 0; g < GM; ++g) {
@@ -157,8 +168,7 @@ decode_kernel(const DecodeArgs a) {
     uint4 kw[kLoads], vw[kLoads];
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
-      const int j = min(tile * kTile + kRowsPerLoad * i + sub, n_keys - 1);
-      kw[i] = *reinterpret_cast<const uint4*>(row_of(a.k_cache, a.k_tail, hk, a.n_kv_heads, j, a.c, a.budget, D) + 8 * piece);
+      kw[i] = k_rows.load(min(tile * kTile + kRowsPerLoad * i + sub, n_keys - 1));
     }
     uint4 qw[GM];
 #pragma unroll
@@ -168,8 +178,7 @@ decode_kernel(const DecodeArgs a) {
     }
 #pragma unroll
     for (int i = 0; i < kLoads; ++i) {
-      const int j = min(tile * kTile + kRowsPerLoad * i + sub, n_keys - 1);
-      vw[i] = *reinterpret_cast<const uint4*>(row_of(a.v_cache, a.v_tail, hk, a.n_kv_heads, j, a.c, a.budget, D) + 8 * piece);
+      vw[i] = v_rows.load(min(tile * kTile + kRowsPerLoad * i + sub, n_keys - 1));
     }
     float p[GM][kLoads];
 #pragma unroll
@@ -251,6 +260,7 @@ template <int D>
 __global__ void __launch_bounds__(kFoldLanes * D)
 decode_fold_kernel(const DecodeArgs a) {
   __shared__ float s_o[kFoldLanes][D], s_m[kFoldLanes], s_l[kFoldLanes];
+  have_arguments(a.out, a.partial, a.n_splits, a.scale_log2);
   const int h = blockIdx.x, tid = threadIdx.x;
   const int ch = tid % D, grp = tid / D;
   const float* const part = a.partial + (size_t)h * a.n_splits * (D + 2);
@@ -306,15 +316,16 @@ template <int D, int kLoads = 1>
 hipError_t launch_head(const DecodeArgs& a, hipStream_t s) {
   if constexpr (kLoads < kHeadLoads)
     if (a.c + a.n_tail > kLoads * kHeadRows<D>) return launch_head<D, kLoads + 1>(a, s);
-  hipLaunchKernelGGL((decode_head_kernel<D, kLoads>), dim3(a.n_q_heads), dim3(kHeadThreads), 0, s, a);
+  hipLaunchKernelGGL((decode_head_kernel<D, kLoads>), dim3(a.n_kv_heads, a.group), dim3(kHeadThreads), 0, s, a);
   return hipGetLastError();
 }
 
 template <int D>
 hipError_t launch_for(const DecodeArgs& a, hipStream_t s) {
-  if ((long long)a.c + a.n_tail <= kHeadLoads * kHeadRows<D>) return launch_head<D>(a, s);
+  // (a row's offset in 32 bits: lists of few keys, KV heads of less than 4 GiB together)
+  if ((long long)a.c + a.n_tail <= kHeadLoads * kHeadRows<D> && a.n_kv_heads <= 8192) return launch_head<D>(a, s);
   const dim3 grid(a.n_splits, a.n_kv_heads);
-  const int group = a.n_q_heads / a.n_kv_heads;
+  const int group = a.group;
   if (group <= 4) hipLaunchKernelGGL((decode_kernel<D, 4>), grid, dim3(kThreads), 0, s, a);
   else if (group <= 8) hipLaunchKernelGGL((decode_kernel<D, 8>), grid, dim3(kThreads), 0, s, a);
   else hipLaunchKernelGGL((decode_kernel<D, 16>), grid, dim3(kThreads), 0, s, a);

@@ -825,6 +825,7 @@ int kvp_decode_step(kvp_cache* c, int32_t layer, const void* q, const void* k_ta
   da.partial = reinterpret_cast<float*>(c->set(layer) + lay.partial_off);
   da.c = L.count; da.n_tail = n_tail;
   da.n_q_heads = cfg.n_q_heads; da.n_kv_heads = cfg.n_kv_heads; da.budget = cfg.budget;
+  da.group = cfg.n_q_heads / cfg.n_kv_heads;
   da.scale_log2 = c->scale * 1.4426950408889634f;
   const size_t have = (size_t)cfg.n_kv_heads * lay.max_partials * lay.cand_stride;   // floats
   da.n_splits = decode_splits((long long)L.count + n_tail, cfg.head_dim, have, cfg.n_q_heads);
@@ -860,6 +861,7 @@ int kvp_decode_step_static(kvp_cache* c, int32_t layer, const void* q, const voi
   da.partial = c->static_scratch;       // the looked-up device address, never the array's name
   da.c = L.count; da.n_tail = n_tail;
   da.n_q_heads = cfg.n_q_heads; da.n_kv_heads = cfg.n_kv_heads; da.budget = cfg.budget;
+  da.group = cfg.n_q_heads / cfg.n_kv_heads;
   da.scale_log2 = c->scale * 1.4426950408889634f;
   da.n_splits = splits;
   hipStream_t s = static_cast<hipStream_t>(stream);

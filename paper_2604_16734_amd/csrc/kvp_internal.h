@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "divide.h"
 #include "key_range.h"
 #include "kvp.h"
 
@@ -22,7 +23,7 @@ constexpr int kColsumWaves = 4;                 // waves per workgroup of the co
 constexpr int kColsumTargetWorkgroups = 512;    // two per CU, all resident: the launch is a single round
 constexpr int kColsumMaxRowSplits = 16;
 constexpr int kSelectThreads = 1024;            // the most of the compaction kernel
-constexpr int kKeydiffRowsPerThread = 16;       // keys a thread of it can hold a piece of (twice as many where it has half the threads)
+constexpr int kKeydiffRowsPerThread = 32;       // keys a thread of it can hold a piece of (of 512 threads)
 constexpr size_t kSelectLdsLimit = 156 * 1024;  // dynamic LDS of the compaction kernel, beside 3.5 KiB of static LDS
 constexpr int kRowstatBlockKeys = 256;          // keys per workgroup of the proxy row-statistics kernel
 constexpr int kKeydiffSliceKeys = 64;           // keys per workgroup of the key-sum kernel
@@ -49,6 +50,25 @@ struct LayerGroup : GroupStrides {
 };
 
 #if defined(__HIPCC__)
+// Kernel arguments come from memory, a line at a time; read where they are first used they are a chain of waits on the
+// way to a workgroup's first load.  This asks for all of its operands at once.
+template <class T>
+__device__ __forceinline__ void have_argument(T x) { asm volatile("" ::"s"(x)); }
+template <class... T>
+__device__ __forceinline__ void have_arguments(T... x) { (have_argument(x), ...); }
+
+// Row p of a list in two parts, the first c rows `old_bytes` apart and the others `new_bytes` apart: choices between values and
+// one multiplication.  (Written as a choice between two addresses this becomes a branch around two long
+// multiplications for every load.)  Offset: unsigned where a part is smaller than 4 GiB (and its rows less than 16 MiB apart).
+template <class Offset>
+__device__ __forceinline__ const u16* row_of_two(const u16* old_rows, unsigned old_bytes, const u16* new_rows, unsigned new_bytes, int p, int c) {
+  const bool old = p < c;
+  const unsigned row = (unsigned)(old ? p : p - c), bytes = old ? old_bytes : new_bytes;
+  const char* const base = reinterpret_cast<const char*>(old ? old_rows : new_rows);
+  if constexpr (sizeof(Offset) == 4) return reinterpret_cast<const u16*>(base + __umul24(row, bytes));
+  else return reinterpret_cast<const u16*>(base + (unsigned long long)row * bytes);
+}
+
 // the same pointer in scratch set (first_set + li) % n_sets instead of set first_set (a group has at most
 // n_sets layers: one subtraction wraps; pointer arithmetic, not integers: the compiler then still
 // knows that it points to global memory)
@@ -75,8 +95,10 @@ struct AttnArgs {
   int n_keys;          // block keys (k_new, v_new rows); the query rows are n
   int shift;           // row r sees block key j iff j <= r + shift (0: causal block; >= n_keys: all)
   int n_row_tiles, work_per_xcd, total_work;   // work items of one layer (grid y = layer)
-  int variant;         // tile shape, chosen by plan_attention
+  int group;           // query heads per KV head
+  unsigned tiles_magic, group_magic;   // divisor_magic of n_row_tiles and of group
   float scale_log2;    // softmax scale times log2(e)
+  int variant;         // tile shape, chosen by plan_attention
   int partial_stride, cand_stride;   // floats from a KV head's partial arrays to the next head's, and from array to array
   GroupStrides g;
   const u16* k_cache;  // the group's first layer: [Hkv, M, D]
@@ -105,6 +127,8 @@ struct ColsumArgs {
   int subtiles;        // 32-key subtiles per wave, chosen by plan_colsum
   int splits_per_wg;   // row splits a workgroup takes one after the other; more than one only where all blocks have as many
   int wgs_per_head;    // = split_prefix[n_kv_blocks] where that is one
+  unsigned wgs_magic;  // its divisor_magic
+  int group;           // query heads per KV head
   int work_per_xcd, total_work;
   float scale_log2;
   GroupStrides g;
@@ -120,9 +144,11 @@ struct ColsumArgs {
 // Row statistics of a short list of proxy queries over all candidates (rowstat.hip).
 struct RowstatArgs {
   int n, c, n_keys, n_q_heads, n_kv_heads, budget, lse_stride;
-  int n_kv_blocks;     // set by launch_rowstat, like the next two
+  int n_kv_blocks;     // set by launch_rowstat, like those up to the magics
   int items_per_wg;    // (query head, 32-row tile) items a workgroup takes
   int item_splits;     // workgroups that share the items of a KV head
+  int group;           // query heads per KV head
+  unsigned splits_magic, tiles_magic, rows_magic;   // divisor_magic of item_splits, of the row tiles and of n
   float scale_log2;
   GroupStrides g;      // a group of layers per launch, as in ColsumArgs
   const u16* k_cache;  // the group's first layer: [Hkv, M, D]
@@ -149,6 +175,7 @@ hipError_t launch_keydiff(KeydiffArgs a, int head_dim, hipStream_t s);
 // One decode step of one layer (decode.hip).
 struct DecodeArgs {
   int c, n_tail, n_q_heads, n_kv_heads, budget, n_splits;
+  int group;           // query heads per KV head
   float scale_log2;
   const u16* q;        // [Hq, D]
   const u16* k_tail;   // [n_tail, Hkv, D]
@@ -186,7 +213,9 @@ struct SelectArgs {
   int table_size;               // entries, a multiple of 8 (hash: a power of two >= 2 * (c + n))
   int quads;                    // fours of neighbouring candidates
   int keydiff;                  // 1: the kernel scores by the keys alone itself, there are no partial arrays
-  int width, groups;            // the threads sum the partial arrays as `groups` groups of `width`
+  int width, groups;            // the threads sum the partial arrays as `groups` groups of `width` (a power of two)
+  int width_log2;
+  unsigned groups_magic;        // divisor_magic of groups
   GroupStrides g;
   const float* partial;         // [Hkv][n_partials][candidates], strides as in AttnArgs
   const float* score_override;  // [Hkv, n_cand] used instead, or null

@@ -41,6 +41,9 @@ void plan_attention(AttnArgs& a, int /*head_dim*/, int forced_shape) {
   const int rows = kAttnRowsOfShape[a.variant];
   a.n_row_tiles = (a.n + rows - 1) / rows;
   a.total_work = a.n_row_tiles * a.n_q_heads;
+  a.group = a.n_q_heads / a.n_kv_heads;
+  a.tiles_magic = divisor_magic((unsigned)a.n_row_tiles);
+  a.group_magic = divisor_magic((unsigned)a.group);
   a.work_per_xcd = (a.total_work + kXcds - 1) / kXcds;
 }
 
@@ -98,6 +101,8 @@ void plan_colsum(ColsumArgs& a, int n_layers) {
     a.wgs_per_head = a.n_kv_blocks * ((splits + a.splits_per_wg - 1) / a.splits_per_wg);
   }
   a.total_work = a.wgs_per_head * a.n_kv_heads;
+  a.wgs_magic = divisor_magic((unsigned)a.wgs_per_head);
+  a.group = a.n_q_heads / a.n_kv_heads;
   a.work_per_xcd = (a.total_work + kXcds - 1) / kXcds;
 }
 
@@ -129,6 +134,9 @@ void plan_select(SelectArgs& a) {
   a.width = a.items > 4 ? a.threads : a.quads <= 64 ? 64 : a.quads <= 128 ? 128 : 256;
   a.groups = a.score_override || a.keydiff ? 1 : a.threads / a.width;
   if (a.groups > a.n_partials) a.groups = a.n_partials < 1 ? 1 : a.n_partials;
+  a.width_log2 = 0;
+  while (1 << a.width_log2 < a.width) ++a.width_log2;
+  a.groups_magic = divisor_magic((unsigned)a.groups);
   a.direct = 1;
   a.table_size = ((a.t0 > n_cand ? a.t0 : n_cand) + 7) / 8 * 8;       // (it becomes the list of destinations, too)
   if (!a.merge || select_lds_bytes(a) > kSelectLdsLimit) {
@@ -140,7 +148,7 @@ void plan_select(SelectArgs& a) {
 
 // Keys that the threads of one workgroup can hold in registers: the compaction then scores by the keys alone itself.
 bool keydiff_in_compaction(int n_cand, int head_dim) {
-  return n_cand <= kKeydiffRowsPerThread * (kSelectThreads / (head_dim / 8));
+  return n_cand <= kKeydiffRowsPerThread * (512 / (head_dim / 8));
 }
 
 // ---- compaction: row pairs (K row and V row of a slot, 16 bytes per lane) a workgroup carries

@@ -56,9 +56,11 @@ rowstat_kernel(const RowstatArgs a) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
-  const int group = a.n_q_heads / a.n_kv_heads;
+  const int group = a.group;
   const int kb = blockIdx.x, li = blockIdx.z;
-  const int hk = blockIdx.y / a.item_splits, isplit = blockIdx.y % a.item_splits;
+  have_arguments(a.layer[li].q, a.layer[li].k_new, a.k_cache, a.part_m, a.part_l, a.g.first_set, a.g.n_sets, a.g.set_stride, a.g.kv_stride,
+                 a.n, a.c, a.n_keys, a.budget, a.item_splits, a.items_per_wg, a.splits_magic, a.tiles_magic, a.group);
+  const int hk = (int)quotient(blockIdx.y, a.splits_magic), isplit = (int)blockIdx.y - hk * a.item_splits;
   const int n_rt = (a.n + 31) / 32;
   const int n_items = group * n_rt;
   const int item0 = isplit * a.items_per_wg, item1 = min(n_items, item0 + a.items_per_wg);
@@ -83,7 +85,7 @@ rowstat_kernel(const RowstatArgs a) {
   // the query tile of item `i` (past the last one: that again), shared out among the waves
   auto issue_item = [&](int i) __attribute__((always_inline)) {
     const int item = min(i, item1 - 1);
-    const int h = hk * group + item / n_rt, rt = item % n_rt;
+    const int head = (int)quotient((unsigned)item, a.tiles_magic), h = hk * group + head, rt = item - head * n_rt;
 #pragma unroll
     for (int j = 0; j < kLoads / kWaves; ++j) {
       const int first = kRowsPerLoad * (wave + kWaves * j);
@@ -167,7 +169,7 @@ rowstat_kernel(const RowstatArgs a) {
     float ll = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) ll += s_l[at][w][row_of] * __builtin_amdgcn_exp2f((s_m[at][w][row_of] - mm) * sl2);
-    const int h = hk * group + item / n_rt, row = 32 * (item % n_rt) + row_of;
+    const int head = (int)quotient((unsigned)item, a.tiles_magic), h = hk * group + head, row = 32 * (item - head * n_rt) + row_of;
     if (row < a.n) {
       const size_t to = ((size_t)kb * a.n_q_heads + h) * a.n + row;
       part_m[to] = mm;
@@ -201,7 +203,9 @@ constexpr int kFoldBatch = 16;
 __global__ void __launch_bounds__(256)
 rowstat_fold_kernel(const RowstatArgs a) {
   // grid (blocks of 256 rows, layers of the group)
-  const int i = blockIdx.x * blockDim.x + threadIdx.x, li = blockIdx.y;
+  const int i = blockIdx.x * 256 + threadIdx.x, li = blockIdx.y;
+  have_arguments(a.lse2, a.part_m, a.part_l, a.g.first_set, a.g.n_sets, a.g.set_stride, a.n, a.n_q_heads, a.n_kv_blocks, a.lse_stride,
+                 a.rows_magic, a.scale_log2);
   const int rows = a.n_q_heads * a.n;
   if (i >= rows) return;
   const float* const part_m = in_set_of(a.part_m, a.g, li) + i;
@@ -230,7 +234,7 @@ rowstat_fold_kernel(const RowstatArgs a) {
       l = __builtin_fmaf(pl[u], first + u < a.n_kv_blocks ? f : 0.f, l);
     }
   }
-  const int h = i / a.n, row = i % a.n;
+  const int h = (int)quotient((unsigned)i, a.rows_magic), row = i - h * a.n;    // (fewer than 8192 rows, n_obs 8192 at most)
   in_set_of(a.lse2, a.g, li)[(size_t)h * a.lse_stride + row] = m * a.scale_log2 + __builtin_log2f(l);
 }
 
@@ -254,6 +258,10 @@ hipError_t launch_rowstat(RowstatArgs a, int head_dim, hipStream_t s) {
   }
   a.item_splits = (n_items + a.items_per_wg - 1) / a.items_per_wg;
   if ((long long)a.n_kv_heads * a.item_splits > 65535) return hipErrorInvalidValue;
+  a.group = a.n_q_heads / a.n_kv_heads;
+  a.splits_magic = divisor_magic((unsigned)a.item_splits);
+  a.tiles_magic = divisor_magic((unsigned)((a.n + 31) / 32));
+  a.rows_magic = divisor_magic((unsigned)a.n);
   const dim3 grid(a.n_kv_blocks, a.n_kv_heads * a.item_splits, a.g.n_layers);
   if (head_dim == 128) hipLaunchKernelGGL(rowstat_kernel<128>, grid, dim3(kThreads), 0, s, a);
   else hipLaunchKernelGGL(rowstat_kernel<64>, grid, dim3(kThreads), 0, s, a);

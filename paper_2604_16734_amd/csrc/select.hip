@@ -8,7 +8,7 @@
 // plans had to go through memory.  What bounds it is the chain of its phases: memory round trips,
 // LDS atomics, block scans, barriers.  With 16 layers in a launch the chains of 128 heads run side by
 // side.
-//   * scores by the keys alone, for up to 16 or 32 rows per thread (1024 candidates at head dimension 128): the workgroup
+//   * scores by the keys alone, for up to 32 rows per thread (1024 candidates at head dimension 128): the workgroup
 //     reads the head's keys once, keeps them in registers, adds them up to the anchor and takes every key's
 //     cosine with it -- a launch pair of 9 us otherwise (keydiff.hip, which serves larger heads).
 //   * other scores: the partial column sums of a head are added up by groups of threads, sixteen bytes per
@@ -193,6 +193,9 @@ compact_kernel(const SelectArgs a) {
   __shared__ SegL s_segs[KVP_MAX_SEGMENTS];
 
   const int hk = blockIdx.x, li = blockIdx.y;          // grid (KV heads, layers of the group)
+  have_arguments(a.token_idx, a.partial, a.segs, a.weight, a.scores, a.k_cache, a.layer[li].k_new, a.g.first_set, a.g.n_sets,
+                 a.g.set_stride, a.g.kv_stride, a.g.meta_stride, a.c, a.n, a.t0, a.budget, a.partial_stride, a.cand_stride,
+                 a.n_partials, a.merge, a.n_kv_heads, a.n_segs, a.items, a.table_size, a.quads, a.keydiff, a.width, a.groups);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int c = a.c, n = a.n, n_cand = c + n, budget = a.budget;
   const int items = a.items;
@@ -226,33 +229,22 @@ compact_kernel(const SelectArgs a) {
   // the threads are `groups` groups of `width`; thread t adds up the fours of neighbouring candidates
   // t % width, + width, ... over the arrays t / width, + groups, ...
   {
+    // (token indices and segments are asked for first and used last, without a condition: one that is loaded under a
+    // condition is waited for on the spot, before the sums are on their way)
     int tokv[kMaxItems];
 #pragma unroll
-    for (int i = 0; i < kMaxItems; ++i) {
-      const int p = tid + i * kThreads;
-      tokv[i] = 0;
-      if (i < items && p < n_cand) tokv[i] = p < c ? token_idx[p] : a.t0 + (p - c);
-    }
+    for (int i = 0; i < kMaxItems; ++i) tokv[i] = token_idx[max(min(tid + i * kThreads, c - 1), 0)];
+    const Seg my_seg = a.segs[min(tid, a.n_segs - 1)];
     for (int i = tid; i < kBins; i += kThreads) l.hist[i] = 0u;
     if (tid == 0) { s_n_members = 0u; s_n_dst = 0u; s_n_src = 0u; }
     if (a.merge) {
       for (int i = tid; i < a.table_size / 8; i += kThreads)
         reinterpret_cast<uint4*>(l.table)[i] = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
       for (int i = tid; i < cand_pad / 4; i += kThreads) l.cnt[i] = 0u;
-      if (tid < a.n_segs) {
-        const Seg g = a.segs[tid];
-        SegL sl;
-        sl.begin = g.begin; sl.n = g.n; sl.kind = g.kind; sl.gh = g.gh; sl.gw = g.gw;
-        sl.planes = g.planes; sl.temporal = g.temporal;
-        sl.per = g.gh * g.gw;
-        sl.inv_per = sl.per > 0 ? 1.f / (float)sl.per : 0.f;
-        sl.inv_gw = g.gw > 0 ? 1.f / (float)g.gw : 0.f;
-        s_segs[tid] = sl;
-      }
     }
     if (a.score_override) {
       for (int p = tid; p < n_cand; p += kThreads) l.sums[p] = a.score_override[(size_t)hk * n_cand + p];
-    } else if (kListsInLds && a.keydiff) {
+    } else if (kThreads == 512 && a.keydiff) {         // (up to 2048 candidates)
       constexpr int kPieces = D / 8, kRows = kThreads / kPieces;
       const int piece = tid % kPieces, row0 = tid / kPieces;
       const u16* const k_old = a.k_cache + (long long)li * a.g.kv_stride + (size_t)hk * budget * D + 8 * piece;
@@ -265,7 +257,7 @@ compact_kernel(const SelectArgs a) {
 #pragma unroll
         for (int i = 0; i < kN; ++i) {
           const int p = min(row0 + i * kRows, n_cand - 1);
-          w[i] = *reinterpret_cast<const u32x4*>(p < c ? k_old + (size_t)p * D : k_add + (size_t)(p - c) * a.n_kv_heads * D);
+          w[i] = *reinterpret_cast<const u32x4*>(row_of_two<unsigned long long>(k_old, 2 * D, k_add, 2 * D * (unsigned)a.n_kv_heads, p, c));
         }
         float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -317,33 +309,39 @@ compact_kernel(const SelectArgs a) {
         }
       };
       const int passes = (n_cand + kRows - 1) / kRows;
-      // (512 threads hold twice the rows each, with twice the registers)
-      constexpr int kRowsEach = kKeydiffRowsPerThread * (kSelectThreads / kThreads);
+      constexpr int kRowsEach = kKeydiffRowsPerThread;
       if (passes <= kRowsEach / 4) score_keys(std::integral_constant<int, kRowsEach / 4>{});
       else if (passes <= kRowsEach / 2) score_keys(std::integral_constant<int, kRowsEach / 2>{});
       else if (passes <= 3 * kRowsEach / 4) score_keys(std::integral_constant<int, 3 * kRowsEach / 4>{});
       else score_keys(std::integral_constant<int, kRowsEach>{});
     } else {
-      const int grp = tid / a.width, quad0 = tid % a.width;              // width is a power of two
-      const int n_arrays = grp < a.groups ? (a.n_partials - grp + a.groups - 1) / a.groups : 0;
-      // a scalar base per array, a lane offset that never changes
-      const float* const part = in_set_of(a.partial, a.g, li) + (size_t)hk * a.partial_stride;
-      const unsigned lane_off = (unsigned)(grp * a.cand_stride + 4 * quad0);
+      // (a group is whole waves: what a wave loads is decided by scalar branches)
+      const int grp = __builtin_amdgcn_readfirstlane(tid >> a.width_log2), quad0 = tid & (a.width - 1);
+      const int n_arrays = grp < a.groups ? (int)quotient((unsigned)(a.n_partials - grp + a.groups - 1), a.groups_magic) : 0;
+      // a scalar base per array, lane offsets that never change (past the end: the last four candidates again, not stored)
+      const float* part = in_set_of(a.partial, a.g, li) + (size_t)hk * a.partial_stride + grp * a.cand_stride;
+      const int step = a.groups * a.cand_stride;
       auto sum_arrays = [&](auto passes, auto batch) __attribute__((always_inline)) {
         constexpr int kPasses = decltype(passes)::value, kBatch = decltype(batch)::value;
         float4 acc[kPasses];
+        unsigned lane_off[kPasses];
 #pragma unroll
-        for (int s = 0; s < kPasses; ++s) acc[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int s = 0; s < kPasses; ++s) {
+          acc[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+          lane_off[s] = 4u * (unsigned)min(quad0 + s * a.width, a.quads - 1);
+        }
         for (int first = 0; first < n_arrays; first += kBatch) {
           float4 v[kBatch][kPasses];
 #pragma unroll
-          for (int u = 0; u < kBatch; ++u)
+          for (int u = 0; u < kBatch; ++u) {
 #pragma unroll
-            for (int s = 0; s < kPasses; ++s) {
-              v[u][s] = make_float4(0.f, 0.f, 0.f, 0.f);
-              if (first + u < n_arrays && quad0 + s * a.width < a.quads)
-                v[u][s] = *reinterpret_cast<const float4*>(part + (size_t)((first + u) * a.groups * a.cand_stride + 4 * s * a.width) + lane_off);
+            for (int s = 0; s < kPasses; ++s) v[u][s] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (first + u < n_arrays) {
+#pragma unroll
+              for (int s = 0; s < kPasses; ++s) v[u][s] = *reinterpret_cast<const float4*>(part + lane_off[s]);
+              part += step;
             }
+          }
 #pragma unroll
           for (int u = 0; u < kBatch; ++u)
 #pragma unroll
@@ -366,7 +364,17 @@ compact_kernel(const SelectArgs a) {
 #pragma unroll
     for (int i = 0; i < kMaxItems; ++i) {
       const int p = tid + i * kThreads;
+      if (p >= c) tokv[i] = a.t0 + (p - c);
       if (i < items && p < n_cand) key_words[2 * p] = ~(unsigned)tokv[i];
+    }
+    if (tid < a.n_segs) {
+      SegL sl;
+      sl.begin = my_seg.begin; sl.n = my_seg.n; sl.kind = my_seg.kind; sl.gh = my_seg.gh; sl.gw = my_seg.gw;
+      sl.planes = my_seg.planes; sl.temporal = my_seg.temporal;
+      sl.per = sl.gh * sl.gw;
+      sl.inv_per = sl.per > 0 ? 1.f / (float)sl.per : 0.f;
+      sl.inv_gw = sl.gw > 0 ? 1.f / (float)sl.gw : 0.f;
+      s_segs[tid] = sl;
     }
     __syncthreads();
     if (a.merge) {
@@ -608,7 +616,7 @@ compact_kernel(const SelectArgs a) {
   if (a.merge) {
     const int n_dst = (int)s_n_dst;
     auto row_at = [&](int pos) __attribute__((always_inline)) {
-      return *reinterpret_cast<const uint4*>(pos < c ? cache + (size_t)pos * D : fresh + (size_t)(pos - c) * fresh_stride);
+      return *reinterpret_cast<const uint4*>(row_of_two<unsigned long long>(cache, 2 * D, fresh, 2 * (unsigned)fresh_stride, pos, c));
     };
     auto weight_at = [&](int pos) __attribute__((always_inline)) { return pos < c ? weight[pos] : 1.f; };
     // sources of destination p in ascending position, unused entries last
