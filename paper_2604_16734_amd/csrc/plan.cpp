@@ -117,18 +117,19 @@ size_t select_lds_bytes(const SelectArgs& a) {
   return cand_pad * (8 + 1 + 2 + 2) + kSelectBins * 4 + (size_t)a.table_size * 2 + (lists > sums ? lists : sums);
 }
 
-// A workgroup has 512 threads up to 2048 candidates (four to a thread), 1024 beyond.  Most of its phases are what every wave
-// does for itself (scans, the search of the histogram) on four SIMDs, so that fewer waves are done sooner, until there are
-// too few for the rows.  Per launch with 512 threads, with 1024: 4 heads of d 64, 192 candidates 10.2, 11.4 us; 4 heads of
-// d 128, 768 candidates, scored by the keys 14.0, 14.5 us; with 256 threads 10.8 and 14.1 us, and 8 layers of 768
-// candidates 3 us more than with 512.
+// A workgroup has 512 threads up to 1024 candidates (and where it holds the keys in registers), 1024 beyond.  Most of its phases are
+// what every wave does for itself (scans, the search of the histogram) on four SIMDs, so that fewer waves are done sooner,
+// until there are too few for the rows.  Per launch with 512 threads, with 1024: 4 heads of d 64, 192 candidates 9.8,
+// 11.0 us; 4 heads of d 128, 768 candidates, scored by the keys 13.8, 14.3 us; 16 layers of 4 heads, 1536 candidates
+// 26.4, 23.8 us, the same scored by proxy queries (more rows merge) 60, 55 us.  With 256 threads the first two
+// take half a microsecond more, and 8 layers of 768 candidates 3 us.
 // A thread owns ceil(n_cand / threads) neighbouring candidates.  For the sums of the partial arrays the threads
 // form groups of 64, 128 or 256 (the fewest that cover the candidates in fours, 256 at most) that take
 // every groups-th array, so that all of them have loads in flight whatever the number of candidates.
 // The token table has an entry for every token before the block where LDS has room for that.
 void plan_select(SelectArgs& a) {
   const int n_cand = a.c + a.n;
-  a.threads = n_cand <= 2048 ? 512 : kSelectThreads;
+  a.threads = n_cand <= 1024 || a.keydiff ? 512 : kSelectThreads;
   a.items = (n_cand + a.threads - 1) / a.threads;
   a.quads = (n_cand + 3) / 4;
   a.width = a.items > 4 ? a.threads : a.quads <= 64 ? 64 : a.quads <= 128 ? 128 : 256;

@@ -244,7 +244,7 @@ compact_kernel(const SelectArgs a) {
     }
     if (a.score_override) {
       for (int p = tid; p < n_cand; p += kThreads) l.sums[p] = a.score_override[(size_t)hk * n_cand + p];
-    } else if (kThreads == 512 && a.keydiff) {         // (up to 2048 candidates)
+    } else if (kThreads == 512 && a.keydiff) {
       constexpr int kPieces = D / 8, kRows = kThreads / kPieces;
       const int piece = tid % kPieces, row0 = tid / kPieces;
       const u16* const k_old = a.k_cache + (long long)li * a.g.kv_stride + (size_t)hk * budget * D + 8 * piece;
