@@ -51,6 +51,7 @@
 // plan.cpp has the rule that picks this kernel and what it measured against the tiles of attention.hip.
 #include <type_traits>
 
+#include "key_scores.h"
 #include "kvp_internal.h"
 #include "mfma_tools.h"
 
@@ -98,12 +99,14 @@ __device__ __forceinline__ float sum_over_half(float (&v)[16], int lane) {
   return two + dpp_lane<0xB1>(two);                        // lane ^ 1
 }
 
-// kKept: key blocks of a wave whose softmax weights stay in registers; 0: the scores take a second sweep
+// kKept: key blocks of a wave whose softmax weights stay in registers; 0: the scores take a second sweep;
+// kScoreByKeys: no scores from the queries, and the first workgroups of the launch score by the keys alone
+constexpr int kScoreByKeys = -1;
 template <int D, int QW, int kKept>
 __global__ void __launch_bounds__((Split<D, QW>::kThreads))
 attention_split_kernel(const AttnArgs a) {
   using S = Split<D, QW>;
-  static_assert(kKept == 0 || QW == 1, "one row tile per workgroup");
+  static_assert(kKept <= 0 || QW == 1, "one row tile per workgroup");
   constexpr int KS = S::KS;
   constexpr int kNK = D / 16;                // K fragments (and MFMAs) of a 32-key block
   constexpr int kND = D / 32;                // channel tiles of O
@@ -121,8 +124,22 @@ attention_split_kernel(const AttnArgs a) {
   u16* const out_rows = a.layer[li].out;
   have_arguments(q_rows, out_rows, a.layer[li].k_new, a.layer[li].v_new, a.k_cache, a.v_cache, a.lse2, a.partial, a.g.first_set,
                  a.g.n_sets, a.g.set_stride, a.g.kv_stride, a.n, a.c, a.work_per_xcd, a.total_work, a.tiles_magic, a.group_magic);
+  int block = (int)blockIdx.x;
+  if constexpr (kKept == kScoreByKeys) {
+    // They start with the launch and take about as long as an attention workgroup.
+    static_assert(S::kThreads == kKeyScoreThreads && (S::kWaves + 1) * D * 4 <= S::kMainBytes);
+    block -= a.key_score_wgs;
+    if (block < 0) {
+      const int hk = (int)blockIdx.x;
+      if (hk < a.n_kv_heads)
+        score_head_by_keys<D>(a.k_cache + (size_t)li * a.g.kv_stride + (size_t)hk * a.budget * D, a.layer[li].k_new + (size_t)hk * D,
+                              a.n_kv_heads, a.c, a.c + a.n_keys, reinterpret_cast<float*>(lds_raw),
+                              in_set_of(a.partial, a.g, li) + (size_t)hk * a.partial_stride);
+      return;
+    }
+  }
   // XCD-aware order: consecutive work items (same KV head) land on one die
-  const int w = (blockIdx.x % kXcds) * a.work_per_xcd + blockIdx.x / kXcds;
+  const int w = (block % kXcds) * a.work_per_xcd + block / kXcds;
   if (w >= a.total_work) return;
   float* const lse2 = in_set_of(a.lse2, a.g, li);
   const int group = a.group;
@@ -394,7 +411,7 @@ attention_split_kernel(const AttnArgs a) {
       stat_l[wave * 32 + l32] = l_run;
     }
   }
-  const bool score = a.partial != nullptr;
+  const bool score = kKept != kScoreByKeys && a.partial != nullptr;
   __syncthreads();
   {
     constexpr int kPerRow = S::kThreads / S::kRows;        // threads that put a row together
@@ -563,7 +580,7 @@ attention_split_kernel(const AttnArgs a) {
 template <int D, int QW, int kKept>
 hipError_t launch_shape(const AttnArgs& a, hipStream_t s) {
   using S = Split<D, QW>;
-  hipLaunchKernelGGL((attention_split_kernel<D, QW, kKept>), dim3(kXcds * a.work_per_xcd, a.g.n_layers), dim3(S::kThreads),
+  hipLaunchKernelGGL((attention_split_kernel<D, QW, kKept>), dim3(kXcds * a.work_per_xcd + a.key_score_wgs, a.g.n_layers), dim3(S::kThreads),
                      S::kLdsBytes, s, a);
   return hipGetLastError();
 }
@@ -578,6 +595,7 @@ hipError_t prepare_shape() {
 // with six; d 64: 209 with eight).  A launch without scores keeps none.
 template <int D>
 hipError_t launch_split32(const AttnArgs& a, hipStream_t s) {
+  if (a.key_score_wgs > 0) return launch_shape<D, 1, kScoreByKeys>(a, s);
   const int blocks = (a.c + 31) / 32 + (a.n_keys + 31) / 32;
   const int need = a.partial != nullptr ? (blocks + Split<D, 1>::KS - 1) / Split<D, 1>::KS : 0;
   if (need >= 1 && need <= 2) return launch_shape<D, 1, 2>(a, s);
@@ -591,9 +609,14 @@ hipError_t launch_split32(const AttnArgs& a, hipStream_t s) {
   return launch_shape<D, 1, 0>(a, s);
 }
 template <int D>
+hipError_t launch_split64(const AttnArgs& a, hipStream_t s) {
+  return a.key_score_wgs > 0 ? launch_shape<D, 2, kScoreByKeys>(a, s) : launch_shape<D, 2, 0>(a, s);
+}
+template <int D>
 hipError_t prepare_split32() {
   hipError_t e;
   if ((e = prepare_shape<D, 1, 0>()) != hipSuccess) return e;
+  if ((e = prepare_shape<D, 1, kScoreByKeys>()) != hipSuccess) return e;
   if ((e = prepare_shape<D, 1, 2>()) != hipSuccess) return e;
   if ((e = prepare_shape<D, 1, 3>()) != hipSuccess) return e;
   if ((e = prepare_shape<D, 1, 4>()) != hipSuccess) return e;
@@ -610,12 +633,14 @@ hipError_t prepare_attention_split() {
   if ((e = prepare_split32<128>()) != hipSuccess) return e;
   if ((e = prepare_split32<64>()) != hipSuccess) return e;
   if ((e = prepare_shape<128, 2, 0>()) != hipSuccess) return e;
-  return prepare_shape<64, 2, 0>();
+  if ((e = prepare_shape<128, 2, kScoreByKeys>()) != hipSuccess) return e;
+  if ((e = prepare_shape<64, 2, 0>()) != hipSuccess) return e;
+  return prepare_shape<64, 2, kScoreByKeys>();
 }
 
 hipError_t launch_attention_split(const AttnArgs& a, int head_dim, hipStream_t s) {
-  if (head_dim == 128) return a.variant == kAttnSplit32 ? launch_split32<128>(a, s) : launch_shape<128, 2, 0>(a, s);
-  return a.variant == kAttnSplit32 ? launch_split32<64>(a, s) : launch_shape<64, 2, 0>(a, s);
+  if (head_dim == 128) return a.variant == kAttnSplit32 ? launch_split32<128>(a, s) : launch_split64<128>(a, s);
+  return a.variant == kAttnSplit32 ? launch_split32<64>(a, s) : launch_split64<64>(a, s);
 }
 
 }  // namespace kvp

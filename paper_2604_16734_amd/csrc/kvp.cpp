@@ -547,15 +547,18 @@ static int prefill_layers(kvp_cache* c, int first, int count, int32_t token_begi
   const bool evicts = cached + n_tokens > cfg.budget;
   const int own_partials = (cfg.n_q_heads / cfg.n_kv_heads) * aa.n_row_tiles;
   const bool fused = evicts && mode == kScoreOwn && own_partials <= lay.max_partials && c->fused_scores;
-  if (fused) {
+  // Scored by the keys alone, the launch of a block that does not fill the chip has room for workgroups that do that.
+  const bool by_keys = evicts && mode == kScoreKeydiff && scores_keys_beside_attention(aa.variant, cached + n_tokens, cfg.head_dim);
+  if (by_keys) aa.key_score_wgs = (cfg.n_kv_heads + kXcds - 1) / kXcds * kXcds;
+  if (fused || by_keys) {
     aa.partial = reinterpret_cast<float*>(set + lay.partial_off);
     aa.partial_stride = lay.partial_stride;
     aa.cand_stride = lay.cand_stride;
   }
   int rc = launch(c, KVP_K_ATTENTION, count, s, [&] { return launch_attention(aa, cfg.head_dim, s); });
   if (rc) return rc;
-  int n_partials = fused ? own_partials : 0, unscored = 0;
-  if (evicts && !fused) {
+  int n_partials = fused ? own_partials : by_keys ? 1 : 0, unscored = 0;
+  if (evicts && !fused && !by_keys) {
     if (mode != kScoreOwn) {
       // a short list of proxy queries, or the keys alone: score_deferred_layers, now or later
       unscored = mode == kScoreKeydiff || proxy_by_rowstat(c, cached + n_tokens, n_obs) ? mode : 0;

@@ -99,6 +99,8 @@ struct AttnArgs {
   unsigned tiles_magic, group_magic;   // divisor_magic of n_row_tiles and of group
   float scale_log2;    // softmax scale times log2(e)
   int variant;         // tile shape, chosen by plan_attention
+  int key_score_wgs;   // workgroups in front that score the candidates by the keys alone (split-key shapes): one per KV head, up to a
+                       // multiple of kXcds; their scores are the one partial array
   int partial_stride, cand_stride;   // floats from a KV head's partial arrays to the next head's, and from array to array
   GroupStrides g;
   const u16* k_cache;  // the group's first layer: [Hkv, M, D]
@@ -267,5 +269,6 @@ int colsum_max_partials(int group, int chunk_max);
 size_t select_lds_bytes(const SelectArgs& a);
 void plan_select(SelectArgs& a);
 bool keydiff_in_compaction(int n_cand, int head_dim);
+bool scores_keys_beside_attention(int variant, int n_cand, int head_dim);
 
 }  // namespace kvp

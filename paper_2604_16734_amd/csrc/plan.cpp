@@ -152,6 +152,14 @@ bool keydiff_in_compaction(int n_cand, int head_dim) {
   return n_cand <= kKeydiffRowsPerThread * (512 / (head_dim / 8));
 }
 
+// The attention launch of the split-key shapes has workgroups that score such heads by the keys: 224 workgroups of 256 rows x 28
+// heads leave CUs idle, and in a grouped launch it is one workgroup more in 56.  28/4 heads, d 128, 256 rows over 768 keys:
+// attention 9.3 -> 9.7 us, compaction 13.8 -> 8.0 us per layer.  (128-row workgroups fill the chip: one more would be a
+// second round.)  By one layer's block alone, like the shape.
+bool scores_keys_beside_attention(int variant, int n_cand, int head_dim) {
+  return (variant == kAttnSplit32 || variant == kAttnSplit64) && keydiff_in_compaction(n_cand, head_dim);
+}
+
 // ---- compaction: row pairs (K row and V row of a slot, 16 bytes per lane) a workgroup carries
 int rows_per_compact_block(int head_dim) { return kCompactThreads / (2 * head_dim / 8); }
 

@@ -8,9 +8,8 @@
 // plans had to go through memory.  What bounds it is the chain of its phases: memory round trips,
 // LDS atomics, block scans, barriers.  With 16 layers in a launch the chains of 128 heads run side by
 // side.
-//   * scores by the keys alone, for up to 32 rows per thread (1024 candidates at head dimension 128): the workgroup
-//     reads the head's keys once, keeps them in registers, adds them up to the anchor and takes every key's
-//     cosine with it -- a launch pair of 9 us otherwise (keydiff.hip, which serves larger heads).
+//   * scores by the keys alone where the attention launch has not left them (key_scores.h): up to 1024 candidates at head
+//     dimension 128 -- a launch pair of 9 us otherwise (keydiff.hip, which serves larger heads).
 //   * other scores: the partial column sums of a head are added up by groups of threads, sixteen bytes per
 //     load and sixteen loads in flight, each group every G-th array; the groups' sums meet in LDS, in a fixed order.
 //   * order: 64-bit key = (score as order-preserving u32) << 32 | ~token, so
@@ -38,6 +37,7 @@
 //   * move: kept block rows, or their staging rows, into the free slots.
 #include <type_traits>
 
+#include "key_scores.h"
 #include "kvp_internal.h"
 #include "lane_tools.h"
 
@@ -245,75 +245,8 @@ compact_kernel(const SelectArgs a) {
     if (a.score_override) {
       for (int p = tid; p < n_cand; p += kThreads) l.sums[p] = a.score_override[(size_t)hk * n_cand + p];
     } else if (kThreads == 512 && a.keydiff) {
-      constexpr int kPieces = D / 8, kRows = kThreads / kPieces;
-      const int piece = tid % kPieces, row0 = tid / kPieces;
-      const u16* const k_old = a.k_cache + (long long)li * a.g.kv_stride + (size_t)hk * budget * D + 8 * piece;
-      const u16* const k_add = a.layer[li].k_new + (size_t)hk * D + 8 * piece;
-      float* const s_part = l.sums + 4 * a.quads;      // [kWaves][D], then the anchor
-      float* const s_mu = s_part + kWaves * D;
-      auto score_keys = [&](auto rows) __attribute__((always_inline)) {
-        constexpr int kN = decltype(rows)::value;
-        u32x4 w[kN];
-#pragma unroll
-        for (int i = 0; i < kN; ++i) {
-          const int p = min(row0 + i * kRows, n_cand - 1);
-          w[i] = *reinterpret_cast<const u32x4*>(row_of_two<unsigned long long>(k_old, 2 * D, k_add, 2 * D * (unsigned)a.n_kv_heads, p, c));
-        }
-        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int i = 0; i < kN; ++i) {
-          if (row0 + i * kRows >= n_cand) w[i] = u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            acc[2 * k] += bf16_lo(w[i][k]);
-            acc[2 * k + 1] += bf16_hi(w[i][k]);
-          }
-          asm volatile("" : "+v"(w[i]));               // or the unpacked channels stay in registers until the second pass
-        }
-        sum_rows<kPieces, 8>(acc);                     // lanes 16 r ..: channels 2 r, 2 r + 1 of the piece
-        if (lane % 16 < kPieces)
-          *reinterpret_cast<float2*>(&s_part[wave * D + 8 * piece + 2 * (lane / 16)]) = make_float2(acc[0], acc[1]);
-        __syncthreads();
-        if (tid < D) {
-          float t = 0.f;
-#pragma unroll
-          for (int w2 = 0; w2 < kWaves; ++w2) t += s_part[w2 * D + tid];
-          s_mu[tid] = t / (float)n_cand;
-        }
-        __syncthreads();
-        float mu[8], mu2 = 0.f;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { mu[e] = s_mu[8 * piece + e]; mu2 = __builtin_fmaf(mu[e], mu[e], mu2); }
-        mu2 = row_sum<kPieces>(mu2);
-        // every lane of a row has its sums; lane i % kPieces keeps those of the i-th row and takes its cosine
-        float my_dot[(kN + kPieces - 1) / kPieces], my_k2[(kN + kPieces - 1) / kPieces];
-#pragma unroll
-        for (int i = 0; i < kN; ++i) {
-          float dot = 0.f, k2 = 0.f;
-#pragma unroll
-          for (int k = 0; k < 4; ++k) {
-            const float x = bf16_lo(w[i][k]), y = bf16_hi(w[i][k]);
-            dot = __builtin_fmaf(x, mu[2 * k], dot); dot = __builtin_fmaf(y, mu[2 * k + 1], dot);
-            k2 = __builtin_fmaf(x, x, k2); k2 = __builtin_fmaf(y, y, k2);
-          }
-          dot = row_sum<kPieces>(dot);
-          k2 = row_sum<kPieces>(k2);
-          my_dot[i / kPieces] = i % kPieces == 0 || piece == i % kPieces ? dot : my_dot[i / kPieces];
-          my_k2[i / kPieces] = i % kPieces == 0 || piece == i % kPieces ? k2 : my_k2[i / kPieces];
-          __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int u = 0; u < (kN + kPieces - 1) / kPieces; ++u) {
-          const int i = u * kPieces + piece, p = row0 + i * kRows;
-          if (i < kN && p < n_cand) l.sums[p] = -my_dot[u] / (sqrtf(my_k2[u]) * sqrtf(mu2));
-        }
-      };
-      const int passes = (n_cand + kRows - 1) / kRows;
-      constexpr int kRowsEach = kKeydiffRowsPerThread;
-      if (passes <= kRowsEach / 4) score_keys(std::integral_constant<int, kRowsEach / 4>{});
-      else if (passes <= kRowsEach / 2) score_keys(std::integral_constant<int, kRowsEach / 2>{});
-      else if (passes <= 3 * kRowsEach / 4) score_keys(std::integral_constant<int, 3 * kRowsEach / 4>{});
-      else score_keys(std::integral_constant<int, kRowsEach>{});
+      score_head_by_keys<D>(a.k_cache + (long long)li * a.g.kv_stride + (size_t)hk * budget * D, a.layer[li].k_new + (size_t)hk * D,
+                            a.n_kv_heads, c, n_cand, l.sums + 4 * a.quads, l.sums);
     } else {
       // (a group is whole waves: what a wave loads is decided by scalar branches)
       const int grp = __builtin_amdgcn_readfirstlane(tid >> a.width_log2), quad0 = tid & (a.width - 1);

@@ -528,6 +528,23 @@ def test_keydiff_scored_by_the_compaction_edges(hq, hkv, d, c, n):
     cache.close()
 
 
+@pytest.mark.parametrize("hq,hkv,d,c,n", [
+    # nothing cached, one key of the block evicted; ten KV heads; the most candidates; two row tiles per workgroup
+    (4, 2, 128, 0, 2), (4, 2, 64, 1, 1), (20, 10, 64, 300, 33), (4, 2, 128, 900, 124), (4, 2, 64, 1900, 148), (28, 4, 128, 512, 512)])
+def test_keys_scored_beside_the_attention(hq, hkv, d, c, n):
+    """Scores by the keys alone from the attention launch of the split-key shapes, and from the compaction launch behind the
+    128-row shape: the same bits."""
+    scores = []
+    for shape in (-1, 2):
+        cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, max(c, n - 1, 1), 600, seed=c + 3 * n, keydiff=True,
+                                                        attention_shape=shape)
+        assert err <= U.OUT_TOL, err
+        scores.append(cache.debug_last(0)[0].cpu().numpy().copy())
+        assert np.abs(scores[-1].astype(np.float64) - scores_ref).max() <= 2e-5
+        cache.close()
+    assert np.array_equal(scores[0].view(np.uint32), scores[1].view(np.uint32))
+
+
 @pytest.mark.parametrize("d,c,n,budget,t0,levels", [
     (64, 700, 324, 700, 700, 5),          # 1024 candidates, one per thread; hundreds of equal scores at the threshold
     (128, 700, 325, 650, 30000, 40),      # one more; a token table with an entry per token of a long prefix
