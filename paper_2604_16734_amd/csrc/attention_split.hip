@@ -44,9 +44,11 @@
 // 768 keys: 9.6 -> 8.4 us per layer of a grouped launch; 32/32 heads, 128 rows over 384 keys: 8.4 -> 7.8 us.  The
 // scores' error against 64 bits is the same (2e-7 in the root mean square).
 //
-// Second sweep (two row tiles, whose waves have too many blocks for that; longer lists): as in attention.hip, S = Q K^T again
+// Second sweep (longer lists; two row tiles, whose waves have more blocks): as in attention.hip, S = Q K^T again
 // with the final normalisers, one key per lane, one partial array of column sums per workgroup.  Query fragments
-// are, register for register, the A operand of this product.
+// are, register for register, the A operand of this product.  With two row tiles the weights of the first four rounds stay in
+// registers all the same, the sums of the two tiles meet in LDS, and the second sweep begins behind them (28/4 heads, d 128,
+// 512 rows over 1536 keys: 27.0 -> 26.4 us; six rounds, with the queries read from LDS every time, 26.6 us).
 //
 // plan.cpp has the rule that picks this kernel and what it measured against the tiles of attention.hip.
 #include <type_traits>
@@ -59,6 +61,9 @@ namespace kvp {
 namespace {
 
 constexpr float kRescueLog2 = 30.f;
+
+// Two row tiles per workgroup: rounds whose weights stay in registers.
+template <int QW> constexpr int kKeptRounds = QW == 2 ? 4 : 0;
 
 template <int D, int QW>
 struct Split {
@@ -74,15 +79,22 @@ struct Split {
   static constexpr int kMainBytes = kStripBytes > kPartBytes ? kStripBytes : kPartBytes;
   static constexpr int kStatBytes = 2 * kWaves * 32 * 4;           // maximum and sum per wave and row
   static constexpr int kQBytes = kRows * D * 2;       // the workgroup's query rows
-  static constexpr int kLdsBytes = kMainBytes + kStatBytes + kQBytes + kRows * 4;
+  static constexpr int kKeptBytes = kWaves * kKeptRounds<QW> * 32 * 4;     // sums of a wave's rows over its kept blocks
+  static constexpr int kLdsBytes = kMainBytes + kStatBytes + kQBytes + kRows * 4 + kKeptBytes;
   static_assert(kLdsBytes <= 160 * 1024, "LDS of a CU");
 };
 
-// Sums over the 32 lanes of each half of the wave; lane l ends up with that of v[8 b4 + 4 b3 + 2 b2 + b1], b0 .. b4 the
-// bits of l: at every step a lane hands the half of its values that its partner keeps to that partner.
-__device__ __forceinline__ float sum_over_half(float (&v)[16], int lane) {
+// Sums of v times the lane's factor over the 32 lanes of each half of the wave; lane l ends up with that of
+// v[8 b4 + 4 b3 + 2 b2 + b1], b0 .. b4 the bits of l: at every step a lane hands the half of its values that its
+// partner keeps to that partner.
+__device__ __forceinline__ float sum_over_half(float (&v)[16], float factor, int lane) {
+  float even = factor, odd = factor;                       // of the rows of sixteen lanes that the swapped values come from
+  swap_lanes<16>(even, odd);
 #pragma unroll
-  for (int i = 0; i < 8; ++i) { swap_lanes<16>(v[i], v[i + 8]); v[i] += v[i + 8]; }
+  for (int i = 0; i < 8; ++i) {
+    swap_lanes<16>(v[i], v[i + 8]);
+    v[i] = __builtin_fmaf(v[i], even, v[i + 8] * odd);
+  }
   const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
@@ -106,7 +118,6 @@ template <int D, int QW, int kKept>
 __global__ void __launch_bounds__((Split<D, QW>::kThreads))
 attention_split_kernel(const AttnArgs a) {
   using S = Split<D, QW>;
-  static_assert(kKept <= 0 || QW == 1, "one row tile per workgroup");
   constexpr int KS = S::KS;
   constexpr int kNK = D / 16;                // K fragments (and MFMAs) of a 32-key block
   constexpr int kND = D / 32;                // channel tiles of O
@@ -118,6 +129,7 @@ attention_split_kernel(const AttnArgs a) {
   float* const stat_l = stat_m + S::kWaves * 32;
   u16* const q_lds = reinterpret_cast<u16*>(stat_l + S::kWaves * 32);            // [kRows][D], chunks swizzled like K's
   float* const lse_lds = reinterpret_cast<float*>(q_lds + S::kRows * D);         // [kRows]
+  float* const kept_lds = lse_lds + S::kRows;                                    // [kWaves][kKeptRounds][32]
 
   const int li = blockIdx.y;
   const u16* const q_rows = a.layer[li].q;
@@ -359,14 +371,21 @@ attention_split_kernel(const AttnArgs a) {
   float kept[kKept > 0 ? kKept : 1][16], kept_m[kKept > 0 ? kKept : 1];      // weights against the references kept_m
   if constexpr (kShared) {
     const int n_rounds = (n_kb + KS - 1) / KS;
-    for (int i = 0; i < n_rounds; ++i) {
+    auto round = [&](int i, float (&p)[16]) __attribute__((always_inline)) {
       wait_older_than(None{});               // this wave's share of round i has landed
       __builtin_amdgcn_s_barrier();          // everybody's has, and everybody is done with round i - 1
       asm volatile("" ::: "memory");
       load_round(i + 1);
-      float p[16];
       if (i < my_blk) attend(i, round_strip(i, false), round_strip(i, true), p, [] {}, [] {});
-    }
+    };
+#pragma unroll
+    for (int i = 0; i < kKept; ++i)
+      if (i < n_rounds) {
+        round(i, kept[i]);
+        kept_m[i] = m_ref;
+      }
+    float p[16];
+    for (int i = kKept > 0 ? kKept : 0; i < n_rounds; ++i) round(i, p);
   } else {
     auto step = [&](int i, float (&p)[16]) __attribute__((always_inline)) {
       const bool more = i + 1 < my_blk;
@@ -465,29 +484,29 @@ attention_split_kernel(const AttnArgs a) {
   // keys that none of this workgroup's rows see: zeros (the selection adds every partial array)
   for (int k = 32 * (n_kb - c_blk) + tid; k < a.n_keys; k += S::kThreads) part[c + k] = 0.f;
 
-  if constexpr (kKept > 0) {
-    // ---- column sums (Eq. 4) of the workgroup's rows, from the weights in registers: a lane's factor brings those of its row
-    // onto the final normaliser, and the sums run over the lanes
+  // ---- column sums (Eq. 4) of the workgroup's rows, from the weights in registers: a lane's factor brings those of its row
+  // onto the final normaliser, and the sums run over the lanes
+  const int kept_r = 8 * ((lane >> 4) & 1) + 4 * ((lane >> 3) & 1) + 2 * ((lane >> 2) & 1) + ((lane >> 1) & 1);
+  const int my_key = 8 * (kept_r >> 2) + 4 * g + (kept_r & 3);               // this lane's, and its neighbour's
+  auto kept_sum = [&](int i, float lse_row) __attribute__((always_inline)) {
+    if (q0 + 32 > n && q0 + l32 >= n) {      // a row past the end of the block
+#pragma unroll
+      for (int e = 0; e < 16; ++e) kept[i][e] = 0.f;
+      kept_m[i] = -INFINITY;
+    }
+    return sum_over_half(kept[i], __builtin_amdgcn_exp2f(__builtin_fmaf(kept_m[i], sl2, -lse_row)), lane);    // (0 where the wave saw nothing)
+  };
+  if constexpr (kKept > 0 && QW == 1) {
     float m = -INFINITY, l = 0.f;
 #pragma unroll
     for (int s = 0; s < KS; ++s) m = fmaxf(m, stat_m[s * 32 + l32]);
 #pragma unroll
     for (int s = 0; s < KS; ++s) l += stat_l[s * 32 + l32] * __builtin_amdgcn_exp2f((stat_m[s * 32 + l32] - m) * sl2);
     const float lse_row = m * sl2 + __builtin_log2f(l);
-    const int r = 8 * ((lane >> 4) & 1) + 4 * ((lane >> 3) & 1) + 2 * ((lane >> 2) & 1) + ((lane >> 1) & 1);
-    const int my_key = 8 * (r >> 2) + 4 * g + (r & 3);
 #pragma unroll
     for (int i = 0; i < kKept; ++i) {
       if (i >= my_blk) continue;
-      if (q0 + 32 > n && q0 + l32 >= n) {    // a row past the end of the block
-#pragma unroll
-        for (int e = 0; e < 16; ++e) kept[i][e] = 0.f;
-        kept_m[i] = -INFINITY;
-      }
-      const float f = __builtin_amdgcn_exp2f(__builtin_fmaf(kept_m[i], sl2, -lse_row));     // 0 where the wave saw nothing
-#pragma unroll
-      for (int e = 0; e < 16; ++e) kept[i][e] *= f;
-      const float tot = sum_over_half(kept[i], lane);
+      const float tot = kept_sum(i, lse_row);
       const Block b = mine(i);
       if ((lane & 1) == 0 && my_key < b.rows) part[(b.cached ? 0 : c) + b.first + my_key] = tot;
     }
@@ -497,7 +516,22 @@ attention_split_kernel(const AttnArgs a) {
   // ---- second sweep: column sums (Eq. 4) of the workgroup's rows; wave w takes key blocks w, w + 8, ...,
   // its two strips in turn
   __syncthreads();                           // the rows' statistics are in LDS, the partial outputs have been read
-  if (wave < n_kb) load_block(kc, kn, block_of(wave), k_strip, false);
+  constexpr int kFirst = kKept > 0 ? kKept * KS : 0;       // (two row tiles: those before it are in registers)
+  if (kFirst + wave < n_kb) load_block(kc, kn, block_of(kFirst + wave), k_strip, false);
+  if constexpr (kKept > 0) {
+    const float lse_row = lse_lds[32 * qw + l32];
+#pragma unroll
+    for (int i = 0; i < kKept; ++i) {
+      const float tot = i < my_blk ? kept_sum(i, lse_row) : 0.f;
+      if ((lane & 1) == 0) kept_lds[(wave * kKept + i) * 32 + my_key] = tot;
+    }
+    __syncthreads();
+    for (int t = tid; t < kFirst * 32; t += S::kThreads) {
+      const int b = t / 32, at = ((b % KS) * kKept + b / KS) * 32 + t % 32;
+      const Block kb = block_of(b);
+      if (b < n_kb && t % 32 < kb.rows) part[(kb.cached ? 0 : c) + kb.first + t % 32] = kept_lds[at] + kept_lds[KS * kKept * 32 + at];
+    }
+  }
   bf16x8 qs[QW][kNK];
 #pragma unroll
   for (int t = 0; t < QW; ++t)
@@ -515,11 +549,15 @@ attention_split_kernel(const AttnArgs a) {
   // The wave's blocks from b up to `end`, by row tiles T0 .. QW - 1 (those before T0 see none of them); returns its first
   // block after those.  (No software pipeline: with the exponentials of one block among the matrix instructions of the
   // next it was a few per cent slower; the two waves of a SIMD fill each other's gaps.)
-  u16* strip = k_strip;
-  u16* other = v_strip;
-  auto sweep = [&](int b, int end, auto tiles_from) __attribute__((always_inline)) -> int {
+  int turn = 0;                              // which strip holds the block
+  auto sweep = [&](int from, int end, auto tiles_from) __attribute__((always_inline)) -> int {
     constexpr int T0 = decltype(tiles_from)::value;
-    for (; b < end; b += S::kWaves) {
+    int at = from;
+    for (; at < end; at += S::kWaves, ++turn) {
+      // (wave-uniform, which the compiler does not see through two loops in a row)
+      const int b = __builtin_amdgcn_readfirstlane(at), odd = __builtin_amdgcn_readfirstlane(turn) & 1;
+      u16* const strip = k_strip + odd * S::kWaves * S::kStrip;          // k_strip or v_strip
+      u16* const other = k_strip + (1 - odd) * S::kWaves * S::kStrip;
       if (b + S::kWaves < n_kb) {
         load_block(kc, kn, block_of(b + S::kWaves), other, false);
         wait_older_than(OneBlock{});
@@ -561,18 +599,15 @@ attention_split_kernel(const AttnArgs a) {
       const float tot = sum_with_other_half(sum[0] + sum[1]);  // lanes l and l + 32 hold the two halves of the rows
       if (g == 0 && l32 < kb.rows) part[(kb.cached ? 0 : c) + kb.first + l32] = tot;
       __builtin_amdgcn_s_setprio(0);
-      u16* const swap = strip;
-      strip = other;
-      other = swap;
     }
-    return b;
+    return at;
   };
   if constexpr (QW == 1) {
-    sweep(wave, n_kb, std::integral_constant<int, 0>{});
+    sweep(kFirst + wave, n_kb, std::integral_constant<int, 0>{});
   } else {
     // blocks that rows of both tiles see, then those that only the late tile's do
     const int n_both = c_blk + (min(a.n_keys, min(n, tile_row(0) + 32) + shift) + 31) / 32;
-    const int b = sweep(wave, min(n_both, n_kb), std::integral_constant<int, 0>{});
+    const int b = sweep(kFirst + wave, min(n_both, n_kb), std::integral_constant<int, 0>{});
     sweep(b, n_kb, std::integral_constant<int, 1>{});
   }
 }
@@ -610,7 +645,8 @@ hipError_t launch_split32(const AttnArgs& a, hipStream_t s) {
 }
 template <int D>
 hipError_t launch_split64(const AttnArgs& a, hipStream_t s) {
-  return a.key_score_wgs > 0 ? launch_shape<D, 2, kScoreByKeys>(a, s) : launch_shape<D, 2, 0>(a, s);
+  if (a.key_score_wgs > 0) return launch_shape<D, 2, kScoreByKeys>(a, s);
+  return a.partial != nullptr ? launch_shape<D, 2, kKeptRounds<2>>(a, s) : launch_shape<D, 2, 0>(a, s);
 }
 template <int D>
 hipError_t prepare_split32() {
@@ -633,6 +669,8 @@ hipError_t prepare_attention_split() {
   if ((e = prepare_split32<128>()) != hipSuccess) return e;
   if ((e = prepare_split32<64>()) != hipSuccess) return e;
   if ((e = prepare_shape<128, 2, 0>()) != hipSuccess) return e;
+  if ((e = prepare_shape<128, 2, kKeptRounds<2>>()) != hipSuccess) return e;
+  if ((e = prepare_shape<64, 2, kKeptRounds<2>>()) != hipSuccess) return e;
   if ((e = prepare_shape<128, 2, kScoreByKeys>()) != hipSuccess) return e;
   if ((e = prepare_shape<64, 2, 0>()) != hipSuccess) return e;
   return prepare_shape<64, 2, kScoreByKeys>();

@@ -164,6 +164,19 @@ def test_scores_from_kept_weights(hq, hkv, d, c, n, scale):
     cache.close()
 
 
+@pytest.mark.parametrize("scale", [0.0, 2.0])
+@pytest.mark.parametrize("hq,hkv,d,c,n", [
+    # 64-row workgroups, whose first 16 key blocks stay in registers: 11, 15, 16, 17 and 27 blocks for the latest rows
+    (28, 4, 128, 0, 330), (28, 4, 128, 100, 330), (28, 4, 128, 160, 330), (28, 4, 128, 161, 330), (16, 4, 64, 333, 512)])
+def test_scores_of_two_row_tiles(hq, hkv, d, c, n, scale):
+    """Scores of the split-key kernel with two row tiles: out of kept weights of both tiles, and a second sweep for the rest."""
+    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, max(c, 1), 512, seed=19 * c + n, scale=scale)
+    assert err <= U.OUT_TOL, err
+    scores_gpu, keep, dst = cache.debug_last(0)
+    U.check_scores(scores_gpu.cpu().numpy(), scores_ref, n * (hq // hkv))
+    cache.close()
+
+
 @pytest.mark.parametrize("fused", [1, 0])
 @pytest.mark.parametrize("hq,hkv,d,c,n,budget,chunk_max,scale", [
     (4, 4, 64, 128, 64, 128, 64, 0.0),
