@@ -65,13 +65,12 @@ __device__ __forceinline__ u16 round_bf16(float r) {
   return (u16)(u >> 16);
 }
 
-__device__ __forceinline__ float dot8(const uint4 k, const float (&q)[8]) {
-  float kx[8];
-  unpack8(k, kx);
-  float s = 0.f;
-#pragma unroll
-  for (int e = 0; e < 8; ++e) s = __builtin_fmaf(kx[e], q[e], s);
-  return s;
+// (pairs of bf16 products into an fp32 sum: both are bf16 in memory, the products exact, and the sum of a pair is rounded once)
+__device__ __forceinline__ float dot8(const uint4 k, const uint4 q) {
+  float s = dot2(k.x, q.x, 0.f);
+  s = dot2(k.y, q.y, s);
+  s = dot2(k.z, q.z, s);
+  return dot2(k.w, q.w, s);
 }
 
 // ---- one workgroup per query head, all keys, no partial results; kLoads rows per thread
@@ -96,12 +95,10 @@ decode_head_kernel(const DecodeArgs a) {
 #pragma unroll
   for (int i = 0; i < kLoads; ++i) vw[i] = v_rows.load(min(kRows * i + sub, n_keys - 1));
   __builtin_amdgcn_sched_barrier(0);             // all loads on their way before the first is waited for
-  float qx[8];
-  unpack8(qw, qx);
   float s[kLoads], mx = -INFINITY;
 #pragma unroll
   for (int i = 0; i < kLoads; ++i) {
-    s[i] = row_sum<kPieces>(dot8(kw[i], qx));
+    s[i] = row_sum<kPieces>(dot8(kw[i], qw));
     s[i] = kRows * i + sub < n_keys ? s[i] : -INFINITY;
     mx = fmaxf(mx, s[i]);
   }
@@ -184,12 +181,10 @@ decode_kernel(const DecodeArgs a) {
 #pragma unroll
     for (int g = 0; g < GM; ++g) {
       if (g >= G) continue;
-      float qx[8];
-      unpack8(qw[g], qx);
       float mx = m[g];
 #pragma unroll
       for (int i = 0; i < kLoads; ++i) {
-        p[g][i] = row_sum<kPieces>(dot8(kw[i], qx));
+        p[g][i] = row_sum<kPieces>(dot8(kw[i], qw[g]));
         p[g][i] = tile * kTile + kRowsPerLoad * i + sub < n_keys ? p[g][i] : -INFINITY;
         mx = fmaxf(mx, p[g][i]);
       }
