@@ -1,5 +1,5 @@
 // The search for the budget-th largest selection key: the range of keys that still holds it, cut into
-// at most kSelectBins bins of equal width.  The selection counts its keys by bin, enters the bin with the
+// at most 2^kBits bins of equal width.  The selection counts its keys by bin, enters the bin with the
 // wanted key and, if that holds too many, divides it in turn.  No device code: the host tests run it, too.
 #pragma once
 
@@ -12,19 +12,24 @@
 
 namespace kvp {
 
-constexpr int kSelectBinBits = 11;
+#ifndef KVP_SELECT_BIN_BITS                          // (the host tests run the search with fewer bins, too)
+#define KVP_SELECT_BIN_BITS 11
+#endif
+constexpr int kSelectBinBits = KVP_SELECT_BIN_BITS;
 constexpr int kSelectBins = 1 << kSelectBinBits;   // histogram bins of the selection
+constexpr int kSelectFewBinBits = 9;               // ... of 1024 candidates at most
 
-struct KeyRange {
+template <int kBits>
+struct KeyRangeOf {
   unsigned long long lo;     // the first key of the range
   int shift;                 // a bin spans 1 << shift keys
   unsigned bins;             // the range ends with this many bins: keys beyond are larger ones, counted before
 
   // every key whose high word lies in [hi_min, hi_max]
-  static KVP_HOST_DEVICE KeyRange over(unsigned hi_min, unsigned hi_max) {
+  static KVP_HOST_DEVICE KeyRangeOf over(unsigned hi_min, unsigned hi_max) {
     const unsigned long long lo = (unsigned long long)hi_min << 32;
     const unsigned long long span = (((unsigned long long)hi_max << 32) | 0xFFFFFFFFull) - lo;
-    return KeyRange{lo, 64 - (int)__builtin_clzll(span) - kSelectBinBits, (unsigned)kSelectBins};   // 32 bits of span or more
+    return KeyRangeOf{lo, 64 - (int)__builtin_clzll(span) - kBits, 1u << kBits};   // 32 bits of span or more
   }
   KVP_HOST_DEVICE bool holds(unsigned long long key, unsigned& bin) const {
     const unsigned long long b = (key - lo) >> shift;
@@ -36,12 +41,13 @@ struct KeyRange {
     lo += (unsigned long long)bin << shift;
     bins = 1u;
   }
-  // A range of one bin, cut anew.  A bin of fewer than kSelectBins keys has one bin for each of them and
+  // A range of one bin, cut anew.  A bin of fewer keys than the histogram has bins has one bin for each of them and
   // no more: as many bins as the histogram has would reach into the range above.
   KVP_HOST_DEVICE void divide() {
-    bins = 1u << (shift < kSelectBinBits ? shift : kSelectBinBits);
-    shift = shift < kSelectBinBits ? 0 : shift - kSelectBinBits;
+    bins = 1u << (shift < kBits ? shift : kBits);
+    shift = shift < kBits ? 0 : shift - kBits;
   }
 };
+using KeyRange = KeyRangeOf<kSelectBinBits>;
 
 }  // namespace kvp

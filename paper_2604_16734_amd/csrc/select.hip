@@ -16,7 +16,7 @@
 //     "higher score first, equal scores by lower token index" is "larger key
 //     first" and all keys are distinct: the kept set is unique.  (Token indices that a caller wrote, kvp_set_state, may
 //     repeat; the kernel then still ends and stays inside its memory.)
-//   * the M-th largest key: one histogram of 2048 bins over the range the keys really span (a scale on
+//   * the M-th largest key: one histogram of 2048 bins (512 of up to 1024 candidates) over the range the keys really span (a scale on
 //     float bits, so roughly logarithmic in the score), the bin that holds it, and then a ranking of
 //     the few keys in that bin by every wave for itself.  Should more than 64 keys share the bin
 //     (equal scores) the range shrinks to the bin and the histogram is taken again (key_range.h).
@@ -48,13 +48,19 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int kMaxItemsAny = KVP_MAX_CANDIDATES / kSelectThreads;   // 8
-constexpr int kBins = kSelectBins;
 constexpr unsigned kNone16 = 0xFFFFu;
 
 __device__ __forceinline__ unsigned order_bits(float x) {
   if (x == 0.f) x = 0.f;   // -0 and +0 rank equal
   const unsigned u = __float_as_uint(x);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+}
+
+// x / w from the rounded reciprocal of w: the quotient's remainder, which is exact, corrects its last bit (Markstein); the
+// fix-up puts infinities, zeros and NaN right.
+__device__ __forceinline__ float divided(float x, float w, float inv) {
+  const float q = x * inv;
+  return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-q, w, x), inv, q), w, x);
 }
 
 __device__ __forceinline__ unsigned hash_tok(int tok, unsigned mask) {
@@ -84,11 +90,14 @@ struct Min { __device__ __forceinline__ unsigned operator()(unsigned a, unsigned
 struct Max { __device__ __forceinline__ unsigned operator()(unsigned a, unsigned b) const { return a > b ? a : b; } };
 __device__ __forceinline__ unsigned last_lane(unsigned x) { return (unsigned)__builtin_amdgcn_readlane((int)x, 63); }
 
-// word of histogram bin b: bins 32 L .. 32 L + 31 are lane L's, and the lanes of a wave read four of theirs at a
+// word of histogram bin b: kPer neighbouring bins are a lane's, and the lanes of a wave read four of theirs at a
 // time from consecutive 16-byte pieces (in bin order the pieces would lie 128 bytes apart, in two of the
 // sixteen bank groups: 2 us of the selection)
-__device__ __forceinline__ unsigned bin_word(unsigned b) { return ((b & 28u) << 6) | ((b >> 5) << 2) | (b & 3u); }
-static_assert(kBins == 32 * 64, "bin_word is a permutation of the bins");
+template <unsigned kPer>
+__device__ __forceinline__ unsigned bin_word(unsigned b) {
+  static_assert(kPer >= 4 && (kPer & (kPer - 1)) == 0, "a permutation of the 64 kPer bins");
+  return ((b % kPer >> 2) << 8) | (b / kPer << 2) | (b & 3u);
+}
 
 struct Lds {
   unsigned long long* key;    // [cand_pad] low word ~token, high word order-preserving score bits; at the end the
@@ -186,6 +195,9 @@ __global__ void __launch_bounds__(kThreads)
 compact_kernel(const SelectArgs a) {
   constexpr int kWaves = kThreads / 64;
   constexpr bool kListsInLds = kMaxItems <= 4;
+  // (every wave searches the histogram for itself, and a few candidates need no fine one)
+  constexpr int kBinBits = kThreads == 512 ? kSelectFewBinBits : kSelectBinBits, kBins = 1 << kBinBits;
+  constexpr unsigned kPer = kBins / 64;
   extern __shared__ __align__(16) unsigned char lds_raw[];
   __shared__ unsigned long long s_members[64];
   __shared__ unsigned s_n_members, s_n_dst, s_n_src;
@@ -354,14 +366,14 @@ compact_kernel(const SelectArgs a) {
   // ---- the budget-th largest key
   unsigned long long threshold;
   {
-    KeyRange range = KeyRange::over(ob_min, ob_max);
+    KeyRangeOf<kBinBits> range = KeyRangeOf<kBinBits>::over(ob_min, ob_max);
     unsigned want = (unsigned)budget, in_bin = 0;
     for (;;) {
 #pragma unroll
       for (int i = 0; i < kMaxItems; ++i)
-        if (unsigned bin; valid[i] && range.holds(key[i], bin)) atomicAdd(&l.hist[bin_word(bin)], 1u);
+        if (unsigned bin; valid[i] && range.holds(key[i], bin)) atomicAdd(&l.hist[bin_word<kPer>(bin)], 1u);
       __syncthreads();
-      // every wave finds the bin for itself: lane L adds up bins 32 L .. 32 L + 31, a scan over the lanes finds
+      // every wave finds the bin for itself: lane L adds up bins kPer L .. kPer L + kPer - 1, a scan over the lanes finds
       // the lane with the wanted key, and a second one, of that lane's bins, the bin
       unsigned mine = 0;
 #pragma unroll
@@ -373,11 +385,11 @@ compact_kernel(const SelectArgs a) {
       const unsigned above = last_lane(upto) - upto;                 // keys in the bins of higher lanes
       const int owner = __builtin_ctzll(__ballot(above < want && want <= above + mine));
       want -= (unsigned)__builtin_amdgcn_readlane((int)above, owner);
-      const unsigned one = lane < 32 ? l.hist[bin_word(32u * (unsigned)owner + (unsigned)lane)] : 0u;
+      const unsigned one = lane < (int)kPer ? l.hist[bin_word<kPer>(kPer * (unsigned)owner + (unsigned)lane)] : 0u;
       const unsigned upto1 = wave_scan(one, 0u, Add{});
       const unsigned above1 = last_lane(upto1) - upto1;
       const int from = __builtin_ctzll(__ballot(above1 < want && want <= above1 + one));
-      const unsigned digit = 32u * (unsigned)owner + (unsigned)from;
+      const unsigned digit = kPer * (unsigned)owner + (unsigned)from;
       want -= (unsigned)__builtin_amdgcn_readlane((int)above1, from);
       in_bin = (unsigned)__builtin_amdgcn_readlane((int)one, from);
       range.enter(digit);
@@ -632,11 +644,14 @@ compact_kernel(const SelectArgs a) {
           for (int k = kEarly; k < kNeighbours; ++k)
             if (k < n_src[u]) add(late[k - kEarly], late_w[k - kEarly]);
         }
+        const float inv = 1.f / sum_w;                 // (eight divisions by the same weight: one, and a correction each)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] = divided(acc[e], sum_w, inv);
         uint4 res;
-        res.x = pack_bf16(acc[0] / sum_w, acc[1] / sum_w);
-        res.y = pack_bf16(acc[2] / sum_w, acc[3] / sum_w);
-        res.z = pack_bf16(acc[4] / sum_w, acc[5] / sum_w);
-        res.w = pack_bf16(acc[6] / sum_w, acc[7] / sum_w);
+        res.x = pack_bf16(acc[0], acc[1]);
+        res.y = pack_bf16(acc[2], acc[3]);
+        res.z = pack_bf16(acc[4], acc[5]);
+        res.w = pack_bf16(acc[6], acc[7]);
         if (p < c) {
           *reinterpret_cast<uint4*>(cache + (size_t)p * D) = res;
           if (sub == 0) weight[p] = sum_w;
@@ -700,9 +715,14 @@ template <int D>
 hipError_t launch_head_dim(const SelectArgs& a, int n_kv_heads, hipStream_t s) {
   const size_t lds = select_lds_bytes(a);
   const dim3 grid(n_kv_heads, a.g.n_layers);
+  // (built for one and two candidates per thread: what a loop over four of them skips is a fifth of the instructions there;
+  // with the 512 bins and one reciprocal per merged row 4 heads of d 64, 192 candidates 9.8 -> 9.2 us, 4 heads of d 128, 768
+  // candidates 8.0 -> 7.6 us)
   if (a.items > 4) hipLaunchKernelGGL((compact_kernel<D, kMaxItemsAny, 1024>), grid, dim3(1024), lds, s, a);
   else if (a.threads == 1024) hipLaunchKernelGGL((compact_kernel<D, 4, 1024>), grid, dim3(1024), lds, s, a);
-  else hipLaunchKernelGGL((compact_kernel<D, 4, 512>), grid, dim3(512), lds, s, a);
+  else if (a.items > 2) hipLaunchKernelGGL((compact_kernel<D, 4, 512>), grid, dim3(512), lds, s, a);
+  else if (a.items == 2) hipLaunchKernelGGL((compact_kernel<D, 2, 512>), grid, dim3(512), lds, s, a);
+  else hipLaunchKernelGGL((compact_kernel<D, 1, 512>), grid, dim3(512), lds, s, a);
   return hipGetLastError();
 }
 
@@ -715,7 +735,9 @@ hipError_t launch_select(const SelectArgs& a, int n_kv_heads, hipStream_t s) {
 // Allows the kernels the dynamic LDS of the largest head they can be given (the attribute
 // belongs to the function on the current device: called at cache creation).
 hipError_t prepare_select() {
-  for (const void* fn : {reinterpret_cast<const void*>(compact_kernel<64, 4, 512>), reinterpret_cast<const void*>(compact_kernel<128, 4, 512>),
+  for (const void* fn : {reinterpret_cast<const void*>(compact_kernel<64, 1, 512>), reinterpret_cast<const void*>(compact_kernel<128, 1, 512>),
+                         reinterpret_cast<const void*>(compact_kernel<64, 2, 512>), reinterpret_cast<const void*>(compact_kernel<128, 2, 512>),
+                         reinterpret_cast<const void*>(compact_kernel<64, 4, 512>), reinterpret_cast<const void*>(compact_kernel<128, 4, 512>),
                          reinterpret_cast<const void*>(compact_kernel<64, 4, 1024>), reinterpret_cast<const void*>(compact_kernel<128, 4, 1024>),
                          reinterpret_cast<const void*>(compact_kernel<64, kMaxItemsAny, 1024>),
                          reinterpret_cast<const void*>(compact_kernel<128, kMaxItemsAny, 1024>)}) {
