@@ -57,6 +57,19 @@ __device__ __forceinline__ void have_argument(T x) { asm volatile("" ::"s"(x)); 
 template <class... T>
 __device__ __forceinline__ void have_arguments(T... x) { (have_argument(x), ...); }
 
+// Values that stay in registers from here on.  The compiler takes an argument for something that it can always load again and
+// does so before each later use, with a wait for the load.
+template <class T>
+__device__ __forceinline__ void keep_argument(T& x) { asm volatile("" : "+s"(x)); }
+template <class T>
+__device__ __forceinline__ void keep_argument(T*& x) {
+  auto global = (__attribute__((address_space(1))) T*)x;     // (it still has to be known as a pointer to global memory)
+  asm volatile("" : "+s"(global));
+  x = (T*)global;
+}
+template <class... T>
+__device__ __forceinline__ void keep_arguments(T&... x) { (keep_argument(x), ...); }
+
 // Row p of a list in two parts, the first c rows `old_bytes` apart and the others `new_bytes` apart: choices between values and
 // one multiplication.  (Written as a choice between two addresses this becomes a branch around two long
 // multiplications for every load.)  Offset: unsigned where a part is smaller than 4 GiB (and its rows less than 16 MiB apart).
@@ -206,7 +219,7 @@ struct LayerBlock {
 
 // Compaction of a group of layers whose block does not fit (select.hip); what a workgroup needs first lies
 // together, as in AttnArgs.
-struct SelectArgs {
+struct SelectPlan {
   int c, n, t0, budget, partial_stride, cand_stride, chunk_max, n_partials, merge;
   int n_kv_heads, head_dim, n_segs;
   int threads;                  // of a workgroup: 512 or 1024
@@ -233,6 +246,8 @@ struct SelectArgs {
   u16* stage;                   // K, then V [chunk_max, D] of every head, over that head's partial arrays
   float* stage_w;               // [Hkv, chunk_max]
   unsigned long long* totals;   // [KVP_T_COUNT] running totals of the cache (kvp_debug_totals)
+};
+struct SelectArgs : SelectPlan {
   LayerBlock layer[kMaxGroupLayers];
 };
 

@@ -192,7 +192,7 @@ struct Lanes {
 // 8 covers the limit, with the source lists in the scratch set)
 template <int D, int kMaxItems, int kThreads>
 __global__ void __launch_bounds__(kThreads)
-compact_kernel(const SelectArgs a) {
+compact_kernel(const SelectArgs args) {
   constexpr int kWaves = kThreads / 64;
   constexpr bool kListsInLds = kMaxItems <= 4;
   // (every wave searches the histogram for itself, and a few candidates need no fine one)
@@ -205,12 +205,14 @@ compact_kernel(const SelectArgs a) {
   __shared__ SegL s_segs[KVP_MAX_SEGMENTS];
 
   const int hk = blockIdx.x, li = blockIdx.y;          // grid (KV heads, layers of the group)
-  have_arguments(a.token_idx, a.partial, a.segs, a.weight, a.scores, a.k_cache, a.layer[li].k_new, a.g.first_set, a.g.n_sets,
+  SelectPlan a = args;
+  const u16* k_new = args.layer[li].k_new;
+  const u16* v_new = args.layer[li].v_new;
+  have_arguments(a.token_idx, a.partial, a.segs, a.weight, a.scores, a.k_cache, k_new, a.g.first_set, a.g.n_sets,
                  a.g.set_stride, a.g.kv_stride, a.g.meta_stride, a.c, a.n, a.t0, a.budget, a.partial_stride, a.cand_stride,
                  a.n_partials, a.merge, a.n_kv_heads, a.n_segs, a.items, a.table_size, a.quads, a.keydiff, a.width, a.groups);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c = a.c, n = a.n, n_cand = c + n, budget = a.budget;
-  const int items = a.items;
+  int c = a.c, n_cand = c + a.n, budget = a.budget, items = a.items;
   const int cand_pad = items * kThreads;
   const unsigned mask = (unsigned)a.table_size - 1u;
   int* const token_idx = a.token_idx + (long long)li * a.g.meta_stride + (size_t)hk * budget;
@@ -257,7 +259,7 @@ compact_kernel(const SelectArgs a) {
     if (a.score_override) {
       for (int p = tid; p < n_cand; p += kThreads) l.sums[p] = a.score_override[(size_t)hk * n_cand + p];
     } else if (kThreads == 512 && a.keydiff) {
-      score_head_by_keys<D>(a.k_cache + (long long)li * a.g.kv_stride + (size_t)hk * budget * D, a.layer[li].k_new + (size_t)hk * D,
+      score_head_by_keys<D>(a.k_cache + (long long)li * a.g.kv_stride + (size_t)hk * budget * D, k_new + (size_t)hk * D,
                             a.n_kv_heads, c, n_cand, l.sums + 4 * a.quads, l.sums);
     } else {
       // (a group is whole waves: what a wave loads is decided by scalar branches)
@@ -334,6 +336,12 @@ compact_kernel(const SelectArgs a) {
       }
     }
   }
+
+  // (what the phases from here on use; loaded again in each of them, with a wait every time: ten blocks of 64 tokens,
+  // 4 heads of d 64, 192 candidates: 126.3 -> 123.3 us.  With the rows' pointers, too, four heads of d 128 and 768 candidates
+  // lost 0.3 %)
+  keep_arguments(a.scores, a.keep, a.dst, a.g.first_set, a.g.n_sets, a.g.set_stride, a.cand_stride, a.t0, a.merge, a.n_segs, a.direct,
+                 c, n_cand, budget, items);
 
   // ---- own candidates, blocked: thread t owns positions [t * items, (t + 1) * items)
   float* const scores = in_set_of(a.scores, a.g, li) + (size_t)hk * a.cand_stride;
@@ -478,8 +486,6 @@ compact_kernel(const SelectArgs a) {
   // per-lane condition would push the arguments to memory)
   u16* const k_cache = a.k_cache;
   u16* const v_cache = a.v_cache;
-  const u16* const k_new = a.layer[li].k_new;
-  const u16* const v_new = a.layer[li].v_new;
   u16* const stage_k = in_set_of(a.stage, a.g, li) + 2 * (size_t)hk * a.partial_stride;
   u16* const stage_v = stage_k + (size_t)a.chunk_max * D;
   u16* const cache = (is_v ? v_cache : k_cache) + (long long)li * a.g.kv_stride + (size_t)hk * budget * D + 8 * piece;
@@ -514,7 +520,7 @@ compact_kernel(const SelectArgs a) {
           } else {
             r[j] = cached ? probe(l, mask, nb[j]) : -1;
           }
-          if (nb[j] >= a.t0 && nb[j] < a.t0 + n) r[j] = c + (nb[j] - a.t0);
+          if (nb[j] >= a.t0 && nb[j] < a.t0 + (n_cand - c)) r[j] = c + (nb[j] - a.t0);
         }
         unsigned long long kr[kNeighbours], best_key = 0;
 #pragma unroll
