@@ -116,7 +116,7 @@ __device__ __forceinline__ float sum_over_half(float (&v)[16], float factor, int
 constexpr int kScoreByKeys = -1;
 template <int D, int QW, int kKept>
 __global__ void __launch_bounds__((Split<D, QW>::kThreads))
-attention_split_kernel(const AttnArgs a) {
+attention_split_kernel(const AttnArgs args) {
   using S = Split<D, QW>;
   constexpr int KS = S::KS;
   constexpr int kNK = D / 16;                // K fragments (and MFMAs) of a 32-key block
@@ -132,10 +132,15 @@ attention_split_kernel(const AttnArgs a) {
   float* const kept_lds = lse_lds + S::kRows;                                    // [kWaves][kKeptRounds][32]
 
   const int li = blockIdx.y;
-  const u16* const q_rows = a.layer[li].q;
-  u16* const out_rows = a.layer[li].out;
-  have_arguments(q_rows, out_rows, a.layer[li].k_new, a.layer[li].v_new, a.k_cache, a.v_cache, a.lse2, a.partial, a.g.first_set,
+  AttnPlan a = args;
+  const u16* const q_rows = args.layer[li].q;
+  u16* const out_rows = args.layer[li].out;
+  have_arguments(q_rows, out_rows, args.layer[li].k_new, args.layer[li].v_new, a.k_cache, a.v_cache, a.lse2, a.partial, a.g.first_set,
                  a.g.n_sets, a.g.set_stride, a.g.kv_stride, a.n, a.c, a.work_per_xcd, a.total_work, a.tiles_magic, a.group_magic);
+  // (loaded again where they are used, eight waits on a wave's way: a whole prefix of 16/4 heads, d 64, 333 rows over
+  // 1444 keys, a layer per launch 7866 -> 7741 us; of 28/4 heads, d 128, 256 rows over 768 keys, eight layers per launch 851 -> 837 us)
+  keep_arguments(a.n_q_heads, a.n_kv_heads, a.n_keys, a.n_row_tiles, a.budget, a.shift, a.group, a.scale_log2, a.lse_stride,
+                 a.partial_stride, a.cand_stride);
   int block = (int)blockIdx.x;
   if constexpr (kKept == kScoreByKeys) {
     // They start with the launch and take about as long as an attention workgroup.
@@ -144,7 +149,7 @@ attention_split_kernel(const AttnArgs a) {
     if (block < 0) {
       const int hk = (int)blockIdx.x;
       if (hk < a.n_kv_heads)
-        score_head_by_keys<D>(a.k_cache + (size_t)li * a.g.kv_stride + (size_t)hk * a.budget * D, a.layer[li].k_new + (size_t)hk * D,
+        score_head_by_keys<D>(a.k_cache + (size_t)li * a.g.kv_stride + (size_t)hk * a.budget * D, args.layer[li].k_new + (size_t)hk * D,
                               a.n_kv_heads, a.c, a.c + a.n_keys, reinterpret_cast<float*>(lds_raw),
                               in_set_of(a.partial, a.g, li) + (size_t)hk * a.partial_stride);
       return;
@@ -176,8 +181,8 @@ attention_split_kernel(const AttnArgs a) {
   const int q0 = tile_row(qw);                             // first query row of this wave
   const u16* const kc = a.k_cache + (size_t)li * a.g.kv_stride + (size_t)hk * a.budget * D;
   const u16* const vc = a.v_cache + (size_t)li * a.g.kv_stride + (size_t)hk * a.budget * D;
-  const u16* const kn = a.layer[li].k_new + (size_t)hk * D;
-  const u16* const vn = a.layer[li].v_new + (size_t)hk * D;
+  const u16* const kn = args.layer[li].k_new + (size_t)hk * D;
+  const u16* const vn = args.layer[li].v_new + (size_t)hk * D;
   const int new_stride = a.n_kv_heads * D;
   const float sl2 = a.scale_log2;
 

@@ -101,7 +101,7 @@ struct AttnLayer {
   const u16* v_new;
   u16* out;            // [n, Hq, D], or null: only the row statistics are wanted
 };
-struct AttnArgs {
+struct AttnPlan {
   // Arguments are read from far memory at every launch, one 64-byte line at a time: what a workgroup
   // needs first lies together, and so do the pointers of a layer.
   int n, c, n_q_heads, n_kv_heads, budget, lse_stride;
@@ -121,6 +121,8 @@ struct AttnArgs {
   float* lse2;         // [Hq, lse_stride]  log2-domain log-sum-exp of every row (first layer's scratch set, like partial)
   float* partial;      // null, or [Hkv][query heads of the group x n_row_tiles][candidates], strides above: the launch
                        // also leaves the column sums of its softmax matrix (Eq. 4), one array per workgroup of a KV head
+};
+struct AttnArgs : AttnPlan {
   AttnLayer layer[kMaxGroupLayers];
 };
 
