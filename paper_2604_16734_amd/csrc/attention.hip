@@ -56,7 +56,7 @@
 // Layers.  One launch takes the block of up to sixteen layers (grid y), for callers that have them
 // all in hand (kvp_prefill_block).  One layer's block is 96 to 256 workgroups, a single round of the
 // chip at best: every launch pays the dispatch, the first tiles and the wait for its slowest
-// workgroup, and small blocks leave CUs idle.  Per layer, scores included: 77 -> 72 us at 32/8 heads, d 128,
+// workgroup, and small blocks leave CUs idle.  Per layer, scores included: 74 -> 68 us at 32/8 heads, d 128,
 // 1024 rows over 3072 keys (16 layers per launch).
 #include <type_traits>
 

@@ -21,7 +21,7 @@
 //            them and writes the result, one launch.  (A CU takes 64 bytes a clock from L2: beyond
 //            about 700 keys that costs more than the second launch below.)  The kernel is built for each
 //            number of rows a thread may hold, one to ten: rows past the end are loaded again at full price,
-//            so a step takes the fewest that cover its keys.  10.3 -> 5.4 us per layer at 32/32 heads, 265 keys
+//            so a step takes the fewest that cover its keys.  10.3 -> 4.7 us per layer at 32/32 heads, 265 keys
 //            (6.4 with ten rows per thread), 15.2 -> 6.0 at 28/4 heads, 553 keys;
 //   else     a workgroup of 256 threads takes 64 keys of one KV head at a time for all G query heads of
 //            the group and leaves (unnormalised output, maximum, sum) per query head; a second kernel

@@ -11,10 +11,10 @@ namespace kvp {
 // three rounds of the chip); below that the split-key shapes of attention_split.hip: 32-row workgroups
 // while all of them fit on the chip at once, 64-row ones (half as many) beyond.  Per launch with scores,
 // against the four-wave 64-row tiles that used to serve these blocks:
-//   16/4 heads, d 64, 333 rows over 1444 keys   28.4 -> 13.2 us
-//   28/4 heads, d 128, 256 rows over 768 keys   22.7 ->  9.5 us (17.3 -> 9 without scores)
-//   32/32 heads, d 128, 128 rows over 384 keys  15.1 ->  7.6 us
-//   28/4 heads, d 128, 512 rows over 1536 keys  34.6 -> 25.5 us (64-row workgroups)
+//   16/4 heads, d 64, 333 rows over 1444 keys   28.4 -> 11.1 us
+//   28/4 heads, d 128, 256 rows over 768 keys   22.7 ->  8.0 us (eight layers per launch)
+//   32/32 heads, d 128, 128 rows over 384 keys  15.1 ->  7.2 us
+//   28/4 heads, d 128, 512 rows over 1536 keys  34.6 -> 26.5 us (64-row workgroups)
 // The choice depends on one layer's block alone, never on how many layers a launch takes, so that
 // grouped and single launches leave the same bits.
 static int shape_for(int n, int n_q_heads) {
@@ -154,7 +154,7 @@ bool keydiff_in_compaction(int n_cand, int head_dim) {
 
 // The attention launch of the split-key shapes has workgroups that score such heads by the keys: 224 workgroups of 256 rows x 28
 // heads leave CUs idle, and in a grouped launch it is one workgroup more in 56.  28/4 heads, d 128, 256 rows over 768 keys:
-// attention 9.3 -> 9.7 us, compaction 13.8 -> 8.0 us per layer.  (128-row workgroups fill the chip: one more would be a
+// attention 9.3 -> 9.7 us, compaction 13.8 -> 7.4 us per layer.  (128-row workgroups fill the chip: one more would be a
 // second round.)  By one layer's block alone, like the shape.
 bool scores_keys_beside_attention(int variant, int n_cand, int head_dim) {
   return (variant == kAttnSplit32 || variant == kAttnSplit64) && keydiff_in_compaction(n_cand, head_dim);

@@ -723,7 +723,7 @@ hipError_t launch_head_dim(const SelectArgs& a, int n_kv_heads, hipStream_t s) {
   const dim3 grid(n_kv_heads, a.g.n_layers);
   // (built for one and two candidates per thread: what a loop over four of them skips is a fifth of the instructions there;
   // with the 512 bins and one reciprocal per merged row 4 heads of d 64, 192 candidates 9.8 -> 9.2 us, 4 heads of d 128, 768
-  // candidates 8.0 -> 7.6 us)
+  // candidates 8.0 -> 7.6 us; with the arguments in registers 8.7 and 7.4)
   if (a.items > 4) hipLaunchKernelGGL((compact_kernel<D, kMaxItemsAny, 1024>), grid, dim3(1024), lds, s, a);
   else if (a.threads == 1024) hipLaunchKernelGGL((compact_kernel<D, 4, 1024>), grid, dim3(1024), lds, s, a);
   else if (a.items > 2) hipLaunchKernelGGL((compact_kernel<D, 4, 512>), grid, dim3(512), lds, s, a);
