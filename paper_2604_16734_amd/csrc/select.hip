@@ -188,7 +188,7 @@ struct Lanes {
   static constexpr int kPairs = kThreads / kPerPair;   // row pairs the workgroup carries at a time
 };
 
-// kMaxItems: candidates a thread can own (4 covers up to 4096 candidates, with the source lists in LDS;
+// kMaxItems: candidates a thread can own (up to 4, i.e. up to 4096 candidates, with the source lists in LDS;
 // 8 covers the limit, with the source lists in the scratch set)
 template <int D, int kMaxItems, int kThreads>
 __global__ void __launch_bounds__(kThreads)
@@ -723,9 +723,13 @@ hipError_t launch_head_dim(const SelectArgs& a, int n_kv_heads, hipStream_t s) {
   const dim3 grid(n_kv_heads, a.g.n_layers);
   // (built for one and two candidates per thread: what a loop over four of them skips is a fifth of the instructions there;
   // with the 512 bins and one reciprocal per merged row 4 heads of d 64, 192 candidates 9.8 -> 9.2 us, 4 heads of d 128, 768
-  // candidates 8.0 -> 7.6 us; with the arguments in registers 8.7 and 7.4)
+  // candidates 8.0 -> 7.6 us; with the arguments in registers 8.7 and 7.4.
+  // Of 1024 threads for two, three and four: a whole prefix of 4 heads of d 64, 1444 candidates, 24 layers 7671 -> 7648 us, of 4 heads
+  // of d 128, 1536 candidates, 16 layers, scored by the prompt 4643 -> 4635 us)
   if (a.items > 4) hipLaunchKernelGGL((compact_kernel<D, kMaxItemsAny, 1024>), grid, dim3(1024), lds, s, a);
-  else if (a.threads == 1024) hipLaunchKernelGGL((compact_kernel<D, 4, 1024>), grid, dim3(1024), lds, s, a);
+  else if (a.threads == 1024 && a.items == 4) hipLaunchKernelGGL((compact_kernel<D, 4, 1024>), grid, dim3(1024), lds, s, a);
+  else if (a.threads == 1024 && a.items == 3) hipLaunchKernelGGL((compact_kernel<D, 3, 1024>), grid, dim3(1024), lds, s, a);
+  else if (a.threads == 1024) hipLaunchKernelGGL((compact_kernel<D, 2, 1024>), grid, dim3(1024), lds, s, a);
   else if (a.items > 2) hipLaunchKernelGGL((compact_kernel<D, 4, 512>), grid, dim3(512), lds, s, a);
   else if (a.items == 2) hipLaunchKernelGGL((compact_kernel<D, 2, 512>), grid, dim3(512), lds, s, a);
   else hipLaunchKernelGGL((compact_kernel<D, 1, 512>), grid, dim3(512), lds, s, a);
@@ -744,6 +748,8 @@ hipError_t prepare_select() {
   for (const void* fn : {reinterpret_cast<const void*>(compact_kernel<64, 1, 512>), reinterpret_cast<const void*>(compact_kernel<128, 1, 512>),
                          reinterpret_cast<const void*>(compact_kernel<64, 2, 512>), reinterpret_cast<const void*>(compact_kernel<128, 2, 512>),
                          reinterpret_cast<const void*>(compact_kernel<64, 4, 512>), reinterpret_cast<const void*>(compact_kernel<128, 4, 512>),
+                         reinterpret_cast<const void*>(compact_kernel<64, 2, 1024>), reinterpret_cast<const void*>(compact_kernel<128, 2, 1024>),
+                         reinterpret_cast<const void*>(compact_kernel<64, 3, 1024>), reinterpret_cast<const void*>(compact_kernel<128, 3, 1024>),
                          reinterpret_cast<const void*>(compact_kernel<64, 4, 1024>), reinterpret_cast<const void*>(compact_kernel<128, 4, 1024>),
                          reinterpret_cast<const void*>(compact_kernel<64, kMaxItemsAny, 1024>),
                          reinterpret_cast<const void*>(compact_kernel<128, kMaxItemsAny, 1024>)}) {

@@ -620,11 +620,11 @@ def _compact_on_given_scores(d, c, n, budget, t0, segs, tokens, scores):
 
 
 @pytest.mark.parametrize("d,c,n", [(64, 3, 1), (128, 400, 112), (64, 400, 113), (128, 700, 324), (64, 700, 325), (128, 1500, 548),
-                                   (64, 1500, 549)])
+                                   (64, 1500, 549), (128, 1900, 1172), (64, 1900, 1173)])
 @pytest.mark.parametrize("t0", [2000, 70000])                 # the two kinds of token table
 def test_compaction_workgroup_sizes(d, c, n, t0):
     """The smallest head, one candidate per thread of 512 and one more, the most candidates that 512 threads take and one
-    more, two per thread of 1024 and one more."""
+    more, two per thread of 1024 and one more, three and one more."""
     planes = (t0 + n) // 256 + 1
     rng = np.random.default_rng(t0 + c + n)
     tokens = np.stack([rng.choice(np.arange(t0 - min(t0, 2 * c), t0), size=c, replace=False) for _ in range(2)])
