@@ -117,7 +117,8 @@ attention_kernel(const AttnArgs args) {
   const u16* const q_rows = args.layer[li].q;
   u16* const out_rows = args.layer[li].out;
   have_arguments(q_rows, out_rows, args.layer[li].k_new, args.layer[li].v_new, a.k_cache, a.v_cache, a.lse2, a.partial, a.g.first_set,
-                 a.g.n_sets, a.g.set_stride, a.g.kv_stride, a.n, a.c, a.work_per_xcd, a.total_work, a.tiles_magic, a.group_magic);
+                 a.g.n_sets, a.g.set_stride, a.g.kv_stride, a.n, a.c, a.work_per_xcd, a.total_work, a.tiles_magic, a.group_magic,
+                 a.tiles_shift, a.group_shift);
   // (a whole prefix of 32/8 heads, d 128, 1024 rows over 3072 keys, a layer per launch 30192 -> 30124 us)
   keep_arguments(a.n_q_heads, a.n_kv_heads, a.n_keys, a.n_row_tiles, a.budget, a.shift, a.group, a.scale_log2, a.lse_stride,
                  a.partial_stride, a.cand_stride);
@@ -127,9 +128,9 @@ attention_kernel(const AttnArgs args) {
   if (w >= a.total_work) return;
   float* const lse2 = in_set_of(a.lse2, a.g, li);
   const int group = a.group;
-  const int h = (int)quotient((unsigned)w, a.tiles_magic);
+  const int h = (int)quotient((unsigned)w, Divisor{a.tiles_magic, a.tiles_shift});
   const int rt = a.n_row_tiles - 1 - (w - h * a.n_row_tiles);    // long rows first
-  const int hk = (int)quotient((unsigned)h, a.group_magic);
+  const int hk = (int)quotient((unsigned)h, Divisor{a.group_magic, a.group_shift});
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;

@@ -109,12 +109,13 @@ struct AttnPlan {
   int shift;           // row r sees block key j iff j <= r + shift (0: causal block; >= n_keys: all)
   int n_row_tiles, work_per_xcd, total_work;   // work items of one layer (grid y = layer)
   int group;           // query heads per KV head
-  unsigned tiles_magic, group_magic;   // divisor_magic of n_row_tiles and of group
+  unsigned tiles_magic, group_magic;   // divisor_of n_row_tiles and of group
   float scale_log2;    // softmax scale times log2(e)
-  int variant;         // tile shape, chosen by plan_attention
+  unsigned tiles_shift;                // 0 in the split-key shapes, of which a layer has fewer than 384 workgroups
   int key_score_wgs;   // workgroups in front that score the candidates by the keys alone (split-key shapes): one per KV head, up to a
                        // multiple of kXcds; their scores are the one partial array
   int partial_stride, cand_stride;   // floats from a KV head's partial arrays to the next head's, and from array to array
+  unsigned group_shift;
   GroupStrides g;
   const u16* k_cache;  // the group's first layer: [Hkv, M, D]
   const u16* v_cache;
@@ -124,6 +125,7 @@ struct AttnPlan {
 };
 struct AttnArgs : AttnPlan {
   AttnLayer layer[kMaxGroupLayers];
+  int variant;         // tile shape, chosen by plan_attention (no kernel reads it)
 };
 
 // Column sums of the softmax matrix (Eq. 4 summed over rows and over the query

@@ -42,8 +42,10 @@ void plan_attention(AttnArgs& a, int /*head_dim*/, int forced_shape) {
   a.n_row_tiles = (a.n + rows - 1) / rows;
   a.total_work = a.n_row_tiles * a.n_q_heads;
   a.group = a.n_q_heads / a.n_kv_heads;
-  a.tiles_magic = divisor_magic((unsigned)a.n_row_tiles);
-  a.group_magic = divisor_magic((unsigned)a.group);
+  const Divisor by_tiles = divisor_of((unsigned)a.n_row_tiles, (unsigned)a.total_work);
+  const Divisor by_group = divisor_of((unsigned)a.group, (unsigned)a.n_q_heads);
+  a.tiles_magic = by_tiles.magic; a.tiles_shift = by_tiles.shift;
+  a.group_magic = by_group.magic; a.group_shift = by_group.shift;
   a.work_per_xcd = (a.total_work + kXcds - 1) / kXcds;
 }
 

@@ -259,6 +259,7 @@ hipError_t launch_rowstat(RowstatArgs a, int head_dim, hipStream_t s) {
   a.item_splits = (n_items + a.items_per_wg - 1) / a.items_per_wg;
   if ((long long)a.n_kv_heads * a.item_splits > 65535) return hipErrorInvalidValue;
   a.group = a.n_q_heads / a.n_kv_heads;
+  // (n_obs * n_q_heads < 8192 here: fewer than 8192 items and rows, fewer than 65536 workgroups along y, products below 2^31)
   a.splits_magic = divisor_magic((unsigned)a.item_splits);
   a.tiles_magic = divisor_magic((unsigned)((a.n + 31) / 32));
   a.rows_magic = divisor_magic((unsigned)a.n);

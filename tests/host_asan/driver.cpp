@@ -1,7 +1,8 @@
 // Drives the C ABI of the host-only sanitized build through the dry-run cases of the Python host
 // tests: configuration and segment validation, sizes, the per-layer state machine over all five
 // workloads and all three ways of scoring, kvp_prefill_block in groups, the decode entry points
-// and their limits; and, with the launches recorded, kvp_prefill_block over layers that depend on each other.  Exits 0 when every check holds; the sanitizers abort on any invalid access.
+// and their limits; and, with the launches recorded, kvp_prefill_block over layers that depend on each other, and
+// the divisions by multiplication of launches of few and of many heads.  Exits 0 when every check holds; the sanitizers abort on any invalid access.
 #include <cstdio>
 #include <cstdlib>
 #include <string>
@@ -141,8 +142,43 @@ static void check_dependent_layers() {
   }
 }
 
+// Blocks of few and of very many heads, every way of scoring and both ways of summing, every launch recorded: the stub
+// launchers check the divisions by multiplication that the kernels would make of their work items.
+static void check_divisions() {
+  struct Heads { int hq, hkv; };
+  for (const Heads& heads : {Heads{46410, 1}, Heads{65900, 2}, Heads{100000, 1}, Heads{3000, 3000}, Heads{190, 1}, Heads{182, 2},
+                             Heads{64, 64}, Heads{28, 4}, Heads{32, 8}, Heads{4, 4}, Heads{1, 1}})
+    for (int chunk : {1, 33, 128, 300, 1024}) {
+      if ((long long)heads.hq * chunk > 20000000) continue;
+      Shape s{"heads", 2, heads.hq, heads.hkv, 64, chunk, 320, 4, 4, 400, 1, 32};
+      const std::vector<kvp_segment> segs = segments_of(s);
+      kvp_config cfg = config_of(s, 2);
+      cfg.flags = 0;
+      std::vector<Launch> seen;
+      recorded = &seen;
+      void* const at = reinterpret_cast<void*>((size_t)1 << 32);
+      kvp_cache* c = nullptr;
+      CHECK(kvp_init_cache(&cfg, segs.data(), 2, at, (size_t)1 << 50, nullptr, &c) == KVP_OK && c);
+      for (int fused : {1, 0})
+        for (int mode = 0; mode < 3; ++mode) {
+          CHECK(kvp_set_score_sweep(c, fused) == KVP_OK);
+          for (int l = 0; l < 2; ++l) {
+            CHECK(kvp_set_state(c, l, s.budget, s.budget) == KVP_OK);
+            const int rc = mode == 0 ? kvp_prefill_chunk(c, l, s.budget, chunk, at, at, at, at, nullptr)
+                         : mode == 1 ? kvp_prefill_chunk_proxy(c, l, s.budget, chunk, at, at, at, at, at, (chunk + 1) / 2, nullptr)
+                                     : kvp_prefill_chunk_keydiff(c, l, s.budget, chunk, at, at, at, at, nullptr);
+            CHECK(rc == KVP_OK);
+          }
+          CHECK(kvp_compact_layers(c, 0, 2, nullptr) == KVP_OK);
+        }
+      kvp_free_cache(c);
+      recorded = nullptr;
+    }
+}
+
 int main() {
   check_dependent_layers();
+  check_divisions();
   CHECK(kvp_strerror(KVP_OK) && kvp_strerror(-77));
   for (const Shape& s : kShapes) {
     const std::vector<kvp_segment> segs = segments_of(s);

@@ -91,6 +91,15 @@ def test_attention_outputs(hq, hkv, d, c, n, budget, chunk_max):
     cache.close()
 
 
+@pytest.mark.parametrize("hq,hkv", [(46410, 1), (65900, 2)])
+def test_many_query_heads_of_a_kv_head(hq, hkv):
+    """A workgroup finds its KV head by a multiplication (csrc/divide.h): the last query heads of more than 46340 to a KV
+    head, where query heads times their number per KV head pass 2^31."""
+    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, 64, 3, 5, 64, 16, seed=hq)
+    assert err <= U.OUT_TOL, err
+    cache.close()
+
+
 @pytest.mark.parametrize("variant", [0, 1, 2])
 @pytest.mark.parametrize("hq,hkv,d,c,n", [(8, 2, 128, 193, 300), (4, 4, 64, 70, 200), (4, 2, 128, 0, 129)])
 def test_every_workgroup_shape(variant, hq, hkv, d, c, n):
