@@ -152,8 +152,9 @@ def test_split_key_attention_edges(hq, hkv, d, c, n):
     the scores that the same launch leaves when the block does not fit."""
     cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, max(c, n // 2, 1), 600, seed=31 * c + n)
     assert err <= U.OUT_TOL, err
-    scores_gpu, keep, dst = cache.debug_last(0)
-    U.check_scores(scores_gpu.cpu().numpy(), scores_ref, n * (hq // hkv))
+    if c + n > max(c, n // 2, 1):                     # (one row of an empty cache fits and is not scored)
+        scores_gpu, keep, dst = cache.debug_last(0)
+        U.check_scores(scores_gpu.cpu().numpy(), scores_ref, n * (hq // hkv))
     cache.close()
 
 
@@ -339,6 +340,47 @@ def test_scores_after_runaway_logits(hq, hkv, d, c, n):
     tok = np.concatenate([oc.idx, np.broadcast_to(np.arange(c, tot), (hkv, n))], axis=1)
     for hk in range(hkv):
         assert np.array_equal(kept[hk].astype(bool), O.select_keep(scores[hk], tok[hk], budget))
+    cache.close()
+
+
+@pytest.mark.parametrize("value", ["nan", "inf", "huge"])     # huge: finite, but logits up to infinity
+@pytest.mark.parametrize("hq,hkv,d,c,n,fused", [
+    (4, 2, 128, 100, 33, 1), (4, 2, 128, 1216, 65, 1), (4, 4, 64, 450, 60, 1), (4, 2, 64, 1985, 65, 1),    # 32-row workgroups
+    (28, 4, 128, 0, 330, 1), (28, 4, 128, 161, 330, 1), (16, 4, 64, 333, 545, 1),                          # 64-row workgroups
+    (32, 8, 128, 256, 800, 1),                                                                             # 128-row workgroups
+    (8, 2, 128, 130, 150, 0)])                                                                             # separate kernel
+def test_scores_beside_a_row_that_is_not_finite(hq, hkv, d, c, n, fused, value):
+    """Rows whose logits are not finite spoil the scores of the keys that they see, and of no others: the block's later keys,
+    in the same block of 32 among them, score what the other rows give them."""
+    rng = np.random.default_rng(23 * c + n)
+    cache = K.Cache(1, hq, hkv, d, max(c, 1), n, [Segment(0, 100000, 0)], merge=False, device=DEV)
+    cache.set_score_sweep(fused)
+    qb, kb, vb = _rand_bits(rng, (n, hq, d)), _rand_bits(rng, (c + n, hkv, d)), _rand_bits(rng, (c + n, hkv, d))
+    q64, k64, v64 = (O.bf16_bits_to_f64(x) for x in (qb, kb, vb))
+    group = hq // hkv
+    bad = {0: 3, hkv - 1: n // 2 + 1}                 # KV head -> row; the last of its query heads
+    qt = U.bits_to_torch(qb)
+    for hk, row in bad.items():
+        q64[row, hk * group + group - 1] = 0.0        # a row that says nothing about later keys, either
+        qt[row, hk * group + group - 1, 5] = {"nan": float("nan"), "inf": float("inf"), "huge": 3e38}[value]
+    oc = O.LayerCache(hkv, d, max(c, 1))
+    if c:
+        oc.compact(0, k64[:c], v64[:c], np.zeros((hkv, c), dtype=np.float32))
+    U.upload_state(cache, 0, oc)
+    cache.set_state(0, c, c)
+    out_ref, scores_ref = oc.attend(c, q64, k64[c:], v64[c:])
+    out = cache.prefill_chunk(0, c, qt, U.bits_to_torch(kb[c:]), U.bits_to_torch(vb[c:]))
+    cache.compact(0)
+    scores = cache.debug_last(0)[0].cpu().numpy()
+    good = np.ones((n, hq), dtype=bool)
+    seen = np.zeros((hkv, c + n), dtype=bool)
+    for hk, row in bad.items():
+        good[row, hk * group + group - 1] = False
+        seen[hk, :c + row + 1] = True
+    assert U.out_rel_err(U.torch_bf16_to_f64(out)[good], out_ref[good]) <= U.OUT_TOL
+    U.check_scores(scores[~seen], scores_ref[~seen], n * group)
+    if value != "huge":
+        assert not np.isfinite(scores[seen]).any()
     cache.close()
 
 
