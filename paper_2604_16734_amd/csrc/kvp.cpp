@@ -547,9 +547,9 @@ static int prefill_layers(kvp_cache* c, int first, int count, int32_t token_begi
   const bool evicts = cached + n_tokens > cfg.budget;
   const int own_partials = (cfg.n_q_heads / cfg.n_kv_heads) * aa.n_row_tiles;
   const bool fused = evicts && mode == kScoreOwn && own_partials <= lay.max_partials && c->fused_scores;
-  // Scored by the keys alone, the launch of a block that does not fill the chip has room for workgroups that do that.
-  const bool by_keys = evicts && mode == kScoreKeydiff && scores_keys_beside_attention(aa.variant, cached + n_tokens, cfg.head_dim);
-  if (by_keys) aa.key_score_wgs = (cfg.n_kv_heads + kXcds - 1) / kXcds * kXcds;
+  // Scored by the keys alone, a launch of the split-key shapes may have workgroups that do that.
+  const bool by_keys = evicts && mode == kScoreKeydiff && scores_keys_beside_attention(aa, count, cached + n_tokens, cfg.head_dim);
+  if (by_keys) aa.key_score_wgs = key_score_workgroups(cfg.n_kv_heads);
   if (fused || by_keys) {
     aa.partial = reinterpret_cast<float*>(set + lay.partial_off);
     aa.partial_stride = lay.partial_stride;

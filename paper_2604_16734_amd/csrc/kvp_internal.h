@@ -288,6 +288,7 @@ int colsum_max_partials(int group, int chunk_max);
 size_t select_lds_bytes(const SelectArgs& a);
 void plan_select(SelectArgs& a);
 bool keydiff_in_compaction(int n_cand, int head_dim);
-bool scores_keys_beside_attention(int variant, int n_cand, int head_dim);
+bool scores_keys_beside_attention(const AttnArgs& a, int n_layers, int n_cand, int head_dim);
+int key_score_workgroups(int n_kv_heads);
 
 }  // namespace kvp

@@ -154,13 +154,29 @@ bool keydiff_in_compaction(int n_cand, int head_dim) {
   return n_cand <= kKeydiffRowsPerThread * (512 / (head_dim / 8));
 }
 
-// The attention launch of the split-key shapes has workgroups that score such heads by the keys: 224 workgroups of 256 rows x 28
-// heads leave CUs idle, and in a grouped launch it is one workgroup more in 56.  28/4 heads, d 128, 256 rows over 768 keys:
-// attention 9.3 -> 9.7 us, compaction 13.8 -> 7.4 us per layer.  (128-row workgroups fill the chip: one more would be a
-// second round.)  By one layer's block alone, like the shape.
-bool scores_keys_beside_attention(int variant, int n_cand, int head_dim) {
-  return (variant == kAttnSplit32 || variant == kAttnSplit64) && keydiff_in_compaction(n_cand, head_dim);
+// The attention launch of the split-key shapes has workgroups that score such heads by the keys, one per KV head (up to a multiple
+// of kXcds), where they cost less than the compaction's own scoring, 6 us in front of its other phases.  Prefixes scored in the
+// compaction, and beside the attention, one layer per launch unless said otherwise:
+//   32-row workgroups are as many as CUs at most, one round of the chip.  While the scoring ones fit into it, too:
+//     28/4 heads, d 128, 256 rows over 768 keys (224 + 8 workgroups) 819 -> 636 us, 8 layers per launch 628 -> 623 us;
+//     16/4 heads, d 64, 333 rows over 1444 keys (176 + 8) 914 -> 712 us.
+//   Beyond, as many attention workgroups wait for a second round: 64/64 heads, 128 rows over 384 keys (256 + 64) 725 -> 772 us,
+//     64/8 heads, 128 rows over 640 keys (256 + 8) 838 -> 863, 32/8 heads, 256 rows over 768 keys (256 + 8) 806 -> 817 us
+//     (32/32 heads, 256 rows over 768 keys, 256 + 32, 893 -> 881 us).
+//   64-row workgroups take two or three times as long as a scoring one: 40/8 heads, d 128, 512 rows over 1024 keys (320 + 8)
+//     1461 -> 1207 us, 8 layers per launch 1305 -> 1267 us.
+//   At d 64 the kernel that scores keys holds one workgroup per CU, the other two.  That shows in launches of many
+//     rounds: 16/4 heads, 333 rows over 1444 keys, 3 layers per launch 633 -> 603 us, 8 layers 489 -> 534; 28/4 heads, 512 rows over
+//     1536 keys, 3 layers (696 workgroups) 978 -> 890 us, 8 layers (1856) 950 -> 965 us.
+// Both ways leave the same bits, so that this may depend on the layers of a launch.
+bool scores_keys_beside_attention(const AttnArgs& a, int n_layers, int n_cand, int head_dim) {
+  if (a.variant != kAttnSplit32 && a.variant != kAttnSplit64) return false;
+  if (!keydiff_in_compaction(n_cand, head_dim)) return false;
+  const int workgroups = a.total_work + key_score_workgroups(a.n_kv_heads);
+  if (a.variant == kAttnSplit32 && workgroups > 256) return false;
+  return head_dim == 128 || workgroups * n_layers <= 3 * 256;
 }
+int key_score_workgroups(int n_kv_heads) { return (n_kv_heads + kXcds - 1) / kXcds * kXcds; }
 
 // ---- compaction: row pairs (K row and V row of a slot, 16 bytes per lane) a workgroup carries
 int rows_per_compact_block(int head_dim) { return kCompactThreads / (2 * head_dim / 8); }

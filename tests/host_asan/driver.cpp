@@ -2,7 +2,7 @@
 // tests: configuration and segment validation, sizes, the per-layer state machine over all five
 // workloads and all three ways of scoring, kvp_prefill_block in groups, the decode entry points
 // and their limits; and, with the launches recorded, kvp_prefill_block over layers that depend on each other, and
-// the divisions by multiplication of launches of few and of many heads.  Exits 0 when every check holds; the sanitizers abort on any invalid access.
+// the divisions by multiplication of launches of few and of many heads, and where blocks are scored by the keys alone.  Exits 0 when every check holds; the sanitizers abort on any invalid access.
 #include <cstdio>
 #include <cstdlib>
 #include <string>
@@ -176,7 +176,57 @@ static void check_divisions() {
     }
 }
 
+// Scored by the keys alone: beside the attention, in the compaction or by kernels of its own, once and only once.
+static void check_key_scoring() {
+  auto launches = [&](int layers, int hq, int hkv, int d, int n, int budget, int shape) {
+    Shape s{"keys", layers, hq, hkv, d, n, budget, 4, 4, 400, 1, 32};
+    const std::vector<kvp_segment> segs = segments_of(s);
+    kvp_config cfg = config_of(s, layers);
+    cfg.flags = 0;
+    std::vector<Launch> seen;
+    recorded = &seen;
+    kvp_cache* c = nullptr;
+    void* const at = reinterpret_cast<void*>((size_t)1 << 32);
+    CHECK(kvp_init_cache(&cfg, segs.data(), 2, at, (size_t)1 << 50, nullptr, &c) == KVP_OK && c);
+    CHECK(kvp_set_attention_shape(c, shape) == KVP_OK);
+    std::vector<const void*> in(layers, at);
+    std::vector<void*> out(layers);
+    for (int l = 0; l < layers; ++l) {
+      CHECK(kvp_set_state(c, l, budget, budget) == KVP_OK);
+      out[l] = reinterpret_cast<void*>((size_t)(l + 2) << 32);
+    }
+    CHECK(kvp_prefill_block(c, budget, n, in.data(), in.data(), in.data(), out.data(), KVP_SCORE_KEYDIFF, nullptr, 0, nullptr, nullptr) == KVP_OK);
+    kvp_free_cache(c);
+    recorded = nullptr;
+    std::string all;
+    for (const Launch& x : seen) all += std::string(x.kernel) + std::to_string(x.layers) + " ";
+    return all;
+  };
+  // 32-row workgroups, one round of 256 with the scoring ones: 224 + 8, 248 + 8, 256 + 8, 240 + 16, 256 + 32
+  EXPECT(launches(1, 28, 4, 128, 256, 512, -1), "attention+keys1 select1 ");
+  EXPECT(launches(1, 31, 1, 128, 256, 512, -1), "attention+keys1 select1 ");
+  EXPECT(launches(1, 32, 8, 128, 256, 512, -1), "attention1 keys+select1 ");
+  EXPECT(launches(1, 60, 10, 128, 128, 512, -1), "attention+keys1 select1 ");
+  EXPECT(launches(1, 32, 32, 128, 256, 512, -1), "attention1 keys+select1 ");
+  EXPECT(launches(8, 28, 4, 128, 256, 512, -1), "attention+keys8 select8 ");
+  // 64-row workgroups, one round or more
+  EXPECT(launches(1, 28, 4, 128, 512, 512, -1), "attention+keys1 select1 ");
+  EXPECT(launches(1, 40, 8, 128, 512, 512, -1), "attention+keys1 select1 ");
+  EXPECT(launches(8, 40, 8, 128, 512, 512, -1), "attention+keys8 select8 ");
+  // d 64: 768 workgroups in all layers of the launch (4 x 184, 5 x 184; 2 x 328, 3 x 328)
+  EXPECT(launches(4, 16, 4, 64, 333, 1111, -1), "attention+keys4 select4 ");
+  EXPECT(launches(5, 16, 4, 64, 333, 1111, -1), "attention5 keys+select5 ");
+  EXPECT(launches(2, 40, 8, 64, 512, 1024, -1), "attention+keys2 select2 ");
+  EXPECT(launches(3, 40, 8, 64, 512, 1024, -1), "attention3 keys+select3 ");
+  // 128-row workgroups, and one more key than a workgroup holds
+  EXPECT(launches(2, 32, 8, 128, 1000, 24, -1), "attention2 keys+select2 ");
+  EXPECT(launches(2, 28, 4, 128, 256, 512, 2), "attention2 keys+select2 ");
+  EXPECT(launches(2, 28, 4, 128, 256, 769, -1), "attention2 keydiff2 select2 ");
+  EXPECT(launches(2, 4, 4, 64, 256, 1793, -1), "attention2 keydiff2 select2 ");
+}
+
 int main() {
+  check_key_scoring();
   check_dependent_layers();
   check_divisions();
   CHECK(kvp_strerror(KVP_OK) && kvp_strerror(-77));

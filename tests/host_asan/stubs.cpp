@@ -40,7 +40,7 @@ hipError_t launch_attention(const AttnArgs& a, int, hipStream_t) {
     check_quotients("attention, row tiles", a.total_work, a.n_row_tiles, Divisor{a.tiles_magic, a.tiles_shift});
     check_quotients("attention, group", a.n_q_heads, a.group, Divisor{a.group_magic, a.group_shift});
   }
-  return note("attention", a.g.n_layers);
+  return note(a.key_score_wgs > 0 ? "attention+keys" : "attention", a.g.n_layers);
 }
 hipError_t launch_colsum(const ColsumArgs& a, int, hipStream_t) {
   check_quotients("colsum, workgroups of a head", a.total_work, a.wgs_per_head, a.wgs_magic);
@@ -48,7 +48,7 @@ hipError_t launch_colsum(const ColsumArgs& a, int, hipStream_t) {
 }
 hipError_t launch_select(const SelectArgs& a, int, hipStream_t) {
   check_quotients("select, groups", a.n_partials + a.groups, a.groups, a.groups_magic);
-  return note("select", a.g.n_layers);
+  return note(a.keydiff ? "keys+select" : "select", a.g.n_layers);
 }
 hipError_t launch_move(const CompactArgs& a, hipStream_t) { return note("move", a.g.n_layers); }
 hipError_t launch_init(int32_t*, float*, size_t, const Seg*, int, Seg*, unsigned long long*, hipStream_t) { return note_nothing(); }

@@ -593,8 +593,10 @@ def test_keydiff_scored_by_the_compaction_edges(hq, hkv, d, c, n):
 
 
 @pytest.mark.parametrize("hq,hkv,d,c,n", [
-    # nothing cached, one key of the block evicted; ten KV heads; the most candidates; two row tiles per workgroup
-    (4, 2, 128, 0, 2), (4, 2, 64, 1, 1), (20, 10, 64, 300, 33), (4, 2, 128, 900, 124), (4, 2, 64, 1900, 148), (28, 4, 128, 512, 512)])
+    # nothing cached, one key of the block evicted; ten KV heads; the most candidates; two row tiles per workgroup; as many
+    # 32-row workgroups as CUs with the scoring ones, and one more
+    (4, 2, 128, 0, 2), (4, 2, 64, 1, 1), (20, 10, 64, 300, 33), (4, 2, 128, 900, 124), (4, 2, 64, 1900, 148), (28, 4, 128, 512, 512),
+    (31, 1, 128, 512, 256), (32, 8, 128, 512, 256)])
 def test_keys_scored_beside_the_attention(hq, hkv, d, c, n):
     """Scores by the keys alone from the attention launch of the split-key shapes, and from the compaction launch behind the
     128-row shape: the same bits."""
@@ -607,6 +609,34 @@ def test_keys_scored_beside_the_attention(hq, hkv, d, c, n):
         assert np.abs(scores[-1].astype(np.float64) - scores_ref).max() <= 2e-5
         cache.close()
     assert np.array_equal(scores[0].view(np.uint32), scores[1].view(np.uint32))
+
+
+def test_key_scores_of_grouped_and_single_launches():
+    """Six layers of 184 workgroups at d 64: scored beside the attention one layer at a time, in the compaction together."""
+    layers, hq, hkv, d, c, n = 6, 16, 4, 64, 1111, 333
+    rng = np.random.default_rng(6)
+    data = [tuple(U.bits_to_torch(_rand_bits(rng, (n, h, d))) for h in (hq, hkv, hkv)) for _ in range(layers)]
+    rows = U.bits_to_torch(_rand_bits(rng, (2, hkv, c, d)))
+    results = []
+    for grouped in (False, True):
+        cache = K.Cache(layers, hq, hkv, d, c, n, [Segment(0, 4000, 0)], merge=False, scratch_sets=layers, device=DEV)
+        outs = [torch.empty_like(q) for q, _, _ in data]
+        for l in range(layers):
+            k, v, idx, w, _, _ = cache.decode_ready(l)
+            k.copy_(rows[0]); v.copy_(rows[1]); w.fill_(1.0)
+            idx.copy_(torch.arange(c, device=DEV, dtype=torch.int32).expand(hkv, c))
+            cache.set_state(l, c, c)
+        if grouped:
+            K.Prefill(cache, layers).block(c, lambda l: data[l], lambda l: outs[l], None, True)
+        else:
+            for l in range(layers):
+                cache.prefill_chunk_keydiff(l, c, *data[l], out=outs[l])
+                cache.compact(l)
+        scores = [cache.debug_last(l)[0] for l in range(layers)]
+        results.append([x.clone() for l in range(layers) for x in cache.decode_ready(l)[:4]] + [x.clone() for x in scores] + outs)
+        cache.close()
+    for a, b in zip(*results):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
 
 
 @pytest.mark.parametrize("d,c,n,budget,t0,levels", [
