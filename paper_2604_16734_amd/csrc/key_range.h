@@ -12,10 +12,7 @@
 
 namespace kvp {
 
-#ifndef KVP_SELECT_BIN_BITS                          // (the host tests run the search with fewer bins, too)
-#define KVP_SELECT_BIN_BITS 11
-#endif
-constexpr int kSelectBinBits = KVP_SELECT_BIN_BITS;
+constexpr int kSelectBinBits = 11;
 constexpr int kSelectBins = 1 << kSelectBinBits;   // histogram bins of the selection
 constexpr int kSelectFewBinBits = 9;               // ... of 1024 candidates at most
 
@@ -48,6 +45,5 @@ struct KeyRangeOf {
     shift = shift < kBits ? 0 : shift - kBits;
   }
 };
-using KeyRange = KeyRangeOf<kSelectBinBits>;
 
 }  // namespace kvp

@@ -10,7 +10,11 @@
 
 #include "key_range.h"
 
-using kvp::KeyRange;
+#ifndef KEY_SEARCH_BITS                    // of the histogram: one of the selection's two sizes
+#define KEY_SEARCH_BITS kvp::kSelectBinBits
+#endif
+constexpr int kBits = KEY_SEARCH_BITS, kBins = 1 << kBits;
+using KeyRange = kvp::KeyRangeOf<kBits>;
 typedef unsigned long long Key;
 
 static unsigned order_bits(float x) {
@@ -32,15 +36,15 @@ static bool right(const std::vector<Key>& keys, unsigned budget, const std::stri
   unsigned want = budget, in_bin = 0;
   std::vector<unsigned> hist;
   for (int pass = 0;; ++pass) {
-    if (pass > 6) {                        // 64 bits, eleven at a time
+    if (pass > 6) {                        // 64 bits, nine or eleven at a time, less what the first range leaves out
       std::printf("%s: no end after %d passes\n", what.c_str(), pass);
       return false;
     }
-    hist.assign(kvp::kSelectBins, 0u);
+    hist.assign(kBins, 0u);
     for (Key k : keys)
       if (unsigned bin; range.holds(k, bin)) ++hist[bin];
     unsigned above = 0;
-    int digit = kvp::kSelectBins - 1;
+    int digit = kBins - 1;
     for (; digit >= 0 && above + hist[digit] < want; --digit) above += hist[digit];
     if (digit < 0) {
       std::printf("%s: fewer keys in the range than wanted\n", what.c_str());
