@@ -724,14 +724,18 @@ hipError_t launch_head_dim(const SelectArgs& a, int n_kv_heads, hipStream_t s) {
   // (built for one and two candidates per thread: what a loop over four of them skips is a fifth of the instructions there;
   // with the 512 bins and one reciprocal per merged row 4 heads of d 64, 192 candidates 9.8 -> 9.2 us, 4 heads of d 128, 768
   // candidates 8.0 -> 7.6 us; with the arguments in registers 8.7 and 7.4.
-  // Of 1024 threads for two, three and four: a whole prefix of 4 heads of d 64, 1444 candidates, 24 layers 7671 -> 7648 us, of 4 heads
-  // of d 128, 1536 candidates, 16 layers, scored by the prompt 4643 -> 4635 us)
+  // Of 1024 threads for two, three and four, against four alone: a whole prefix of 4 heads of d 64, 1444 candidates, 24 layers
+  // 7719 -> 7689 us, of 4 heads of d 128, 1536 candidates, 16 layers, scored by the prompt 4697 -> 4687 us, of 8 heads of d 128,
+  // 3072 candidates, 32 layers 33908 -> 33850 us; runs of one side differ by 0.1 %)
   if (a.items > 4) hipLaunchKernelGGL((compact_kernel<D, kMaxItemsAny, 1024>), grid, dim3(1024), lds, s, a);
   else if (a.threads == 1024 && a.items == 4) hipLaunchKernelGGL((compact_kernel<D, 4, 1024>), grid, dim3(1024), lds, s, a);
   else if (a.threads == 1024 && a.items == 3) hipLaunchKernelGGL((compact_kernel<D, 3, 1024>), grid, dim3(1024), lds, s, a);
   else if (a.threads == 1024) hipLaunchKernelGGL((compact_kernel<D, 2, 1024>), grid, dim3(1024), lds, s, a);
-  else if (a.items > 2) hipLaunchKernelGGL((compact_kernel<D, 4, 512>), grid, dim3(512), lds, s, a);
-  else if (a.items == 2) hipLaunchKernelGGL((compact_kernel<D, 2, 512>), grid, dim3(512), lds, s, a);
+  else if (a.items > 2) {
+    // (512 threads and more than 1024 candidates: scored by the keys, of which they hold 2048 at d 64 only)
+    if constexpr (D == 64) hipLaunchKernelGGL((compact_kernel<D, 4, 512>), grid, dim3(512), lds, s, a);
+    else return hipErrorInvalidValue;
+  } else if (a.items == 2) hipLaunchKernelGGL((compact_kernel<D, 2, 512>), grid, dim3(512), lds, s, a);
   else hipLaunchKernelGGL((compact_kernel<D, 1, 512>), grid, dim3(512), lds, s, a);
   return hipGetLastError();
 }
@@ -747,7 +751,7 @@ hipError_t launch_select(const SelectArgs& a, int n_kv_heads, hipStream_t s) {
 hipError_t prepare_select() {
   for (const void* fn : {reinterpret_cast<const void*>(compact_kernel<64, 1, 512>), reinterpret_cast<const void*>(compact_kernel<128, 1, 512>),
                          reinterpret_cast<const void*>(compact_kernel<64, 2, 512>), reinterpret_cast<const void*>(compact_kernel<128, 2, 512>),
-                         reinterpret_cast<const void*>(compact_kernel<64, 4, 512>), reinterpret_cast<const void*>(compact_kernel<128, 4, 512>),
+                         reinterpret_cast<const void*>(compact_kernel<64, 4, 512>),
                          reinterpret_cast<const void*>(compact_kernel<64, 2, 1024>), reinterpret_cast<const void*>(compact_kernel<128, 2, 1024>),
                          reinterpret_cast<const void*>(compact_kernel<64, 3, 1024>), reinterpret_cast<const void*>(compact_kernel<128, 3, 1024>),
                          reinterpret_cast<const void*>(compact_kernel<64, 4, 1024>), reinterpret_cast<const void*>(compact_kernel<128, 4, 1024>),

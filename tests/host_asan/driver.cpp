@@ -221,6 +221,8 @@ static void check_key_scoring() {
   // 128-row workgroups, and one more key than a workgroup holds
   EXPECT(launches(2, 32, 8, 128, 1000, 24, -1), "attention2 keys+select2 ");
   EXPECT(launches(2, 28, 4, 128, 256, 512, 2), "attention2 keys+select2 ");
+  EXPECT(launches(2, 28, 4, 128, 256, 768, 2), "attention2 keys+select2 ");
+  EXPECT(launches(2, 4, 4, 64, 256, 1792, 2), "attention2 keys+select2 ");
   EXPECT(launches(2, 28, 4, 128, 256, 769, -1), "attention2 keydiff2 select2 ");
   EXPECT(launches(2, 4, 4, 64, 256, 1793, -1), "attention2 keydiff2 select2 ");
 }

@@ -47,6 +47,11 @@ hipError_t launch_colsum(const ColsumArgs& a, int, hipStream_t) {
   return note("colsum", a.g.n_layers);
 }
 hipError_t launch_select(const SelectArgs& a, int, hipStream_t) {
+  // the kernels that select.hip is built for
+  if (a.threads != 1024 && (a.threads != 512 || a.items > (a.head_dim == 64 ? 4 : 2))) {
+    std::fprintf(stderr, "select: %d threads, %d candidates each at d %d\n", a.threads, a.items, a.head_dim);
+    std::exit(1);
+  }
   check_quotients("select, groups", a.n_partials + a.groups, a.groups, a.groups_magic);
   return note(a.keydiff ? "keys+select" : "select", a.g.n_layers);
 }
