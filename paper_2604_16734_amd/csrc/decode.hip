@@ -65,7 +65,8 @@ __device__ __forceinline__ u16 round_bf16(float r) {
   return (u16)(u >> 16);
 }
 
-// (pairs of bf16 products into an fp32 sum: both are bf16 in memory, the products exact, and the sum of a pair is rounded once)
+// (pairs of bf16 products into an fp32 sum: both are bf16 in memory, the products exact, and the sum of a pair is rounded once;
+// denormal keys and queries count in full)
 __device__ __forceinline__ float dot8(const uint4 k, const uint4 q) {
   float s = dot2(k.x, q.x, 0.f);
   s = dot2(k.y, q.y, s);

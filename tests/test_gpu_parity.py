@@ -444,6 +444,55 @@ def test_decode_step_edges(hq, hkv, d, n_keys):
     cache.close()
 
 
+@pytest.mark.parametrize("d,c", [(64, 90), (128, 90), (128, 900)])       # the kernel of few keys, and of many
+@pytest.mark.parametrize("keys,queries", [(0, 0), (-128, 125), (125, -128)])
+def test_decode_logits(d, c, keys, queries):
+    """Logits of a decode step to fp32 rounding: keys that differ by little, under a large softmax scale.  Keys or queries times
+    2^-128 are denormal numbers, the others large."""
+    rng = np.random.default_rng(d + c)
+    hq, hkv = 8, 4
+    scale = 32.0 * 2.0 ** -(keys + queries)
+    base = np.round(np.clip(rng.standard_normal((1, hkv, d)), -3, 3) * 32) / 32
+    rows = np.repeat(base, c + 5, axis=0)                  # one channel of each is off by up to 3/32: bf16 has these numbers
+    rows[np.arange(c + 5)[:, None], np.arange(hkv)[None], rng.integers(0, d, (c + 5, hkv))] += rng.integers(0, 4, (c + 5, hkv)) / 32
+    q = np.round(np.clip(rng.standard_normal((hq, d)), -3, 3) * 32) / 32
+    kb, qb = O.f64_to_bf16_bits(rows * 2.0 ** keys), O.f64_to_bf16_bits(q * 2.0 ** queries)
+    vb = _rand_bits(rng, (c + 5, hkv, d))
+    q64, k64, v64 = (O.bf16_bits_to_f64(x) for x in (qb, kb, vb))
+    cache = K.Cache(1, hq, hkv, d, c, 64, [Segment(0, 100000, 0)], merge=False, softmax_scale=scale, device=DEV)
+    oc = O.LayerCache(hkv, d, c)
+    oc.compact(0, k64[:c], v64[:c], np.zeros((hkv, c), dtype=np.float32))
+    U.upload_state(cache, 0, oc)
+    cache.set_state(0, c, c)
+    _, _, k_all, v_all = oc.candidates(c, k64[c:], v64[c:])
+    ref = O.decode_step(q64, k_all, v_all, scale)
+    out = U.torch_bf16_to_f64(cache.decode_step(0, U.bits_to_torch(qb), U.bits_to_torch(kb[c:]), U.bits_to_torch(vb[c:])))
+    # a logit is the sum of d products, each of which meets at most twelve roundings (8 of a lane, sixteen lanes); an error e of the
+    # logits changes a weight by a factor of exp(2 e) at most; the output is rounded to bf16 once
+    most = np.abs(q64).sum(axis=1).max() * np.abs(k64).max()
+    e = scale * 12 * 2.0 ** -24 * most
+    assert e < 0.02
+    assert np.abs(out - ref).max() <= (2.1 * e + 2.0 ** -8) * np.abs(v64).max()
+    cache.close()
+
+
+@pytest.mark.parametrize("hkv", [8192, 8193, 65537])       # one launch of few keys, two of more KV heads than 32-bit offsets reach
+def test_decode_step_of_many_kv_heads(hkv):
+    rng = np.random.default_rng(hkv)
+    cache = K.Cache(1, hkv, hkv, 64, 3, 1, [Segment(0, 100, 0)], merge=False, device=DEV)
+    oc = O.LayerCache(hkv, 64, 3)
+    kb0, vb0, kb, vb = (_rand_bits(rng, (m, hkv, 64)) for m in (3, 3, 2, 2))
+    oc.compact(0, O.bf16_bits_to_f64(kb0), O.bf16_bits_to_f64(vb0), np.zeros((hkv, 3), dtype=np.float32))
+    U.upload_state(cache, 0, oc)
+    cache.set_state(0, 3, 3)
+    qb = _rand_bits(rng, (hkv, 64))
+    _, _, k_all, v_all = oc.candidates(3, O.bf16_bits_to_f64(kb), O.bf16_bits_to_f64(vb))
+    ref = O.decode_step(O.bf16_bits_to_f64(qb), k_all, v_all)
+    out = cache.decode_step(0, U.bits_to_torch(qb), U.bits_to_torch(kb), U.bits_to_torch(vb))
+    assert U.out_rel_err(U.torch_bf16_to_f64(out), ref) <= 5e-3      # as above
+    cache.close()
+
+
 def test_decode_step_after_prefill():
     """Prefill a layer block by block, then generate three tokens over what it kept."""
     wl = get_workload("tiled_image")
