@@ -7,6 +7,9 @@ within 1e-3 relative plus one smallest normal fp32 number per contributing row
 kept sets, merge plans, token indices and weights bit-exact when selection is
 fed the oracle's fp32 scores; merged rows within one bf16 ulp (fp32 vs fp64
 averaging before the single rounding); untouched rows bit-exact."""
+import os
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -158,15 +161,29 @@ def test_split_key_attention_edges(hq, hkv, d, c, n):
     cache.close()
 
 
-@pytest.mark.parametrize("scale", [0.0, 2.0])      # 2: logits of hundreds, so that references move in later blocks
-@pytest.mark.parametrize("hq,hkv,d,c,n", [
+def _rows_of_a_workgroup(n, hq):
+    """Query rows of the workgroups that csrc/plan.cpp picks for a block."""
+    if -(-n // 128) * hq >= 192:
+        return 128
+    return 32 if -(-n // 32) * hq <= 256 else 64
+
+
+KEPT_WEIGHTS = [
     # 32-row workgroups of eight waves: 1 to 8 key blocks per wave whose weights stay in registers (up to 6 at d 128),
     # and one more, for which the scores take a second sweep; one row past a tile, a last block of one key
     (4, 2, 128, 100, 33), (4, 2, 128, 481, 33), (4, 2, 128, 705, 32), (8, 2, 128, 930, 65), (4, 2, 128, 1216, 33),
     (4, 2, 128, 1472, 33), (4, 2, 128, 1473, 33), (4, 4, 64, 450, 33), (4, 2, 64, 704, 33), (4, 2, 64, 960, 64),
-    (4, 2, 64, 1217, 1), (4, 2, 64, 1472, 33), (4, 2, 64, 1985, 33), (4, 2, 64, 1985, 65)])
+    (4, 2, 64, 1217, 1), (4, 2, 64, 1472, 33), (4, 2, 64, 1985, 33), (4, 2, 64, 1985, 65),
+    # the fewest and the most blocks of a kernel: 9 and 16, 25 and 32; at d 64 8 and 9, 49 and 56, 57 and 64
+    (4, 2, 128, 224, 33), (4, 2, 128, 448, 33), (4, 2, 128, 736, 33), (4, 2, 128, 960, 33), (4, 2, 64, 192, 33),
+    (4, 2, 64, 224, 33), (4, 2, 64, 1504, 33), (4, 2, 64, 1728, 33), (4, 2, 64, 1760, 33), (4, 2, 64, 1984, 33)]
+
+
+@pytest.mark.parametrize("scale", [0.0, 2.0])      # 2: logits of hundreds, so that references move in later blocks
+@pytest.mark.parametrize("hq,hkv,d,c,n", KEPT_WEIGHTS)
 def test_scores_from_kept_weights(hq, hkv, d, c, n, scale):
     """Scores out of the weights that a wave of the split-key kernel holds, for every number of blocks it is built for."""
+    assert _rows_of_a_workgroup(n, hq) == 32
     cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, c, 96, seed=13 * c + n, scale=scale)
     assert err <= U.OUT_TOL, err
     scores_gpu, keep, dst = cache.debug_last(0)
@@ -174,13 +191,29 @@ def test_scores_from_kept_weights(hq, hkv, d, c, n, scale):
     cache.close()
 
 
+@pytest.mark.parametrize("head_dim", [64, 128])
+def test_kept_weights_of_every_kernel(head_dim):
+    """The cases above reach each kernel of this head dimension, with every number of blocks per wave that it serves."""
+    with open(os.path.join(os.path.dirname(K.__file__), "csrc", "attention_split.hip")) as f:
+        text = f.read()
+    built = {int(x) for x in re.findall(r"if \(\(?e = prepare_shape<D, 1, (\d+)>", text)}
+    built |= {int(x) for x in re.findall(r"if constexpr \(D == 64\) e = prepare_shape<D, 1, (\d+)>", text) if head_dim == 64}
+    most = max(built)
+    needed = {-(-(-(-c // 32) - (-n // 32)) // 8) for _, _, d, c, n in KEPT_WEIGHTS if d == head_dim}
+    assert needed == set(range(1, most + 2))
+    assert {min((k for k in built if k >= need), default=0) for need in needed} == built
+
+
 @pytest.mark.parametrize("scale", [0.0, 2.0])
 @pytest.mark.parametrize("hq,hkv,d,c,n", [
-    # 64-row workgroups, whose first 16 key blocks stay in registers: 11, 15, 16, 17 and 27 blocks for the latest rows
-    (28, 4, 128, 0, 330), (28, 4, 128, 100, 330), (28, 4, 128, 160, 330), (28, 4, 128, 161, 330), (16, 4, 64, 333, 512)])
+    # 64-row workgroups, whose first 16 key blocks stay in registers: 11, 15, 16 and 17 blocks for the latest rows; the last block
+    # of 32-row workgroups (27 key blocks) and the first of 64-row ones (28); eight rounds of the second sweep (48)
+    (28, 4, 128, 0, 330), (28, 4, 128, 100, 330), (28, 4, 128, 160, 330), (28, 4, 128, 161, 330), (16, 4, 64, 333, 512),
+    (16, 4, 64, 333, 513), (28, 4, 128, 1024, 512)])
 def test_scores_of_two_row_tiles(hq, hkv, d, c, n, scale):
     """Scores of the split-key kernel with two row tiles: out of kept weights of both tiles, and a second sweep for the rest."""
-    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, max(c, 1), 512, seed=19 * c + n, scale=scale)
+    assert _rows_of_a_workgroup(n, hq) == (32 if (hq, n) == (16, 512) else 64)
+    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, max(c, 1), max(512, n), seed=19 * c + n, scale=scale)
     assert err <= U.OUT_TOL, err
     scores_gpu, keep, dst = cache.debug_last(0)
     U.check_scores(scores_gpu.cpu().numpy(), scores_ref, n * (hq // hkv))
