@@ -659,12 +659,19 @@ def test_odd_sizes_lockstep():
         cache.close()
 
 
+@pytest.mark.parametrize("shape", [-1, 2])
 @pytest.mark.parametrize("hq,hkv,d,c,n", [(2, 2, 128, 200, 55), (2, 1, 128, 700, 324), (2, 1, 128, 700, 325), (4, 2, 64, 100, 413),
-                                          (2, 1, 64, 1500, 548), (2, 1, 64, 1500, 549)])
-def test_keydiff_scored_by_the_compaction_edges(hq, hkv, d, c, n):
-    """Scores by the keys alone inside the compaction launch: its four and sixteen rows per thread, and the first
-    heads that are too large for it."""
-    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, c, 600, seed=c + n, keydiff=True)
+                                          (2, 1, 64, 1500, 548), (2, 1, 64, 1500, 549),
+                                          # 8, 16 and 24 rows per thread, and one key more
+                                          (2, 2, 128, 200, 56), (2, 2, 128, 200, 57), (2, 1, 128, 400, 112), (2, 1, 128, 400, 113),
+                                          (2, 1, 128, 700, 68), (2, 1, 128, 700, 69), (4, 2, 64, 100, 412), (2, 1, 64, 700, 324),
+                                          (2, 1, 64, 700, 325), (2, 1, 64, 1500, 36), (2, 1, 64, 1500, 37)])
+def test_keydiff_scored_by_the_compaction_edges(hq, hkv, d, c, n, shape):
+    """Scores by the keys alone beside the attention (shape -1: the split-key shapes) and inside the compaction launch (shape 2):
+    each of the up to 32 rows per thread that this is built for, and the first heads that are too large for both."""
+    assert _rows_of_a_workgroup(n, hq) == 32
+    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, c, 600, seed=c + n, keydiff=True, attention_shape=shape)
+    assert err <= U.OUT_TOL, err
     scores_gpu, keep, _ = cache.debug_last(0)
     got = scores_gpu.cpu().numpy().astype(np.float64)
     assert np.abs(got - scores_ref).max() <= 2e-5
