@@ -299,8 +299,10 @@ int kvp_set_score_sweep(kvp_cache* cache, int32_t fused);
  * first -- kvp_compact_layers for up to 16 layers of the range per launch, which
  * is what makes it worth while: these passes are launch-sized for one layer.
  * The result is the same bit for bit.  (A head with few candidates, up to 1024 at
- * head_dim 128 and 2048 at 64, is always scored by its keys inside the compaction
- * launch.)  While a layer waits, its q_obs (and, as
+ * head_dim 128 and 2048 at 64, has no scoring pass by its keys to put off: it is
+ * scored inside the attention launch, on the stream of the call that leaves the layer
+ * PENDING, where a small block's launch has room for that, and inside the compaction
+ * launch otherwise.)  While a layer waits, its q_obs (and, as
  * always, its k and v) must stay valid, and kvp_debug_last has nothing to show
  * for it.  kvp_prefill_block does the same by itself and ignores this setting. */
 int kvp_set_deferred_scoring(kvp_cache* cache, int32_t on);
