@@ -14,7 +14,7 @@ namespace kvp {
 
 constexpr int kSelectBinBits = 11;
 constexpr int kSelectBins = 1 << kSelectBinBits;   // histogram bins of the selection
-constexpr int kSelectFewBinBits = 9;               // ... of 1024 candidates at most
+constexpr int kSelectFewBinBits = 9;               // ... of one with 512 threads (kvp_internal.h: SelectPlan::threads)
 
 template <int kBits>
 struct KeyRangeOf {

@@ -16,7 +16,7 @@
 //     "higher score first, equal scores by lower token index" is "larger key
 //     first" and all keys are distinct: the kept set is unique.  (Token indices that a caller wrote, kvp_set_state, may
 //     repeat; the kernel then still ends and stays inside its memory.)
-//   * the M-th largest key: one histogram of 2048 bins (512 of up to 1024 candidates) over the range the keys really span (a scale on
+//   * the M-th largest key: one histogram of 2048 bins (512 with 512 threads) over the range the keys really span (a scale on
 //     float bits, so roughly logarithmic in the score), the bin that holds it, and then a ranking of
 //     the few keys in that bin by every wave for itself.  Should more than 64 keys share the bin
 //     (equal scores) the range shrinks to the bin and the histogram is taken again (key_range.h).
@@ -43,8 +43,6 @@
 
 namespace kvp {
 
-typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
-
 namespace {
 
 constexpr int kMaxItemsAny = KVP_MAX_CANDIDATES / kSelectThreads;   // 8
@@ -56,8 +54,10 @@ __device__ __forceinline__ unsigned order_bits(float x) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// x / w from the rounded reciprocal of w: the quotient's remainder, which is exact, corrects its last bit (Markstein); the
-// fix-up puts infinities, zeros and NaN right.
+// x / w from the rounded reciprocal of w (Markstein): q is at most 1.5 units of its last place off, and with q's remainder added
+// the last rounding is that of a number within 2^-22 units of x / w.  It goes the way of x / w's own, because w is a whole
+// number, a merge multiplicity: for w up to 2^20 no quotient is that near to the middle of two fp32 numbers.
+// Below 2^-126, where the remainder is rounded, the last fp32 bit may differ.  The fix-up puts infinities, zeros and NaN right.
 __device__ __forceinline__ float divided(float x, float w, float inv) {
   const float q = x * inv;
   return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-q, w, x), inv, q), w, x);
@@ -495,7 +495,7 @@ compact_kernel(const SelectArgs args) {
   float* const staged_w = in_set_of(a.stage_w, a.g, li) + (size_t)hk * a.chunk_max;
 
   if (a.merge) {
-    // ---- merge plan: the e-th evicted candidate (thread e, e + 1024, ...) picks its best kept
+    // ---- merge plan: the e-th evicted candidate (thread e % kThreads) picks its best kept
     // grid neighbour and enters itself there
     for (unsigned e = tid; e < total_ev; e += kThreads) {
       const int p = l.evicted[e];
