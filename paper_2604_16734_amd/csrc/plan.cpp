@@ -13,8 +13,8 @@ namespace kvp {
 // against the four-wave 64-row tiles that used to serve these blocks:
 //   16/4 heads, d 64, 333 rows over 1444 keys   28.4 -> 11.1 us
 //   28/4 heads, d 128, 256 rows over 768 keys   22.7 ->  8.0 us (eight layers per launch)
-//   32/32 heads, d 128, 128 rows over 384 keys  15.1 ->  7.2 us
-//   28/4 heads, d 128, 512 rows over 1536 keys  34.6 -> 26.5 us (64-row workgroups)
+//   32/32 heads, d 128, 128 rows over 384 keys  15.1 ->  8.1 us
+//   28/4 heads, d 128, 512 rows over 1536 keys  34.6 -> 26.9 us (64-row workgroups)
 // The choice depends on one layer's block alone, never on how many layers a launch takes, so that
 // grouped and single launches leave the same bits.
 static int shape_for(int n, int n_q_heads) {
