@@ -18,11 +18,23 @@
 //   S = K(i) Q^T from the K strip, then the load of K(i + 1) into it; P = exp(S - m);
 //   O += P V(i) from the V strip, then the load of V(i + 1).
 // With two row tiles (one from the front of the head, one from the back, for equal work) the waves of a pair need the
-// same blocks: one wave of the pair brings in K and the other V, a round ahead, with one barrier per round.
-// (A software pipeline as in attention.hip -- S(i + 1) and P(i - 1) V(i - 1) among the exponentials of block i --
-// was built and measured slower: a round of two waves per SIMD takes the sum of their matrix and vector time
-// either way, and the pipeline works out one block more per wave.  So was a touch of all the head's cache lines up
-// front: the blocks do not wait for memory.)
+// same blocks: one wave of the pair brings in K and the other V, a round ahead, with one barrier per round.  In round i the
+// products S(i + 1) carry the exponentials of S(i) and the loads between them, and the products with V(i) the maxima of S(i + 1).
+// A round of 64 rows over 128 keys takes 0.94 us (1.2 before that; 28/4 heads, d 128, 512 rows over 1536 keys: 27.0 -> 25.6 us, a launch
+// without scores 14.9 -> 13.6 us, 28/4 heads of d 64 19.0 -> 17.0 us).  The second sweep laid out this way was 2 % slower.  (A software pipeline
+// as in attention.hip, the products with V a round later still, was slower with one row tile; a touch of all the head's cache lines up
+// front gave nothing: the blocks do not wait for memory.)
+//
+// What a wave does for a block beside its products counts as much as they do: it issues one instruction in about five
+// cycles.  Blocks therefore come through buffer descriptors, whose end takes care of a block's missing rows, and their addresses, the
+// blocks that need a mask and the reference's margin are carried along instead of being worked out for each (68 -> 26 scalar
+// instructions per block); and all fragments of a product are asked for before the first of them is used.  16/4 heads, d 64, 333 rows over 1444
+// keys: 11.2 -> 10.4 us; 28/4 heads, d 128, 256 rows over 768 keys: 10.6 -> 10.3 us.
+//
+// The partial results of a row meet in LDS as they lie in the accumulators; a wave's own are written over its own strips, with no barrier
+// in front, and with kept weights a wave puts together one slice of the channels of the rows that its lanes have anyway: 0.3 us of each
+// of these launches, 0.1 us of the 64-row ones, against whole padded rows behind a barrier.
+//
 // Two waves share a SIMD: one has matrix work while the other has vector work.  They start together and would stay
 // in step, both at the same kind of work; a wave therefore raises its priority once its products S are on their way and
 // lowers it at the end of the block, so that the one that is ahead stays ahead (16/4 heads, d 64, 333 rows over 1444
@@ -40,15 +52,15 @@
 // them into the softmax weights of its row, and the column sums run over the lanes: 54 vector instructions per block,
 // where a second sweep takes the keys from L2, the products and the exponentials again.  The kernel is built for each
 // number of kept blocks that its registers have room for (16 each: up to 6 at d 128, 8 at d 64; the unrolled loop also
-// spares the rest).  16/4 heads, d 64, 333 rows over 1444 keys: 13.6 -> 11.4 us per launch; 28/4 heads, d 128, 256 rows over
+// spares the rest).  16/4 heads, d 64, 333 rows over 1444 keys, when it was built: 13.6 -> 11.4 us per launch; 28/4 heads, d 128, 256 rows over
 // 768 keys: 9.6 -> 8.4 us per layer of a grouped launch; 32/32 heads, 128 rows over 384 keys: 8.4 -> 7.8 us.  The
 // scores' error against 64 bits is the same (2e-7 in the root mean square).
 //
 // Second sweep (longer lists; two row tiles, whose waves have more blocks): as in attention.hip, S = Q K^T again
 // with the final normalisers, one key per lane, one partial array of column sums per workgroup.  Query fragments
-// are, register for register, the A operand of this product.  With two row tiles the weights of the first four rounds stay in
+// are, register for register, the A operand of this product.  With two row tiles the weights of the first two rounds (four at d 64) stay in
 // registers all the same, the sums of the two tiles meet in LDS, and the second sweep begins behind them (28/4 heads, d 128,
-// 512 rows over 1536 keys: 27.0 -> 26.4 us; six rounds, with the queries read from LDS every time, 26.6 us).
+// 512 rows over 1536 keys, with no round kept, two, three, four: 26.6, 25.8, 25.8, 26.8 us; more than two spill).
 //
 // plan.cpp has the rule that picks this kernel and what it measured against the tiles of attention.hip.
 #include <type_traits>
@@ -63,7 +75,7 @@ namespace {
 constexpr float kRescueLog2 = 30.f;
 
 // Two row tiles per workgroup: rounds whose weights stay in registers.
-template <int QW> constexpr int kKeptRounds = QW == 2 ? 4 : 0;
+template <int D, int QW> constexpr int kKeptRounds = QW == 1 ? 0 : D == 64 ? 4 : 2;
 
 template <int D, int QW>
 struct Split {
@@ -72,14 +84,10 @@ struct Split {
   static constexpr int kThreads = 64 * kWaves;
   static constexpr int kRows = 32 * QW;
   static constexpr int kStrip = 32 * D;               // bf16 elements of a strip: 32 rows of K or V
-  static constexpr int kORow = D + 4;                 // floats of a partial output row, padded
-  static constexpr int kPartFloats = 32 * kORow;      // partial output of a wave
-  static constexpr int kStripBytes = 2 * kWaves * kStrip * 2;
-  static constexpr int kPartBytes = kWaves * kPartFloats * 4;
-  static constexpr int kMainBytes = kStripBytes > kPartBytes ? kStripBytes : kPartBytes;
+  static constexpr int kMainBytes = 2 * kWaves * kStrip * 2;       // strips; later the partial outputs, a wave's in as much
   static constexpr int kStatBytes = 2 * kWaves * 32 * 4;           // maximum and sum per wave and row
   static constexpr int kQBytes = kRows * D * 2;       // the workgroup's query rows
-  static constexpr int kKeptBytes = kWaves * kKeptRounds<QW> * 32 * 4;     // sums of a wave's rows over its kept blocks
+  static constexpr int kKeptBytes = kWaves * kKeptRounds<D, QW> * 32 * 4;     // sums of a wave's rows over its kept blocks
   static constexpr int kLdsBytes = kMainBytes + kStatBytes + kQBytes + kRows * 4 + kKeptBytes;
   static_assert(kLdsBytes <= 160 * 1024, "LDS of a CU");
 };
@@ -217,26 +225,11 @@ attention_split_kernel(const AttnArgs args) {
   const int ld_sub = lane / kChunks, ld_pos = lane % kChunks;
   const int ld_chunk_k = ld_pos ^ ld_sub, ld_chunk_v = ld_pos ^ v_swizzle<D>(ld_sub);
   // rows [0, rows) at `base`, `stride` elements apart; rows past the end: the last one again
-  auto load_strip = [&](const u16* base, int stride, int rows, u16* strip, bool is_v, int j) __attribute__((always_inline)) {
+  auto load_strip = [&](const u16* base, int stride, int rows, u16* strip, int j) __attribute__((always_inline)) {
     // row kRowsPerLoad j + ld_sub of the strip: its swizzle is the lane's, with bits of j where a row has 16 chunks
-    const int chunk = is_v ? ld_chunk_v : ld_chunk_k ^ ((kRowsPerLoad * j) % kChunks);
+    const int chunk = ld_chunk_k ^ ((kRowsPerLoad * j) % kChunks);
     const int row = min(kRowsPerLoad * j + ld_sub, rows - 1);
     load_row16(base, 2u * (unsigned)(row * stride + 8 * chunk), lds_addr(strip + j * kRowsPerLoad * D));
-  };
-  auto load_block = [&](const u16* cache, const u16* fresh, const Block& b, u16* strip, bool is_v) __attribute__((always_inline)) {
-    const int stride = b.cached ? D : new_stride;
-    const u16* const base = (b.cached ? cache : fresh) + (size_t)b.first * stride;
-    if (b.rows == 32) {
-      const unsigned lane_row = 2u * (unsigned)(ld_sub * stride);
-#pragma unroll
-      for (int j = 0; j < kLoads; ++j) {
-        const int chunk = is_v ? ld_chunk_v : ld_chunk_k ^ ((kRowsPerLoad * j) % kChunks);
-        load_row16(base + (size_t)(kRowsPerLoad * j * stride), lane_row + 16u * (unsigned)chunk, lds_addr(strip + j * kRowsPerLoad * D));
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < kLoads; ++j) load_strip(base, stride, b.rows, strip, is_v, j);
-    }
   };
   auto wait_older_than = [&](auto newest) __attribute__((always_inline)) {   // all but the `newest` latest loads have landed
     constexpr int k = decltype(newest)::value;
@@ -267,34 +260,88 @@ attention_split_kernel(const AttnArgs args) {
   auto mine = [&](int i) __attribute__((always_inline)) { return block_of(ks + KS * i); };
   const int wg_rows_end = min(n, tile_row(QW - 1) + 32);
   const int n_kb = c_blk + (min(a.n_keys, wg_rows_end + shift) + 31) / 32;   // blocks some row of the workgroup sees
-  // Two row tiles share their blocks: the waves (0, ks) and (1, ks) bring in K and V of block (ks, i) for both, a
-  // round of KS blocks ahead, into the half of the strips that the round before has left.
+  // A block comes in through a buffer descriptor that ends with it: rows past its end come as zeros, and so does a block that
+  // does not exist.  What a block needs of scalar work is kept from block to block.
+  // Two row tiles share their blocks: of the waves (0, ks) and (1, ks) one brings in K and the other V for both, a
+  // round of KS blocks ahead, into the strips that the round before has left.
   constexpr bool kShared = QW == 2;
-  auto round_strip = [&](int i, bool is_v) __attribute__((always_inline)) {
-    return reinterpret_cast<u16*>(lds_raw) + ((i & 1) * S::kWaves + (is_v ? KS : 0) + ks) * S::kStrip;
+  const u16* const k_mine = reinterpret_cast<const u16*>(lds_raw) + ks * S::kStrip;      // [2][KS][kStrip], then V's
+  const u16* const v_mine = k_mine + 2 * KS * S::kStrip;
+  const unsigned my_to = lds_addr(qw == 0 ? k_mine : v_mine);
+  const unsigned chunk_k = 16u * (unsigned)ld_chunk_k, chunk_v = 16u * (unsigned)ld_chunk_v;
+  const unsigned my_chunk = qw == 0 ? chunk_k : chunk_v;
+  const unsigned new_bytes = 2u * (unsigned)new_stride;
+  const unsigned lane_cached = (unsigned)ld_sub * (2u * D), lane_fresh = (unsigned)ld_sub * new_bytes;
+  struct Source {
+    u32x4 buffer;
+    unsigned row_bytes, lane;
   };
-  auto load_round = [&](int i) __attribute__((always_inline)) {
-    if (ks + KS * i >= n_kb) return;
-    if (qw == 0) load_block(kc, kn, mine(i), round_strip(i, false), false);
-    else load_block(vc, vn, mine(i), round_strip(i, true), true);
+  // the block that the wave brings in next: where it begins in the cache, and in the block's own rows, which begin where the
+  // cache's blocks end (unsigned arithmetic wraps there and back); the rows from there on
+  unsigned long long cached_at, fresh_at;
+  int cached_left, fresh_left;
+  auto begin_at = [&](int b, int end) __attribute__((always_inline)) {       // block b of those before `end`
+    cached_at = 64ull * D * (unsigned)b;
+    fresh_at = 32ull * new_bytes * (unsigned long long)(long long)(b - c_blk);
+    cached_left = c - 32 * b;
+    fresh_left = min(a.n_keys, 32 * (end - c_blk)) - 32 * (b - c_blk);
   };
+  begin_at(ks, kShared ? n_kb : n_blk);
+  auto source_of = [&](const u16* cache, const u16* fresh, unsigned chunk) __attribute__((always_inline)) -> Source {
+    const bool cached = cached_left > 0;
+    unsigned long long in_cache = (unsigned long long)cache + cached_at, in_fresh = (unsigned long long)fresh + fresh_at;
+    asm("" : "+s"(in_cache), "+s"(in_fresh));              // (choices between values, no branch)
+    const unsigned long long base = cached ? in_cache : in_fresh;
+    const int rows = min(cached ? cached_left : fresh_left, 32);
+    const unsigned row_bytes = cached ? 2u * D : new_bytes, bytes = rows > 0 ? (unsigned)(rows - 1) * row_bytes + 2u * D : 0u;
+    // (through the first lane: the compiler would carry the descriptor from round to round in vector registers)
+    return Source{u32x4{(unsigned)__builtin_amdgcn_readfirstlane((unsigned)base),
+                        (unsigned)__builtin_amdgcn_readfirstlane((unsigned)(base >> 32) & 0xFFFFu),
+                        (unsigned)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u},
+                  row_bytes, (cached ? lane_cached : lane_fresh) + chunk};
+  };
+  auto advance = [&]() __attribute__((always_inline)) {                     // KS blocks on
+    cached_at += 64ull * KS * D;
+    fresh_at += 32ull * KS * new_bytes;
+    cached_left -= 32 * KS;
+    fresh_left -= 32 * KS;
+  };
+  // k_bits: all ones for K, whose chunks are swizzled by the row, zero for V
+  auto load_one = [&](const Source& from, int j, unsigned to, unsigned k_bits) __attribute__((always_inline)) {
+    const unsigned lane_bytes = (from.lane ^ (16u * ((kRowsPerLoad * j) % kChunks) & k_bits)) + (unsigned)(kRowsPerLoad * j) * from.row_bytes;
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(lane_bytes), "s"(from.buffer),
+                 "s"(to + 2u * (unsigned)(j * kRowsPerLoad * D)) : "m0", "memory");
+  };
+  auto load_all = [&](const Source& from, unsigned to, unsigned k_bits) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < kLoads; ++j) load_one(from, j, to, k_bits);
+  };
+  const unsigned my_bits = qw == 0 ? ~0u : 0u;
 
   // the workgroup's query rows (each wave brings in its share), the wave's first block
   for (int j = wave; j < QW * kLoads; j += S::kWaves) {
     const int first_row = tile_row(j / kLoads);                // rows past the block are computed, not stored
     load_strip(q_rows + ((size_t)min(first_row, n - 1) * a.n_q_heads + h) * D, a.n_q_heads * D, max(min(32, n - first_row), 1),
-               q_lds + (j / kLoads) * S::kStrip, false, j % kLoads);
+               q_lds + (j / kLoads) * S::kStrip, j % kLoads);
   }
+  Source shared_next;                        // (two row tiles)
+  auto next_shared = [&]() __attribute__((always_inline)) {
+    advance();
+    shared_next = source_of(qw == 0 ? kc : vc, qw == 0 ? kn : vn, my_chunk);
+  };
   if constexpr (kShared) {
-    load_round(0);
-    if (ks < n_kb) wait_older_than(OneBlock{});
-    else wait_older_than(None{});
-  } else if (my_blk > 0) {
-    load_block(kc, kn, mine(0), k_strip, false);
-    load_block(vc, vn, mine(0), v_strip, true);
-    wait_older_than(TwoBlocks{});
+    load_all(source_of(qw == 0 ? kc : vc, qw == 0 ? kn : vn, my_chunk), my_to, my_bits);       // K(0) or V(0)
+    next_shared();
+    if (qw == 0) {
+      load_all(shared_next, my_to + 2u * (unsigned)(KS * S::kStrip), my_bits);                 // K(1)
+      next_shared();
+    }
+    wait_older_than(OneBlock{});
   } else {
-    wait_older_than(None{});
+    load_all(source_of(kc, kn, chunk_k), lds_addr(k_strip), ~0u);
+    load_all(source_of(vc, vn, chunk_v), lds_addr(v_strip), 0u);
+    advance();
+    wait_older_than(TwoBlocks{});
   }
   __builtin_amdgcn_s_barrier();              // the query rows are in LDS
   asm volatile("" ::: "memory");
@@ -307,6 +354,40 @@ attention_split_kernel(const AttnArgs args) {
   for (int dt = 0; dt < kND; ++dt) o[dt] = zero;
   float m_ref = -INFINITY, l_run = 0.f;
   const float rescue_raw = kRescueLog2 / sl2;              // the margin in units of the raw dot product
+  float limit = -INFINITY, neg = 0.f;        // m_ref + rescue_raw; -m_ref in the exponent, 0 while the row has seen nothing
+  // of this wave's blocks: the part block of the cache, if it has that one; the first of which some row may not see some key
+  const int part_blk = c % 32 != 0 && (c_blk - 1 - ks) % KS == 0 ? (c_blk - 1 - ks) / KS : -1;
+  const int edge = c_blk + min((q0 + shift + 1) / 32, a.n_keys / 32) - ks;
+  const int edge_blk = edge > 0 ? (edge + KS - 1) / KS : 0;
+  auto max_of = [&](const f32x16& x) __attribute__((always_inline)) {
+    float m = x[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) m = fmaxf(m, x[r]);
+    return max_with_other_half(m);
+  };
+  // hides what the rows of the tile may not see of block i
+  auto hide = [&](int i, f32x16& s) __attribute__((always_inline)) {
+    const Block b = mine(i);
+    const int last = b.cached ? b.rows - 1 : min(b.rows - 1, q0 + l32 + shift - b.first);
+    const int lim = last - 4 * g;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = (8 * (r >> 2) + (r & 3) <= lim) ? s[r] : -INFINITY;
+  };
+  // a new reference at block i for rows whose maximum is far above it, or which see their first key
+  auto new_reference = [&](int i, float mx) __attribute__((always_inline)) {
+    const float m_new = fmaxf(m_ref, mx);
+    if (i > 0) {
+      const float f = m_ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_ref - m_new) * sl2);
+      l_run *= f;
+#pragma unroll
+      for (int dt = 0; dt < kND; ++dt)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[dt][r] *= f;
+    }
+    m_ref = m_new;
+    limit = m_ref + rescue_raw;
+    neg = -(m_ref == -INFINITY ? 0.f : m_ref) * sl2;
+  };
 
   auto p_frag = [](const unsigned (&p)[8], int mm) __attribute__((always_inline)) {
     const u32x4 pw = {p[4 * mm], p[4 * mm + 1], p[4 * mm + 2], p[4 * mm + 3]};
@@ -314,38 +395,18 @@ attention_split_kernel(const AttnArgs args) {
   };
   // block i of this wave, K and V in LDS; k_read runs when K has been read, v_wait before V is
   auto attend = [&](int i, const u16* k_from, const u16* v_from, float (&p)[16], auto&& k_read, auto&& v_wait) __attribute__((always_inline)) {
-    const Block b = mine(i);
     f32x16 s;
     bf16x8 kf[kNK];
 #pragma unroll
     for (int st = 0; st < kNK; ++st) kf[st] = lds_read_b128(k_from + k_off[st]);
+    __builtin_amdgcn_sched_barrier(0);       // all on their way before the first product
 #pragma unroll
     for (int st = 0; st < kNK; ++st) s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[st], qf[st], st == 0 ? zero : s, 0, 0, 0);
-    if constexpr (!kShared) __builtin_amdgcn_s_setprio(1);
+    __builtin_amdgcn_s_setprio(1);
     k_read();
-    if (b.rows < 32 || (!b.cached && b.first + 31 > q0 + shift)) {         // some row may not see some key
-      const int last = b.cached ? b.rows - 1 : min(b.rows - 1, q0 + l32 + shift - b.first);
-      const int lim = last - 4 * g;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s[r] = (8 * (r >> 2) + (r & 3) <= lim) ? s[r] : -INFINITY;
-    }
-    float mx = s[0];
-#pragma unroll
-    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-    mx = max_with_other_half(mx);
-    if (__any(mx > m_ref + rescue_raw || (m_ref == -INFINITY && mx > -INFINITY))) {
-      const float m_new = fmaxf(m_ref, mx);
-      if (i > 0) {
-        const float f = m_ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m_ref - m_new) * sl2);
-        l_run *= f;
-#pragma unroll
-        for (int dt = 0; dt < kND; ++dt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[dt][r] *= f;
-      }
-      m_ref = m_new;
-    }
-    const float neg = -(m_ref == -INFINITY ? 0.f : m_ref) * sl2;
+    if (i >= edge_blk || i == part_blk) hide(i, s);
+    const float mx = max_of(s);
+    if (__any(mx > limit)) new_reference(i, mx);
     unsigned pw[8];
     float sum = 0.f;
     auto weigh_pair = [&](int k) __attribute__((always_inline)) {
@@ -363,6 +424,7 @@ attention_split_kernel(const AttnArgs args) {
       vf[dt] = lds_read_vt(v_from + v_off[dt], 8 * D);
       vf[kND + dt] = lds_read_vt(v_from + v_off[dt] + 16 * D, 8 * D);
     }
+    __builtin_amdgcn_sched_barrier(0);
     // the products with the first sixteen keys run beside the exponentials of the other sixteen
 #pragma unroll
     for (int dt = 0; dt < kND; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[dt], p_frag(pw, 0), o[dt], 0, 0, 0);
@@ -371,26 +433,116 @@ attention_split_kernel(const AttnArgs args) {
 #pragma unroll
     for (int dt = 0; dt < kND; ++dt) o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kND + dt], p_frag(pw, 1), o[dt], 0, 0, 0);
     l_run += sum;
-    if constexpr (!kShared) __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_s_setprio(0);
   };
   float kept[kKept > 0 ? kKept : 1][16], kept_m[kKept > 0 ? kKept : 1];      // weights against the references kept_m
   if constexpr (kShared) {
+    // Round i: S(i + 1) = K(i + 1) Q^T with the exponentials of S(i) between the products, then O += P(i) V(i).
+    constexpr int kNV = 2 * kND;
+    constexpr int kAhead = D / 32;           // fragments read ahead of their product
+    f32x16 s2[2];
+    float mx;                                // of the row's logits in the block that comes next
+    auto phase = [&](int i, auto parity, float (&p)[16]) __attribute__((always_inline)) {
+      constexpr int par = decltype(parity)::value;
+      f32x16& s = s2[par];
+      f32x16& s_new = s2[par ^ 1];
+      unsigned pw[8];
+      const u16* const kt = k_mine + (par ^ 1) * KS * S::kStrip;
+      const u16* const vt = v_mine + par * KS * S::kStrip;
+      bf16x8 kfr[kNK], vfr[kNV];
+      auto read_k = [&](int st) __attribute__((always_inline)) { kfr[st] = lds_read_b128(kt + k_off[st]); };
+      auto read_v = [&](int vi) __attribute__((always_inline)) { vfr[vi] = lds_read_vt(vt + v_off[vi % kND] + 16 * (vi / kND) * D, 8 * D); };
+#pragma unroll
+      for (int st = 0; st < kAhead; ++st) read_k(st);
+      __builtin_amdgcn_sched_barrier(0);
+      if (i >= edge_blk || i == part_blk) {
+        hide(i, s);
+        mx = max_of(s);
+      }
+      if (__any(mx > limit)) new_reference(i, mx);
+      __builtin_amdgcn_sched_barrier(0);
+      float sum = 0.f, arg = __builtin_fmaf(s[0], sl2, neg), pe1 = 0.f, pe2 = 0.f;
+      auto finish_element = [&](int e) __attribute__((always_inline)) {      // element e: pe1, the one before: pe2
+        sum += pe1;
+        asm volatile("" : "+v"(sum));
+        p[e] = pe1;
+        if (e & 1) pw[e >> 1] = pack_bf16(pe2, pe1);
+      };
+      auto weigh = [&](int from, int end) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = from; e < end; ++e) {
+          const float pe = __builtin_amdgcn_exp2f(arg);
+          if (e + 1 < 16) arg = __builtin_fmaf(s[e + 1], sl2, neg);
+          if (e >= 1) finish_element(e - 1);
+          pe2 = pe1;
+          pe1 = pe;
+        }
+      };
+#pragma unroll
+      for (int st = 0; st < kNK; ++st) {
+        if (st + kAhead < kNK) read_k(st + kAhead);
+        else read_v(st + kAhead - kNK);
+        s_new = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[st], qf[st], st == 0 ? zero : s_new, 0, 0, 0);
+        weigh(10 * st / kNK, 10 * (st + 1) / kNK);
+        if (st < kLoads) load_one(shared_next, st, my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      float m = -INFINITY;
+#pragma unroll
+      for (int vi = 0; vi < kNV; ++vi) {
+        if (vi + kAhead < kNV) read_v(vi + kAhead);
+        o[vi % kND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[vi], p_frag(pw, vi / kND), o[vi % kND], 0, 0, 0);
+        if (vi < kND) {                      // beside the products with the first sixteen keys
+          weigh(10 + 6 * vi / kND, 10 + 6 * (vi + 1) / kND);
+          if (vi == kND - 1) finish_element(15);
+        } else {
+          if (vi == kND) next_shared();
+#pragma unroll
+          for (int r = 16 * (vi - kND) / kND; r < 16 * (vi - kND + 1) / kND; r += 2) m = fmaxf(fmaxf(m, s_new[r]), s_new[r + 1]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      l_run += sum;
+      mx = max_with_other_half(m);
+    };
     const int n_rounds = (n_kb + KS - 1) / KS;
-    auto round = [&](int i, float (&p)[16]) __attribute__((always_inline)) {
-      wait_older_than(None{});               // this wave's share of round i has landed
+    auto round = [&](int i, auto parity, float (&p)[16]) __attribute__((always_inline)) {
+      wait_older_than(None{});               // this wave's share of the blocks has landed
       __builtin_amdgcn_s_barrier();          // everybody's has, and everybody is done with round i - 1
       asm volatile("" ::: "memory");
-      load_round(i + 1);
-      if (i < my_blk) attend(i, round_strip(i, false), round_strip(i, true), p, [] {}, [] {});
+      if (i < my_blk) {
+        phase(i, parity, p);
+      } else {
+        constexpr int par = decltype(parity)::value;
+#pragma unroll
+        for (int j = 0; j < kLoads; ++j) load_one(shared_next, j, my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
+        next_shared();
+      }
     };
+    typedef std::integral_constant<int, 0> Even;
+    typedef std::integral_constant<int, 1> Odd;
+    {                                        // S(0), with nothing beside it
+      bf16x8 kfr[kNK];
+#pragma unroll
+      for (int st = 0; st < kNK; ++st) kfr[st] = lds_read_b128(k_mine + k_off[st]);
+#pragma unroll
+      for (int st = 0; st < kNK; ++st) s2[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[st], qf[st], st == 0 ? zero : s2[0], 0, 0, 0);
+      mx = max_of(s2[0]);
+    }
 #pragma unroll
     for (int i = 0; i < kKept; ++i)
       if (i < n_rounds) {
-        round(i, kept[i]);
+        if (i & 1) round(i, Odd{}, kept[i]);
+        else round(i, Even{}, kept[i]);
         kept_m[i] = m_ref;
       }
+    constexpr int kFrom = kKept > 0 ? kKept : 0;
     float p[16];
-    for (int i = kKept > 0 ? kKept : 0; i < n_rounds; ++i) round(i, p);
+    for (int i = kFrom; i < n_rounds; i += 2) {
+      round(i, std::integral_constant<int, kFrom & 1>{}, p);
+      if (i + 1 < n_rounds) round(i + 1, std::integral_constant<int, (kFrom & 1) ^ 1>{}, p);
+    }
+    wait_older_than(None{});
   } else {
     auto step = [&](int i, float (&p)[16]) __attribute__((always_inline)) {
       const bool more = i + 1 < my_blk;
@@ -398,14 +550,15 @@ attention_split_kernel(const AttnArgs args) {
       attend(i, k_strip, v_strip, p,
              [&]() __attribute__((always_inline)) {
                __builtin_amdgcn_s_waitcnt(0xC07F);         // the strip has been read
-               if (more) load_block(kc, kn, mine(i + 1), k_strip, false);
+               if (more) load_all(source_of(kc, kn, chunk_k), lds_addr(k_strip), ~0u);
              },
              [&]() __attribute__((always_inline)) {
                if (more) wait_older_than(OneBlock{});      // V(i) is in its strip; K(i + 1) may still be on its way
                else wait_older_than(None{});
              });
       __builtin_amdgcn_s_waitcnt(0xC07F);    // the strip has been read
-      if (more) load_block(vc, vn, mine(i + 1), v_strip, true);
+      if (more) load_all(source_of(vc, vn, chunk_v), lds_addr(v_strip), 0u);
+      advance();
     };
     if constexpr (kKept > 0) {
 #pragma unroll
@@ -420,66 +573,78 @@ attention_split_kernel(const AttnArgs args) {
     }
   }
 
-  // ---- merge the KS partial results of every row through LDS
+  // ---- merge the KS partial results of every row through LDS, as they lie in the accumulators: the channels are cut into KS
+  // slices, every wave leaves its part of all of them (one row tile: in its own strips, with nobody to wait for) and adds up one
+  // slice over the waves of its tile
+  constexpr int kSlice = 16 * kND / KS;      // registers of a slice
+  wait_older_than(None{});                   // (the block after the last one does not exist, but is asked for)
+  auto slice_at = [&](int of_wave, int sl) __attribute__((always_inline)) {
+    return reinterpret_cast<f32x4*>(reinterpret_cast<u16*>(lds_raw) + (of_wave + (sl < KS / 2 ? 0 : S::kWaves)) * S::kStrip) +
+           (sl % (KS / 2)) * (kSlice / 4) * 64 + lane;
+  };
   l_run = sum_with_other_half(l_run);        // lanes l and l + 32 each summed half of the keys of a row
-  __syncthreads();                           // nobody needs the strips any more
-  {
-    float* const part_o = reinterpret_cast<float*>(lds_raw) + wave * S::kPartFloats + l32 * S::kORow + 4 * g;
+  if constexpr (kShared) __syncthreads();    // nobody needs the strips any more
 #pragma unroll
-    for (int dt = 0; dt < kND; ++dt)
+  for (int sl = 0; sl < KS; ++sl) {
+    f32x4* const to = slice_at(wave, sl);
 #pragma unroll
-      for (int j = 0; j < 4; ++j)
-        *reinterpret_cast<f32x4*>(part_o + 32 * dt + 8 * j) = f32x4{o[dt][4 * j], o[dt][4 * j + 1], o[dt][4 * j + 2], o[dt][4 * j + 3]};
-    if (g == 0) {
-      stat_m[wave * 32 + l32] = m_ref;
-      stat_l[wave * 32 + l32] = l_run;
+    for (int k = 0; k < kSlice / 4; ++k) {
+      const int r = sl * kSlice + 4 * k;
+      to[64 * k] = f32x4{o[r / 16][r % 16], o[r / 16][r % 16 + 1], o[r / 16][r % 16 + 2], o[r / 16][r % 16 + 3]};
     }
+  }
+  if (g == 0) {
+    stat_m[wave * 32 + l32] = m_ref;
+    stat_l[wave * 32 + l32] = l_run;
   }
   const bool score = kKept != kScoreByKeys && a.partial != nullptr;
   __syncthreads();
+  float lse_row;                             // of row l32 of the wave's tile
   {
-    constexpr int kPerRow = S::kThreads / S::kRows;        // threads that put a row together
-    constexpr int kCh = D / kPerRow;                       // channels of each
-    static_assert(kCh % 4 == 0, "four floats at a time");
-    const int row = tid / kPerRow, ch0 = (tid % kPerRow) * kCh;
-    const int first_wave = (row / 32) * KS, r = row % 32;
-    float m = -INFINITY;
+    float m = -INFINITY, l = 0.f, f[KS];
 #pragma unroll
-    for (int s = 0; s < KS; ++s) m = fmaxf(m, stat_m[(first_wave + s) * 32 + r]);
-    float f[KS], l = 0.f;
+    for (int s = 0; s < KS; ++s) m = fmaxf(m, stat_m[(qw * KS + s) * 32 + l32]);
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      f[s] = __builtin_amdgcn_exp2f((stat_m[(first_wave + s) * 32 + r] - m) * sl2);    // 0 for a wave that saw nothing
-      l += stat_l[(first_wave + s) * 32 + r] * f[s];
+      f[s] = __builtin_amdgcn_exp2f((stat_m[(qw * KS + s) * 32 + l32] - m) * sl2);       // 0 for a wave that saw nothing
+      l += stat_l[(qw * KS + s) * 32 + l32] * f[s];
     }
-    const float inv = 1.f / l;
-    float acc[kCh];
+    lse_row = m * sl2 + __builtin_log2f(l);
+    f32x4 acc[kSlice / 4];
 #pragma unroll
-    for (int k = 0; k < kCh; ++k) acc[k] = 0.f;
+    for (int k = 0; k < kSlice / 4; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      const float* const from = reinterpret_cast<const float*>(lds_raw) + (first_wave + s) * S::kPartFloats + r * S::kORow + ch0;
+      const f32x4* const from = slice_at(qw * KS + s, ks);
 #pragma unroll
-      for (int k = 0; k < kCh; k += 4) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(from + k);
+      for (int k = 0; k < kSlice / 4; ++k) {
+        const f32x4 v = from[64 * k];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[k + e] += f[s] * v[e];
+        for (int e = 0; e < 4; ++e) acc[k][e] += f[s] * v[e];
       }
     }
-    const int orow = tile_row(row / 32) + row % 32;
-    const float lse_row = m * sl2 + __builtin_log2f(l);
-    if (tid % kPerRow == 0) {
-      lse_lds[row] = lse_row;
+    const int orow = q0 + l32;
+    if (ks == 0 && g == 0) {
+      lse_lds[32 * qw + l32] = lse_row;
       if (orow < n) lse2[(size_t)h * a.lse_stride + orow] = lse_row;
     }
-    if (orow < n && out_rows != nullptr) {
-      u16* const dst = out_rows + ((size_t)orow * a.n_q_heads + h) * D + ch0;
+    if (out_rows != nullptr) {
+      // registers 4 k .. 4 k + 3 of the slice are channels 8 k + 4 g .. + 3 of its 2 kSlice; of two neighbouring fours the
+      // halves of the wave exchange one, and each lane has eight channels in a row
+      const float inv = 1.f / l;
+      u16* const dst = out_rows + ((size_t)min(orow, n - 1) * a.n_q_heads + h) * D + 2 * kSlice * ks;
+      u32x2 pk[kSlice / 4];
 #pragma unroll
-      for (int k = 0; k < kCh; k += 4) {
-        u32x2 pk;
-        pk.x = pack_bf16(acc[k] * inv, acc[k + 1] * inv);
-        pk.y = pack_bf16(acc[k + 2] * inv, acc[k + 3] * inv);
-        *reinterpret_cast<u32x2*>(dst + k) = pk;
+      for (int k = 0; k < kSlice / 4; ++k) pk[k] = u32x2{pack_bf16(acc[k][0] * inv, acc[k][1] * inv), pack_bf16(acc[k][2] * inv, acc[k][3] * inv)};
+      if constexpr (kSlice == 4) {
+        if (orow < n) *reinterpret_cast<u32x2*>(dst + 4 * g) = pk[0];
+      } else {
+#pragma unroll
+        for (int k = 0; k < kSlice / 4; k += 2) {
+          const auto x = __builtin_amdgcn_permlane32_swap(pk[k].x, pk[k + 1].x, false, false);
+          const auto y = __builtin_amdgcn_permlane32_swap(pk[k].y, pk[k + 1].y, false, false);
+          if (orow < n) *reinterpret_cast<u32x4*>(dst + 8 * (k + g)) = u32x4{x[0], y[0], x[1], y[1]};
+        }
       }
     }
   }
@@ -520,12 +685,6 @@ attention_split_kernel(const AttnArgs args) {
     lse_row = 0.f;
   };
   if constexpr (kKept > 0 && QW == 1) {
-    float m = -INFINITY, l = 0.f;
-#pragma unroll
-    for (int s = 0; s < KS; ++s) m = fmaxf(m, stat_m[s * 32 + l32]);
-#pragma unroll
-    for (int s = 0; s < KS; ++s) l += stat_l[s * 32 + l32] * __builtin_amdgcn_exp2f((stat_m[s * 32 + l32] - m) * sl2);
-    float lse_row = m * sl2 + __builtin_log2f(l);
     settle_odd_rows(lse_row);
 #pragma unroll
     for (int i = 0; i < kKept; ++i) {
@@ -541,9 +700,9 @@ attention_split_kernel(const AttnArgs args) {
   // its two strips in turn
   __syncthreads();                           // the rows' statistics are in LDS, the partial outputs have been read
   constexpr int kFirst = kKept > 0 ? kKept * KS : 0;       // (two row tiles: those before it are in registers)
-  if (kFirst + wave < n_kb) load_block(kc, kn, block_of(kFirst + wave), k_strip, false);
+  begin_at(kFirst + wave, n_kb);
+  load_all(source_of(kc, kn, chunk_k), lds_addr(k_strip), ~0u);
   if constexpr (kKept > 0) {
-    float lse_row = lse_lds[32 * qw + l32];
     settle_odd_rows(lse_row);
 #pragma unroll
     for (int i = 0; i < kKept; ++i) {
@@ -582,13 +741,9 @@ attention_split_kernel(const AttnArgs args) {
       // (wave-uniform, which the compiler does not see through two loops in a row)
       const int b = __builtin_amdgcn_readfirstlane(at), odd = __builtin_amdgcn_readfirstlane(turn) & 1;
       u16* const strip = k_strip + odd * S::kWaves * S::kStrip;          // k_strip or v_strip
-      u16* const other = k_strip + (1 - odd) * S::kWaves * S::kStrip;
-      if (b + S::kWaves < n_kb) {
-        load_block(kc, kn, block_of(b + S::kWaves), other, false);
-        wait_older_than(OneBlock{});
-      } else {
-        wait_older_than(None{});
-      }
+      begin_at(b + S::kWaves, n_kb);
+      load_all(source_of(kc, kn, chunk_k), lds_addr(k_strip + (1 - odd) * S::kWaves * S::kStrip), ~0u);
+      wait_older_than(OneBlock{});
       bf16x8 kf[kNK];
 #pragma unroll
       for (int st = 0; st < kNK; ++st) kf[st] = lds_read_b128(strip + k_off[st]);
@@ -635,6 +790,7 @@ attention_split_kernel(const AttnArgs args) {
     const int b = sweep(kFirst + wave, min(n_both, n_kb), std::integral_constant<int, 0>{});
     sweep(b, n_kb, std::integral_constant<int, 1>{});
   }
+  wait_older_than(None{});                   // no load into LDS outlives the workgroup
 }
 
 template <int D, int QW, int kKept>
@@ -671,7 +827,7 @@ hipError_t launch_split32(const AttnArgs& a, hipStream_t s) {
 template <int D>
 hipError_t launch_split64(const AttnArgs& a, hipStream_t s) {
   if (a.key_score_wgs > 0) return launch_shape<D, 2, kScoreByKeys>(a, s);
-  return a.partial != nullptr ? launch_shape<D, 2, kKeptRounds<2>>(a, s) : launch_shape<D, 2, 0>(a, s);
+  return a.partial != nullptr ? launch_shape<D, 2, kKeptRounds<D, 2>>(a, s) : launch_shape<D, 2, 0>(a, s);
 }
 template <int D>
 hipError_t prepare_split32() {
@@ -694,8 +850,8 @@ hipError_t prepare_attention_split() {
   if ((e = prepare_split32<128>()) != hipSuccess) return e;
   if ((e = prepare_split32<64>()) != hipSuccess) return e;
   if ((e = prepare_shape<128, 2, 0>()) != hipSuccess) return e;
-  if ((e = prepare_shape<128, 2, kKeptRounds<2>>()) != hipSuccess) return e;
-  if ((e = prepare_shape<64, 2, kKeptRounds<2>>()) != hipSuccess) return e;
+  if ((e = prepare_shape<128, 2, kKeptRounds<128, 2>>()) != hipSuccess) return e;
+  if ((e = prepare_shape<64, 2, kKeptRounds<64, 2>>()) != hipSuccess) return e;
   if ((e = prepare_shape<128, 2, kScoreByKeys>()) != hipSuccess) return e;
   if ((e = prepare_shape<64, 2, 0>()) != hipSuccess) return e;
   return prepare_shape<64, 2, kScoreByKeys>();

@@ -11,10 +11,10 @@ namespace kvp {
 // three rounds of the chip); below that the split-key shapes of attention_split.hip: 32-row workgroups
 // while all of them fit on the chip at once, 64-row ones (half as many) beyond.  Per launch with scores,
 // against the four-wave 64-row tiles that used to serve these blocks:
-//   16/4 heads, d 64, 333 rows over 1444 keys   28.4 -> 11.1 us
-//   28/4 heads, d 128, 256 rows over 768 keys   22.7 ->  8.0 us (eight layers per launch)
-//   32/32 heads, d 128, 128 rows over 384 keys  15.1 ->  8.1 us
-//   28/4 heads, d 128, 512 rows over 1536 keys  34.6 -> 26.9 us (64-row workgroups)
+//   16/4 heads, d 64, 333 rows over 1444 keys   28.4 ->  9.7 us
+//   28/4 heads, d 128, 256 rows over 768 keys   22.7 ->  7.3 us (eight layers per launch)
+//   32/32 heads, d 128, 128 rows over 384 keys  15.1 ->  7.5 us
+//   28/4 heads, d 128, 512 rows over 1536 keys  34.6 -> 25.6 us (64-row workgroups)
 // The choice depends on one layer's block alone, never on how many layers a launch takes, so that
 // grouped and single launches leave the same bits.
 static int shape_for(int n, int n_q_heads) {

@@ -220,6 +220,38 @@ def test_scores_of_two_row_tiles(hq, hkv, d, c, n, scale):
     cache.close()
 
 
+@pytest.mark.parametrize("hq,hkv,d,c,n", [
+    # 32-row workgroups: waves with no block, one, two; the cache's part block first, in between, last of a wave
+    (4, 4, 64, 0, 5), (4, 2, 128, 1, 30), (4, 2, 64, 257, 33), (6, 2, 128, 290, 63), (4, 4, 64, 511, 1),
+    # 64-row workgroups: the part block of the cache in every wave; one, two and three rounds; an odd and an even number of them
+    (28, 4, 128, 0, 293), (28, 4, 128, 31, 300), (28, 4, 128, 33, 300), (32, 32, 128, 65, 290), (16, 4, 64, 97, 530), (28, 4, 64, 129, 330)])
+def test_rows_past_the_end_of_a_block(hq, hkv, d, c, n):
+    """Key blocks of the split-key kernel that end early: what lies behind the cached entries and behind the block's rows in memory is
+    NaN and stays out of outputs and scores."""
+    rng = np.random.default_rng(100 * c + n)
+    cache = K.Cache(1, hq, hkv, d, c + n - 1, n, [Segment(0, 100000, 0)], device=DEV)
+    k_all, v_all, q = _rand_bits(rng, (c + n, hkv, d)), _rand_bits(rng, (c + n, hkv, d)), _rand_bits(rng, (n, hq, d))
+    oc = O.LayerCache(hkv, d, c + n - 1)
+    if c:
+        oc.compact(0, *(O.bf16_bits_to_f64(x[:c]) for x in (k_all, v_all)), np.zeros((hkv, c), dtype=np.float32))
+    U.upload_state(cache, 0, oc)
+    for t in cache.decode_ready(0)[:2]:
+        t[:, c:] = float("nan")
+    cache.set_state(0, c, c)
+    fresh = []
+    for x in (k_all, v_all):
+        wide = torch.full((n + 40, hkv, d), float("nan"), dtype=torch.bfloat16, device=DEV)
+        wide[:n] = U.bits_to_torch(x[c:])
+        fresh.append(wide[:n])
+    out = cache.prefill_chunk(0, c, U.bits_to_torch(q), *fresh)
+    out_ref, scores_ref = oc.attend(c, O.bf16_bits_to_f64(q), O.bf16_bits_to_f64(k_all[c:]), O.bf16_bits_to_f64(v_all[c:]), None)
+    err = U.out_rel_err(U.torch_bf16_to_f64(out), out_ref)
+    assert err <= U.OUT_TOL, err
+    cache.compact(0)
+    U.check_scores(cache.debug_last(0)[0].cpu().numpy(), scores_ref, n * (hq // hkv))
+    cache.close()
+
+
 @pytest.mark.parametrize("fused", [1, 0])
 @pytest.mark.parametrize("hq,hkv,d,c,n,budget,chunk_max,scale", [
     (4, 4, 64, 128, 64, 128, 64, 0.0),
