@@ -43,7 +43,15 @@
 //             and, first thing after the barrier, the loads of K(t+2) and
 //             V(t+1) into the buffers whose last readers were in phase 1.
 // LDS holds two K tiles and two V tiles; one barrier per tile is enough because
-// a buffer is only overwritten in the phase after its last reader.
+// a buffer is only overwritten in the phase after its last reader.  The first K fragments of a phase 1 are read at
+// the end of the phase before it.
+//
+// What stands between the products is kept out of the loop: the tiles come through descriptors that move on by a tile, a load's
+// place in its tile is a scalar, and how many tiles go which way is worked out once (as a search, tile by tile, it took 4500 of a
+// workgroup's 115,000 cycles).  A plain tile takes 2520 cycles, 39 for each matrix instruction of a SIMD, of which the pipe needs 33 (2950 with
+// 110 scalar instructions a tile; a tile with a mask 448 instructions instead of 587).  32/8 heads, d 128, 1024 rows over 3072 keys, one
+// layer: 57.0 -> 53.9 us without scores, 78 -> 75 us with them.  The clock gives part of it back: with this loop and
+// ordinary data the chip draws all the power it may and runs at 1.6 to 2.0 of 2.4 GHz (zeros for data: 46.6 -> 42.6 and 59.2 -> 55.5 us).
 //
 // Softmax reference.  exp(S - m) is exact for ANY per-row reference m as long as
 // nothing overflows, so the fast loop fixes m at the maximum of the row's first
@@ -81,18 +89,15 @@ struct Shape {
   static constexpr int kLoadsPerWave = kTk / kRowGroup;            // per tensor and tile
   static constexpr int kTile = kTk * D;               // bf16 elements of a K or V tile, unpadded
   static constexpr int kTileBytes = 4 * kTile * 2;    // two K and two V buffers
-  static constexpr int kMergeFloats = QT * (D / 32) * 16 * 64 + 2 * QT * 64;  // per wave
-  static constexpr int kMergeBytes = (KS - 1) * QW * kMergeFloats * 4;
-  static constexpr int kStripRow = 2 * D + 16;        // bytes of an output row staged in LDS, padded
-  static constexpr int kEpilogueBytes = kMergeBytes + QW * 32 * kStripRow;
   // at the end of the tile buffers, when the tiles are done with: the finished row statistics of the workgroup's
   // rows for the score sweep, and before them a word per wave (does it want its rows redone)
   static constexpr int kScoreBytes = QW * QT * 32 * 4;
   static constexpr int kFlagBytes = kWaves * 4;
-  static_assert(kEpilogueBytes + kScoreBytes + kFlagBytes <= kTileBytes, "room for the statistics");
-  // and the key strips of the score sweep, one block of 32 keys per wave, at the front
+  // in the K buffers what the waves leave for each other of their partial results, and the key strips of the score sweep, one block
+  // of 32 keys per wave; at the front of the V buffers the waves' row maxima and sums and the half rows that they store
   static constexpr int kStrip = 32 * D;
-  static_assert(kWaves * kStrip * 2 + kScoreBytes + kFlagBytes <= kTileBytes, "strips and statistics");
+  static_assert(kWaves * QT * kStrip * 2 <= kTileBytes / 2, "what the waves leave for each other");
+  static_assert(kWaves * QT * 64 * 4 + kWaves * 32 * D + kScoreBytes + kFlagBytes <= kTileBytes / 2, "statistics and rows");
   static constexpr int kQBytes = kRows * D * 2;       // behind the tiles: the workgroup's query rows, for both sweeps
   static constexpr int kLdsBytes = kTileBytes + kQBytes;
   static_assert(kLdsBytes <= 160 * 1024, "LDS of a CU");
@@ -260,6 +265,39 @@ attention_kernel(const AttnArgs args) {
     }
   }
 
+  // ---- the score sweep's key blocks, blocks of 32 keys that some row of the workgroup sees: they come in whole rows through a strip
+  // of LDS of the wave's own, block i + 1 on its way into it while block i is worked on from registers.  (In operand layout straight from
+  // memory they took a CU's address path at a quarter of its rate.  Statistics to the last sum, 32/8 heads, 1024 rows over 3072
+  // keys: 27.3 -> 24.5 us, a quarter of that from the query rows that are there already; a prefill of 16640 tokens through 32
+  // such layers 36.3 -> 35.1 ms.)
+  const int n_kb = (min(n_cand, c + wg_rows_end + shift) + 31) / 32;
+  u16* const k_strip = lds_k + wave_s * QT * S::kStrip;
+  constexpr int kStripLoads = 32 / S::kRowsPerLoad;
+  const int strip_chunk = ld_pos ^ ld_sub;             // of load 0; load j: bits of j where a row has 16 chunks
+  const unsigned lane_cache = 2u * (unsigned)(ld_sub * D + 8 * strip_chunk);
+  const unsigned lane_new = 2u * (unsigned)(ld_sub * new_stride + 8 * strip_chunk);
+  auto load_keys = [&](int kbi) __attribute__((always_inline)) {
+    const int kb0 = kbi * 32;
+    const bool cached = kb0 + 32 <= c;
+    if (cached || (kb0 >= c && kb0 + 32 <= n_cand)) {
+      const int stride = cached ? D : new_stride;
+      const u16* const base = cached ? kc + (size_t)kb0 * D : kn + (size_t)(kb0 - c) * new_stride;
+      const unsigned lane_off = cached ? lane_cache : lane_new;
+#pragma unroll
+      for (int j = 0; j < kStripLoads; ++j)
+        load16_scalar_base(base + (size_t)(S::kRowsPerLoad * j) * stride, lane_off ^ (16u * ((S::kRowsPerLoad * j) % S::kChunks)),
+                           lds_base + 2u * (unsigned)((int)(k_strip - lds_k) + S::kRowsPerLoad * j * D));
+    } else {
+#pragma unroll
+      for (int j = 0; j < kStripLoads; ++j) {
+        const int kv = min(kb0 + S::kRowsPerLoad * j + ld_sub, n_cand - 1);      // past the end: any real row, never stored
+        const u16* src = kv < c ? kc + (size_t)kv * D : kn + (size_t)(kv - c) * new_stride;
+        load16(src + 8 * (strip_chunk ^ ((S::kRowsPerLoad * j) % S::kChunks)),
+               lds_base + 2u * (unsigned)((int)(k_strip - lds_k) + S::kRowsPerLoad * j * D));
+      }
+    }
+  };
+
   // ================================================================ fast path
   bool redo = false;
   {
@@ -327,13 +365,15 @@ attention_kernel(const AttnArgs args) {
     //   s_exp -> p_out   P = exp2((S - m) * scale) for the block whose scores are ready
     //   s_new            S^T of the next block = K[kt rows] Q^T
     //   p_pend, vt       O^T += V^T P^T for the block exponentiated one phase ago
+    //   first            the first K fragments, read already where kHave; with kNext those of the next phase at the end
+    constexpr int kAhead = D / 32;
+    bf16x8 first[kAhead];
     auto phase_core = [&](const f32x16 (&s_exp)[QT], unsigned (&p_out)[QT][8], f32x16 (&s_new)[QT],
-                          const u16* kt, const unsigned (&p_pend)[QT][8], const u16* vt, auto&& after_mfma)
-        __attribute__((always_inline)) {
+                          const u16* kt, const unsigned (&p_pend)[QT][8], const u16* vt, auto have, auto next, const u16* next_kt,
+                          auto&& after_mfma) __attribute__((always_inline)) {
+      constexpr bool kHave = decltype(have)::value, kNext = decltype(next)::value;
       constexpr int kNK = D / 16;            // K fragments
       constexpr int kNV = (D / 32) * 2;      // V^T fragments
-      constexpr int kAhead = D / 32;
-      constexpr int kPerMfma = 128 / D;      // elements exponentiated per MFMA
       float neg[QT], sum[QT];
 #pragma unroll
       for (int t = 0; t < QT; ++t) {
@@ -350,7 +390,7 @@ attention_kernel(const AttnArgs args) {
       // pack) and an instruction that needs the result of the one before it stalls the wave, the
       // exponential most of all.  So the chain is skewed over the MFMAs: each call computes the
       // argument of the next element, the exponential of this one, and adds and packs the one before.
-      constexpr int kElems = QT * 16;
+      constexpr int kElems = QT * 16, kMfmas = QT * (kNK + kNV);
       int ei = 0;   // next element to exponentiate
       float arg = __builtin_fmaf(s_exp[0][0], sl2, neg[0]), pe1 = 0.f, pe2 = 0.f;
       auto finish_element = [&](int e) __attribute__((always_inline)) {      // element e: pe1, the one before: pe2
@@ -361,9 +401,9 @@ attention_kernel(const AttnArgs args) {
         asm volatile("" : "+v"(sum[t]));
         if (r & 1) p_out[t][r >> 1] = pack_bf16(pe2, pe1);
       };
-      auto exp_some = [&]() __attribute__((always_inline)) {
+      auto exp_until = [&](int end) __attribute__((always_inline)) {
 #pragma unroll
-        for (int k = 0; k < kPerMfma; ++k, ++ei) {
+        for (; ei < end; ++ei) {
           const float pe = __builtin_amdgcn_exp2f(arg);
           if (ei + 1 < kElems) arg = __builtin_fmaf(s_exp[(ei + 1) / 16][(ei + 1) % 16], sl2, neg[(ei + 1) / 16]);
           if (ei >= 1) finish_element(ei - 1);
@@ -373,8 +413,12 @@ attention_kernel(const AttnArgs args) {
       };
       const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int st = 0; st < kAhead; ++st) read_k(st);
+      for (int st = 0; st < kAhead; ++st) {
+        if constexpr (kHave) kfr[st] = first[st];
+        else read_k(st);
+      }
       __builtin_amdgcn_sched_barrier(0);     // all of them before the first MFMA
+      auto share = [&](int i) __attribute__((always_inline)) { exp_until(kElems * (i + 1) / kMfmas); };    // of MFMA i
 #pragma unroll
       for (int st = 0; st < kNK; ++st) {
         if (st + kAhead < kNK) read_k(st + kAhead);
@@ -382,7 +426,7 @@ attention_kernel(const AttnArgs args) {
 #pragma unroll
         for (int t = 0; t < QT; ++t) {
           s_new[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[st], qf[t][st], st == 0 ? zero : s_new[t], 0, 0, 0);
-          exp_some();
+          share(st * QT + t);
           after_mfma(std::integral_constant<int, 0>{}, st * QT + t);
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -390,12 +434,13 @@ attention_kernel(const AttnArgs args) {
 #pragma unroll
       for (int vi = 0; vi < kNV; ++vi) {
         if (vi + kAhead < kNV) read_v(vi + kAhead);
+        else if constexpr (kNext) first[vi + kAhead - kNV] = lds_read_b128(next_kt + k_off[vi + kAhead - kNV]);
         const int dt = vi / 2, mm = vi % 2;
 #pragma unroll
         for (int t = 0; t < QT; ++t) {
           const u32x4 pw = {p_pend[t][4 * mm], p_pend[t][4 * mm + 1], p_pend[t][4 * mm + 2], p_pend[t][4 * mm + 3]};
           o[t][dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[vi], __builtin_bit_cast(bf16x8, pw), o[t][dt], 0, 0, 0);
-          exp_some();
+          share((kNK + vi) * QT + t);
           after_mfma(std::integral_constant<int, 1>{}, vi * QT + t);
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -437,19 +482,45 @@ attention_kernel(const AttnArgs args) {
       }
     }
 
+    // The steady-state tiles that this wave brings in come through descriptors that move on by a tile at a time: K of tile t + 2 and V of
+    // tile t + 1, in the cache or among the block's rows.  A load has its place in the tile in a scalar register.
+    struct TileFeed {
+      u32x4 buffer;
+      unsigned lane, group_bytes;            // the lane's part of an address; bytes from a load's rows to the next load's
+    };
+    auto feed_at = [&](const u16* cache, const u16* fresh, unsigned lane_cache, unsigned lane_new, int t) __attribute__((always_inline)) -> TileFeed {
+      const UniformSrc src = uniform_src(cache, fresh, t);
+      const unsigned long long base = (unsigned long long)src.base;
+      return TileFeed{u32x4{(unsigned)base, (unsigned)(base >> 32) & 0xFFFFu, 0xFFFFFFFFu, 0x00020000u}, src.cached ? lane_cache : lane_new,
+                      2u * (unsigned)(S::kRowGroup * src.stride)};
+    };
+    auto move_on = [&](TileFeed& f) __attribute__((always_inline)) {
+      const unsigned long long at = ((unsigned long long)f.buffer.y << 32 | f.buffer.x) + (unsigned long long)f.group_bytes * (S::kTk / S::kRowGroup);
+      f.buffer.x = (unsigned)at;
+      f.buffer.y = (unsigned)(at >> 32);
+    };
+    auto load_fed = [&](const TileFeed& f, int j, unsigned lds_addr) __attribute__((always_inline)) {
+      asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds" ::"v"(f.lane), "s"(f.buffer),
+                   "s"(f.group_bytes * (unsigned)j), "s"(lds_addr)
+                   : "m0", "memory");
+    };
+    TileFeed k_feed, v_feed;
+
     // kTag = t & 1 as a compile-time constant in the steady-state loop, -1 for "use t & 1".
-    // The steady-state loop also knows that the tiles it prefetches are uniform.
-    auto body = [&](int t, auto buf_tag, auto mask, auto track) __attribute__((always_inline)) {
+    // The steady-state loop also knows that the tiles it prefetches are uniform, and has the first K fragments of its first phase.
+    auto body = [&](int t, auto buf_tag, auto fed, auto mask, auto track) __attribute__((always_inline)) {
       constexpr int kTag = decltype(buf_tag)::value;
+      constexpr bool kSteady = kTag >= 0, kFed = decltype(fed)::value;
       const int buf = kTag >= 0 ? kTag : (t & 1);
       const int kb = t * S::kTk + ks * 64;
       u16* k_cur = lds_k + buf * S::kTile;
       u16* k_nxt = lds_k + (buf ^ 1) * S::kTile;
       u16* v_cur = lds_v + buf * S::kTile;
       u16* v_prv = lds_v + (buf ^ 1) * S::kTile;
+      typedef std::integral_constant<bool, kSteady> Steady;
       // ---- phase 1: P_X(t), S_Y(t), O += P_Y(t-1) V(t-1)
       prepare(sx, kb, mask, track);
-      phase_core(sx, px, sy, k_cur + blk_off + 32 * D, py, v_prv + blk_off + 32 * D, [](auto, int) {});
+      phase_core(sx, px, sy, k_cur + blk_off + 32 * D, py, v_prv + blk_off + 32 * D, Steady{}, std::false_type{}, nullptr, [](auto, int) {});
       // P_X is only read in phase 2, and the compiler would gladly take its exponentials there,
       // all in a lump behind the barrier: make them due here, in the shadow of this phase's MFMAs
 #pragma unroll
@@ -465,52 +536,64 @@ attention_kernel(const AttnArgs args) {
       constexpr int kPerHalf = QT * (D / 16);              // MFMAs in each half of a phase
       constexpr int kEvery = kPerHalf / S::kLoadsPerWave;  // one load every kEvery MFMAs
       static_assert(kEvery >= 1 && kPerHalf % S::kLoadsPerWave == 0, "loads must fit the phase");
-      if (kTag >= 0) {
-        const UniformSrc k_src = uniform_src(kc, kn, t + 2 < n_tiles ? t + 2 : t);
-        const UniformSrc v_src = uniform_src(vc, vn, t + 1 < n_tiles ? t + 1 : t);
-        const unsigned k_lane = k_src.cached ? lane_k_cache : lane_k_new;
-        const unsigned v_lane = v_src.cached ? lane_v_cache : lane_v_new;
-        phase_core(sy, py, sx, k_nxt + blk_off, px, v_cur + blk_off, [&](auto half, int i) __attribute__((always_inline)) {
-          if (i % kEvery != 0) return;
-          const int j = i / kEvery;
-          if (decltype(half)::value == 0)
-            load16_scalar_base(k_src.base + (size_t)(S::kRowGroup * j) * k_src.stride, k_lane, lds_dst(k_cur, j));
-          else
-            load16_scalar_base(v_src.base + (size_t)(S::kRowGroup * j) * v_src.stride, v_lane, lds_dst(v_prv, j));
-        });
-      } else {
-        phase_core(sy, py, sx, k_nxt + blk_off, px, v_cur + blk_off, [&](auto half, int i) __attribute__((always_inline)) {
-          if (i % kEvery != 0) return;
-          const int j = i / kEvery;
-          if (decltype(half)::value == 0) issue_any_one(kc, kn, k_cur, t + 2, ld_chunk_k, j);
-          else issue_any_one(vc, vn, v_prv, t + 1, ld_chunk_v, j);
-        });
-      }
+      // (behind the last fragments of this phase the first of the next one's, of the tile that the barrier has just published)
+      phase_core(sy, py, sx, k_nxt + blk_off, px, v_cur + blk_off, std::false_type{}, Steady{}, k_nxt + blk_off + 32 * D,
+                 [&](auto half, int i) __attribute__((always_inline)) {
+                   if (i % kEvery != 0) return;
+                   const int j = i / kEvery;
+                   if constexpr (kFed) {
+                     if (decltype(half)::value == 0) load_fed(k_feed, j, lds_dst(k_cur, j));
+                     else load_fed(v_feed, j, lds_dst(v_prv, j));
+                   } else {
+                     if (decltype(half)::value == 0) issue_any_one(kc, kn, k_cur, t + 2, ld_chunk_k, j);
+                     else issue_any_one(vc, vn, v_prv, t + 1, ld_chunk_v, j);
+                   }
+                 });
     };
     typedef std::integral_constant<int, 0> Even;
     typedef std::integral_constant<int, 1> Odd;
     typedef std::integral_constant<int, -1> Any;
-    // The fast body of tile t needs: tile t visible in full to every row of the workgroup, and the
-    // tiles it prefetches (V of t + 1, K of t + 2) uniform, or past the workgroup's last tile (then
-    // it fetches its own tile again, into a buffer nobody reads any more).
-    auto fast_ok = [&](int t) __attribute__((always_inline)) -> bool {
-      return t < n_plain && tile_is_uniform(t + 1 < n_tiles ? t + 1 : t) && tile_is_uniform(t + 2 < n_tiles ? t + 2 : t);
+    // The steady body of tile t needs the tiles that it prefetches (V of t + 1, K of t + 2) uniform, or past the workgroup's last tile
+    // (then it fetches an earlier tile again, into a buffer nobody reads any more).  Not uniform are the tile in which the cache ends and
+    // the block's rows begin, and one that ends past the last key; tile 0 may be either, but where it is fetched again.
+    const int first_new = (c + S::kTk - 1) / S::kTk, part_new = n_cand / S::kTk;
+    int n_fed = my_tiles;          // tiles the steady bodies take
+    if (c % S::kTk != 0 && first_new - 1 < n_tiles && (first_new > 1 || n_tiles <= 2)) n_fed = min(n_fed, max(first_new - 3, 0));
+    if (part_new < n_tiles) n_fed = min(n_fed, max(part_new - 2, 0));
+    if (new_stride >= 1 << 23) n_fed = 0;        // (bytes within a tile are 32-bit numbers)
+    const int n_fast = min(n_plain, n_fed) & ~1;      // of these the ones that every row of the wave sees in full, two at a time
+    // the feed of tile `t`: from the one before it, or, where the block's own rows begin, anew
+    auto next_feed = [&](TileFeed& f, const u16* cache, const u16* fresh, unsigned lane_cache, unsigned lane_new, int t) __attribute__((always_inline)) {
+      if (t >= n_tiles) return;
+      if (t == first_new) f = feed_at(cache, fresh, lane_cache, lane_new, t);
+      else move_on(f);
     };
-    int n_fast = 0;                // tiles the fast bodies take, two at a time
-    while (fast_ok(n_fast) && fast_ok(n_fast + 1)) n_fast += 2;
+    typedef std::true_type Yes;
+    typedef std::false_type No;
     int t = 0;
-    if (n_fast >= 2) {
-      // tile 0 is plain: it gives every row its reference, and nothing after it looks at maxima
-      body(0, Even{}, std::false_type{}, std::true_type{});
-      body(1, Odd{}, std::false_type{}, std::false_type{});
-      t = 2;
+    auto fed_body = [&](auto buf_tag, auto mask, auto track) __attribute__((always_inline)) {
+      body(t, buf_tag, Yes{}, mask, track);
+      ++t;
+      next_feed(k_feed, kc, kn, lane_k_cache, lane_k_new, t + 2);
+      next_feed(v_feed, vc, vn, lane_v_cache, lane_v_new, t + 1);
+    };
+    if (n_fed > 0) {
+      k_feed = feed_at(kc, kn, lane_k_cache, lane_k_new, 2 < n_tiles ? 2 : 0);
+      v_feed = feed_at(vc, vn, lane_v_cache, lane_v_new, 1 < n_tiles ? 1 : 0);
     }
-    for (; t < n_fast; t += 2) {
-      body(t, Even{}, std::false_type{}, std::false_type{});
-      body(t + 1, Odd{}, std::false_type{}, std::false_type{});
+    if (n_fast > 0) {
+#pragma unroll
+      for (int st = 0; st < kAhead; ++st) first[st] = lds_read_b128(lds_k + blk_off + 32 * D + k_off[st]);
+      // tile 0 is plain: it gives every row its reference, and no plain tile after it looks at maxima
+      fed_body(Even{}, No{}, Yes{});
+      fed_body(Odd{}, No{}, No{});
     }
-    for (; t < my_tiles; ++t)      // masking a fully visible tile is harmless
-      body(t, Any{}, std::true_type{}, std::true_type{});
+    while (t < n_fast) {
+      fed_body(Even{}, No{}, No{});
+      fed_body(Odd{}, No{}, No{});
+    }
+    while (t < n_fed) fed_body(Any{}, Yes{}, Yes{});       // masking a fully visible tile is harmless
+    for (; t < my_tiles; ++t) body(t, Any{}, No{}, Yes{}, Yes{});
     {
       // O += P_Y V of this wave's last tile.  That V was published by the barrier inside the last
       // body and is overwritten only after the barrier of the next tile, which this wave has
@@ -543,92 +626,92 @@ attention_kernel(const AttnArgs args) {
     for (int tq = 0; tq < QT; ++tq) redo |= !(l_run[tq] <= 0x1p64f);
     if (__any(redo)) redo = true;
     if (lane == 0) flag_lds[wave] = redo ? 1u : 0u;
-    __syncthreads();               // (the tiles were done with before the barrier above)
+    // ---- merge the two partial results of every row through LDS and store it.  Of a row tile's two waves each finishes half of
+    // the channels: it leaves its part of the other half with the other wave, as it lies in the accumulators.  Where a wave finds what
+    // was left for it its key strip lies too: the first block of the score sweep is on its way while the rows are stored.
+    // (One wave of the two with all of the channels, in single words, and the keys after that: 6870 cycles from the last tile to the
+    // score sweep; this way 5500.)
+    static_assert(KS == 2, "two waves to a row tile");
+    constexpr int kHalf = D / 64;                // channel tiles of a half
+    float* const stat_lds = reinterpret_cast<float*>(lds_v);     // [kWaves][QT][2][32]
+    auto left_for = [&](int w, int tq, int k) __attribute__((always_inline)) {       // fours k of a half
+      return reinterpret_cast<f32x4*>(lds_k + (w * QT + tq) * S::kStrip) + 64 * k + lane;
+    };
+    auto half_of = [&](int tq, int half, int k) __attribute__((always_inline)) -> f32x4 {
+      const f32x16& x = o[tq][half * kHalf + k / 4];
+      const int r = 4 * (k % 4);
+      return f32x4{x[r], x[r + 1], x[r + 2], x[r + 3]};
+    };
+#pragma unroll
+    for (int tq = 0; tq < QT; ++tq) {
+      l_run[tq] = sum_with_other_half(l_run[tq]);            // lanes l and l + 32 each summed half of the keys of a row
+#pragma unroll
+      for (int k = 0; k < 4 * kHalf; ++k) {
+        const f32x4 lo = half_of(tq, 0, k), hi = half_of(tq, 1, k);
+        *left_for(wave_s ^ 1, tq, k) = ks == 0 ? hi : lo;
+      }
+      if (g == 0) {
+        stat_lds[(wave_s * QT + tq) * 64 + l32] = m_ref[tq];
+        stat_lds[(wave_s * QT + tq) * 64 + 32 + l32] = l_run[tq];
+      }
+    }
+    __syncthreads();
     redo = false;                  // workgroup-uniform from here on
 #pragma unroll
     for (int w2 = 0; w2 < S::kWaves; ++w2) redo |= flag_lds[w2] != 0u;
 
     if (!redo) {
-      // lanes l and l + 32 each summed half of the keys of a row
+      f32x4 sum[QT][4 * kHalf];
+      float l_row[QT];
 #pragma unroll
-      for (int tq = 0; tq < QT; ++tq) l_run[tq] = sum_with_other_half(l_run[tq]);
-      // ---- merge the KS partial results of every row through LDS
-      if (KS > 1) {
-        float* mrg = reinterpret_cast<float*>(lds_raw);
-        if (ks > 0) {
-          float* mine = mrg + (size_t)((ks - 1) * QW + qw) * S::kMergeFloats;
+      for (int tq = 0; tq < QT; ++tq) {
+        const float m_other = stat_lds[((wave_s ^ 1) * QT + tq) * 64 + l32], l_other = stat_lds[((wave_s ^ 1) * QT + tq) * 64 + 32 + l32];
+        const float m0 = ks == 0 ? m_ref[tq] : m_other, m1 = ks == 0 ? m_other : m_ref[tq];
+        const float mt = fmaxf(m0, m1), m_use = mt == -INFINITY ? 0.f : mt;
+        const float f0 = __builtin_amdgcn_exp2f((m0 - m_use) * sl2), f1 = __builtin_amdgcn_exp2f((m1 - m_use) * sl2);
+        l_row[tq] = (ks == 0 ? l_run[tq] : l_other) * f0;
+        l_row[tq] += (ks == 0 ? l_other : l_run[tq]) * f1;
 #pragma unroll
-          for (int tq = 0; tq < QT; ++tq) {
+        for (int k = 0; k < 4 * kHalf; ++k) {
+          const f32x4 other = *left_for(wave_s, tq, k), lo = half_of(tq, 0, k), hi = half_of(tq, 1, k);
 #pragma unroll
-            for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-              for (int r = 0; r < 16; ++r)
-                mine[((tq * (D / 32) + dt) * 16 + r) * 64 + lane] = o[tq][dt][r];
-            mine[QT * (D / 32) * 16 * 64 + tq * 64 + lane] = m_ref[tq];
-            mine[QT * (D / 32) * 16 * 64 + (QT + tq) * 64 + lane] = l_run[tq];
+          for (int e = 0; e < 4; ++e) {
+            sum[tq][k][e] = (ks == 0 ? lo[e] : other[e]) * f0;
+            sum[tq][k][e] += f1 * (ks == 0 ? other[e] : hi[e]);
           }
         }
-        __syncthreads();
-        if (ks == 0) {
-#pragma unroll
-          for (int tq = 0; tq < QT; ++tq) {
-            float mt = m_ref[tq];
-            for (int s2 = 1; s2 < KS; ++s2) {
-              const float* other = mrg + (size_t)((s2 - 1) * QW + qw) * S::kMergeFloats;
-              mt = fmaxf(mt, other[QT * (D / 32) * 16 * 64 + tq * 64 + lane]);
-            }
-            const float m_use = (mt == -INFINITY) ? 0.f : mt;
-            const float f0 = __builtin_amdgcn_exp2f((m_ref[tq] - m_use) * sl2);
-            l_run[tq] *= f0;
-#pragma unroll
-            for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-              for (int r = 0; r < 16; ++r) o[tq][dt][r] *= f0;
-            for (int s2 = 1; s2 < KS; ++s2) {
-              const float* other = mrg + (size_t)((s2 - 1) * QW + qw) * S::kMergeFloats;
-              const float ms = other[QT * (D / 32) * 16 * 64 + tq * 64 + lane];
-              const float ls = other[QT * (D / 32) * 16 * 64 + (QT + tq) * 64 + lane];
-              const float fs = __builtin_amdgcn_exp2f((ms - m_use) * sl2);
-              l_run[tq] += ls * fs;
-#pragma unroll
-              for (int dt = 0; dt < D / 32; ++dt)
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                  o[tq][dt][r] += fs * other[((tq * (D / 32) + dt) * 16 + r) * 64 + lane];
-            }
-            m_ref[tq] = mt;
-          }
+        const float lse_row = mt * sl2 + __builtin_log2f(l_row[tq]);
+        const int row = q0 + 32 * tq + l32;
+        if (ks == 0 && g == 0) {
+          lse_lds[(qw * QT + tq) * 32 + l32] = lse_row;
+          if (row < n) lse2[(size_t)h * a.lse_stride + row] = lse_row;
         }
       }
-      // ---- normalise and store; lane holds O[row][32 dt + 8 j + 4 g + 0..3].  The rows go
-      // through a private LDS strip of the wave so that the global stores are whole 16-byte
-      // chunks of consecutive addresses (a row of the output is 2 D contiguous bytes).
-      if (ks == 0) {
-        unsigned char* strip = lds_raw + S::kMergeBytes + (size_t)qw * 32 * S::kStripRow;
+#pragma unroll
+      for (int tq = 0; tq < QT; ++tq)
+#pragma unroll
+        for (int k = 0; k < 4 * kHalf; ++k) asm volatile("" : "+v"(sum[tq][k]));       // what was left has been read
+      if (a.partial != nullptr && wave_s < n_kb) load_keys(wave_s);
+      if (out_rows != nullptr) {
+        // fours k of the half are its channels 8 k + 4 g .. + 3: of two neighbouring ones the halves of the wave exchange one, and each
+        // lane has eight channels in a row; then through LDS, so that the global stores are whole rows of the half.
+        constexpr int kRowChunks = D / 16;         // 16-byte chunks of a half row, swizzled by the row
+        u32x4* const rows = reinterpret_cast<u32x4*>(lds_v) + S::kWaves * QT * 16 + wave_s * 32 * kRowChunks;      // (behind the statistics)
 #pragma unroll
         for (int tq = 0; tq < QT; ++tq) {
-          const int row = q0 + 32 * tq + l32;
-          const float inv = 1.f / l_run[tq];
+          const float inv = 1.f / l_row[tq];
 #pragma unroll
-          for (int dt = 0; dt < D / 32; ++dt)
+          for (int k = 0; k < 4 * kHalf; k += 2) {
+            const f32x4 x = sum[tq][k], y = sum[tq][k + 1];
+            const auto lo = __builtin_amdgcn_permlane32_swap(pack_bf16(x[0] * inv, x[1] * inv), pack_bf16(y[0] * inv, y[1] * inv), false, false);
+            const auto hi = __builtin_amdgcn_permlane32_swap(pack_bf16(x[2] * inv, x[3] * inv), pack_bf16(y[2] * inv, y[3] * inv), false, false);
+            rows[l32 * kRowChunks + ((k + g) ^ (l32 % kRowChunks))] = u32x4{lo[0], hi[0], lo[1], hi[1]};
+          }
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              u32x2 pk;
-              pk.x = pack_bf16(o[tq][dt][4 * j] * inv, o[tq][dt][4 * j + 1] * inv);
-              pk.y = pack_bf16(o[tq][dt][4 * j + 2] * inv, o[tq][dt][4 * j + 3] * inv);
-              *reinterpret_cast<u32x2*>(strip + l32 * S::kStripRow + 2 * (32 * dt + 8 * j + 4 * g)) = pk;
-            }
-          const float lse_row = m_ref[tq] * sl2 + __builtin_log2f(l_run[tq]);
-          if (g == 0) lse_lds[(qw * QT + tq) * 32 + l32] = lse_row;
-          if (g == 0 && row < n) lse2[(size_t)h * a.lse_stride + row] = lse_row;
-#pragma unroll
-          for (int it = 0; it < D / 16; ++it) {
-            const int idx = it * 64 + lane;
-            const int r = idx / (D / 8), ch = idx % (D / 8);
-            const u32x4 val = *reinterpret_cast<const u32x4*>(strip + r * S::kStripRow + 16 * ch);
-            const int orow = q0 + 32 * tq + r;
-            if (orow < n && out_rows != nullptr)
-              *reinterpret_cast<u32x4*>(out_rows + ((size_t)orow * a.n_q_heads + h) * D + 8 * ch) = val;
+          for (int it = 0; it < kRowChunks / 2; ++it) {
+            const int r = (64 * it + lane) / kRowChunks, ch = lane % kRowChunks, row = q0 + 32 * tq + r;
+            const u32x4 val = rows[r * kRowChunks + (ch ^ (r % kRowChunks))];
+            if (row < n) *reinterpret_cast<u32x4*>(out_rows + ((size_t)row * a.n_q_heads + h) * D + (D / 2) * ks + 8 * ch) = val;
           }
         }
       }
@@ -747,43 +830,10 @@ attention_kernel(const AttnArgs args) {
     constexpr int kRowTiles = QW * QT;
     static_assert(kRowTiles % 2 == 0, "the two accumulator sets alternate over the row tiles");
     __syncthreads();               // the statistics are in LDS; nobody needs the tile buffers any more
-    // blocks of 32 keys that some row of the workgroup sees
-    const int n_kb = (min(n_cand, c + wg_rows_end + shift) + 31) / 32;
     const int split = (h - hk * group) * a.n_row_tiles + rt;
     float* const part = in_set_of(a.partial, a.g, li) + (size_t)hk * a.partial_stride + (size_t)split * a.cand_stride;
     const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-    // ---- a wave's key blocks come in whole rows through a strip of LDS of its own: block i + 1 is on its way into
-    // it while block i is worked on from registers.  (In operand layout straight from memory they took a CU's address
-    // path at a quarter of its rate.  Statistics to the last sum, 32/8 heads, 1024 rows over 3072 keys: 27.3 -> 24.5 us,
-    // a quarter of that from the query rows that are there already; a prefill of 16640 tokens through 32
-    // such layers 36.3 -> 35.1 ms.)
-    u16* const k_strip = lds_k + wave_s * S::kStrip;
-    constexpr int kStripLoads = 32 / S::kRowsPerLoad;
-    const int strip_chunk = ld_pos ^ ld_sub;           // of load 0; load j: bits of j where a row has 16 chunks
-    const unsigned lane_cache = 2u * (unsigned)(ld_sub * D + 8 * strip_chunk);
-    const unsigned lane_new = 2u * (unsigned)(ld_sub * new_stride + 8 * strip_chunk);
-    auto load_keys = [&](int kbi) __attribute__((always_inline)) {
-      const int kb0 = kbi * 32;
-      const bool cached = kb0 + 32 <= c;
-      if (cached || (kb0 >= c && kb0 + 32 <= n_cand)) {
-        const int stride = cached ? D : new_stride;
-        const u16* const base = cached ? kc + (size_t)kb0 * D : kn + (size_t)(kb0 - c) * new_stride;
-        const unsigned lane_off = cached ? lane_cache : lane_new;
-#pragma unroll
-        for (int j = 0; j < kStripLoads; ++j)
-          load16_scalar_base(base + (size_t)(S::kRowsPerLoad * j) * stride, lane_off ^ (16u * ((S::kRowsPerLoad * j) % S::kChunks)),
-                             lds_base + 2u * (unsigned)((int)(k_strip - lds_k) + S::kRowsPerLoad * j * D));
-      } else {
-#pragma unroll
-        for (int j = 0; j < kStripLoads; ++j) {
-          const int kv = min(kb0 + S::kRowsPerLoad * j + ld_sub, n_cand - 1);      // past the end: any real row, never stored
-          const u16* src = kv < c ? kc + (size_t)kv * D : kn + (size_t)(kv - c) * new_stride;
-          load16(src + 8 * (strip_chunk ^ ((S::kRowsPerLoad * j) % S::kChunks)),
-                 lds_base + 2u * (unsigned)((int)(k_strip - lds_k) + S::kRowsPerLoad * j * D));
-        }
-      }
-    };
     // the block in the strip into registers, the next one on its way
     auto next_keys = [&](bf16x8 (&kf)[kNK], int next_kbi) __attribute__((always_inline)) {
       wait_loads();
@@ -949,7 +999,7 @@ attention_kernel(const AttnArgs args) {
     };
     // This wave's key blocks are wave, wave + kWaves, ...
     bf16x8 kf[kNK];
-    if (wave_s < n_kb) load_keys(wave_s);
+    if (redo && wave_s < n_kb) load_keys(wave_s);      // (else it is on its way)
     for (int kbi = wave_s; kbi < n_kb; kbi += S::kWaves) {
       next_keys(kf, kbi + S::kWaves);
       do_block(kf, kbi);

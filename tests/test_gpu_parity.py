@@ -129,6 +129,21 @@ def test_every_workgroup_shape_scores(variant, fused, hq, hkv, d, c, n, budget):
     cache.close()
 
 
+@pytest.mark.parametrize("variant", [0, 2])
+@pytest.mark.parametrize("hq,hkv,d,c,n", [
+    # tiles of 128 keys: one, two, three and more, odd and even numbers of plain ones; the cache ends with the first, the second or a later
+    # tile, just before or behind its end; the block's rows end with a tile, one row behind it, one before
+    (4, 2, 128, 0, 128), (4, 4, 64, 128, 128), (4, 2, 128, 128, 257), (4, 2, 128, 127, 129), (4, 4, 64, 129, 255), (4, 2, 128, 256, 128),
+    (4, 2, 128, 255, 385), (4, 2, 64, 384, 256), (4, 2, 128, 385, 127), (2, 2, 128, 640, 384), (2, 1, 64, 1, 511), (2, 1, 128, 896, 129)])
+def test_tiles_of_cache_and_block(variant, hq, hkv, d, c, n):
+    """The loop over key tiles of attention.hip: whole ones through descriptors that move on, masked or not, and the others row by row."""
+    budget = c + n - 1
+    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, budget, 512, seed=23 * c + n + variant, attention_shape=variant)
+    assert err <= U.OUT_TOL, err
+    U.check_scores(cache.debug_last(0)[0].cpu().numpy(), scores_ref, n * (hq // hkv))
+    cache.close()
+
+
 @pytest.mark.parametrize("variant", [0, 1, 2])
 @pytest.mark.parametrize("hq,hkv,d,c,n", [
     # key blocks of 32: all of the cache, one that holds cached and new keys, a last one of one key, fewer than waves
