@@ -27,7 +27,8 @@
 //     beyond.  Every evicted visual candidate looks at its grid neighbours, takes the kept one with the
 //     largest key and writes itself into that destination's list of at most six sources.
 //     (Walking the hash table was 3 of the 4.5 us of this phase: six chains of dependent LDS reads per lane,
-//     and the wave waits for its longest.)
+//     and the wave waits for its longest.)  With one candidate per thread its owner does that as soon as it knows the
+//     threshold, without a list of the evicted and the two barriers around it: 192 candidates, 4 heads of d 64 6.8 -> 5.9 us.
 //   * merge: destination and sources of a row pair (the K row and the V row of one slot, 16 bytes per lane)
 //     are fetched together, four destinations in flight per group of lanes; sources are sorted by
 //     candidate position first, so that the fp32 sum is taken in one fixed order.  A destination in the
@@ -35,8 +36,6 @@
 //     ones); one among the block's tokens goes to a staging row, because the slot it will get may
 //     still be a source.  The staging rows lie over the head's own partial arrays, read by then.
 //   * move: kept block rows, or their staging rows, into the free slots.
-#include <type_traits>
-
 #include "key_scores.h"
 #include "kvp_internal.h"
 #include "lane_tools.h"
@@ -156,28 +155,31 @@ __device__ __forceinline__ void div_mod(int u, int d, float inv_d, int& q, int& 
 
 // grid neighbours of a visual token: left, right, up, down, previous plane, next plane;
 // out[j] = -1 where there is none.  Returns false for a text token.
-__device__ __forceinline__ bool neighbours(const SegL* segs, int n_segs, int tok, int (&out)[kNeighbours]) {
+// (`first` is segs[0], which the caller has in registers: a prefix is mostly one visual segment with text behind it)
+__device__ __forceinline__ bool neighbours(const SegL& first, const SegL* segs, int n_segs, int tok, int (&out)[kNeighbours]) {
 #pragma unroll
   for (int j = 0; j < kNeighbours; ++j) out[j] = -1;
-  for (int s = 0; s < n_segs; ++s) {
+  SegL sg = first;
+  bool found = tok >= first.begin && tok < first.begin + first.n;
+  for (int s = 1; s < n_segs && __any(!found); ++s) {
     const int begin = segs[s].begin;
-    if (tok < begin || tok >= begin + segs[s].n) continue;
-    const SegL sg = segs[s];
-    if (sg.kind != KVP_VISUAL) return false;
-    int plane, rem, y, x;
-    div_mod(tok - sg.begin, sg.per, sg.inv_per, plane, rem);
-    div_mod(rem, sg.gw, sg.inv_gw, y, x);
-    if (x > 0) out[0] = tok - 1;
-    if (x + 1 < sg.gw) out[1] = tok + 1;
-    if (y > 0) out[2] = tok - sg.gw;
-    if (y + 1 < sg.gh) out[3] = tok + sg.gw;
-    if (sg.temporal) {
-      if (plane > 0) out[4] = tok - sg.per;
-      if (plane + 1 < sg.planes) out[5] = tok + sg.per;
-    }
-    return true;
+    if (found || tok < begin || tok >= begin + segs[s].n) continue;
+    sg = segs[s];
+    found = true;
   }
-  return false;
+  if (!found || sg.kind != KVP_VISUAL) return false;
+  int plane, rem, y, x;
+  div_mod(tok - sg.begin, sg.per, sg.inv_per, plane, rem);
+  div_mod(rem, sg.gw, sg.inv_gw, y, x);
+  if (x > 0) out[0] = tok - 1;
+  if (x + 1 < sg.gw) out[1] = tok + 1;
+  if (y > 0) out[2] = tok - sg.gw;
+  if (y + 1 < sg.gh) out[3] = tok + sg.gw;
+  if (sg.temporal) {
+    if (plane > 0) out[4] = tok - sg.per;
+    if (plane + 1 < sg.planes) out[5] = tok + sg.per;
+  }
+  return true;
 }
 
 // One row pair of `D` channels: 2 D / 8 lanes of 16 bytes, K row then V row.
@@ -268,45 +270,41 @@ compact_kernel(const SelectArgs args) {
       // a scalar base per array, lane offsets that never change (past the end: the last four candidates again, not stored)
       const float* part = in_set_of(a.partial, a.g, li) + (size_t)hk * a.partial_stride + grp * a.cand_stride;
       const int step = a.groups * a.cand_stride;
-      auto sum_arrays = [&](auto passes, auto batch) __attribute__((always_inline)) {
-        constexpr int kPasses = decltype(passes)::value, kBatch = decltype(batch)::value;
-        float4 acc[kPasses];
-        unsigned lane_off[kPasses];
+      // (as many passes as the candidates of this kernel need, and sixteen loads in flight with them.  With four passes wherever
+      // a group does not cover the candidates at once, half of the loads of 1536 candidates were the last four again: 56 arrays
+      // of them 8.3 -> 4.2 us)
+      constexpr int kWidth = kMaxItems > 4 ? kThreads : 256, kPasses = (kMaxItems * kThreads / 4 + kWidth - 1) / kWidth;
+      constexpr int kBatch = 16 / kPasses;
+      float4 acc[kPasses];
+      unsigned lane_off[kPasses];
 #pragma unroll
-        for (int s = 0; s < kPasses; ++s) {
-          acc[s] = make_float4(0.f, 0.f, 0.f, 0.f);
-          lane_off[s] = 4u * (unsigned)min(quad0 + s * a.width, a.quads - 1);
-        }
-        for (int first = 0; first < n_arrays; first += kBatch) {
-          float4 v[kBatch][kPasses];
-#pragma unroll
-          for (int u = 0; u < kBatch; ++u) {
-#pragma unroll
-            for (int s = 0; s < kPasses; ++s) v[u][s] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (first + u < n_arrays) {
-#pragma unroll
-              for (int s = 0; s < kPasses; ++s) v[u][s] = *reinterpret_cast<const float4*>(part + lane_off[s]);
-              part += step;
-            }
-          }
-#pragma unroll
-          for (int u = 0; u < kBatch; ++u)
-#pragma unroll
-            for (int s = 0; s < kPasses; ++s) {
-              acc[s].x += v[u][s].x; acc[s].y += v[u][s].y; acc[s].z += v[u][s].z; acc[s].w += v[u][s].w;
-            }
-        }
-#pragma unroll
-        for (int s = 0; s < kPasses; ++s)
-          if (n_arrays > 0 && quad0 + s * a.width < a.quads)
-            *reinterpret_cast<float4*>(l.sums + (size_t)(grp * a.quads + quad0 + s * a.width) * 4) = acc[s];
-      };
-      if constexpr (kMaxItems > 4) {
-        sum_arrays(std::integral_constant<int, 2>{}, std::integral_constant<int, 8>{});
-      } else {
-        if (a.quads <= a.width) sum_arrays(std::integral_constant<int, 1>{}, std::integral_constant<int, 16>{});
-        else sum_arrays(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
+      for (int s = 0; s < kPasses; ++s) {
+        acc[s] = make_float4(0.f, 0.f, 0.f, 0.f);
+        lane_off[s] = 4u * (unsigned)min(quad0 + s * a.width, a.quads - 1);
       }
+      for (int first = 0; first < n_arrays; first += kBatch) {
+        float4 v[kBatch][kPasses];
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u) {
+#pragma unroll
+          for (int s = 0; s < kPasses; ++s) v[u][s] = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (first + u < n_arrays) {
+#pragma unroll
+            for (int s = 0; s < kPasses; ++s) v[u][s] = *reinterpret_cast<const float4*>(part + lane_off[s]);
+            part += step;
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+          for (int s = 0; s < kPasses; ++s) {
+            acc[s].x += v[u][s].x; acc[s].y += v[u][s].y; acc[s].z += v[u][s].z; acc[s].w += v[u][s].w;
+          }
+      }
+#pragma unroll
+      for (int s = 0; s < kPasses; ++s)
+        if (n_arrays > 0 && quad0 + s * a.width < a.quads)
+          *reinterpret_cast<float4*>(l.sums + (size_t)(grp * a.quads + quad0 + s * a.width) * 4) = acc[s];
     }
 #pragma unroll
     for (int i = 0; i < kMaxItems; ++i) {
@@ -342,6 +340,9 @@ compact_kernel(const SelectArgs args) {
   // lost 0.3 %)
   keep_arguments(a.scores, a.keep, a.dst, a.g.first_set, a.g.n_sets, a.g.set_stride, a.cand_stride, a.t0, a.merge, a.n_segs, a.direct,
                  c, n_cand, budget, items);
+
+  SegL first_seg;
+  if (a.merge) first_seg = s_segs[0];
 
   // ---- own candidates, blocked: thread t owns positions [t * items, (t + 1) * items)
   float* const scores = in_set_of(a.scores, a.g, li) + (size_t)hk * a.cand_stride;
@@ -435,8 +436,54 @@ compact_kernel(const SelectArgs args) {
   }
 
   // ---- keep flags; rank the free slots, the kept block tokens and the evicted candidates
+  // (one candidate per thread: its owner plans the merge of an evicted one, before the barrier that the ranks wait for.  With more
+  // of them, an owner would plan one after the other: there the list deals them out to all threads.)
+  constexpr bool kOwnPlan = kMaxItems == 1;
   uint8_t* const keep_out = in_set_of(a.keep, a.g, li) + (size_t)hk * a.cand_stride;
   int32_t* const dst_out = in_set_of(a.dst, a.g, li) + (size_t)hk * a.cand_stride;
+  // ---- merge plan: evicted candidate p picks its best kept grid neighbour and enters itself there
+  auto plan_merge = [&](int p, int tok) __attribute__((always_inline)) {
+    int best = -1;
+    int nb[kNeighbours];
+    if (neighbours(first_seg, s_segs, a.n_segs, tok, nb)) {
+      // of cached slots that share a token index the one in the table merges: a destination then has at most
+      // one source per neighbour, which is what its list has room for
+      // (the two kinds of table are asked in branches of their own, so that the entries of the direct one come together:
+      // with the choice inside, each was waited for before the next was asked for, 0.4 us)
+      int self = p, r[kNeighbours];
+      if (a.direct) {
+        const unsigned self_entry = direct[(unsigned)tok < (unsigned)a.t0 ? tok : 0];
+        unsigned entry[kNeighbours];
+#pragma unroll
+        for (int j = 0; j < kNeighbours; ++j) entry[j] = direct[(unsigned)nb[j] < (unsigned)a.t0 ? nb[j] : 0];
+#pragma unroll
+        for (int j = 0; j < kNeighbours; ++j) r[j] = (unsigned)nb[j] < (unsigned)a.t0 && entry[j] != kNone16 ? (int)entry[j] : -1;
+        if (p < c) self = (unsigned)tok < (unsigned)a.t0 ? (int)self_entry : -1;
+      } else {
+        if (p < c) self = probe(l, mask, tok);
+#pragma unroll
+        for (int j = 0; j < kNeighbours; ++j) r[j] = (unsigned)nb[j] < (unsigned)a.t0 ? probe(l, mask, nb[j]) : -1;
+      }
+      // (a token of the block sits at a known position, one after it nowhere)
+#pragma unroll
+      for (int j = 0; j < kNeighbours; ++j)
+        if (nb[j] >= a.t0 && nb[j] < a.t0 + (n_cand - c)) r[j] = c + (nb[j] - a.t0);
+      unsigned long long kr[kNeighbours], best_key = 0;
+#pragma unroll
+      for (int j = 0; j < kNeighbours; ++j) kr[j] = l.key[max(r[j], 0)];
+#pragma unroll
+      for (int j = 0; j < kNeighbours; ++j)
+        if (r[j] >= 0 && kr[j] >= threshold && (best < 0 || kr[j] > best_key)) { best = r[j]; best_key = kr[j]; }
+      if (self != p) best = -1;
+    }
+    dst_out[p] = best;
+    if (best >= 0) {
+      const unsigned old = atomicAdd(&l.cnt[best >> 2], 1u << (8 * (best & 3)));
+      sources[best * kNeighbours + ((old >> (8 * (best & 3))) & 0xFFu)] = (unsigned short)p;
+    }
+    const unsigned long long merged = __ballot(best >= 0);
+    if (merged && lane == __builtin_ctzll(__ballot(true))) atomicAdd(&s_n_src, (unsigned)__builtin_popcountll(merged));
+  };
   bool keep[kMaxItems];
   unsigned n_free = 0, n_new = 0, n_ev = 0;
 #pragma unroll
@@ -452,8 +499,11 @@ compact_kernel(const SelectArgs args) {
     }
   }
   const unsigned packed = n_free | (n_new << 16);
-  const unsigned incl = wave_scan(packed, 0u, Add{}), incl_ev = wave_scan(n_ev, 0u, Add{});
+  const unsigned incl = wave_scan(packed, 0u, Add{});
+  unsigned incl_ev = 0;
+  if constexpr (!kOwnPlan) incl_ev = wave_scan(n_ev, 0u, Add{});
   if (lane == 63) { s_wave_tot[wave] = incl; s_wave_ev[wave] = incl_ev; }
+  if (kOwnPlan && a.merge && valid[0] && !keep[0]) plan_merge(tid, (int)~(unsigned)key[0]);
   __syncthreads();
   unsigned base = incl - packed, base_ev = incl_ev - n_ev;
   unsigned total = 0, total_ev = 0;
@@ -473,10 +523,10 @@ compact_kernel(const SelectArgs args) {
     const int p = tid * items + i;
     if (valid[i]) {
       if (p < budget && (p >= c || !keep[i])) l.free_slot[base_free++] = (unsigned short)p;
-      if (!keep[i]) l.evicted[base_ev++] = (unsigned short)p;
+      if (!kOwnPlan && !keep[i]) l.evicted[base_ev++] = (unsigned short)p;
     }
   }
-  __syncthreads();
+  if constexpr (!kOwnPlan) __syncthreads();
 
   using L = Lanes<D, kThreads>;
   const int sub = tid % L::kPerPair;
@@ -494,48 +544,9 @@ compact_kernel(const SelectArgs args) {
   u16* const staged = (is_v ? stage_v : stage_k) + 8 * piece;
   float* const staged_w = in_set_of(a.stage_w, a.g, li) + (size_t)hk * a.chunk_max;
 
-  if (a.merge) {
-    // ---- merge plan: the e-th evicted candidate (thread e % kThreads) picks its best kept
-    // grid neighbour and enters itself there
-    for (unsigned e = tid; e < total_ev; e += kThreads) {
-      const int p = l.evicted[e];
-      const int tok = (int)~key_words[2 * p];
-      int best = -1;
-      int nb[kNeighbours];
-      if (neighbours(s_segs, a.n_segs, tok, nb)) {
-        // of cached slots that share a token index the one in the table merges: a destination then has at most
-        // one source per neighbour, which is what its list has room for
-        int self = p;
-        if (p < c) {
-          if (!a.direct) self = probe(l, mask, tok);
-          else self = (unsigned)tok < (unsigned)a.t0 ? (int)direct[tok] : -1;
-        }
-        int r[kNeighbours];              // a token of the block sits at a known position, one after it nowhere
-#pragma unroll
-        for (int j = 0; j < kNeighbours; ++j) {
-          const bool cached = nb[j] >= 0 && nb[j] < a.t0;
-          if (a.direct) {
-            const unsigned e = direct[cached ? nb[j] : 0];
-            r[j] = cached && e != kNone16 ? (int)e : -1;
-          } else {
-            r[j] = cached ? probe(l, mask, nb[j]) : -1;
-          }
-          if (nb[j] >= a.t0 && nb[j] < a.t0 + (n_cand - c)) r[j] = c + (nb[j] - a.t0);
-        }
-        unsigned long long kr[kNeighbours], best_key = 0;
-#pragma unroll
-        for (int j = 0; j < kNeighbours; ++j) kr[j] = l.key[max(r[j], 0)];
-#pragma unroll
-        for (int j = 0; j < kNeighbours; ++j)
-          if (r[j] >= 0 && kr[j] >= threshold && (best < 0 || kr[j] > best_key)) { best = r[j]; best_key = kr[j]; }
-        if (self != p) best = -1;
-      }
-      dst_out[p] = best;
-      if (best >= 0) {
-        const unsigned old = atomicAdd(&l.cnt[best >> 2], 1u << (8 * (best & 3)));
-        sources[best * kNeighbours + ((old >> (8 * (best & 3))) & 0xFFu)] = (unsigned short)p;
-      }
-    }
+  if (a.merge && !kOwnPlan) {
+    // (one evicted candidate per thread, whichever threads own them)
+    for (unsigned e = tid; e < total_ev; e += kThreads) plan_merge((int)l.evicted[e], (int)~key_words[2 * l.evicted[e]]);
     __syncthreads();
   }
 
@@ -544,7 +555,7 @@ compact_kernel(const SelectArgs args) {
   unsigned short* const dests = reinterpret_cast<unsigned short*>(l.table);
   unsigned short* const moved = l.evicted;
   {
-    unsigned n_src_mine = 0, rank = base_new;
+    unsigned rank = base_new;
 #pragma unroll
     for (int i = 0; i < kMaxItems; ++i) {
       if (!valid[i]) continue;
@@ -553,14 +564,12 @@ compact_kernel(const SelectArgs args) {
       if (a.merge) {
         const unsigned k = (l.cnt[p >> 2] >> (8 * (p & 3))) & 0xFFu;
         if (k) {
-          n_src_mine += k;
           const unsigned at = atomicAdd(&s_n_dst, 1u);
           dests[at] = (unsigned short)p;
           key_words[2 * p + 1] = at;
         }
       }
     }
-    if (n_src_mine) atomicAdd(&s_n_src, n_src_mine);
   }
   __syncthreads();
 
@@ -600,7 +609,13 @@ compact_kernel(const SelectArgs args) {
           int from[kNeighbours];
           pos[u] = p;
           n_src[u] = (int)((l.cnt[p >> 2] >> (8 * (p & 3))) & 0xFFu);
-          sorted_sources(p, n_src[u], from);
+          if (__all(n_src[u] <= kEarly)) {               // (what most have)
+            const int one = sources[p * kNeighbours], other = sources[p * kNeighbours + 1];
+            from[0] = n_src[u] == 2 ? min(one, other) : one;
+            from[1] = max(one, other);
+          } else {
+            sorted_sources(p, n_src[u], from);
+          }
           rows[u][0] = row_at(p);
           wt[u][0] = weight_at(p);
 #pragma unroll

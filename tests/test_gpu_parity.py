@@ -851,6 +851,35 @@ def test_compaction_workgroup_sizes(d, c, n, t0):
     cache.close()
 
 
+@pytest.mark.parametrize("d,c,n", [(64, 60, 4), (128, 400, 112), (64, 400, 113), (128, 1500, 549)])   # owners plan up to 512, any thread beyond
+@pytest.mark.parametrize("t0", [2000, 70000])                 # the two kinds of token table
+@pytest.mark.parametrize("first", ["text", "visual"])
+def test_merge_plan_of_several_segments(d, c, n, t0, first):
+    """Evicted tokens in the first segment, in later ones and in text; neighbours cached and in the block, in still and moving
+    pictures, up to the segment's edges."""
+    head = (Segment(0, 24, 0),) if first == "text" else (Segment(0, 24, 1, 4, 6, 1, 0),)
+    still = Segment(24, (t0 - c // 2) // 64 * 64, 1, 8, 8, (t0 - c // 2) // 64, 0)
+    at = 24 + still.n_tokens + 9
+    planes = (t0 + n - at) // 30 + 1
+    segs = head + (still, Segment(at - 9, 9, 0), Segment(at, planes * 30, 1, 5, 6, planes, 1), Segment(at + planes * 30, 1000, 0))
+    rng = np.random.default_rng(t0 + c + n)
+    tokens = np.stack([np.r_[np.arange(12), rng.choice(np.arange(max(12, t0 - 2 * c), t0), size=c - 12, replace=False)] for _ in range(2)])
+    scores = (rng.integers(0, 50, size=(2, c + n)).astype(np.float32) + 1) / 7
+    cache, merged = _compact_on_given_scores(d, c, n, c, t0, segs, tokens, scores)
+    assert merged > 0 or c < 100
+    cache.close()
+
+
+@pytest.mark.parametrize("total", [512, 1024, 1025, 2048, 2049, 3072, 3073, 4096, 4097])
+def test_sums_of_many_partial_arrays(total):
+    """Own scores summed by the compaction from more partial arrays than its loads in flight, at the edges of its passes."""
+    n, hq, hkv, d = 330, 8, 1, 64
+    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, total - n, n, total - 1, 512, seed=total)
+    assert err <= U.OUT_TOL, err
+    U.check_scores(cache.debug_last(0)[0].cpu().numpy(), scores_ref, n * hq)
+    cache.close()
+
+
 @pytest.mark.parametrize("d,c,n,budget,t0", [(128, 2048, 1024, 2048, 2048),     # the bench shape
                                              (64, 1536, 512, 1536, 1536), (64, 512, 256, 512, 700), (64, 4100, 200, 4100, 5000)])
 @pytest.mark.parametrize("kind", ["equal", "half_zero", "zeros"])
