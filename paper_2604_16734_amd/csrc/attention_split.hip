@@ -103,18 +103,32 @@ __device__ __forceinline__ float sum_over_half(float (&v)[16], float factor, int
     swap_lanes<16>(v[i], v[i + 8]);
     v[i] = __builtin_fmaf(v[i], even, v[i + 8] * odd);
   }
-  const bool b3 = lane & 8, b2 = lane & 4, b1 = lane & 2;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const float mine = b3 ? v[i + 4] : v[i], theirs = b3 ? v[i] : v[i + 4];
-    v[i] = mine + dpp_lane<0x128>(theirs);                 // the other eight of sixteen
-  }
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const float mine = b2 ? v[i + 2] : v[i], theirs = b2 ? v[i] : v[i + 2];
-    v[i] = mine + dpp_lane<0x141>(theirs);                 // the other four of eight
-  }
-  const float mine = b1 ? v[1] : v[0], theirs = b1 ? v[0] : v[1];
+  // (each step adds twice, the second time in the banks of four lanes that keep the other value alone: with the choices of
+  // what to keep and what to hand on there were three instructions for two.  24 layers of 16/4 heads of d 64, 333 rows over 1444
+  // keys 6948 -> 6900 us.  The waits are those between a vector instruction and one that reads its result from other lanes, which
+  // the compiler does not see to here.)
+  float w[4], x[2];
+  asm("s_nop 1\n\t"
+      "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %2, %6, %6 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %3, %7, %7 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %8, %8 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %1, %9, %9 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %2, %10, %10 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %3, %11, %11 row_ror:8 row_mask:0xf bank_mask:0xc"
+      : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+      : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]));
+  asm("s_nop 1\n\t"
+      "v_add_f32_dpp %0, %2, %2 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %1, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %1, %5, %5 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "s_nop 1"
+      : "=&v"(x[0]), "=&v"(x[1])
+      : "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]));
+  const bool b1 = lane & 2;
+  const float mine = b1 ? x[1] : x[0], theirs = b1 ? x[0] : x[1];
   const float two = mine + dpp_lane<0x4E>(theirs);         // lane ^ 2
   return two + dpp_lane<0xB1>(two);                        // lane ^ 1
 }
