@@ -134,8 +134,10 @@ decode_head_kernel(const DecodeArgs a) {
 }
 
 // ---- grid (n_splits, Hkv).  G = query heads per KV head, at most GM (the compiled bound, which
-// sizes the register arrays; queries beyond G read as zero and their results are dropped).
-template <int D, int GM>
+// sizes the register arrays; queries beyond G read as zero and their results are dropped).  kGroup: G where the kernel is
+// built for that number alone, 0 for any: without the questions whether a query head is there, the heads' chains of
+// cross-lane additions run among one another.
+template <int D, int GM, int kGroup>
 __global__ void __launch_bounds__(kThreads)
 decode_kernel(const DecodeArgs a) {
   constexpr int kPieces = D / 8;                 // 16-byte pieces per row
@@ -146,7 +148,7 @@ decode_kernel(const DecodeArgs a) {
   have_arguments(a.q, a.k_tail, a.v_tail, a.partial, a.k_cache, a.v_cache, a.c, a.n_tail, a.n_kv_heads, a.budget, a.group, a.n_splits,
                  a.scale_log2);
   const int split = blockIdx.x, hk = blockIdx.y;
-  const int G = a.group;
+  const int G = kGroup ? kGroup : a.group;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int piece = tid % kPieces, sub = tid / kPieces;
   const int n_keys = a.c + a.n_tail;
@@ -316,15 +318,28 @@ hipError_t launch_head(const DecodeArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int D, int GM, int kGroup>
+void launch_split(const DecodeArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((decode_kernel<D, GM, kGroup>), dim3(a.n_splits, a.n_kv_heads), dim3(kThreads), 0, s, a);
+}
+
 template <int D>
 hipError_t launch_for(const DecodeArgs& a, hipStream_t s) {
   // (a row's offset in 32 bits: lists of few keys, KV heads of less than 4 GiB together)
   if ((long long)a.c + a.n_tail <= kHeadLoads * kHeadRows<D> && a.n_kv_heads <= 8192) return launch_head<D>(a, s);
-  const dim3 grid(a.n_splits, a.n_kv_heads);
-  const int group = a.group;
-  if (group <= 4) hipLaunchKernelGGL((decode_kernel<D, 4>), grid, dim3(kThreads), 0, s, a);
-  else if (group <= 8) hipLaunchKernelGGL((decode_kernel<D, 8>), grid, dim3(kThreads), 0, s, a);
-  else hipLaunchKernelGGL((decode_kernel<D, 16>), grid, dim3(kThreads), 0, s, a);
+  // Built for the number of query heads where that is faster (whole passes of 16 to 32 layers, any number against this one: 28/4 heads of d 128,
+  // 1100 keys 147.6 -> 134.4 us, 5000 keys 423 -> 414; 24/4 heads, 2099 keys 228 -> 209; 10/2, 3000 keys 288 -> 264; 32/4, 803 keys 149 -> 139;
+  // 12/2 of d 64, 3000 keys 273 -> 262; 16/4 of d 64, 4099 keys 199.4 -> 197.2).  Four of d 128 and one are not: 32/8 heads, 2176 keys
+  // 307.2 -> 311.5, 32/32 heads, 2068 keys 187.4 -> 189.6.
+  switch (a.group) {
+    case 1: case 2: case 3: launch_split<D, 4, 0>(a, s); break;
+    case 4: launch_split<D, 4, D == 64 ? 4 : 0>(a, s); break;
+    case 5: launch_split<D, 8, 5>(a, s); break;
+    case 6: launch_split<D, 8, 6>(a, s); break;
+    case 7: launch_split<D, 8, 7>(a, s); break;
+    case 8: launch_split<D, 8, 8>(a, s); break;
+    default: launch_split<D, 16, 0>(a, s);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(decode_fold_kernel<D>, dim3(a.n_q_heads), dim3(kFoldLanes * D), 0, s, a);

@@ -524,6 +524,13 @@ def test_decode_step_edges(hq, hkv, d, n_keys):
     cache.close()
 
 
+@pytest.mark.parametrize("d,n_keys", [(64, 64 * 21 + 1), (128, 64 * 11 + 1), (128, 64 * 11 - 1)])
+@pytest.mark.parametrize("hq,hkv", [(3, 1), (8, 2), (5, 1), (12, 2), (7, 1), (16, 2), (9, 1)])
+def test_decode_step_of_every_group(hq, hkv, d, n_keys):
+    """More keys than one workgroup takes, for the numbers of query heads per KV head that the kernel is built for, and others."""
+    test_decode_step_edges(hq, hkv, d, n_keys)
+
+
 @pytest.mark.parametrize("d,c", [(64, 90), (128, 90), (128, 900)])       # the kernel of few keys, and of many
 @pytest.mark.parametrize("keys,queries", [(0, 0), (-128, 125), (125, -128)])
 def test_decode_logits(d, c, keys, queries):
