@@ -180,6 +180,9 @@ decode_kernel(const DecodeArgs a) {
     for (int i = 0; i < kLoads; ++i) {
       vw[i] = v_rows.load(min(tile * kTile + kRowsPerLoad * i + sub, n_keys - 1));
     }
+    // all loads on their way before the first is waited for (with up to four query heads: 32/8 heads of d 128, 2176 keys, 32 layers 308 -> 302 us,
+    // where the constant number of heads alone gave 311; 32/32 heads, 2068 keys, 16 layers 187 -> 182; 28/4 heads, 1100 keys 134.1 -> 136.3)
+    if constexpr (GM == 4) __builtin_amdgcn_sched_barrier(0);
     float p[GM][kLoads];
 #pragma unroll
     for (int g = 0; g < GM; ++g) {
@@ -327,13 +330,14 @@ template <int D>
 hipError_t launch_for(const DecodeArgs& a, hipStream_t s) {
   // (a row's offset in 32 bits: lists of few keys, KV heads of less than 4 GiB together)
   if ((long long)a.c + a.n_tail <= kHeadLoads * kHeadRows<D> && a.n_kv_heads <= 8192) return launch_head<D>(a, s);
-  // Built for the number of query heads where that is faster (whole passes of 16 to 32 layers, any number against this one: 28/4 heads of d 128,
+  // Built for the number of query heads up to eight (whole passes of 16 to 32 layers, any number against this one: 28/4 heads of d 128,
   // 1100 keys 147.6 -> 134.4 us, 5000 keys 423 -> 414; 24/4 heads, 2099 keys 228 -> 209; 10/2, 3000 keys 288 -> 264; 32/4, 803 keys 149 -> 139;
-  // 12/2 of d 64, 3000 keys 273 -> 262; 16/4 of d 64, 4099 keys 199.4 -> 197.2).  Four of d 128 and one are not: 32/8 heads, 2176 keys
-  // 307.2 -> 311.5, 32/32 heads, 2068 keys 187.4 -> 189.6.
+  // 12/2 of d 64, 3000 keys 273 -> 262; 16/4 of d 64, 4099 keys 199.4 -> 193.7; 32/8 and 32/32 with the fence behind the loads).
   switch (a.group) {
-    case 1: case 2: case 3: launch_split<D, 4, 0>(a, s); break;
-    case 4: launch_split<D, 4, D == 64 ? 4 : 0>(a, s); break;
+    case 1: launch_split<D, 4, 1>(a, s); break;
+    case 2: launch_split<D, 4, 2>(a, s); break;
+    case 3: launch_split<D, 4, 3>(a, s); break;
+    case 4: launch_split<D, 4, 4>(a, s); break;
     case 5: launch_split<D, 8, 5>(a, s); break;
     case 6: launch_split<D, 8, 6>(a, s); break;
     case 7: launch_split<D, 8, 7>(a, s); break;
