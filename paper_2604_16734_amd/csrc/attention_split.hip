@@ -399,7 +399,7 @@ attention_split_kernel(const AttnArgs args) {
         for (int r = 0; r < 16; ++r) o[dt][r] *= f;
     }
     m_ref = m_new;
-    limit = m_ref + rescue_raw;
+    limit = m_ref == -INFINITY ? -INFINITY : m_ref + rescue_raw;         // (a scale below 1e-37: infinite margin)
     neg = -(m_ref == -INFINITY ? 0.f : m_ref) * sl2;
   };
 

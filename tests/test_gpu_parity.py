@@ -423,6 +423,32 @@ def test_scores_after_runaway_logits(hq, hkv, d, c, n):
     cache.close()
 
 
+@pytest.mark.parametrize("scale", [0.0, 1e-38])         # 1e-38: the margin for a row's reference, in units of the dot product, is infinite
+@pytest.mark.parametrize("hq,hkv,d,c,n", [(4, 2, 64, 512, 33), (4, 2, 128, 515, 70), (28, 4, 128, 520, 300), (16, 4, 64, 517, 530)])
+def test_first_keys_at_minus_infinity(hq, hkv, d, c, n, scale):
+    """Split-key kernel: the first 256 keys have logits of minus infinity in every other row and of plus infinity in the
+    rows between them.  The former average over the other keys; the latter are not finite."""
+    assert _rows_of_a_workgroup(n, hq) < 128
+    rng = np.random.default_rng(c + n)
+    cache = K.Cache(1, hq, hkv, d, c + n, n, [Segment(0, 100000, 0)], softmax_scale=scale, device=DEV)
+    k_all, v_all, q = _rand_bits(rng, (c + n, hkv, d)), _rand_bits(rng, (c + n, hkv, d)), _rand_bits(rng, (n, hq, d))
+    q[0::2, :, 5] &= 0x7FFF
+    q[1::2, :, 5] |= 0x8000
+    k_all[:256, :, 5] = 0xFF80
+    k64, v64, q64 = (O.bf16_bits_to_f64(x) for x in (k_all, v_all, q))
+    oc = O.LayerCache(hkv, d, c + n)
+    oc.compact(0, k64[:c], v64[:c], np.zeros((hkv, c), dtype=np.float32))
+    U.upload_state(cache, 0, oc)
+    cache.set_state(0, c, c)
+    out = cache.prefill_chunk(0, c, U.bits_to_torch(q), U.bits_to_torch(k_all[c:]), U.bits_to_torch(v_all[c:]))
+    finite = O.LayerCache(hkv, d, c + n)
+    finite.compact(0, k64[256:c], v64[256:c], np.zeros((hkv, c - 256), dtype=np.float32))
+    out_ref, _ = finite.attend(c - 256, q64, k64[c:], v64[c:], scale or None)
+    err = U.out_rel_err(U.torch_bf16_to_f64(out)[0::2], out_ref[0::2])
+    assert err <= U.OUT_TOL, err
+    cache.close()
+
+
 @pytest.mark.parametrize("value", ["nan", "inf", "huge"])     # huge: finite, but logits up to infinity
 @pytest.mark.parametrize("hq,hkv,d,c,n,fused", [
     (4, 2, 128, 100, 33, 1), (4, 2, 128, 1216, 65, 1), (4, 4, 64, 450, 60, 1), (4, 2, 64, 1985, 65, 1),    # 32-row workgroups
