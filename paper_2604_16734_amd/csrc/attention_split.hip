@@ -367,7 +367,8 @@ attention_split_kernel(const AttnArgs args) {
 #pragma unroll
   for (int dt = 0; dt < kND; ++dt) o[dt] = zero;
   float m_ref = -INFINITY, l_run = 0.f;
-  const float rescue_raw = kRescueLog2 / sl2;              // the margin in units of the raw dot product
+  // the margin in units of the raw dot product; finite, whatever the scale, so that a row without a reference keeps its limit
+  const float rescue_raw = fminf(kRescueLog2 / sl2, __FLT_MAX__);
   float limit = -INFINITY, neg = 0.f;        // m_ref + rescue_raw; -m_ref in the exponent, 0 while the row has seen nothing
   // of this wave's blocks: the part block of the cache, if it has that one; the first of which some row may not see some key
   const int part_blk = c % 32 != 0 && (c_blk - 1 - ks) % KS == 0 ? (c_blk - 1 - ks) / KS : -1;
@@ -399,7 +400,7 @@ attention_split_kernel(const AttnArgs args) {
         for (int r = 0; r < 16; ++r) o[dt][r] *= f;
     }
     m_ref = m_new;
-    limit = m_ref == -INFINITY ? -INFINITY : m_ref + rescue_raw;         // (a scale below 1e-37: infinite margin)
+    limit = m_ref + rescue_raw;
     neg = -(m_ref == -INFINITY ? 0.f : m_ref) * sl2;
   };
 
