@@ -136,10 +136,17 @@ __device__ __forceinline__ float sum_over_half(float (&v)[16], float factor, int
 // kKept: key blocks of a wave whose softmax weights stay in registers; 0: the scores take a second sweep;
 // kScoreByKeys: no scores from the queries, and the first workgroups of the launch score by the keys alone
 constexpr int kScoreByKeys = -1;
+//
+// Without scores a workgroup at d 64 has 110 (one row tile) or 126 (two) registers a lane, and two of them fit on a CU.  With two row tiles
+// that takes the second sweep out (launches with scores keep weights) and the loop over the rounds in one piece: the first rounds
+// taken apart from the others, as the compiler would, had 138 and one workgroup per CU.  Whole prefixes, 8 layers per launch: 16/4
+// heads, 640 rows over 1920 keys, proxy queries 965 -> 825 us, 1300 over 3900 1141 -> 978; 32/32 heads, 512 rows over 1536 keys 1954 -> 1647;
+// 28/4 heads, 512 rows over 1536 keys, scored by the keys 1199 -> 1006.
 template <int D, int QW, int kKept>
 __global__ void __launch_bounds__((Split<D, QW>::kThreads))
 attention_split_kernel(const AttnArgs args) {
   using S = Split<D, QW>;
+  constexpr bool kScores = kKept > 0 || (kKept == 0 && QW == 1);       // where launches with scores come
   constexpr int KS = S::KS;
   constexpr int kNK = D / 16;                // K fragments (and MFMAs) of a 32-key block
   constexpr int kND = D / 32;                // channel tiles of O
@@ -553,6 +560,7 @@ attention_split_kernel(const AttnArgs args) {
       }
     constexpr int kFrom = kKept > 0 ? kKept : 0;
     float p[16];
+#pragma nounroll
     for (int i = kFrom; i < n_rounds; i += 2) {
       round(i, std::integral_constant<int, kFrom & 1>{}, p);
       if (i + 1 < n_rounds) round(i + 1, std::integral_constant<int, (kFrom & 1) ^ 1>{}, p);
@@ -612,7 +620,7 @@ attention_split_kernel(const AttnArgs args) {
     stat_m[wave * 32 + l32] = m_ref;
     stat_l[wave * 32 + l32] = l_run;
   }
-  const bool score = kKept != kScoreByKeys && a.partial != nullptr;
+  const bool score = kScores && a.partial != nullptr;
   __syncthreads();
   float lse_row;                             // of row l32 of the wave's tile
   {

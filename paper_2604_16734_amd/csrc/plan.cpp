@@ -166,8 +166,9 @@ bool keydiff_in_compaction(int n_cand, int head_dim) {
 //   64-row workgroups take two or three times as long as a scoring one: 40/8 heads, d 128, 512 rows over 1024 keys (320 + 8)
 //     1461 -> 1207 us, 8 layers per launch 1305 -> 1267 us.
 //   At d 64 the kernel that scores keys holds one workgroup per CU, the other two.  That shows in launches of many
-//     rounds: 16/4 heads, 333 rows over 1444 keys, 3 layers per launch 633 -> 603 us, 8 layers 489 -> 534; 28/4 heads, 512 rows over
-//     1536 keys, 3 layers (696 workgroups) 978 -> 890 us, 8 layers (1856) 950 -> 965 us.
+//     rounds: 28/4 heads, 512 rows over 1536 keys (232 workgroups a layer), 2 layers per launch 1971 -> 1821 us, 3 layers 1200 -> 1154,
+//     4 layers 1377 -> 1380, 8 layers 993 -> 1131; 16/4 heads, 333 rows over 1444 keys (184 a layer), 3 layers 1366 -> 1210 us,
+//     4 layers 1477 -> 1293, 8 layers 988 -> 970.
 // Both ways leave the same bits, so that this may depend on the layers of a launch.
 bool scores_keys_beside_attention(const AttnArgs& a, int n_layers, int n_cand, int head_dim) {
   if (a.variant != kAttnSplit32 && a.variant != kAttnSplit64) return false;
