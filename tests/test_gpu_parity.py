@@ -129,7 +129,7 @@ def test_every_workgroup_shape_scores(variant, fused, hq, hkv, d, c, n, budget):
     cache.close()
 
 
-@pytest.mark.parametrize("variant", [0, 2])
+@pytest.mark.parametrize("variant", [0, 1, 2])
 @pytest.mark.parametrize("hq,hkv,d,c,n", [
     # tiles of 128 keys: one, two, three and more, odd and even numbers of plain ones; the cache ends with the first, the second or a later
     # tile, just before or behind its end; the block's rows end with a tile, one row behind it, one before
@@ -243,8 +243,22 @@ def test_scores_of_two_row_tiles(hq, hkv, d, c, n, scale):
 def test_rows_past_the_end_of_a_block(hq, hkv, d, c, n):
     """Key blocks of the split-key kernel that end early: what lies behind the cached entries and behind the block's rows in memory is
     NaN and stays out of outputs and scores."""
+    _rows_past_the_end(hq, hkv, d, c, n)
+
+
+@pytest.mark.parametrize("shape", [0, 1, 2])
+@pytest.mark.parametrize("hq,hkv,d,c,n", [
+    # tiles of 128 keys: the first holds all there is, or cached and new keys; a later one does; whole tiles and a last one of a few keys
+    (4, 4, 64, 0, 5), (4, 2, 128, 127, 129), (4, 4, 64, 129, 255), (4, 2, 128, 300, 200), (4, 2, 64, 512, 130), (2, 1, 128, 900, 641)])
+def test_rows_past_the_end_of_a_tile(shape, hq, hkv, d, c, n):
+    """The same for the key tiles of the shapes that a caller can force."""
+    _rows_past_the_end(hq, hkv, d, c, n, shape)
+
+
+def _rows_past_the_end(hq, hkv, d, c, n, shape=-1):
     rng = np.random.default_rng(100 * c + n)
     cache = K.Cache(1, hq, hkv, d, c + n - 1, n, [Segment(0, 100000, 0)], device=DEV)
+    cache.set_attention_shape(shape)
     k_all, v_all, q = _rand_bits(rng, (c + n, hkv, d)), _rand_bits(rng, (c + n, hkv, d)), _rand_bits(rng, (n, hq, d))
     oc = O.LayerCache(hkv, d, c + n - 1)
     if c:
