@@ -17,7 +17,8 @@
 // is gathered in exactly that key order.
 //
 // Staging.  K and V tiles go from global memory straight into LDS
-// (global_load_lds, 16 bytes per lane, no registers, no LDS store
+// (buffer_load ... lds through descriptors that move on by a tile; global_load_lds where a tile straddles
+// the cache and the block or ends past the last key; 16 bytes per lane, no registers, no LDS store
 // instructions), row-major as they are in memory.  A wave instruction fills
 // 1 KiB of consecutive LDS, so rows cannot be padded; instead the 16-byte chunks
 // of a row are XOR-swizzled by the row number on the way in, each tensor with
@@ -68,6 +69,7 @@
 // 1024 rows over 3072 keys (16 layers per launch).
 #include <type_traits>
 
+#include "key_tiles.h"
 #include "kvp_internal.h"
 #include "mfma_tools.h"
 
@@ -193,9 +195,9 @@ attention_kernel(const AttnArgs args) {
   // Issued as inline assembly on purpose: the compiler then does not know that these loads write
   // LDS and does not make every later LDS read wait for them.  Ordering is this kernel's job:
   // wait_loads() before the barrier that publishes a tile.
-  // Two address forms: a 64-bit address per lane (tiles that straddle the cache and the block or
-  // run past the end), and a scalar base with a 32-bit offset per lane (uniform tiles: the base
-  // moves from tile to tile on the scalar unit, the lane offsets never change).
+  // Three address forms: a 64-bit address per lane (tiles that straddle the cache and the block or
+  // run past the end), a scalar base with a 32-bit offset per lane (key strips of the score sweep), and
+  // a buffer descriptor (load_fed below: the uniform tiles, in the cache or in the block as a whole).
   auto load16 = [&](const u16* src, unsigned lds_addr) __attribute__((always_inline)) {
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_addr)
                  : "m0", "memory");
@@ -207,11 +209,6 @@ attention_kernel(const AttnArgs args) {
   };
   auto wait_loads = [&]() __attribute__((always_inline)) {
     __builtin_amdgcn_s_waitcnt(0x0F70);    // vmcnt(0), nothing else
-  };
-  // tile t lies entirely in the cache or entirely in the block: one base, one stride
-  auto tile_is_uniform = [&](int t) __attribute__((always_inline)) -> bool {
-    const int base = t * S::kTk;
-    return base + S::kTk <= c || (base >= c && base + S::kTk <= n_cand);
   };
   // A uniform tile: the scalar address of the first row this wave brings in, the row stride, and
   // which of the lane offsets goes with it.  The lane part of an address is
@@ -553,13 +550,10 @@ attention_kernel(const AttnArgs args) {
     typedef std::integral_constant<int, 0> Even;
     typedef std::integral_constant<int, 1> Odd;
     typedef std::integral_constant<int, -1> Any;
-    // The steady body of tile t needs the tiles that it prefetches (V of t + 1, K of t + 2) uniform, or past the workgroup's last tile
-    // (then it fetches an earlier tile again, into a buffer nobody reads any more).  Not uniform are the tile in which the cache ends and
-    // the block's rows begin, and one that ends past the last key; tile 0 may be either, but where it is fetched again.
-    const int first_new = (c + S::kTk - 1) / S::kTk, part_new = n_cand / S::kTk;
-    int n_fed = my_tiles;          // tiles the steady bodies take
-    if (c % S::kTk != 0 && first_new - 1 < n_tiles && (first_new > 1 || n_tiles <= 2)) n_fed = min(n_fed, max(first_new - 3, 0));
-    if (part_new < n_tiles) n_fed = min(n_fed, max(part_new - 2, 0));
+    // The steady body of tile t needs the tiles that it prefetches (V of t + 1, K of t + 2) uniform, in the cache or in the block as a
+    // whole, or past the workgroup's last tile (then it fetches an earlier tile again, into a buffer nobody reads any more).
+    const int first_new = (c + S::kTk - 1) / S::kTk;
+    int n_fed = min(my_tiles, fed_tiles(c, n_cand, S::kTk, n_tiles));      // tiles the steady bodies take
     if (new_stride >= 1 << 23) n_fed = 0;        // (bytes within a tile are 32-bit numbers)
     const int n_fast = min(n_plain, n_fed) & ~1;      // of these the ones that every row of the wave sees in full, two at a time
     // the feed of tile `t`: from the one before it, or, where the block's own rows begin, anew
