@@ -33,7 +33,7 @@ PEAK_HBM_GBS = 8000.0         # MI355X HBM3E, vendor figure
 # HBM bytes per attention launch (fetch + write) over the long_video prefill, from the rocprofv3 --pmc FETCH_SIZE /
 # WRITE_SIZE runs summarised in profiles/ (launch-weighted mean, counters scaled by what they read for a plain 256 MiB
 # copy), and the layers a launch of those runs covered: (layers, bytes)
-ATTENTION_TRAFFIC = {"long_video": (16, 815553083)}
+ATTENTION_TRAFFIC = {"long_video": (16, 489323898)}
 
 
 def attention_traffic(workload, layers_per_launch):

@@ -49,10 +49,10 @@
 //
 // What stands between the products is kept out of the loop: the tiles come through descriptors that move on by a tile, a load's
 // place in its tile is a scalar, and how many tiles go which way is worked out once (as a search, tile by tile, it took 4500 of a
-// workgroup's 115,000 cycles).  A plain tile takes 2520 cycles, 39 for each matrix instruction of a SIMD, of which the pipe needs 33 (2950 with
-// 110 scalar instructions a tile; a tile with a mask 448 instructions instead of 587).  32/8 heads, d 128, 1024 rows over 3072 keys, one
-// layer: 57.0 -> 53.9 us without scores, 78 -> 75 us with them.  The clock gives part of it back: with this loop and
-// ordinary data the chip draws all the power it may and runs at 1.6 to 2.0 of 2.4 GHz (zeros for data: 46.6 -> 42.6 and 59.2 -> 55.5 us).
+// workgroup's 115,000 cycles).  A plain tile takes 2640 cycles, 41 for each matrix instruction of a SIMD, of which the pipe needs 33 (2940 with
+// 110 scalar instructions a tile; 1.80 instead of 1.92 us; a tile with a mask 448 instructions instead of 587).  32/8 heads, d 128, 1024 rows over 3072 keys, one
+// layer: 57.0 -> 53.9 us without scores, 78 -> 75 us with them.  The clock gives part of it back: with
+// ordinary data launches of 16 layers run at 1.6 to 1.9 of 2.4 GHz (zeros for data, one layer: 46.6 -> 42.6 and 59.2 -> 55.5 us).
 //
 // Softmax reference.  exp(S - m) is exact for ANY per-row reference m as long as
 // nothing overflows, so the fast loop fixes m at the maximum of the row's first

@@ -49,7 +49,7 @@
 //
 // Scores (Eq. 4), one row tile per workgroup: a wave has few key blocks (three at 768 keys), so the fp32 weights
 // exp(S - m) of all of them stay in its registers.  When the rows' normalisers are known, a lane's factor exp(m - lse) turns
-// them into the softmax weights of its row, and the column sums run over the lanes: 54 vector instructions per block,
+// them into the softmax weights of its row, and the column sums run over the lanes: some 50 vector instructions per block,
 // where a second sweep takes the keys from L2, the products and the exponentials again.  The kernel is built for each
 // number of kept blocks that its registers have room for (16 each: up to 6 at d 128, 8 at d 64; the unrolled loop also
 // spares the rest).  16/4 heads, d 64, 333 rows over 1444 keys, when it was built: 13.6 -> 11.4 us per launch; 28/4 heads, d 128, 256 rows over
@@ -830,8 +830,8 @@ hipError_t prepare_shape() {
                              hipFuncAttributeMaxDynamicSharedMemorySize, Split<D, QW>::kLdsBytes);
 }
 
-// 32-row workgroups: as many kept blocks per wave as the list needs, where registers have room for them (d 128: 250 of 256
-// with six; d 64: 209 with eight).  A launch without scores keeps none.
+// 32-row workgroups: as many kept blocks per wave as the list needs, where registers have room for them (d 128: 248 of 256
+// with six; d 64: 214 with eight).  A launch without scores keeps none.
 template <int D>
 hipError_t launch_split32(const AttnArgs& a, hipStream_t s) {
   if (a.key_score_wgs > 0) return launch_shape<D, 1, kScoreByKeys>(a, s);

@@ -121,10 +121,10 @@ size_t select_lds_bytes(const SelectArgs& a) {
 
 // A workgroup has 512 threads up to 1024 candidates (and where it holds the keys in registers), 1024 beyond.  Most of its phases are
 // what every wave does for itself (scans, the search of the histogram) on four SIMDs, so that fewer waves are done sooner,
-// until there are too few for the rows.  Per launch with 512 threads, with 1024: 4 heads of d 64, 192 candidates 9.8,
-// 11.0 us; 4 heads of d 128, 768 candidates, scored by the keys 13.8, 14.3 us; 16 layers of 4 heads, 1536 candidates
-// 26.4, 23.8 us, the same scored by proxy queries (more rows merge) 60, 55 us.  With 256 threads the first two
-// take half a microsecond more, and 8 layers of 768 candidates 3 us.
+// until there are too few for the rows.  Per launch with 512 threads, with 1024: 4 heads of d 64, 192 candidates 7.7,
+// 9.3 us; 4 heads of d 128, 768 candidates 12.4, 13.2 us, 8 layers of them 12.9, 13.8 us; 1536 candidates 19.4, 16.8 us, 16 layers
+// of them 23.0, 20.3 us.  (With 256 threads, in an earlier kernel, the first two took half a microsecond more, and 8 layers of 768
+// candidates 3 us.)
 // A thread owns ceil(n_cand / threads) neighbouring candidates.  For the sums of the partial arrays the threads
 // form groups of 64, 128 or 256 (the fewest that cover the candidates in fours, 256 at most) that take
 // every groups-th array, so that all of them have loads in flight whatever the number of candidates.
