@@ -140,13 +140,15 @@ constexpr int kScoreByKeys = -1;
 // Without scores a workgroup at d 64 has 110 (one row tile) or 126 (two) registers a lane, and two of them fit on a CU.  With two row tiles
 // that takes the second sweep out (launches with scores keep weights) and the loop over the rounds in one piece: the first rounds
 // taken apart from the others, as the compiler would, had 138 and one workgroup per CU.  Whole prefixes, 8 layers per launch: 16/4
-// heads, 640 rows over 1920 keys, proxy queries 965 -> 825 us, 1300 over 3900 1141 -> 978; 32/32 heads, 512 rows over 1536 keys 1954 -> 1647;
-// 28/4 heads, 512 rows over 1536 keys, scored by the keys 1199 -> 1006.
+// heads, 640 rows over 1920 keys, proxy queries 969 -> 812 us, 1300 over 3900 1141 -> 978; 32/32 heads, 512 rows over 1536 keys 1954 -> 1647;
+// 28/4 heads, 512 rows over 1536 keys, scored by the keys 1199 -> 1006.  At d 128, where one workgroup fits either way, the first rounds
+// apart are the faster way, and without the sweep the compiler orders the loop worse (28/4 heads, 512 rows over 1536 keys, proxy queries, 16
+// layers, without the sweep 4194 -> 4253 us, 8 layers 1983 -> 2009): there it stays, though no launch reaches it.
 template <int D, int QW, int kKept>
 __global__ void __launch_bounds__((Split<D, QW>::kThreads))
 attention_split_kernel(const AttnArgs args) {
   using S = Split<D, QW>;
-  constexpr bool kScores = kKept > 0 || (kKept == 0 && QW == 1);       // where launches with scores come
+  constexpr bool kScores = kKept > 0 || (kKept == 0 && (QW == 1 || D == 128));       // where launches with scores come (and see above)
   constexpr int KS = S::KS;
   constexpr int kNK = D / 16;                // K fragments (and MFMAs) of a 32-key block
   constexpr int kND = D / 32;                // channel tiles of O
@@ -560,10 +562,15 @@ attention_split_kernel(const AttnArgs args) {
       }
     constexpr int kFrom = kKept > 0 ? kKept : 0;
     float p[16];
-#pragma nounroll
-    for (int i = kFrom; i < n_rounds; i += 2) {
+    auto two_rounds = [&](int i) __attribute__((always_inline)) {
       round(i, std::integral_constant<int, kFrom & 1>{}, p);
       if (i + 1 < n_rounds) round(i + 1, std::integral_constant<int, (kFrom & 1) ^ 1>{}, p);
+    };
+    if constexpr (D == 64 && kKept == 0) {
+#pragma nounroll
+      for (int i = kFrom; i < n_rounds; i += 2) two_rounds(i);
+    } else {
+      for (int i = kFrom; i < n_rounds; i += 2) two_rounds(i);
     }
     wait_older_than(None{});
   } else {

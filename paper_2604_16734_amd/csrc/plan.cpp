@@ -15,6 +15,14 @@ namespace kvp {
 //   28/4 heads, d 128, 256 rows over 768 keys   22.7 ->  7.3 us (eight layers per launch)
 //   32/32 heads, d 128, 128 rows over 384 keys  15.1 ->  7.5 us
 //   28/4 heads, d 128, 512 rows over 1536 keys  34.6 -> 25.6 us (64-row workgroups)
+// The lines, whole prefixes with the shape on this side and on the other, one layer per launch (8 layers):
+//   at 192 workgroups of 128 rows, 64-row ones instead: 28/4 heads, d 128, 896 rows (196) 4318 -> 4683 us (2616 -> 2752), 32/8 heads, 768 rows
+//     (192) 3930 -> 4654 (2415 -> 2769); 28/4 heads, 800 rows (196) 4166 -> 4525 (2706 -> 2639); at d 64 they are ahead, 16/4 heads, 1500 rows (192)
+//     2329 -> 2210 (1250 -> 1183);
+//   above 256 workgroups of 32 rows, 32-row ones instead: 28/4 heads, d 128, 320 rows (280) 5235 -> 6008 (1979 -> 2419), 32/8 heads, 512 rows (512)
+//     4445 -> 5072 (2754 -> 3279), 16/4 heads, d 64, 600 rows (304) 2907 -> 2962 (1064 -> 1117); 32/8 heads, 288 rows (288) 5990 -> 5788 (2462 -> 2335);
+//   up to 256, 64-row ones instead: 28/4 heads, d 128, 256 rows (224) 4440 -> 5461 (1658 -> 1710), 32/32 heads, 256 rows (256) 4678 -> 5836 (2200 -> 2131),
+//     16/4 heads, d 64, 500 rows (256) 2613 -> 3242 (963 -> 1004).
 // The choice depends on one layer's block alone, never on how many layers a launch takes, so that
 // grouped and single launches leave the same bits.
 static int shape_for(int n, int n_q_heads) {
