@@ -27,9 +27,12 @@
 //
 // What a wave does for a block beside its products counts as much as they do: it issues one instruction in about five
 // cycles.  Blocks therefore come through buffer descriptors, whose end takes care of a block's missing rows, and their addresses, the
-// blocks that need a mask and the reference's margin are carried along instead of being worked out for each (68 -> 26 scalar
-// instructions per block); and all fragments of a product are asked for before the first of them is used.  16/4 heads, d 64, 333 rows over 1444
-// keys: 11.2 -> 10.4 us; 28/4 heads, d 128, 256 rows over 768 keys: 10.6 -> 10.3 us.
+// blocks that need a mask and the reference's margin are carried along instead of being worked out for each; and all fragments of a product
+// are asked for before the first of them is used.  16/4 heads, d 64, 333 rows over 1444 keys: 11.2 -> 10.4 us; 28/4 heads, d 128, 256 rows over
+// 768 keys: 10.6 -> 10.3 us.  From one whole block to the next a descriptor only moves on, and four loads share a setting of M0 (Feed: a
+// block of d 64 had 56 scalar instructions, now 19): 16/4 heads, d 64, 333 rows over 1444 keys 9.06 -> 8.78 us, 28/4 heads, d 128, 256 rows
+// over 768 keys 8.55 -> 8.37, 16 layers of 28/4 heads, 512 rows over 1536 keys 4858 -> 4766 us a prefix.  What bounds the 32-row launches beside
+// that is the path into the CU: the blocks of a round are 64 KiB at d 64 and 128 at d 128, 1024 and 2048 of its 1270 and 2000 cycles.
 //
 // The partial results of a row meet in LDS as they lie in the accumulators; a wave's own are written over its own strips, with no barrier
 // in front, and with kept weights a wave puts together one slice of the channels of the rows that its lanes have anyway: 0.3 us of each
@@ -142,13 +145,12 @@ constexpr int kScoreByKeys = -1;
 // taken apart from the others, as the compiler would, had 138 and one workgroup per CU.  Whole prefixes, 8 layers per launch: 16/4
 // heads, 640 rows over 1920 keys, proxy queries 969 -> 812 us, 1300 over 3900 1141 -> 978; 32/32 heads, 512 rows over 1536 keys 1954 -> 1647;
 // 28/4 heads, 512 rows over 1536 keys, scored by the keys 1199 -> 1006.  At d 128, where one workgroup fits either way, the first rounds
-// apart are the faster way, and without the sweep the compiler orders the loop worse (28/4 heads, 512 rows over 1536 keys, proxy queries, 16
-// layers, without the sweep 4194 -> 4253 us, 8 layers 1983 -> 2009): there it stays, though no launch reaches it.
+// apart are the faster way.
 template <int D, int QW, int kKept>
 __global__ void __launch_bounds__((Split<D, QW>::kThreads))
 attention_split_kernel(const AttnArgs args) {
   using S = Split<D, QW>;
-  constexpr bool kScores = kKept > 0 || (kKept == 0 && (QW == 1 || D == 128));       // where launches with scores come (and see above)
+  constexpr bool kScores = kKept > 0 || (kKept == 0 && QW == 1);      // where launches with scores come
   constexpr int KS = S::KS;
   constexpr int kNK = D / 16;                // K fragments (and MFMAs) of a 32-key block
   constexpr int kND = D / 32;                // channel tiles of O
@@ -284,60 +286,103 @@ attention_split_kernel(const AttnArgs args) {
   const int wg_rows_end = min(n, tile_row(QW - 1) + 32);
   const int n_kb = c_blk + (min(a.n_keys, wg_rows_end + shift) + 31) / 32;   // blocks some row of the workgroup sees
   // A block comes in through a buffer descriptor that ends with it: rows past its end come as zeros, and so does a block that
-  // does not exist.  What a block needs of scalar work is kept from block to block.
-  // Two row tiles share their blocks: of the waves (0, ks) and (1, ks) one brings in K and the other V for both, a
+  // does not exist.  Two row tiles share their blocks: of the waves (0, ks) and (1, ks) one brings in K and the other V for both, a
   // round of KS blocks ahead, into the strips that the round before has left.
   constexpr bool kShared = QW == 2;
   const u16* const k_mine = reinterpret_cast<const u16*>(lds_raw) + ks * S::kStrip;      // [2][KS][kStrip], then V's
   const u16* const v_mine = k_mine + 2 * KS * S::kStrip;
   const unsigned my_to = lds_addr(qw == 0 ? k_mine : v_mine);
-  const unsigned chunk_k = 16u * (unsigned)ld_chunk_k, chunk_v = 16u * (unsigned)ld_chunk_v;
-  const unsigned my_chunk = qw == 0 ? chunk_k : chunk_v;
   const unsigned new_bytes = 2u * (unsigned)new_stride;
-  const unsigned lane_cached = (unsigned)ld_sub * (2u * D), lane_fresh = (unsigned)ld_sub * new_bytes;
-  struct Source {
-    u32x4 buffer;
-    unsigned row_bytes, lane;
+  // What brings in a wave's blocks, every `step` blocks of the list.  From one whole block to the next of the cache, or of the block's
+  // own rows, the addresses move on and nothing else changes; the rest is worked out where the kind of block changes.  Load j brings in
+  // rows kRowsPerLoad j .. of a block; its immediate offset moves both of its addresses, that in memory and that in LDS, by 1 KiB from load
+  // to load, and the lane's part of an address takes that back where the rows lie further apart.  A lane keeps its part for each load
+  // of four, or only that of the first where registers are short.
+  constexpr int kLaneParts = (D == 64 && kKept == 0) || (D == 128 && kKept == 6) ? 1 : 4;
+  struct Feed {
+    u32x4 k, v;                              // descriptors: from the block's first row to its last one's end
+    int whole;                               // blocks after this one that only move on
+    bool cached;
+    unsigned by;                             // bytes to the next block
+    unsigned k_lane[kLaneParts], v_lane[kLaneParts];       // lanes' parts of an address
+    unsigned further;                        // bytes in memory from a load to the load four on; or to the next one, beyond the 1 KiB
   };
-  // the block that the wave brings in next: where it begins in the cache, and in the block's own rows, which begin where the
-  // cache's blocks end (unsigned arithmetic wraps there and back); the rows from there on
-  unsigned long long cached_at, fresh_at;
-  int cached_left, fresh_left;
-  auto begin_at = [&](int b, int end) __attribute__((always_inline)) {       // block b of those before `end`
-    cached_at = 64ull * D * (unsigned)b;
-    fresh_at = 32ull * new_bytes * (unsigned long long)(long long)(b - c_blk);
-    cached_left = c - 32 * b;
-    fresh_left = min(a.n_keys, 32 * (end - c_blk)) - 32 * (b - c_blk);
+  typedef std::true_type Yes;
+  typedef std::false_type No;
+  // `two`: K and V; else one tensor, in the place of K, whose chunks are K's or V's (`like_k`)
+  auto feed_lanes = [&](Feed& f, auto two, bool like_k) __attribute__((always_inline)) {
+    const unsigned row_bytes = f.cached ? 2u * D : new_bytes;
+    f.further = kLaneParts == 4 ? 4 * kRowsPerLoad * row_bytes : kRowsPerLoad * row_bytes - 1024u;
+#pragma unroll
+    for (int j = 0; j < kLaneParts; ++j) {
+      const unsigned row = (unsigned)(kRowsPerLoad * j + ld_sub) * row_bytes - 1024u * j;
+      const int chunk_k = ld_chunk_k ^ ((kRowsPerLoad * j) % kChunks);
+      f.k_lane[j] = row + 16u * (unsigned)(like_k ? chunk_k : ld_chunk_v);
+      if constexpr (decltype(two)::value) f.v_lane[j] = row + 16u * (unsigned)ld_chunk_v;
+    }
   };
-  begin_at(ks, kShared ? n_kb : n_blk);
-  auto source_of = [&](const u16* cache, const u16* fresh, unsigned chunk) __attribute__((always_inline)) -> Source {
-    const bool cached = cached_left > 0;
-    unsigned long long in_cache = (unsigned long long)cache + cached_at, in_fresh = (unsigned long long)fresh + fresh_at;
-    asm("" : "+s"(in_cache), "+s"(in_fresh));              // (choices between values, no branch)
-    const unsigned long long base = cached ? in_cache : in_fresh;
-    const int rows = min(cached ? cached_left : fresh_left, 32);
-    const unsigned row_bytes = cached ? 2u * D : new_bytes, bytes = rows > 0 ? (unsigned)(rows - 1) * row_bytes + 2u * D : 0u;
-    // (through the first lane: the compiler would carry the descriptor from round to round in vector registers)
-    return Source{u32x4{(unsigned)__builtin_amdgcn_readfirstlane((unsigned)base),
-                        (unsigned)__builtin_amdgcn_readfirstlane((unsigned)(base >> 32) & 0xFFFFu),
-                        (unsigned)__builtin_amdgcn_readfirstlane(bytes), 0x00020000u},
-                  row_bytes, (cached ? lane_cached : lane_fresh) + chunk};
+  auto buffer_at = [&](unsigned long long at, unsigned bytes) __attribute__((always_inline)) -> u32x4 {
+    return u32x4{(unsigned)at, (unsigned)(at >> 32) & 0xFFFFu, bytes, 0x00020000u};
   };
-  auto advance = [&]() __attribute__((always_inline)) {                     // KS blocks on
-    cached_at += 64ull * KS * D;
-    fresh_at += 32ull * KS * new_bytes;
-    cached_left -= 32 * KS;
-    fresh_left -= 32 * KS;
+  struct Tensors {
+    const u16 *kc, *kn, *vc, *vn;            // (one tensor: in the place of K)
+    int end;                                 // blocks from this one on are not wanted
+  };
+  auto feed_at = [&](Feed& f, const Tensors& of, int b, int step, auto two) __attribute__((always_inline)) {
+    f.cached = b < c_blk;
+    const int first = 32 * (f.cached ? b : b - c_blk), after = (f.cached ? c : min(a.n_keys, 32 * (of.end - c_blk))) - first - 32;
+    const unsigned row_bytes = f.cached ? 2u * D : new_bytes;
+    const unsigned long long at = (unsigned long long)(unsigned)first * row_bytes;
+    unsigned long long ka = (unsigned long long)of.kc, kb = (unsigned long long)of.kn;
+    asm("" : "+s"(ka), "+s"(kb));            // (choices between values, no branch)
+    const int rows = min(after + 32, 32);
+    const unsigned bytes = rows > 0 ? (unsigned)(rows - 1) * row_bytes + 2u * D : 0u;
+    f.k = buffer_at((f.cached ? ka : kb) + at, bytes);
+    if constexpr (decltype(two)::value) {
+      unsigned long long va = (unsigned long long)of.vc, vb = (unsigned long long)of.vn;
+      asm("" : "+s"(va), "+s"(vb));
+      f.v = buffer_at((f.cached ? va : vb) + at, bytes);
+    }
+    f.by = 32u * (unsigned)step * row_bytes;
+    f.whole = after > 0 && row_bytes < 1u << 23 ? (int)((unsigned)after / (32u * (unsigned)step)) : 0;       // (`by` is a 32-bit number)
+  };
+  auto move_on = [&](u32x4& buffer, unsigned by) __attribute__((always_inline)) {
+    const unsigned long long at = ((unsigned long long)buffer.y << 32 | buffer.x) + by;
+    buffer.x = (unsigned)at;
+    buffer.y = (unsigned)(at >> 32);
+  };
+  // On to block b, `step` blocks after the one that the feed is at.
+  auto feed_moves = [&](Feed& f, auto two) __attribute__((always_inline)) {
+    --f.whole;
+    move_on(f.k, f.by);
+    if constexpr (decltype(two)::value) move_on(f.v, f.by);
+  };
+  auto feed_anew = [&](Feed& f, const Tensors& of, int b, int step, auto two, bool like_k) __attribute__((always_inline)) {
+    const bool was = f.cached;
+    feed_at(f, of, b, step, two);
+    if (f.cached != was) feed_lanes(f, two, like_k);
+  };
+  auto feed_on = [&](Feed& f, const Tensors& of, int b, int step, auto two, bool like_k) __attribute__((always_inline)) {
+    if (f.whole > 0) feed_moves(f, two);
+    else feed_anew(f, of, b, step, two, like_k);
   };
   // k_bits: all ones for K, whose chunks are swizzled by the row, zero for V
-  auto load_one = [&](const Source& from, int j, unsigned to, unsigned k_bits) __attribute__((always_inline)) {
-    const unsigned lane_bytes = (from.lane ^ (16u * ((kRowsPerLoad * j) % kChunks) & k_bits)) + (unsigned)(kRowsPerLoad * j) * from.row_bytes;
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(lane_bytes), "s"(from.buffer),
-                 "s"(to + 2u * (unsigned)(j * kRowsPerLoad * D)) : "m0", "memory");
+  auto load_one = [&](const u32x4& from, const unsigned (&lane_at)[kLaneParts], unsigned further, int j, unsigned to, unsigned k_bits)
+      __attribute__((always_inline)) {
+    unsigned at;
+    if constexpr (kLaneParts == 4) at = lane_at[j % 4] + (j / 4) * further;
+    else at = (lane_at[0] ^ (16u * ((kRowsPerLoad * j) % kChunks) & k_bits)) + (unsigned)j * further + 4096u * (j / 4);
+    // (through the first lane: the compiler would carry the descriptor from block to block in vector registers)
+    const u32x4 buffer = {(unsigned)__builtin_amdgcn_readfirstlane(from.x), (unsigned)__builtin_amdgcn_readfirstlane(from.y),
+                          (unsigned)__builtin_amdgcn_readfirstlane(from.z), 0x00020000u};
+    if (j % 4 == 0)
+      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(at), "s"(buffer), "s"(to + 1024u * j) : "m0", "memory");
+    else                                     // (nothing else sets M0 between the four)
+      asm volatile("buffer_load_dwordx4 %0, %1, 0 offen offset:%2 lds" ::"v"(at), "s"(buffer), "n"(1024 * (j % 4)) : "memory");
   };
-  auto load_all = [&](const Source& from, unsigned to, unsigned k_bits) __attribute__((always_inline)) {
+  auto load_all = [&](const u32x4& from, const unsigned (&lane_at)[kLaneParts], unsigned further, unsigned to, unsigned k_bits) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < kLoads; ++j) load_one(from, j, to, k_bits);
+    for (int j = 0; j < kLoads; ++j) load_one(from, lane_at, further, j, to, k_bits);
   };
   const unsigned my_bits = qw == 0 ? ~0u : 0u;
 
@@ -347,23 +392,23 @@ attention_split_kernel(const AttnArgs args) {
     load_strip(q_rows + ((size_t)min(first_row, n - 1) * a.n_q_heads + h) * D, a.n_q_heads * D, max(min(32, n - first_row), 1),
                q_lds + (j / kLoads) * S::kStrip, j % kLoads);
   }
-  Source shared_next;                        // (two row tiles)
-  auto next_shared = [&]() __attribute__((always_inline)) {
-    advance();
-    shared_next = source_of(qw == 0 ? kc : vc, qw == 0 ? kn : vn, my_chunk);
-  };
+  Feed feed;                                 // one row tile: of block i and then i + 1; two: of the block that comes in next
+  const Tensors tensors = kShared ? Tensors{qw == 0 ? kc : vc, qw == 0 ? kn : vn, nullptr, nullptr, n_kb} : Tensors{kc, kn, vc, vn, n_blk};
+  typedef std::integral_constant<bool, !kShared> Both;
+  auto next_shared = [&](int i) __attribute__((always_inline)) { feed_on(feed, tensors, ks + KS * i, KS, No{}, qw == 0); };
+  feed_at(feed, tensors, ks, KS, Both{});
+  feed_lanes(feed, Both{}, kShared ? qw == 0 : true);
   if constexpr (kShared) {
-    load_all(source_of(qw == 0 ? kc : vc, qw == 0 ? kn : vn, my_chunk), my_to, my_bits);       // K(0) or V(0)
-    next_shared();
+    load_all(feed.k, feed.k_lane, feed.further, my_to, my_bits);                       // K(0) or V(0)
+    next_shared(1);
     if (qw == 0) {
-      load_all(shared_next, my_to + 2u * (unsigned)(KS * S::kStrip), my_bits);                 // K(1)
-      next_shared();
+      load_all(feed.k, feed.k_lane, feed.further, my_to + 2u * (unsigned)(KS * S::kStrip), my_bits);        // K(1)
+      next_shared(2);
     }
     wait_older_than(OneBlock{});
   } else {
-    load_all(source_of(kc, kn, chunk_k), lds_addr(k_strip), ~0u);
-    load_all(source_of(vc, vn, chunk_v), lds_addr(v_strip), 0u);
-    advance();
+    load_all(feed.k, feed.k_lane, feed.further, lds_addr(k_strip), ~0u);
+    load_all(feed.v, feed.v_lane, feed.further, lds_addr(v_strip), 0u);
     wait_older_than(TwoBlocks{});
   }
   __builtin_amdgcn_s_barrier();              // the query rows are in LDS
@@ -464,6 +509,9 @@ attention_split_kernel(const AttnArgs args) {
     // Round i: S(i + 1) = K(i + 1) Q^T with the exponentials of S(i) between the products, then O += P(i) V(i).
     constexpr int kNV = 2 * kND;
     constexpr int kAhead = D / 32;           // fragments read ahead of their product
+    // where the loads go: spread over all products, or over those of the first half (28/4 heads, d 128, 512 rows over 1536 keys, 16 layers, a
+    // prefix without scores 4165 us against 4200, with them 4933 against 4875)
+    constexpr bool kSpread = kKept <= 0 && D == 128;
     f32x16 s2[2];
     float mx;                                // of the row's logits in the block that comes next
     auto phase = [&](int i, auto parity, float (&p)[16]) __attribute__((always_inline)) {
@@ -508,7 +556,7 @@ attention_split_kernel(const AttnArgs args) {
         else read_v(st + kAhead - kNK);
         s_new = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[st], qf[st], st == 0 ? zero : s_new, 0, 0, 0);
         weigh(10 * st / kNK, 10 * (st + 1) / kNK);
-        if (st < kLoads) load_one(shared_next, st, my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
+        if (kSpread ? (st * kLoads) % (kNK + kNV) == 0 : st < kLoads) load_one(feed.k, feed.k_lane, feed.further, (kSpread ? st * kLoads / (kNK + kNV) : st), my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
         __builtin_amdgcn_sched_barrier(0);
       }
       float m = -INFINITY;
@@ -516,15 +564,21 @@ attention_split_kernel(const AttnArgs args) {
       for (int vi = 0; vi < kNV; ++vi) {
         if (vi + kAhead < kNV) read_v(vi + kAhead);
         o[vi % kND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[vi], p_frag(pw, vi / kND), o[vi % kND], 0, 0, 0);
+        if (kSpread && ((kNK + vi) * kLoads) % (kNK + kNV) == 0) load_one(feed.k, feed.k_lane, feed.further, (kNK + vi) * kLoads / (kNK + kNV), my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
         if (vi < kND) {                      // beside the products with the first sixteen keys
           weigh(10 + 6 * vi / kND, 10 + 6 * (vi + 1) / kND);
           if (vi == kND - 1) finish_element(15);
         } else {
-          if (vi == kND) next_shared();
+          if (kSpread && vi == kNV - 1) feed_moves(feed, No{});
 #pragma unroll
           for (int r = 16 * (vi - kND) / kND; r < 16 * (vi - kND + 1) / kND; r += 2) m = fmaxf(fmaxf(m, s_new[r]), s_new[r + 1]);
         }
         __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (kSpread) {
+        if (feed.whole < 0) feed_anew(feed, tensors, ks + KS * (i + (qw == 0 ? 3 : 2)), KS, No{}, qw == 0);
+      } else {
+        next_shared(i + (qw == 0 ? 3 : 2));
       }
       l_run += sum;
       mx = max_with_other_half(m);
@@ -539,8 +593,8 @@ attention_split_kernel(const AttnArgs args) {
       } else {
         constexpr int par = decltype(parity)::value;
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) load_one(shared_next, j, my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
-        next_shared();
+        for (int j = 0; j < kLoads; ++j) load_one(feed.k, feed.k_lane, feed.further, j, my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
+        next_shared(i + (qw == 0 ? 3 : 2));
       }
     };
     typedef std::integral_constant<int, 0> Even;
@@ -580,15 +634,17 @@ attention_split_kernel(const AttnArgs args) {
       attend(i, k_strip, v_strip, p,
              [&]() __attribute__((always_inline)) {
                __builtin_amdgcn_s_waitcnt(0xC07F);         // the strip has been read
-               if (more) load_all(source_of(kc, kn, chunk_k), lds_addr(k_strip), ~0u);
+               if (more) {
+                 feed_on(feed, tensors, ks + KS * (i + 1), KS, Yes{}, true);
+                 load_all(feed.k, feed.k_lane, feed.further, lds_addr(k_strip), ~0u);
+               }
              },
              [&]() __attribute__((always_inline)) {
                if (more) wait_older_than(OneBlock{});      // V(i) is in its strip; K(i + 1) may still be on its way
                else wait_older_than(None{});
              });
       __builtin_amdgcn_s_waitcnt(0xC07F);    // the strip has been read
-      if (more) load_all(source_of(vc, vn, chunk_v), lds_addr(v_strip), 0u);
-      advance();
+      if (more) load_all(feed.v, feed.v_lane, feed.further, lds_addr(v_strip), 0u);
     };
     if constexpr (kKept > 0) {
 #pragma unroll
@@ -730,8 +786,10 @@ attention_split_kernel(const AttnArgs args) {
   // its two strips in turn
   __syncthreads();                           // the rows' statistics are in LDS, the partial outputs have been read
   constexpr int kFirst = kKept > 0 ? kKept * KS : 0;       // (two row tiles: those before it are in registers)
-  begin_at(kFirst + wave, n_kb);
-  load_all(source_of(kc, kn, chunk_k), lds_addr(k_strip), ~0u);
+  const Tensors keys = {kc, kn, nullptr, nullptr, n_kb};
+  feed_at(feed, keys, kFirst + wave, S::kWaves, No{});
+  feed_lanes(feed, No{}, true);
+  load_all(feed.k, feed.k_lane, feed.further, lds_addr(k_strip), ~0u);
   if constexpr (kKept > 0) {
     settle_odd_rows(lse_row);
 #pragma unroll
@@ -771,8 +829,8 @@ attention_split_kernel(const AttnArgs args) {
       // (wave-uniform, which the compiler does not see through two loops in a row)
       const int b = __builtin_amdgcn_readfirstlane(at), odd = __builtin_amdgcn_readfirstlane(turn) & 1;
       u16* const strip = k_strip + odd * S::kWaves * S::kStrip;          // k_strip or v_strip
-      begin_at(b + S::kWaves, n_kb);
-      load_all(source_of(kc, kn, chunk_k), lds_addr(k_strip + (1 - odd) * S::kWaves * S::kStrip), ~0u);
+      feed_on(feed, keys, b + S::kWaves, S::kWaves, No{}, true);
+      load_all(feed.k, feed.k_lane, feed.further, lds_addr(k_strip + (1 - odd) * S::kWaves * S::kStrip), ~0u);
       wait_older_than(OneBlock{});
       bf16x8 kf[kNK];
 #pragma unroll

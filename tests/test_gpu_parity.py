@@ -176,6 +176,21 @@ def test_split_key_attention_edges(hq, hkv, d, c, n):
     cache.close()
 
 
+@pytest.mark.parametrize("evicts", [False, True])
+@pytest.mark.parametrize("hq,hkv,d,c,n", [
+    # 32-row workgroups: a wave's blocks go on and on in the cache, then in the block's rows, with a part block at the end of either or of neither
+    (4, 2, 128, 2048, 60), (4, 1, 128, 1100, 900), (4, 4, 64, 1025, 640), (8, 8, 64, 0, 1000), (16, 16, 128, 290, 500), (4, 2, 64, 4100, 33),
+    # 64-row workgroups: the same with the tensors of two waves apart
+    (28, 4, 128, 1500, 300), (32, 32, 128, 0, 700), (16, 4, 64, 1030, 600), (16, 16, 64, 95, 1200), (28, 28, 128, 1024, 320)])
+def test_blocks_that_a_wave_moves_over(hq, hkv, d, c, n, evicts):
+    """The split-key kernel's way from block to block: whole ones one after the other, and every change of kind, with scores and without."""
+    cache, oc, err, scores_ref, _ = _attention_case(hq, hkv, d, c, n, max(c, n // 2) if evicts else c + n, 1200, seed=7 * c + n)
+    assert err <= U.OUT_TOL, err
+    if evicts:
+        U.check_scores(cache.debug_last(0)[0].cpu().numpy(), scores_ref, n * (hq // hkv))
+    cache.close()
+
+
 def _rows_of_a_workgroup(n, hq):
     """Query rows of the workgroups that csrc/plan.cpp picks for a block."""
     if -(-n // 128) * hq >= 192:
