@@ -1034,6 +1034,36 @@ def test_cached_tokens_that_repeat(copies, t0):
         cache.close()
 
 
+@pytest.mark.parametrize("merge", [False, True])
+@pytest.mark.parametrize("hkv,layers", [(2, 1), (8, 6)])
+def test_running_totals(merge, hkv, layers):
+    """Every compaction adds what its plan says to the counters."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(hkv)
+    cache = K.Cache(layers, hkv, hkv, 64, 96, 64, [K.KvpSegment(0, 800, K.KVP_VISUAL, 10, 10, 8, 1)], merge=merge, scratch_sets=layers,
+                    device=DEV)
+    want = [0, 0, 0, 0]
+    for t0 in range(0, 448, 64):
+        for layer in range(layers):
+            draw = lambda: torch.randn((64, hkv, 64), generator=gen, device="cuda", dtype=torch.bfloat16)
+            cache.prefill_chunk(layer, t0, draw(), draw(), draw())
+        count = min(t0, 96)
+        cache.compact_layers(0, layers)
+        if count + 64 <= 96:
+            continue
+        for layer in range(layers):
+            _, keep, dst = cache.debug_last(layer)
+            merged = (dst >= 0) & (keep == 0)
+            want[0] += hkv
+            want[1] += int(keep[:, count:].sum())
+            want[2] += sum(len(torch.unique(dst[h][merged[h]])) for h in range(hkv))
+            want[3] += int(merged.sum())
+    totals = cache.totals()
+    assert [totals[name] for name in K.binding.TOTALS] == want
+    assert want[1] > 0 and (want[3] > 0) == merge
+    cache.close()
+
+
 def test_maximum_candidates_lockstep():
     """budget + block at the library's limit (8192 candidates per head): the select kernel's
     eight-candidates-per-thread shape, its largest LDS layout, 2048-row blocks."""
