@@ -127,6 +127,37 @@ def lib():
     return _lib
 
 
+# ---- the per-layer calls of Cache without ctypes
+def _not_taken(*_):
+    return None
+
+
+def _entry(name):
+    """Address of an entry point of the library."""
+    return ctypes.cast(getattr(lib(), name), ctypes.c_void_p).value
+
+
+class _Entries:
+    """Addresses of the entry points that Cache calls natively, looked up at the first use."""
+
+    def __getattr__(self, name):
+        address = _entry(name)
+        setattr(self, name, address)
+        return address
+
+
+_entries = _Entries()
+
+
+def _fast_call():
+    """csrc/fast_calls.cpp's call, where it has been built for this Python and torch."""
+    try:
+        from ._fast_calls import call
+    except ImportError:
+        return _not_taken
+    return call
+
+
 def _segments(segs):
     arr = (KvpSegment * len(segs))()
     for i, s in enumerate(segs):
@@ -309,12 +340,16 @@ class Cache:
         self.device = torch.device(device)
         # What every call needs, looked up once.  A step of a small model is a few microseconds on the GPU,
         # and a generating host has to stay ahead of it: with torch.cuda.current_stream() (2 us a call, against
-        # 0.2 for the raw handle below) and attribute chains a decode step cost 7.5 us of host time, now 4.6.
+        # 0.2 for the raw handle below) and attribute chains a decode step cost 7.5 us of host time, then 5.4, of which the checks of
+        # the tensors and ctypes' conversions were 3.5.  csrc/fast_calls.cpp does both natively (4 layers of 32/32 heads, 265 keys: 21.8 -> 17.0 us a token).  What it does
+        # not take comes back as None and goes the way through Python, which says what is wrong.
         self._bf16 = torch.bfloat16
         self._q_row = (n_q_heads, head_dim)
         self._kv_row = (n_kv_heads, head_dim)
         self._raw_stream = torch._C._cuda_getCurrentRawStream if self.device.index is not None else None
         self._lib = lib()
+        self._index = self.device.index
+        self._call = _fast_call() if self._index is not None else _not_taken
         self.nbytes = nbytes
         self.persistent_bytes = kvp_persistent_bytes(self.cfg)
         # Optional guard bands: the whole allocation is filled with 0xFF (a NaN pattern in bf16 and
@@ -364,15 +399,25 @@ class Cache:
         return n, ptr(q, bf), ptr(k, bf), ptr(v, bf), ptr(out, bf), out
 
     def prefill_chunk(self, layer, token_begin, q, k, v, out=None, stream=None):
-        n, qp, kp, vp, op, out = self._prefill_args(q, k, v, out)
-        rc = self._lib.kvp_prefill_chunk(self.handle, layer, token_begin, n, qp, kp, vp, op, self._stream(stream))
+        if out is None:
+            out = self.torch.empty_like(q)
+        rc = self._call(_entries.kvp_prefill_chunk, self.handle, layer, (q, k, v, out), self._q_row, self._kv_row, self._index,
+                        self._stream(stream), token_begin)
+        if rc is None:
+            n, qp, kp, vp, op, out = self._prefill_args(q, k, v, out)
+            rc = self._lib.kvp_prefill_chunk(self.handle, layer, token_begin, n, qp, kp, vp, op, self._stream(stream))
         if rc:
             raise KvpError(rc, "kvp_prefill_chunk")
         return out
 
     def prefill_chunk_keydiff(self, layer, token_begin, q, k, v, out=None, stream=None):
-        n, qp, kp, vp, op, out = self._prefill_args(q, k, v, out)
-        rc = self._lib.kvp_prefill_chunk_keydiff(self.handle, layer, token_begin, n, qp, kp, vp, op, self._stream(stream))
+        if out is None:
+            out = self.torch.empty_like(q)
+        rc = self._call(_entries.kvp_prefill_chunk_keydiff, self.handle, layer, (q, k, v, out), self._q_row, self._kv_row, self._index,
+                        self._stream(stream), token_begin)
+        if rc is None:
+            n, qp, kp, vp, op, out = self._prefill_args(q, k, v, out)
+            rc = self._lib.kvp_prefill_chunk_keydiff(self.handle, layer, token_begin, n, qp, kp, vp, op, self._stream(stream))
         if rc:
             raise KvpError(rc, "kvp_prefill_chunk_keydiff")
         return out
@@ -389,23 +434,34 @@ class Cache:
         """q [Hq, d]; k_tail, v_tail [n_tail, Hkv, d] (the generated tokens, the current one last)."""
         if out is None:
             out = self.torch.empty_like(q)
-        rc = self._lib.kvp_decode_step(self.handle, layer, *self._decode_args(q, k_tail, v_tail, out), self._stream(stream))
+        rc = self._call(_entries.kvp_decode_step, self.handle, layer, (q, k_tail, v_tail, out), self._q_row, self._kv_row, self._index,
+                        self._stream(stream), None)
+        if rc is None:
+            rc = self._lib.kvp_decode_step(self.handle, layer, *self._decode_args(q, k_tail, v_tail, out), self._stream(stream))
         if rc:
             raise KvpError(rc, "kvp_decode_step")
         return out
 
     def decode_step_static(self, layer, q, k_tail, v_tail, out, stream=None):
         """decode_step with the library's static scratch; `out` must be given (nothing is allocated)."""
-        rc = self._lib.kvp_decode_step_static(self.handle, layer, *self._decode_args(q, k_tail, v_tail, out), self._stream(stream))
+        rc = self._call(_entries.kvp_decode_step_static, self.handle, layer, (q, k_tail, v_tail, out), self._q_row, self._kv_row, self._index,
+                        self._stream(stream), None)
+        if rc is None:
+            rc = self._lib.kvp_decode_step_static(self.handle, layer, *self._decode_args(q, k_tail, v_tail, out), self._stream(stream))
         if rc:
             raise KvpError(rc, "kvp_decode_step_static")
         return out
 
     def prefill_chunk_proxy(self, layer, token_begin, q, k, v, q_obs, out=None, stream=None):
-        n, qp, kp, vp, op, out = self._prefill_args(q, k, v, out)
-        assert q_obs.shape[1:] == q.shape[1:]
-        rc = self._lib.kvp_prefill_chunk_proxy(self.handle, layer, token_begin, n, qp, kp, vp, op,
-                                               self._ptr(q_obs, self._bf16), q_obs.shape[0], self._stream(stream))
+        if out is None:
+            out = self.torch.empty_like(q)
+        rc = self._call(_entries.kvp_prefill_chunk_proxy, self.handle, layer, (q, k, v, out, q_obs), self._q_row, self._kv_row,
+                        self._index, self._stream(stream), token_begin)
+        if rc is None:
+            n, qp, kp, vp, op, out = self._prefill_args(q, k, v, out)
+            assert q_obs.shape[1:] == q.shape[1:]
+            rc = self._lib.kvp_prefill_chunk_proxy(self.handle, layer, token_begin, n, qp, kp, vp, op,
+                                                   self._ptr(q_obs, self._bf16), q_obs.shape[0], self._stream(stream))
         if rc:
             raise KvpError(rc, "kvp_prefill_chunk_proxy")
         return out

@@ -12,6 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkvp.so")
+FAST_CALLS = os.path.join(HERE, "_fast_calls.so")
 SOURCES = ["attention.hip", "attention_split.hip", "colsum.hip", "rowstat.hip", "keydiff.hip", "decode.hip", "select.hip", "compact.hip", "probe.hip", "plan.cpp", "kvp.cpp"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -38,6 +39,21 @@ def _run(cmd):
     return out
 
 
+def build_fast_calls():
+    """The Python module of csrc/fast_calls.cpp, for the Python and torch that run this."""
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+    cmd += ["-I" + d for d in include_paths() + [sysconfig.get_paths()["include"]]]
+    cmd += [os.path.join(CSRC, "fast_calls.cpp"), "-o", FAST_CALLS, "-L" + torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
+            "-Wl,-rpath," + torch_lib]
+    _run(cmd)
+    return FAST_CALLS
+
+
 def build(verbose=False):
     hipcc = _hipcc()
     obj_dir = os.path.join(ROOT, "_build")
@@ -50,10 +66,12 @@ def build(verbose=False):
         cmd = [hipcc] + FLAGS + (["-x", "hip"] if src.endswith(".cpp") else []) + \
               ["-c", os.path.join(CSRC, src), "-o", obj]
         jobs.append(cmd)
-    with ThreadPoolExecutor(max_workers=min(8, len(jobs))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(jobs) + 1)) as ex:
+        fast_calls = ex.submit(build_fast_calls)
         for out in ex.map(_run, jobs):
             if verbose and out:
                 print(out)
+        fast_calls.result()
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs)
     return LIB
 

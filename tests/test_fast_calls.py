@@ -1,0 +1,105 @@
+"""The native way of Cache's per-layer calls: the same bits and the same refusals as the way through ctypes."""
+import pytest
+import torch
+
+import paper_2604_16734_amd as K
+from paper_2604_16734_amd import binding as B
+
+BF16 = torch.bfloat16
+
+
+def test_module_is_built_and_leaves_what_it_does_not_know():
+    call = B._fast_call()
+    assert call is not B._not_taken, "build the library: paper_2604_16734_amd.build builds the module, too"
+    q, k = torch.zeros(4, 64, dtype=BF16), torch.zeros(3, 2, 64, dtype=BF16)
+    # (no entry point is ever reached: these tensors are not on a GPU)
+    good = [1, 1, 0, (q, k, k, q), (4, 64), (2, 64), 0, 0, None]
+    assert call(*good) is None
+    for at, other in [(0, None), (0, 0), (1, None), (1, "1"), (2, 1.0), (2, 1 << 40), (3, [q, k, k, q]), (3, (q, k, k)), (3, (q, k, k, None)),
+                      (4, (4,)), (4, None), (5, [2, 64]), (6, None), (7, None), (7, -1), (8, "0"), (8, 1 << 40)]:
+        assert call(*(good[:at] + [other] + good[at + 1:])) is None, (at, other)
+    with pytest.raises(TypeError):
+        call(*good[:-1])
+
+
+def _cache(**more):
+    cache = K.Cache(2, 8, 2, 64, 96, 64, [K.KvpSegment(0, 4000, K.KVP_TEXT, 0, 0, 0, 0)], scratch_sets=2, device="cuda:0", **more)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(5)
+    for layer in range(2):
+        k, v, token, weight, _, _ = cache.decode_ready(layer)
+        k.copy_(torch.randn(k.shape, generator=gen, device="cuda"))
+        v.copy_(torch.randn(v.shape, generator=gen, device="cuda"))
+        token.copy_(torch.arange(96, device="cuda", dtype=torch.int32).expand(2, 96))
+        weight.fill_(1.0)
+        cache.set_state(layer, 96, 200)
+    return cache
+
+
+def _tensors(n, heads):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(n + heads)
+    return torch.randn((n, heads, 64), generator=gen, device="cuda", dtype=BF16)
+
+
+CALLS = {
+    "prefill_chunk": lambda c, out: c.prefill_chunk(1, 200, _tensors(40, 8), _tensors(40, 2), _tensors(41, 2)[:40], out),
+    "keydiff": lambda c, out: c.prefill_chunk_keydiff(1, 200, _tensors(40, 8), _tensors(40, 2), _tensors(41, 2)[1:], out),
+    "proxy": lambda c, out: c.prefill_chunk_proxy(1, 200, _tensors(40, 8), _tensors(40, 2), _tensors(41, 2)[1:], _tensors(9, 8), out),
+    "decode": lambda c, out: c.decode_step(1, _tensors(3, 8)[1], _tensors(5, 2), _tensors(6, 2)[1:], None if out is None else out[0]),
+    "decode_static": lambda c, out: c.decode_step_static(1, _tensors(3, 8)[1], _tensors(5, 2), _tensors(6, 2)[1:],
+                                                         torch.empty_like(_tensors(1, 8)[0]) if out is None else out[0]),
+}
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", CALLS)
+@pytest.mark.parametrize("given", [False, True])
+def test_same_bits_as_through_ctypes(name, given):
+    got = []
+    for native in (True, False):
+        cache = _cache()
+        taken = []
+        fast = cache._call
+        assert fast is not B._not_taken
+        cache._call = (lambda *a: taken.append(fast(*a)) or taken[-1]) if native else B._not_taken
+        out = CALLS[name](cache, torch.zeros((40, 8, 64), device="cuda", dtype=BF16) if given else None)
+        assert not native or taken == [0]
+        if not name.startswith("decode"):
+            cache.compact(1)
+            got.append([out] + list(cache.decode_ready(1)[:4]))
+        else:
+            got.append([out])
+        cache.close()
+    for a, b in zip(*got):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+def test_refusals(native):
+    cache = _cache()
+    if not native:
+        cache._call = B._not_taken
+    q, k, out = _tensors(3, 8)[0], _tensors(5, 2), torch.empty((8, 64), device="cuda", dtype=BF16)
+    cache.decode_step(0, q, k, k, out)
+    for bad in [(q.float(), k, k, out), (q.cpu(), k, k, out), (q, k, k[1:], out), (q, k.transpose(0, 1), k, out), (q[:4], k, k, out),
+                (q, k, k, out.t().contiguous().t()), (q, k, k, _tensors(3, 8)[:1]), (q, _tensors(5, 3), _tensors(5, 3), out)]:
+        with pytest.raises(AssertionError):
+            cache.decode_step(0, *bad)
+    for layer, tail in [(2, k), (-1, k), (0, k[:0])]:
+        with pytest.raises(K.KvpError) as e:
+            cache.decode_step(layer, q, tail, tail, out)
+        assert e.value.code == B.KVP_EINVAL
+    block_q, block_k = _tensors(40, 8), _tensors(40, 2)
+    with pytest.raises(K.KvpError) as e:
+        cache.prefill_chunk(0, 199, block_q, block_k, block_k)      # not the next token
+    first = e.value.code
+    with pytest.raises(AssertionError):
+        cache.prefill_chunk_proxy(0, 200, block_q, block_k, block_k, _tensors(9, 4))
+    with pytest.raises(AssertionError):
+        cache.prefill_chunk(0, 200, block_q, block_k[1:], block_k[1:])
+    assert first == B.KVP_ESTATE or first == B.KVP_EINVAL
+    cache.close()
+    with pytest.raises(K.KvpError):
+        cache.decode_step(0, q, k, k, out)
