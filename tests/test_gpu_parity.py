@@ -15,7 +15,7 @@ import pytest
 import torch
 
 import paper_2604_16734_amd as K
-from kvp_workload import Segment, Workload, get_workload, layer_inputs, bf16_bits_to_f32, chunk_ranges
+from kvp_workload import Segment, Workload, get_workload, layer_inputs, bf16_bits_to_f32, chunk_ranges, f32_to_bf16_bits
 from oracle import kvp_oracle as O
 from tests import gpu_util as U
 
@@ -615,6 +615,51 @@ def test_decode_logits(d, c, keys, queries):
     e = scale * 12 * 2.0 ** -24 * most
     assert e < 0.02
     assert np.abs(out - ref).max() <= (2.1 * e + 2.0 ** -8) * np.abs(v64).max()
+    cache.close()
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_keys", [
+    (8, 2, 128, 100), (4, 4, 128, 333), (8, 2, 128, 560), (8, 2, 64, 900),       # one workgroup per query head, few rows per thread and many
+    (4, 4, 128, 900), (4, 2, 128, 900), (8, 2, 64, 1500),                        # partial results, by vector instructions
+    (6, 2, 128, 900), (8, 2, 128, 8900), (14, 2, 128, 8900), (20, 2, 128, 8900), (32, 2, 128, 700)])      # by matrix instructions, and several tiles
+@pytest.mark.parametrize("kind", ["growing", "denormal", "infinite"])
+def test_decode_values(hq, hkv, d, n_keys, kind):
+    """Weights against references that later keys leave behind, values too small for a normal number, and infinite ones."""
+    rng = np.random.default_rng(n_keys + hq)
+    tail = 2900 if n_keys > 6000 else 50
+    c, g = n_keys - tail, hq // hkv
+    kb, vb, qb = _rand_bits(rng, (n_keys, hkv, d)), _rand_bits(rng, (n_keys, hkv, d)), _rand_bits(rng, (hq, d))
+    k64, v64, q64 = O.bf16_bits_to_f64(kb), O.bf16_bits_to_f64(vb), O.bf16_bits_to_f64(qb)
+    if kind == "growing":
+        k64 = O.bf16_bits_to_f64(f32_to_bf16_bits((k64 * np.linspace(0.1, 4, n_keys)[:, None, None]).astype(np.float32)))
+        k64[rng.permutation(n_keys)[:n_keys // 3]] = 0.0
+    elif kind == "denormal":
+        v64 = O.bf16_bits_to_f64(f32_to_bf16_bits((v64 * 2.0 ** -128).astype(np.float32)))
+    else:
+        v64[rng.integers(n_keys // 2), 0, 3] = np.inf
+        v64[n_keys // 3, 0, 5] = -np.inf     # (not among the last keys, whose values and results are read again for what is not there)
+        v64[[0, n_keys // 2], 0, 7] = np.inf, -np.inf
+    to_gpu = lambda x: torch.from_numpy(np.ascontiguousarray(x)).to(torch.bfloat16).to(DEV)      # (exact)
+    cache = K.Cache(1, hq, hkv, d, c, min(c, 512), [Segment(0, 100000, 0)], merge=False, device=DEV)
+    k, v, token, weight, _, _ = cache.decode_ready(0)
+    k.copy_(to_gpu(k64[:c].transpose(1, 0, 2)))
+    v.copy_(to_gpu(v64[:c].transpose(1, 0, 2)))
+    token.copy_(torch.arange(c, device=DEV, dtype=torch.int32).expand(hkv, c))
+    weight.fill_(1.0)
+    cache.set_state(0, c, c)
+    out = U.torch_bf16_to_f64(cache.decode_step(0, to_gpu(q64), to_gpu(k64[c:]), to_gpu(v64[c:])))
+    with np.errstate(invalid="ignore"):
+        ref = O.decode_step(q64, k64.transpose(1, 0, 2), v64.transpose(1, 0, 2))
+    if kind == "infinite":
+        assert np.isposinf(ref[:g, 3]).all() and np.isneginf(ref[:g, 5]).all() and np.isnan(ref[:g, 7]).all()
+        assert np.array_equal(np.isposinf(out), np.isposinf(ref)) and np.array_equal(np.isneginf(out), np.isneginf(ref))
+        assert np.array_equal(np.isnan(out), np.isnan(ref))
+        ok = np.isfinite(ref)
+        assert np.abs(out[ok] - ref[ok]).max() <= 5e-3 * np.abs(ref[ok]).max()
+    elif kind == "denormal":     # half a unit of the smallest bf16 numbers, and as much for the fp32 sums of two roundings
+        assert np.abs(out - ref).max() <= 2.0 ** -133 + 5e-3 * np.abs(ref).max()
+    else:
+        assert U.out_rel_err(out, ref) <= 5e-3       # fp32 throughout: the rounding of the output to bf16 alone
     cache.close()
 
 
