@@ -509,9 +509,9 @@ attention_split_kernel(const AttnArgs args) {
     // Round i: S(i + 1) = K(i + 1) Q^T with the exponentials of S(i) between the products, then O += P(i) V(i).
     constexpr int kNV = 2 * kND;
     constexpr int kAhead = D / 32;           // fragments read ahead of their product
-    // where the loads go: spread over all products, or over those of the first half (28/4 heads, d 128, 512 rows over 1536 keys, 16 layers, a
-    // prefix without scores 4165 us against 4200, with them 4933 against 4875)
-    constexpr bool kSpread = kKept <= 0 && D == 128;
+    // The loads go with the first products, and the feed moves on among the products with V, a branch and all: 16 layers of 28/4 heads,
+    // d 128, 512 rows over 1536 keys, a layer per launch 4764 us a prefix with the feed behind the products, 4734 with it here.  (Moved on
+    // without a branch, and set anew behind the products where the kind of block changes: 0.8 % slower.)
     f32x16 s2[2];
     float mx;                                // of the row's logits in the block that comes next
     auto phase = [&](int i, auto parity, float (&p)[16]) __attribute__((always_inline)) {
@@ -556,7 +556,7 @@ attention_split_kernel(const AttnArgs args) {
         else read_v(st + kAhead - kNK);
         s_new = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[st], qf[st], st == 0 ? zero : s_new, 0, 0, 0);
         weigh(10 * st / kNK, 10 * (st + 1) / kNK);
-        if (kSpread ? (st * kLoads) % (kNK + kNV) == 0 : st < kLoads) load_one(feed.k, feed.k_lane, feed.further, (kSpread ? st * kLoads / (kNK + kNV) : st), my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
+        if (st < kLoads) load_one(feed.k, feed.k_lane, feed.further, st, my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
         __builtin_amdgcn_sched_barrier(0);
       }
       float m = -INFINITY;
@@ -564,21 +564,15 @@ attention_split_kernel(const AttnArgs args) {
       for (int vi = 0; vi < kNV; ++vi) {
         if (vi + kAhead < kNV) read_v(vi + kAhead);
         o[vi % kND] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr[vi], p_frag(pw, vi / kND), o[vi % kND], 0, 0, 0);
-        if (kSpread && ((kNK + vi) * kLoads) % (kNK + kNV) == 0) load_one(feed.k, feed.k_lane, feed.further, (kNK + vi) * kLoads / (kNK + kNV), my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
         if (vi < kND) {                      // beside the products with the first sixteen keys
           weigh(10 + 6 * vi / kND, 10 + 6 * (vi + 1) / kND);
           if (vi == kND - 1) finish_element(15);
         } else {
-          if (kSpread && vi == kNV - 1) feed_moves(feed, No{});
+          if (vi == kND) next_shared(i + (qw == 0 ? 3 : 2));
 #pragma unroll
           for (int r = 16 * (vi - kND) / kND; r < 16 * (vi - kND + 1) / kND; r += 2) m = fmaxf(fmaxf(m, s_new[r]), s_new[r + 1]);
         }
         __builtin_amdgcn_sched_barrier(0);
-      }
-      if constexpr (kSpread) {
-        if (feed.whole < 0) feed_anew(feed, tensors, ks + KS * (i + (qw == 0 ? 3 : 2)), KS, No{}, qw == 0);
-      } else {
-        next_shared(i + (qw == 0 ? 3 : 2));
       }
       l_run += sum;
       mx = max_with_other_half(m);
