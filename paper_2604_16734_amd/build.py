@@ -76,6 +76,13 @@ def build(verbose=False):
     return LIB
 
 
+def assembly(src, out_dir):
+    """The device code of a source as it is built, as assembly text; returns the file's path."""
+    out = os.path.join(out_dir, src.rsplit(".", 1)[0] + ".s")
+    _run([_hipcc()] + FLAGS + ["--cuda-device-only", "-S", os.path.join(CSRC, src), "-o", out])
+    return out
+
+
 def build_host_sanitized(out_dir):
     """The host side alone (kvp.cpp and plan.cpp; kernel launchers and HIP runtime calls stubbed) with
     the driver of tests/host_asan, compiled by g++ with the address and undefined-behaviour

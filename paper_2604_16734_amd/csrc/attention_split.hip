@@ -29,7 +29,7 @@
 // cycles.  Blocks therefore come through buffer descriptors, whose end takes care of a block's missing rows, and their addresses, the
 // blocks that need a mask and the reference's margin are carried along instead of being worked out for each; and all fragments of a product
 // are asked for before the first of them is used.  16/4 heads, d 64, 333 rows over 1444 keys: 11.2 -> 10.4 us; 28/4 heads, d 128, 256 rows over
-// 768 keys: 10.6 -> 10.3 us.  From one whole block to the next a descriptor only moves on, and four loads share a setting of M0 (Feed: a
+// 768 keys: 10.6 -> 10.3 us.  From one whole block to the next a descriptor only moves on, and four loads go out in one statement with one setting of M0 (Feed: a
 // block of d 64 had 56 scalar instructions, now 19): 16/4 heads, d 64, 333 rows over 1444 keys 9.06 -> 8.78 us, 28/4 heads, d 128, 256 rows
 // over 768 keys 8.55 -> 8.37, 16 layers of 28/4 heads, 512 rows over 1536 keys 4858 -> 4766 us a prefix.  What bounds the 32-row launches beside
 // that is the path into the CU: the blocks of a round are 64 KiB at d 64 and 128 at d 128, 1024 and 2048 of its 1270 and 2000 cycles.
@@ -366,23 +366,29 @@ attention_split_kernel(const AttnArgs args) {
     if (f.whole > 0) feed_moves(f, two);
     else feed_anew(f, of, b, step, two, like_k);
   };
-  // k_bits: all ones for K, whose chunks are swizzled by the row, zero for V
-  auto load_one = [&](const u32x4& from, const unsigned (&lane_at)[kLaneParts], unsigned further, int j, unsigned to, unsigned k_bits)
+  // Loads 4 i .. 4 i + 3 of a block, in one statement: what sets M0 and what reads it stay together.  k_bits: all ones for K, whose
+  // chunks are swizzled by the row, zero for V.
+  auto load_four = [&](const u32x4& from, const unsigned (&lane_at)[kLaneParts], unsigned further, int i, unsigned to, unsigned k_bits)
       __attribute__((always_inline)) {
-    unsigned at;
-    if constexpr (kLaneParts == 4) at = lane_at[j % 4] + (j / 4) * further;
-    else at = (lane_at[0] ^ (16u * ((kRowsPerLoad * j) % kChunks) & k_bits)) + (unsigned)j * further + 4096u * (j / 4);
+    unsigned at[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if constexpr (kLaneParts == 4) at[j] = lane_at[j] + (unsigned)i * further;
+      else at[j] = (lane_at[0] ^ (16u * ((kRowsPerLoad * j) % kChunks) & k_bits)) + (unsigned)(4 * i + j) * further + 4096u * i;
+    }
     // (through the first lane: the compiler would carry the descriptor from block to block in vector registers)
     const u32x4 buffer = {(unsigned)__builtin_amdgcn_readfirstlane(from.x), (unsigned)__builtin_amdgcn_readfirstlane(from.y),
                           (unsigned)__builtin_amdgcn_readfirstlane(from.z), 0x00020000u};
-    if (j % 4 == 0)
-      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, 0 offen lds" ::"v"(at), "s"(buffer), "s"(to + 1024u * j) : "m0", "memory");
-    else                                     // (nothing else sets M0 between the four)
-      asm volatile("buffer_load_dwordx4 %0, %1, 0 offen offset:%2 lds" ::"v"(at), "s"(buffer), "n"(1024 * (j % 4)) : "memory");
+    asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\t"
+                 "buffer_load_dwordx4 %0, %4, 0 offen lds\n\t"
+                 "buffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\t"
+                 "buffer_load_dwordx4 %2, %4, 0 offen offset:2048 lds\n\t"
+                 "buffer_load_dwordx4 %3, %4, 0 offen offset:3072 lds" ::"v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "s"(buffer), "s"(to + 4096u * i)
+                 : "m0", "memory");
   };
-  auto load_all = [&](const u32x4& from, const unsigned (&lane_at)[kLaneParts], unsigned further, unsigned to, unsigned k_bits) __attribute__((always_inline)) {
+  auto load_all = [&](const Feed& f, const u32x4& from, const unsigned (&lane_at)[kLaneParts], unsigned to, unsigned k_bits) __attribute__((always_inline)) {
 #pragma unroll
-    for (int j = 0; j < kLoads; ++j) load_one(from, lane_at, further, j, to, k_bits);
+    for (int i = 0; i < kLoads / 4; ++i) load_four(from, lane_at, f.further, i, to, k_bits);
   };
   const unsigned my_bits = qw == 0 ? ~0u : 0u;
 
@@ -399,16 +405,16 @@ attention_split_kernel(const AttnArgs args) {
   feed_at(feed, tensors, ks, KS, Both{});
   feed_lanes(feed, Both{}, kShared ? qw == 0 : true);
   if constexpr (kShared) {
-    load_all(feed.k, feed.k_lane, feed.further, my_to, my_bits);                       // K(0) or V(0)
+    load_all(feed, feed.k, feed.k_lane, my_to, my_bits);                       // K(0) or V(0)
     next_shared(1);
     if (qw == 0) {
-      load_all(feed.k, feed.k_lane, feed.further, my_to + 2u * (unsigned)(KS * S::kStrip), my_bits);        // K(1)
+      load_all(feed, feed.k, feed.k_lane, my_to + 2u * (unsigned)(KS * S::kStrip), my_bits);        // K(1)
       next_shared(2);
     }
     wait_older_than(OneBlock{});
   } else {
-    load_all(feed.k, feed.k_lane, feed.further, lds_addr(k_strip), ~0u);
-    load_all(feed.v, feed.v_lane, feed.further, lds_addr(v_strip), 0u);
+    load_all(feed, feed.k, feed.k_lane, lds_addr(k_strip), ~0u);
+    load_all(feed, feed.v, feed.v_lane, lds_addr(v_strip), 0u);
     wait_older_than(TwoBlocks{});
   }
   __builtin_amdgcn_s_barrier();              // the query rows are in LDS
@@ -514,6 +520,11 @@ attention_split_kernel(const AttnArgs args) {
     // without a branch, and set anew behind the products where the kind of block changes: 0.8 % slower.)
     f32x16 s2[2];
     float mx;                                // of the row's logits in the block that comes next
+    static_assert(kLoads == kNK);
+    auto shared_loads = [&](int k, auto parity) __attribute__((always_inline)) {           // four loads of the block that comes in
+      constexpr int par = decltype(parity)::value;
+      load_four(feed.k, feed.k_lane, feed.further, k, my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
+    };
     auto phase = [&](int i, auto parity, float (&p)[16]) __attribute__((always_inline)) {
       constexpr int par = decltype(parity)::value;
       f32x16& s = s2[par];
@@ -556,7 +567,7 @@ attention_split_kernel(const AttnArgs args) {
         else read_v(st + kAhead - kNK);
         s_new = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[st], qf[st], st == 0 ? zero : s_new, 0, 0, 0);
         weigh(10 * st / kNK, 10 * (st + 1) / kNK);
-        if (st < kLoads) load_one(feed.k, feed.k_lane, feed.further, st, my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
+        if (st % 4 == 0) shared_loads(st / 4, parity);
         __builtin_amdgcn_sched_barrier(0);
       }
       float m = -INFINITY;
@@ -585,9 +596,8 @@ attention_split_kernel(const AttnArgs args) {
       if (i < my_blk) {
         phase(i, parity, p);
       } else {
-        constexpr int par = decltype(parity)::value;
 #pragma unroll
-        for (int j = 0; j < kLoads; ++j) load_one(feed.k, feed.k_lane, feed.further, j, my_to + 2u * (unsigned)((qw == 0 ? par : par ^ 1) * KS * S::kStrip), my_bits);
+        for (int k = 0; k < kLoads / 4; ++k) shared_loads(k, parity);
         next_shared(i + (qw == 0 ? 3 : 2));
       }
     };
@@ -630,7 +640,7 @@ attention_split_kernel(const AttnArgs args) {
                __builtin_amdgcn_s_waitcnt(0xC07F);         // the strip has been read
                if (more) {
                  feed_on(feed, tensors, ks + KS * (i + 1), KS, Yes{}, true);
-                 load_all(feed.k, feed.k_lane, feed.further, lds_addr(k_strip), ~0u);
+                 load_all(feed, feed.k, feed.k_lane, lds_addr(k_strip), ~0u);
                }
              },
              [&]() __attribute__((always_inline)) {
@@ -638,7 +648,7 @@ attention_split_kernel(const AttnArgs args) {
                else wait_older_than(None{});
              });
       __builtin_amdgcn_s_waitcnt(0xC07F);    // the strip has been read
-      if (more) load_all(feed.v, feed.v_lane, feed.further, lds_addr(v_strip), 0u);
+      if (more) load_all(feed, feed.v, feed.v_lane, lds_addr(v_strip), 0u);
     };
     if constexpr (kKept > 0) {
 #pragma unroll
@@ -783,7 +793,7 @@ attention_split_kernel(const AttnArgs args) {
   const Tensors keys = {kc, kn, nullptr, nullptr, n_kb};
   feed_at(feed, keys, kFirst + wave, S::kWaves, No{});
   feed_lanes(feed, No{}, true);
-  load_all(feed.k, feed.k_lane, feed.further, lds_addr(k_strip), ~0u);
+  load_all(feed, feed.k, feed.k_lane, lds_addr(k_strip), ~0u);
   if constexpr (kKept > 0) {
     settle_odd_rows(lse_row);
 #pragma unroll
@@ -824,7 +834,7 @@ attention_split_kernel(const AttnArgs args) {
       const int b = __builtin_amdgcn_readfirstlane(at), odd = __builtin_amdgcn_readfirstlane(turn) & 1;
       u16* const strip = k_strip + odd * S::kWaves * S::kStrip;          // k_strip or v_strip
       feed_on(feed, keys, b + S::kWaves, S::kWaves, No{}, true);
-      load_all(feed.k, feed.k_lane, feed.further, lds_addr(k_strip + (1 - odd) * S::kWaves * S::kStrip), ~0u);
+      load_all(feed, feed.k, feed.k_lane, lds_addr(k_strip + (1 - odd) * S::kWaves * S::kStrip), ~0u);
       wait_older_than(OneBlock{});
       bf16x8 kf[kNK];
 #pragma unroll
