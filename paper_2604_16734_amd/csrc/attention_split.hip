@@ -235,7 +235,8 @@ attention_split_kernel(const AttnArgs args) {
   // ---- global memory -> LDS, 16 bytes per lane.  Instruction j brings in rows kRowsPerLoad j + (0 ..
   // kRowsPerLoad - 1) of a 32-row strip; the 16-byte chunks of a row are XOR-swizzled on the way so that the
   // fragment reads are free of bank conflicts (K and Q: by the row, V: v_swizzle).  Inline assembly for the
-  // reasons given in attention.hip; the waits are this kernel's own.
+  // reasons given in attention.hip; the waits are this kernel's own.  (s_nop 3: a load may read a scalar register five wait states after a
+  // vector instruction, such as one that reads the first lane, has written it, and the compiler does not see to that here.)
   u16* const k_strip = reinterpret_cast<u16*>(lds_raw) + wave * S::kStrip;
   u16* const v_strip = k_strip + S::kWaves * S::kStrip;
   const unsigned lds_base =
@@ -244,7 +245,7 @@ attention_split_kernel(const AttnArgs args) {
     return lds_base + 2u * (unsigned)(p - reinterpret_cast<u16*>(lds_raw));
   };
   auto load_row16 = [&](const u16* base, unsigned lane_bytes, unsigned to) __attribute__((always_inline)) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_bytes), "s"(base), "s"(to)
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 3\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_bytes), "s"(base), "s"(to)
                  : "m0", "memory");
   };
   const int ld_sub = lane / kChunks, ld_pos = lane % kChunks;
@@ -379,7 +380,7 @@ attention_split_kernel(const AttnArgs args) {
     // (through the first lane: the compiler would carry the descriptor from block to block in vector registers)
     const u32x4 buffer = {(unsigned)__builtin_amdgcn_readfirstlane(from.x), (unsigned)__builtin_amdgcn_readfirstlane(from.y),
                           (unsigned)__builtin_amdgcn_readfirstlane(from.z), 0x00020000u};
-    asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\t"
+    asm volatile("s_mov_b32 m0, %5\n\ts_nop 3\n\t"
                  "buffer_load_dwordx4 %0, %4, 0 offen lds\n\t"
                  "buffer_load_dwordx4 %1, %4, 0 offen offset:1024 lds\n\t"
                  "buffer_load_dwordx4 %2, %4, 0 offen offset:2048 lds\n\t"
