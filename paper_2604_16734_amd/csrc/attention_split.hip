@@ -516,9 +516,15 @@ attention_split_kernel(const AttnArgs args) {
     // Round i: S(i + 1) = K(i + 1) Q^T with the exponentials of S(i) between the products, then O += P(i) V(i).
     constexpr int kNV = 2 * kND;
     constexpr int kAhead = D / 32;           // fragments read ahead of their product
-    // The loads go with the first products, and the feed moves on among the products with V, a branch and all: 16 layers of 28/4 heads,
-    // d 128, 512 rows over 1536 keys, a layer per launch 4764 us a prefix with the feed behind the products, 4734 with it here.  (Moved on
-    // without a branch, and set anew behind the products where the kind of block changes: 0.8 % slower.)
+    // The feed moves on among the products with V, a branch and all: 16 layers of 28/4 heads, d 128, 512 rows over 1536 keys, a layer
+    // per launch 4764 us a prefix with the feed behind the products, 4734 with it here.  (Set anew for every block, without a branch, with the
+    // loop in one piece or not: 16 layers per launch without scores 0.8 % slower.)
+    //
+    // The loads go out four at a time beside two of the products with K, which ones was measured.  The same prefix, a layer per launch with
+    // scores: 4867 us with a load beside each product, 4788 with four beside products 0 and 4, 4883 with 2 and 10.  16 layers per launch without
+    // scores, where a CU has one workgroup after the other: 3940 us with a load beside each, 3920 with 0 and 4, 3900 with 1 and 6; 0 and 1
+    // were 1.6 % slower than 0 and 4.
+    constexpr int kLoadsWith[2] = {kKept > 0 ? 0 : 1, kKept > 0 ? 5 : 6};
     f32x16 s2[2];
     float mx;                                // of the row's logits in the block that comes next
     static_assert(kLoads == kNK);
@@ -568,7 +574,9 @@ attention_split_kernel(const AttnArgs args) {
         else read_v(st + kAhead - kNK);
         s_new = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr[st], qf[st], st == 0 ? zero : s_new, 0, 0, 0);
         weigh(10 * st / kNK, 10 * (st + 1) / kNK);
-        if (st % 4 == 0) shared_loads(st / 4, parity);
+#pragma unroll
+        for (int k = 0; k < kLoads / 4; ++k)
+          if (st == kLoadsWith[k]) shared_loads(k, parity);
         __builtin_amdgcn_sched_barrier(0);
       }
       float m = -INFINITY;
