@@ -39,7 +39,7 @@ def _run(cmd):
     return out
 
 
-def build_fast_calls():
+def build_fast_calls(out=FAST_CALLS, defines=()):
     """The Python module of csrc/fast_calls.cpp, for the Python and torch that run this."""
     import sysconfig
     import torch
@@ -47,11 +47,12 @@ def build_fast_calls():
     torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
+    cmd += ["-D" + d for d in defines]
     cmd += ["-I" + d for d in include_paths() + [sysconfig.get_paths()["include"]]]
-    cmd += [os.path.join(CSRC, "fast_calls.cpp"), "-o", FAST_CALLS, "-L" + torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
+    cmd += [os.path.join(CSRC, "fast_calls.cpp"), "-o", out, "-L" + torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
             "-Wl,-rpath," + torch_lib]
     _run(cmd)
-    return FAST_CALLS
+    return out
 
 
 def build(verbose=False):

@@ -4,13 +4,18 @@
 //
 // call(entry, handle, layer, tensors, q_row, kv_row, device, stream, token_begin) -> the entry point's code, or None where anything
 // about the arguments is not plainly as it should be: the caller then takes its Python path, which has the same checks and says what is
-// wrong.  Nothing is kept from one call to the next.
+// wrong.  Nothing is kept from one call to the next, and no C++ exception leaves: what a tensor throws when it is looked at counts as not plain.
 #include <Python.h>
 
 #include <ATen/core/Tensor.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <cstdint>
+
+// where the tensors have to be (the tests build the module for the CPU, too)
+#ifndef KVP_TENSOR_DEVICE
+#define KVP_TENSOR_DEVICE c10::DeviceType::CUDA
+#endif
 
 namespace {
 
@@ -20,14 +25,14 @@ constexpr int kMostTensors = 5;
 bool plain(PyObject* o, int64_t device, const at::Tensor** out) {
   if (!THPVariable_CheckExact(o)) return false;
   const at::Tensor& t = THPVariable_Unpack(o);
-  if (!t.defined()) return false;
+  if (!t.defined() || t.is_nested()) return false;
   const auto keys = t.key_set();
   if (keys.has_any(c10::DispatchKeySet({c10::DispatchKey::Python, c10::DispatchKey::FuncTorchBatched, c10::DispatchKey::FuncTorchGradWrapper,
                                         c10::DispatchKey::Functionalize, c10::DispatchKey::Batched, c10::DispatchKey::ZeroTensor})))
     return false;
   if (t.layout() != at::kStrided || !t.has_storage() || t.scalar_type() != at::kBFloat16 || !t.is_contiguous()) return false;
   const c10::Device d = t.device();
-  if (!d.is_cuda() || d.index() != device) return false;
+  if (d.type() != KVP_TENSOR_DEVICE || d.index() != device) return false;
   *out = &t;
   return true;
 }
@@ -66,6 +71,23 @@ bool rows_of(const at::Tensor& t, const int64_t (&row)[2], int64_t rows) {      
   return t.dim() == 3 && t.size(0) == rows && t.size(1) == row[0] && t.size(2) == row[1];
 }
 
+// the tensors' addresses, the rows of K and those of q_obs, where all are plain and of the shapes that belong together
+bool plain_tensors(PyObject* list, Py_ssize_t n_tensors, bool step, const int64_t (&q_row)[2], const int64_t (&kv_row)[2], int64_t device,
+                   void* (&p)[kMostTensors], int64_t* rows, int64_t* n_obs) {
+  const at::Tensor* t[kMostTensors];
+  for (Py_ssize_t i = 0; i < n_tensors; ++i) {
+    if (!plain(PyTuple_GET_ITEM(list, i), device, &t[i])) return false;
+    p[i] = t[i]->numel() > 0 ? t[i]->mutable_data_ptr() : nullptr;
+  }
+  *rows = t[1]->dim() == 3 ? t[1]->size(0) : -1;
+  *n_obs = n_tensors == 5 && t[4]->dim() == 3 ? t[4]->size(0) : 0;
+  if (*rows < 0 || *rows > INT32_MAX || *n_obs > INT32_MAX || !rows_of(*t[1], kv_row, *rows) || !rows_of(*t[2], kv_row, *rows)) return false;
+  for (const int i : {0, 3}) {
+    if (step ? t[i]->dim() != 2 || t[i]->size(0) != q_row[0] || t[i]->size(1) != q_row[1] : !rows_of(*t[i], q_row, *rows)) return false;
+  }
+  return n_tensors < 5 || rows_of(*t[4], q_row, *n_obs);
+}
+
 // `tensors`: (q, k_tail, v_tail, out) of a step, token_begin None; or (q, k, v, out[, q_obs]) of a block
 PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
   if (n_args != 9) {
@@ -83,18 +105,14 @@ PyObject* call(PyObject*, PyObject* const* args, Py_ssize_t n_args) {
     Py_RETURN_NONE;
   const Py_ssize_t n_tensors = PyTuple_GET_SIZE(list);
   if (n_tensors < 4 || n_tensors > (step ? 4 : kMostTensors)) Py_RETURN_NONE;
-  const at::Tensor* t[kMostTensors];
   void* p[kMostTensors];
-  for (Py_ssize_t i = 0; i < n_tensors; ++i) {
-    if (!plain(PyTuple_GET_ITEM(list, i), device, &t[i])) Py_RETURN_NONE;
-    p[i] = t[i]->numel() > 0 ? t[i]->mutable_data_ptr() : nullptr;
+  int64_t rows = -1, n_obs = 0;
+  try {
+    if (!plain_tensors(list, n_tensors, step, q_row, kv_row, device, p, &rows, &n_obs)) Py_RETURN_NONE;
+  } catch (...) {
+    PyErr_Clear();
+    Py_RETURN_NONE;
   }
-  const int64_t rows = t[1]->dim() == 3 ? t[1]->size(0) : -1, n_obs = n_tensors == 5 && t[4]->dim() == 3 ? t[4]->size(0) : 0;
-  if (rows < 0 || rows > INT32_MAX || n_obs > INT32_MAX || !rows_of(*t[1], kv_row, rows) || !rows_of(*t[2], kv_row, rows)) Py_RETURN_NONE;
-  for (const int i : {0, 3}) {
-    if (step ? t[i]->dim() != 2 || t[i]->size(0) != q_row[0] || t[i]->size(1) != q_row[1] : !rows_of(*t[i], q_row, rows)) Py_RETURN_NONE;
-  }
-  if (n_tensors == 5 && !rows_of(*t[4], q_row, n_obs)) Py_RETURN_NONE;
   int code;
   Py_BEGIN_ALLOW_THREADS;                    // (as ctypes does: a launch may have to wait)
   if (step)

@@ -1,9 +1,14 @@
 """The native way of Cache's per-layer calls: the same bits and the same refusals as the way through ctypes."""
+import ctypes
+import importlib.util
+import os
+
 import pytest
 import torch
 
 import paper_2604_16734_amd as K
 from paper_2604_16734_amd import binding as B
+from paper_2604_16734_amd import build as build_module
 
 BF16 = torch.bfloat16
 
@@ -20,6 +25,33 @@ def test_module_is_built_and_leaves_what_it_does_not_know():
         assert call(*(good[:at] + [other] + good[at + 1:])) is None, (at, other)
     with pytest.raises(TypeError):
         call(*good[:-1])
+
+
+@pytest.fixture(scope="module")
+def cpu_call(tmp_path_factory):
+    """The module's call, built for tensors on the CPU."""
+    path = build_module.build_fast_calls(os.path.join(str(tmp_path_factory.mktemp("fast_calls")), "_fast_calls.so"),
+                                         ["KVP_TENSOR_DEVICE=c10::DeviceType::CPU"])
+    spec = importlib.util.spec_from_file_location("_fast_calls", path)
+    module = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(module)
+    return module.call
+
+
+STEP = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32,
+                        ctypes.c_void_p, ctypes.c_void_p)
+
+
+@pytest.mark.filterwarnings("ignore:The PyTorch API of nested tensors")
+@pytest.mark.parametrize("rows", [(2, 2, 2), (2, 3, 4)])
+def test_nested_tensors_are_left(cpu_call, rows):
+    """A list of rows that may differ in length is no tensor of the cache, whatever its address; and asking for its sizes throws."""
+    entry = STEP(lambda *_: 7)
+    q = torch.zeros(4, 64, dtype=BF16)
+    k = torch.nested.nested_tensor([torch.zeros(r, 64, dtype=BF16) for r in rows])
+    args = lambda k: (ctypes.cast(entry, ctypes.c_void_p).value, 1, 0, (q, k, k, q), (4, 64), (2, 64), -1, 0, None)
+    assert cpu_call(*args(torch.zeros(3, 2, 64, dtype=BF16))) == 7
+    assert cpu_call(*args(k)) is None
 
 
 def _cache(**more):
