@@ -150,12 +150,13 @@ _entries = _Entries()
 
 
 def _fast_call():
-    """csrc/fast_calls.cpp's call, where it has been built for this Python and torch."""
+    """csrc/fast_calls.cpp's call, where it has been built for this Python (by its file's name) and this torch."""
+    import torch
     try:
-        from ._fast_calls import call
+        from . import _fast_calls
     except ImportError:
         return _not_taken
-    return call
+    return _fast_calls.call if getattr(_fast_calls, "torch_version", None) == str(torch.__version__) else _not_taken
 
 
 def _segments(segs):

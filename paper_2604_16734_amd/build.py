@@ -6,13 +6,14 @@ to this file; object files go to ``_build/`` at the repository root.
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkvp.so")
-FAST_CALLS = os.path.join(HERE, "_fast_calls.so")
+FAST_CALLS = os.path.join(HERE, "_fast_calls" + sysconfig.get_config_var("EXT_SUFFIX"))       # for this Python alone
 SOURCES = ["attention.hip", "attention_split.hip", "colsum.hip", "rowstat.hip", "keydiff.hip", "decode.hip", "select.hip", "compact.hip", "probe.hip", "plan.cpp", "kvp.cpp"]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -41,13 +42,12 @@ def _run(cmd):
 
 def build_fast_calls(out=FAST_CALLS, defines=()):
     """The Python module of csrc/fast_calls.cpp, for the Python and torch that run this."""
-    import sysconfig
     import torch
     from torch.utils.cpp_extension import include_paths
     torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI]
-    cmd += ["-D" + d for d in defines]
+    cmd += ["-D" + d for d in ('KVP_TORCH_VERSION="%s"' % torch.__version__,) + tuple(defines)]
     cmd += ["-I" + d for d in include_paths() + [sysconfig.get_paths()["include"]]]
     cmd += [os.path.join(CSRC, "fast_calls.cpp"), "-o", out, "-L" + torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10",
             "-Wl,-rpath," + torch_lib]

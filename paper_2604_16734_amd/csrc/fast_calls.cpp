@@ -133,4 +133,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_fast_calls", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__fast_calls() { return PyModule_Create(&module); }
+// torch_version: that of the headers the module was built with, whose layouts of a tensor are part of its code
+PyMODINIT_FUNC PyInit__fast_calls() {
+  PyObject* const m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "torch_version", KVP_TORCH_VERSION) != 0) {
+    Py_DECREF(m);
+    return nullptr;
+  }
+  return m;
+}

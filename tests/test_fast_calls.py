@@ -1,5 +1,6 @@
 """The native way of Cache's per-layer calls: the same bits and the same refusals as the way through ctypes."""
 import ctypes
+import importlib.machinery
 import importlib.util
 import os
 
@@ -25,6 +26,13 @@ def test_module_is_built_and_leaves_what_it_does_not_know():
         assert call(*(good[:at] + [other] + good[at + 1:])) is None, (at, other)
     with pytest.raises(TypeError):
         call(*good[:-1])
+
+
+def test_module_of_another_torch_is_not_called(monkeypatch):
+    """It links against any torch that has the symbols, but the layout of a tensor is compiled into it."""
+    monkeypatch.setattr(torch, "__version__", torch.__version__ + ".another")
+    assert B._fast_call() is B._not_taken
+    assert build_module.FAST_CALLS.endswith(importlib.machinery.EXTENSION_SUFFIXES[0])      # (a name that another Python does not look for)
 
 
 @pytest.fixture(scope="module")
