@@ -28,6 +28,22 @@ def test_module_is_built_and_leaves_what_it_does_not_know():
         call(*good[:-1])
 
 
+def test_library_is_linked_without_the_module(monkeypatch, tmp_path, capsys):
+    """hipcc alone makes the library: what the module needs besides may be missing."""
+    commands = []
+    monkeypatch.setattr(build_module, "ROOT", str(tmp_path))
+    monkeypatch.setattr(build_module, "FAST_CALLS", str(tmp_path / "module.so"))
+    monkeypatch.setattr(build_module, "_run", lambda cmd: commands.append(cmd) or "")
+
+    def no_headers():
+        raise RuntimeError("Python.h: No such file or directory")
+    monkeypatch.setattr(build_module, "build_fast_calls", no_headers)
+    (tmp_path / "module.so").write_bytes(b"of older sources")
+    assert build_module.build() == build_module.LIB
+    assert commands[-1][commands[-1].index("-o") + 1] == build_module.LIB and len(commands) == len(build_module.SOURCES) + 1
+    assert "Python.h" in capsys.readouterr().err and not (tmp_path / "module.so").exists()
+
+
 def test_module_of_another_torch_is_not_called(monkeypatch):
     """It links against any torch that has the symbols, but the layout of a tensor is compiled into it."""
     monkeypatch.setattr(torch, "__version__", torch.__version__ + ".another")
