@@ -14,18 +14,8 @@ from paper_2604_16734_amd import build as build_module
 BF16 = torch.bfloat16
 
 
-def test_module_is_built_and_leaves_what_it_does_not_know():
-    call = B._fast_call()
-    assert call is not B._not_taken, "build the library: paper_2604_16734_amd.build builds the module, too"
-    q, k = torch.zeros(4, 64, dtype=BF16), torch.zeros(3, 2, 64, dtype=BF16)
-    # (no entry point is ever reached: these tensors are not on a GPU)
-    good = [1, 1, 0, (q, k, k, q), (4, 64), (2, 64), 0, 0, None]
-    assert call(*good) is None
-    for at, other in [(0, None), (0, 0), (1, None), (1, "1"), (2, 1.0), (2, 1 << 40), (3, [q, k, k, q]), (3, (q, k, k)), (3, (q, k, k, None)),
-                      (4, (4,)), (4, None), (5, [2, 64]), (6, None), (7, None), (7, -1), (8, "0"), (8, 1 << 40)]:
-        assert call(*(good[:at] + [other] + good[at + 1:])) is None, (at, other)
-    with pytest.raises(TypeError):
-        call(*good[:-1])
+def test_module_is_built():
+    assert B._fast_call() is not B._not_taken, "build the library: paper_2604_16734_amd.build builds the module, too"
 
 
 def test_library_is_linked_without_the_module(monkeypatch, tmp_path, capsys):
@@ -64,6 +54,52 @@ def cpu_call(tmp_path_factory):
 
 STEP = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_int32, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int32,
                         ctypes.c_void_p, ctypes.c_void_p)
+
+
+def test_what_is_not_plain_is_left(cpu_call):
+    """One argument at a time of a call that is taken."""
+    taken = []
+    entry = STEP(lambda *args: taken.append(args) or 7)
+    q, k, out = torch.zeros(4, 64, dtype=BF16), torch.zeros(3, 2, 64, dtype=BF16), torch.zeros(4, 64, dtype=BF16)
+    good = [ctypes.cast(entry, ctypes.c_void_p).value, 11, 5, (q, k, k, out), (4, 64), (2, 64), -1, 13, None]
+    assert cpu_call(*good) == 7
+    assert taken == [(11, 5, q.data_ptr(), k.data_ptr(), k.data_ptr(), 3, out.data_ptr(), 13)]
+    wide = torch.zeros(3, 2, 128, dtype=BF16)
+    for at, others in [
+            (0, [None, 0, "1", -1]), (1, [None, 0, "1", -1, 1 << 64]), (2, [None, 1.0, "1", True, 1 << 40, -(1 << 40)]),
+            (3, [[q, k, k, out], (q, k, k), (q, k, k, None), (q, k, k, out, q), (q.float(), k, k, out), (q[:3], k, k, out), (q[None], k, k, out),
+                 (q, k[:2], k, out), (q, k, k[:2], out), (q, k[0], k[0], out), (q, wide[..., :64], k, out), (q, k, wide[..., ::2], out),
+                 (q, k.transpose(1, 2), k, out), (q, k, k, out[:3]), (q, k, k, out[None]), (q, k.to_sparse(), k, out), (q.numpy, k, k, out),
+                 (torch.nn.Parameter(q).to("meta"), k, k, out)]),
+            (4, [(4,), None, [4, 64], (4, 64, 1), (4.0, 64), (1 << 40, 64), (5, 64), (4, 32)]), (5, [(2,), None, [2, 64], (3, 64), (2, 128)]),
+            (6, [None, 0, "0", 1 << 40]), (7, [None, -1, "0", 1 << 64]), (8, ["0", 1.0, 1 << 40, 0])]:
+        for other in others:
+            assert cpu_call(*(good[:at] + [other] + good[at + 1:])) is None, (at, other)
+    assert len(taken) == 1
+    for n in (8, 10):
+        with pytest.raises(TypeError):
+            cpu_call(*(good + [None])[:n])
+
+
+def test_blocks_that_are_not_plain_are_left(cpu_call):
+    taken = []
+    block = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, *[ctypes.c_void_p] * 5)
+    proxy = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, *[ctypes.c_void_p] * 5, ctypes.c_int32,
+                             ctypes.c_void_p)
+    q, k, obs = torch.zeros(3, 4, 64, dtype=BF16), torch.zeros(3, 2, 64, dtype=BF16), torch.zeros(9, 4, 64, dtype=BF16)
+    p = [t.data_ptr() for t in (q, k, k, q, obs)]
+    for kind, more in [(block, ()), (proxy, (obs,))]:
+        entry = kind(lambda *args: taken.append(args) or -5)
+        args = lambda *tensors, begin=17: (ctypes.cast(entry, ctypes.c_void_p).value, 11, 5, tensors, (4, 64), (2, 64), -1, 13, begin)
+        assert cpu_call(*args(q, k, k, q, *more)) == -5
+        assert taken.pop() == (11, 5, 17, 3) + tuple(p[:4]) + ((p[4], 9) if more else ()) + (13,)
+        for bad in [(q[:2], k, k, q), (q, k[:2], k, q), (q, k, k[:2], q), (q, k, k, q[:2]), (q, k, k, q.float())]:
+            assert cpu_call(*args(*bad, *more)) is None
+        for begin in ("17", 1.0, 1 << 40):
+            assert cpu_call(*args(q, k, k, q, *more, begin=begin)) is None
+    for bad in (obs[0], obs[:, :3], obs.float(), obs.transpose(0, 1)):
+        assert cpu_call(*args(q, k, k, q, bad)) is None
+    assert not taken
 
 
 @pytest.mark.filterwarnings("ignore:The PyTorch API of nested tensors")
