@@ -136,6 +136,7 @@ __device__ __forceinline__ float of_parts(const f32x4& d) {
 // 16 launches, vector instructions against this: 28/4 heads of d 128, 509 keys 85.3 -> 79.0 us, 629 98.8 -> 92.4; 32/32 heads of d 64, 709
 // keys 82.6 -> 76.4, 8/2, 1269 100.6 -> 92.5; with five rows 32/32 heads of d 128, 265 keys 69.8 -> 68.0, 28/4, 309 61.5 -> 62.8; one row, 29 keys
 // 39.6 -> 45.8.  What bounds it then is the path into the CU: 283 KB of 28/4 heads and 553 keys are 4400 of its clocks.
+constexpr float kDownscale = 0x1p-32f;           // far enough for the rows of a wave
 template <int D, int kLoads>
 __global__ void __launch_bounds__(kHeadThreads)
 decode_head_kernel(const DecodeArgs a) {
@@ -193,10 +194,32 @@ decode_head_kernel(const DecodeArgs a) {
     // Register r of lane l is row 4 (l / 16) + r of the result, column l % 16.  At d 64 the odd rows of the wave lie in lanes 8 .. 15 of
     // sixteen: their parts are rows 8 .. 10, their columns 8 .. 15.
     const int slot = D == 64 && lane >= 32 ? kHeadWaves + wave : wave;
-    if (D == 128 ? lane < 16 : lane < 8 || (lane >= 40 && lane < 48)) {
+    const bool leaves = D == 128 ? lane < 16 : lane < 8 || (lane >= 40 && lane < 48);
+    float o[8];
+    auto have_sums = [&]() __attribute__((always_inline)) {      // are all of them finite?
+      bool finite = true;
 #pragma unroll
-      for (int e = 0; e < 8; e += 4)
-        *reinterpret_cast<float4*>(&s_o[slot][8 * piece + e]) = make_float4(of_parts(d[e]), of_parts(d[e + 1]), of_parts(d[e + 2]), of_parts(d[e + 3]));
+      for (int e = 0; e < 8; ++e) {
+        o[e] = of_parts(d[e]);
+        finite = finite && __builtin_fabsf(o[e]) <= __FLT_MAX__;
+      }
+      return finite || !leaves;
+    };
+    // Values near the largest number there is may be too much for sums against the wave's own maximum, where the row's is far above that:
+    // then the weights are taken against a reference further up.
+    if (!__all(have_sums()) && mx != -INFINITY) {
+#pragma unroll
+      for (int i = 0; i < kLoads; ++i) parts[i] = __float_as_uint(__uint_as_float(parts[i]) * kDownscale);
+      l *= kDownscale;
+      if (lane == 0) s_m[wave] = ref - __builtin_log2f(kDownscale) / a.scale_log2;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) d[e] = f32x4{0.f, 0.f, 0.f, 0.f};
+      weigh_rows<kLoads>(parts, vw, d);
+      have_sums();
+    }
+    if (leaves) {
+#pragma unroll
+      for (int e = 0; e < 8; e += 4) *reinterpret_cast<float4*>(&s_o[slot][8 * piece + e]) = make_float4(o[e], o[e + 1], o[e + 2], o[e + 3]);
     }
   } else {
     float o[8];

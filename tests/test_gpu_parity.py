@@ -618,13 +618,25 @@ def test_decode_logits(d, c, keys, queries):
     cache.close()
 
 
-@pytest.mark.parametrize("hq,hkv,d,n_keys", [
-    (8, 2, 128, 100), (4, 4, 128, 333), (8, 2, 128, 560), (8, 2, 64, 900),       # one workgroup per query head, few rows per thread and many
+ONE_WORKGROUP = [(8, 2, 128, 100), (4, 4, 128, 333), (8, 2, 128, 560), (8, 2, 64, 900)]      # per query head, few rows per thread and many
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_keys", ONE_WORKGROUP + [
     (4, 4, 128, 900), (4, 2, 128, 900), (8, 2, 64, 1500),                        # partial results, by vector instructions
     (6, 2, 128, 900), (8, 2, 128, 8900), (14, 2, 128, 8900), (20, 2, 128, 8900), (32, 2, 128, 700)])      # by matrix instructions, and several tiles
 @pytest.mark.parametrize("kind", ["growing", "denormal", "infinite"])
 def test_decode_values(hq, hkv, d, n_keys, kind):
     """Weights against references that later keys leave behind, values too small for a normal number, and infinite ones."""
+    _decode_values(hq, hkv, d, n_keys, kind)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_keys", ONE_WORKGROUP)
+def test_decode_values_near_the_largest(hq, hkv, d, n_keys):
+    """Sums that only the small weights of their values keep finite, over keys that some waves have to themselves."""
+    _decode_values(hq, hkv, d, n_keys, "large")
+
+
+def _decode_values(hq, hkv, d, n_keys, kind):
     rng = np.random.default_rng(n_keys + hq)
     tail = 2900 if n_keys > 6000 else 50
     c, g = n_keys - tail, hq // hkv
@@ -635,6 +647,11 @@ def test_decode_values(hq, hkv, d, n_keys, kind):
         k64[rng.permutation(n_keys)[:n_keys // 3]] = 0.0
     elif kind == "denormal":
         v64 = O.bf16_bits_to_f64(f32_to_bf16_bits((v64 * 2.0 ** -128).astype(np.float32)))
+    elif kind == "large":
+        q64[:] = rng.choice([-1.0, 1.0], size=d)
+        large = np.arange(n_keys) % 64 // 8 == 2
+        k64[large] = -2 * q64[0]             # 2 sqrt(d) below the mean of the others' logits
+        v64[large] = 2.0 ** 127
     else:
         v64[rng.integers(n_keys // 2), 0, 3] = np.inf
         v64[n_keys // 3, 0, 5] = -np.inf     # (not among the last keys, whose values and results are read again for what is not there)
