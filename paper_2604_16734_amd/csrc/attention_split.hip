@@ -29,10 +29,11 @@
 // cycles.  Blocks therefore come through buffer descriptors, whose end takes care of a block's missing rows, and their addresses, the
 // blocks that need a mask and the reference's margin are carried along instead of being worked out for each; and all fragments of a product
 // are asked for before the first of them is used.  16/4 heads, d 64, 333 rows over 1444 keys: 11.2 -> 10.4 us; 28/4 heads, d 128, 256 rows over
-// 768 keys: 10.6 -> 10.3 us.  From one whole block to the next a descriptor only moves on, and four loads go out in one statement with one setting of M0 (Feed: a
-// block of d 64 had 56 scalar instructions, now 19): 16/4 heads, d 64, 333 rows over 1444 keys 9.06 -> 8.78 us, 28/4 heads, d 128, 256 rows
-// over 768 keys 8.55 -> 8.37, 16 layers of 28/4 heads, 512 rows over 1536 keys 4858 -> 4766 us a prefix.  What bounds the 32-row launches beside
-// that is the path into the CU: the blocks of a round are 64 KiB at d 64 and 128 at d 128, 1024 and 2048 of its 1270 and 2000 cycles.
+// 768 keys: 10.6 -> 10.3 us.  From one whole block to the next a descriptor only moves on, and four loads go out in one statement with one
+// setting of M0 (Feed: a block of d 64 had 56 scalar instructions, now 19): 16/4 heads, d 64, 333 rows over 1444 keys 9.06 -> 8.78 us, 28/4
+// heads, d 128, 256 rows over 768 keys 8.55 -> 8.37, 16 layers of 28/4 heads, 512 rows over 1536 keys 4863 -> 4646 us a prefix.  What bounds the
+// 32-row launches beside that is the path into the CU: the blocks of a round are 64 KiB at d 64 and 128 at d 128, 1024 and 2048 of its 1270 and
+// 2000 cycles.
 //
 // The partial results of a row meet in LDS as they lie in the accumulators; a wave's own are written over its own strips, with no barrier
 // in front, and with kept weights a wave puts together one slice of the channels of the rows that its lanes have anyway: 0.3 us of each
@@ -140,12 +141,13 @@ __device__ __forceinline__ float sum_over_half(float (&v)[16], float factor, int
 // kScoreByKeys: no scores from the queries, and the first workgroups of the launch score by the keys alone
 constexpr int kScoreByKeys = -1;
 //
-// Without scores a workgroup at d 64 has 110 (one row tile) or 126 (two) registers a lane, and two of them fit on a CU.  With two row tiles
+// Without scores a workgroup at d 64 has 112 (one row tile) or 124 (two) registers a lane, and two of them fit on a CU.  With two row tiles
 // that takes the second sweep out (launches with scores keep weights) and the loop over the rounds in one piece: the first rounds
 // taken apart from the others, as the compiler would, had 138 and one workgroup per CU.  Whole prefixes, 8 layers per launch: 16/4
 // heads, 640 rows over 1920 keys, proxy queries 969 -> 812 us, 1300 over 3900 1141 -> 978; 32/32 heads, 512 rows over 1536 keys 1954 -> 1647;
 // 28/4 heads, 512 rows over 1536 keys, scored by the keys 1199 -> 1006.  At d 128, where one workgroup fits either way, the first rounds
-// apart are the faster way.
+// apart are the faster way: 16 layers of 28/4 heads, 512 rows over 1536 keys, proxy queries, a prefix 3710 us, in one piece 3726, with the
+// second sweep left in 3723.
 template <int D, int QW, int kKept>
 __global__ void __launch_bounds__((Split<D, QW>::kThreads))
 attention_split_kernel(const AttnArgs args) {
@@ -908,8 +910,8 @@ hipError_t prepare_shape() {
                              hipFuncAttributeMaxDynamicSharedMemorySize, Split<D, QW>::kLdsBytes);
 }
 
-// 32-row workgroups: as many kept blocks per wave as the list needs, where registers have room for them (d 128: 248 of 256
-// with six; d 64: 214 with eight).  A launch without scores keeps none.
+// 32-row workgroups: as many kept blocks per wave as the list needs, where registers have room for them (d 128: all 256
+// with six; d 64: 228 with eight).  A launch without scores keeps none.
 template <int D>
 hipError_t launch_split32(const AttnArgs& a, hipStream_t s) {
   if (a.key_score_wgs > 0) return launch_shape<D, 1, kScoreByKeys>(a, s);

@@ -14,15 +14,16 @@
 //            added on the DPP network, so that every lane of a row knows its logit;
 //   weights  every lane then has the exponentials of its own rows, against a maximum of the wave or the
 //            workgroup;
-//   values   it scales its V pieces; the sums over the rows of a wave are taken pairwise by lane swaps (a
-//            swap and an addition halve two values at once), those over the waves through LDS.
+//   values   with few rows per thread, or few query heads per KV head, it scales its V pieces, and the sums over the rows of a
+//            wave are taken pairwise by lane swaps (a swap and an addition halve two values at once); else the products of weights and
+//            values, sums over the wave included, are matrix instructions (weigh_rows).  Those over the waves go through LDS.
 // Two ways to spread the work:
 //   few keys (up to 640 at head dimension 128): one workgroup of 1024 threads per QUERY head takes all of
 //            them and writes the result, one launch.  (A CU takes 64 bytes a clock from L2: beyond
 //            about 700 keys that costs more than the second launch below.)  The kernel is built for each
 //            number of rows a thread may hold, one to ten: rows past the end are loaded again at full price,
-//            so a step takes the fewest that cover its keys.  10.3 -> 4.7 us per layer at 32/32 heads, 265 keys
-//            (6.4 with ten rows per thread), 15.2 -> 6.0 at 28/4 heads, 553 keys;
+//            so a step takes the fewest that cover its keys.  4.3 us per layer at 32/32 heads, 265 keys, 5.4 at 28/4 heads, 553
+//            keys;
 //   else     a workgroup of 256 threads takes 64 keys of one KV head at a time for all G query heads of
 //            the group and leaves (unnormalised output, maximum, sum) per query head; a second kernel
 //            folds the workgroups' partials in a fixed order and rounds once to bfloat16.

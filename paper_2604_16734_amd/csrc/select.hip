@@ -576,7 +576,7 @@ compact_kernel(const SelectArgs args) {
 
   // Running totals for the benchmark's byte counts (integer atomics: the order does not matter), a lane of the last wave each, on their way
   // while the rows move.  The heads of all dies add to one line of memory: by one lane after the other, at the kernel's end, that kept it
-  // from ending for 0.35 us (4 heads) to 2.9 (128).  4 layers of 32 heads of d 128, 384 candidates, a whole prefix 191.6 -> 178.5 us.
+  // from ending for 0.35 us (4 heads) to 2.8 (128).  4 layers of 32 heads of d 128, 384 candidates, a whole prefix 191.6 -> 178.5 us.
   static_assert(KVP_T_EVICTING_HEADS == 0 && KVP_T_MOVED_ROWS == 1 && KVP_T_MERGE_DESTINATIONS == 2 && KVP_T_MERGE_SOURCES == 3);
   if (const int t = tid - (kThreads - 64); t >= 0 && t < (a.merge ? 4 : 2))
     atomicAdd(&a.totals[t], (unsigned long long)(t == 0 ? 1u : t == 1 ? total_new : t == 2 ? s_n_dst : s_n_src));
